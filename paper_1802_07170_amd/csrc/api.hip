@@ -3,9 +3,8 @@
 // the method happens here.
 //
 // Schedule of one training step:
-//   gathers -> encoder bottom layer (input GEMM batched over all source positions, then both
-//   directions in one fused recurrent kernel per position) -> upper encoder layers as a wavefront
-//   over (layer, position) -> attention-key hoist K = H_s W_a -> decoder time loop (per step: one
+//   gathers -> encoder layers (per layer the input GEMM batched over all source positions, then the whole
+//   recurrence as one launch, the bottom layer's two directions together) -> attention-key hoist K = H_s W_a -> decoder time loop (per step: one
 //   fused LSTM kernel per layer, attention, attentional tanh layer) -> output layer in slabs of
 //   target positions (projection + log-sum-exp partials, e -> dz rescale, dH_o and dW_o GEMMs) ->
 //   decoder loop backwards -> deferred attention gradients -> encoder loops backwards.  Everything
@@ -52,12 +51,14 @@ struct LD {
   char* YdT = nullptr;               // ... and its transpose [Hh, L*Bp]; used only while dropout is on
   float* dh = nullptr; float* dc = nullptr;   // [Bp, Hh]
   float* bwdp = nullptr;             // [8][Bp][2Hh] backward step-GEMM planes
-  // fragment-major copies read by the per-step kernels (bf16 path, Hh a multiple of 32; see fm_offset)
+  // decoder: fragment-major copies read by the per-step kernels (bf16 path, Hh a multiple of 32; see fm_offset)
   int Kstep = 0;                     // width of the per-step input segment: the x columns [Kin - Kstep, Kin) of W
   char* Wfm = nullptr;               // gate rows of W, columns [Kin - Kstep, Kin + Hh)
   char* HstF = nullptr;              // [(Lmax+1)] slots of [Bp, Hh]
   char* YdF = nullptr;               // [Lmax] slots of [Bp, Hh] (the layer's output after dropout)
   bool fm = false;
+  // encoder: exchange slots of the whole-recurrence kernels, for the states and for the gate gradients (recur.hip)
+  char* X = nullptr; char* XG = nullptr;
   char* WtF = nullptr;               // W^T [Kin+Hh, 4Hh] (backward step GEMMs; needs Kin a multiple of 16)
   char* dGF = nullptr;               // [Lmax] slots of [Bp, 4Hh]
   bool fmb = false;
@@ -135,6 +136,7 @@ struct cmt_handle {
   int32_t *ce_pos = nullptr, *ce_row = nullptr, *ce_nvalid = nullptr, *labels_c = nullptr;
   char* Hoc = nullptr; char* HocT = nullptr;   // H_o (as the output layer sees it) of the valid positions, and its transpose
   float* loss = nullptr; int* flags = nullptr; float* colscr = nullptr;
+  int* tickets = nullptr;               // SEQ_TICKETS counters, one per recurrence launch of a pass (layers <= 8)
   char* dzs = nullptr; char* dzTs = nullptr; float* dbo_parts = nullptr;
   std::vector<GemmProb> dw_group;       // weight-gradient GEMMs collected for one grouped launch (flush_dw_group)
   int ce_rows = 0, ce_pitch = 0;        // row capacity of an output-layer slab and the row pitch of its buffers
@@ -152,8 +154,8 @@ struct cmt_handle {
   // decoding (greedy, beam): the bottom decoder layer contracts [embedding; H_o; h] in one step, so it needs the gate
   // rows of all E + 2H columns of its weights and its input [Bp, E + H] in fragment-major form
   char* Wdec0F = nullptr; char* xcatF = nullptr;
-  int kb_bwd = 0, kb_wc = 0;            // caps on the k blocks of the backward step GEMMs (0 = default)
-  int kb_bwd_dec = 0;                   // the same for the decoder's k-split form (one instance per launch)
+  int kb_wc = 0;                        // caps on the k blocks of the decoder's k-split step GEMMs (0 = default): dpre W_c, and
+  int kb_bwd_dec = 0;                   // the layers' backward GEMMs
   // Workgroup caps of the second stream's GEMMs (weight gradients; dW_o), 0 = none, -1 = by batch width: with all
   // 256 CUs taken by 256 x 256 tiles for tens of microseconds at a time, the recurrences' kernels on the caller's
   // stream queue behind them; capped at 128 workgroups the GEMMs take twice as long (still hidden) and leave half the
@@ -162,16 +164,10 @@ struct cmt_handle {
   int side_wgs = -1, side_wgs_wo = -1;
   int side_cap(int v) const { return v >= 0 ? v : (Bp <= 64 ? 128 : 0); }
   int wc_whole_k = 1;                   // fused decoder loop: dpre W_c with the whole k range per workgroup (env CMT_WC_WHOLE_K)
-  // backward loops that use the whole-k step GEMM with the consumer in its epilogue (env CMT_BWD_FUSED, a bit
-  // mask): 1 = decoder (up to 128 sentences: 8.1 against 8.7 ms for the large workload's backward loop; wider
-  // batches keep the k-split GEMM + pointwise pair), 2 = upper encoder layers, 4 = bottom encoder layer.  Without
-  // the switch (bwd_fused_auto) bits 1 and 4 are set and the upper encoder layers choose per step: their launches
-  // carry up to L - 1 layer-steps, each re-reading all gate gradients from L2 in the fused form, so it wins while
-  // (L - 1) * Bp * H^2 is small (step time fused / pair, ms: 512 x 2 layers 5.07 / 5.22, 512 x 4 6.89 / 7.09,
-  // 1024 x 2 6.30 / 6.45, 512 x 2 at 32 sentences x 120 positions 11.77 / 12.13; 1024 x 4 at 64 sentences
-  // 9.43 / 9.41; at 128 sentences 26.4 / 25.3): fused up to 2^27.
-  int bwd_fused = 5;
-  bool bwd_fused_auto = true;
+  // decoder's backward loop with the whole-k step GEMM and the consumer in its epilogue (env CMT_BWD_FUSED, bit 1), up
+  // to 128 sentences: 8.1 against 8.7 ms for the large workload's loop; wider batches keep the k-split GEMM +
+  // pointwise pair
+  int bwd_fused = 1;
   // phase timing of a step on the caller's stream (measurement aid, env CMT_PHASE_TIMING=1)
   int phase_timing = 0;
   std::vector<hipEvent_t> phase_ev; std::vector<const char*> phase_name; size_t phase_n = 0;
@@ -198,6 +194,7 @@ int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 // jobs for launch_fill_multi / launch_copy2d_multi (units of 32-bit words; esz = bytes per T element)
 void add_fill(std::vector<FillJob>& v, void* p, size_t elems, size_t esz) { v.push_back(FillJob{p, elems * esz / 4}); }
+void add_empty(std::vector<FillJob>& v, void* p, size_t elems, size_t esz) { v.push_back(FillJob{p, elems * esz / 4, 0xffffffffu}); }
 void add_copy(std::vector<CopyJob>& v, const void* s, int lds, void* d, int ldd, int rows, int cols, size_t esz) {
   const int f = (int)(4 / esz);                    // elements per word: row pitches and widths are multiples of it
   v.push_back(CopyJob{s, lds / f, d, ldd / f, rows, cols / f});
@@ -253,21 +250,22 @@ size_t layout(cmt_handle* h, char* base) {
   h->PH = H + ACT_PAD;
   const size_t PH = h->PH;
   h->Pc = c.precision ? a.take(h->nparams * esz) : (char*)h->params;
-  auto ld_alloc = [&](LD& d, int Kin, int Hh, int Lm, bool gx, int Kstep) {
+  auto ld_alloc = [&](LD& d, int Kin, int Hh, int Lm, bool gx, int Kstep, bool encoder) {
     d.Kin = Kin; d.Hh = Hh; d.ph = Hh + ACT_PAD; d.pg = 4 * Hh + ACT_PAD;
     const size_t M = (size_t)Lm * Bp;
     d.Kstep = Kstep;
-    d.fm = c.precision && Hh % 32 == 0 && Kstep % 32 == 0;
+    d.fm = !encoder && c.precision && Hh % 32 == 0 && Kstep % 32 == 0;
     if (d.fm) {
       d.Wfm = a.take((size_t)4 * Hh * (Kstep + Hh) * esz);
       d.HstF = a.take((M + Bp) * Hh * esz);
       d.YdF = a.take(M * Hh * esz);
     }
-    d.fmb = c.precision && Hh % 32 == 0 && Kin % 16 == 0;
+    d.fmb = !encoder && c.precision && Hh % 32 == 0 && Kin % 16 == 0;
     if (d.fmb) {
       d.WtF = a.take((size_t)(Kin + Hh) * 4 * Hh * esz);
       d.dGF = a.take(M * 4 * Hh * esz);
     }
+    if (encoder) { d.X = a.take(seq_exchange_elems(Lm + 1, Bp, Hh) * esz); d.XG = a.take(M * 4 * Hh * esz); }
     d.Wt = a.take((size_t)(Kin + Hh) * 4 * Hh * esz);
     d.Hst = a.take((M + Bp) * d.ph * esz);
     d.Cst = (float*)a.take((M + Bp) * Hh * 4);
@@ -284,13 +282,13 @@ size_t layout(cmt_handle* h, char* base) {
   };
   h->enc.assign(L + 1, LD());
   h->dec.assign(L, LD());
-  // per-step input segment: none for the layers whose input part is batched over time (bottom encoder layers,
-  // encoder layer 1), the fed H_o for the decoder's bottom layer, the layer below's state for the others
-  ld_alloc(h->enc[0], E, Hd, Sm, true, 0);
-  ld_alloc(h->enc[1], E, Hd, Sm, true, 0);
-  for (int l = 1; l < L; ++l) ld_alloc(h->enc[l + 1], H, H, Sm, true, l == 1 ? 0 : H);
-  ld_alloc(h->dec[0], E + H, H, Tm, true, H);
-  for (int l = 1; l < L; ++l) ld_alloc(h->dec[l], H, H, Tm, false, H);
+  // the encoder's input parts are batched over time; per-step input segment of the decoder: the fed H_o for the bottom
+  // layer, the layer below's state for the others
+  ld_alloc(h->enc[0], E, Hd, Sm, true, 0, true);
+  ld_alloc(h->enc[1], E, Hd, Sm, true, 0, true);
+  for (int l = 1; l < L; ++l) ld_alloc(h->enc[l + 1], H, H, Sm, true, 0, true);
+  ld_alloc(h->dec[0], E + H, H, Tm, true, H, false);
+  for (int l = 1; l < L; ++l) ld_alloc(h->dec[l], H, H, Tm, false, H, false);
   if (c.precision && H % 32 == 0) {
     h->HoFeedF = a.take((Mt + Bp) * H * esz);
     h->WcF = a.take((size_t)2 * H * H * esz); h->WcTF = a.take((size_t)2 * H * H * esz);
@@ -359,7 +357,7 @@ size_t layout(cmt_handle* h, char* base) {
   h->ce_pos = (int32_t*)a.take(Mt * 4); h->ce_row = (int32_t*)a.take(Mt * 4); h->labels_c = (int32_t*)a.take(Mt * 4);
   h->ce_nvalid = (int32_t*)a.take(256);
   h->Hoc = a.take(Mt * PH * esz); h->HocT = a.take(Mt * H * esz);
-  h->loss = (float*)a.take(256); h->flags = (int*)a.take(256);
+  h->loss = (float*)a.take(256); h->flags = (int*)a.take(256); h->tickets = (int*)a.take(SEQ_TICKETS * 4);
   h->colscr = (float*)a.take((size_t)16 * 4 * H * 4);
   h->dzs = a.take(slab_elems * esz); h->dzTs = a.take(slab_elems * esz);
   h->dbo_parts = (float*)a.take((Mt / 64 + Mt / 256 + 4) * c.tgt_vocab * 4);
@@ -579,13 +577,9 @@ void dec_lstm_fwd(cmt_handle* h, int l, int j) {
     d.hprev_fm = e.HstF + j * BH * esz; d.hnext_fm = e.HstF + (j + 1) * BH * esz;
     if (d.ycat) d.ycat_fm = e.YdF + j * BH * esz;
   }
-  launch_lstm_fwd(h->prec, &d, 1, Bp, H, h->st);
+  launch_lstm_fwd(h->prec, d, Bp, H, h->st);
 }
 
-// Encoder forward for the batch whose source embeddings, masks and lengths are in the workspace
-// (gather done by the caller): bottom layer (both directions per launch), upper layers as a
-// wavefront, attention keys, and the decoder's initial states.  Returns H_s (top-layer states) and
-// its row pitch.
 // Attention and attentional layer of decoder step j on the projected source rows P_i = W_c1 H_s^i (Eq. 3-7
 // regrouped: W_c [C_s; H_t] = sum_i a_i P_i + W_c2 H_t), two dependent launches: the scores together with the sums
 // W_c2 H_t (both wait for the top layer's state alone), then softmax, mix, tanh -> H_o and its copies.
@@ -620,13 +614,17 @@ void dec_att_bwd_proj(cmt_handle* h, int j, int S, bool last) {
   g.part[1].kind = BWD_EPI_STORE; g.part[1].ncols = H; g.part[1].out = h->wcp; g.part[1].ldout = H;
   g.dg_fm = dpreF; g.Wt_fm = dpreF ? h->WcTF : nullptr; g.wt_tile0 = 0;
   const AttScores sc{h->Pmat, H, dpre, PH, h->len_s, S, H, h->dots, 1};
-  launch_step_bwd_fused(p, &g, 1, Bp, h->st, &sc);
+  launch_step_bwd_fused(p, g, Bp, h->st, &sc);
   LstmBwdPoint top = dec_cell(h, L - 1, j);
   top.dhrec = Planes{h->dec[L - 1].bwdp, H, last ? 0 : 1, 0};
   launch_att_bwd_mix(p, h->Kmat, H, Planes{h->wcp, H, 1, 0}, 0, h->att_a + (size_t)j * Bp * S, h->len_s, S, Bp, H, h->dots,
                      h->att_ds + (size_t)j * Bp * S, h->dHt, h->st, &top);
 }
 
+// Encoder forward for the batch whose source embeddings, masks and lengths are in the workspace (gather done by the
+// caller): per layer one GEMM for the input part of all positions and one launch for the whole recurrence (bottom layer:
+// both directions), then the attention keys and the decoder's initial states.  Returns H_s (top-layer states) and its
+// row pitch.
 void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
   const cmt_config& c = h->cfg;
   const int p = h->prec, E = c.emb_dim, H = c.hidden, Hd = H / 2, L = c.layers, Bp = h->Bp;
@@ -638,86 +636,50 @@ void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
   const bool drop = h->drop_p > 0.f;
   const size_t BP = (size_t)Bp * PH;
   float* P = h->params;
-  // ---- encoder layer 0: two directions ------------------------------------------------------------
   LD& ef = h->enc[0]; LD& eb = h->enc[1];
-  for (LD* d : {&ef, &eb})
-    launch_gemm_nt(p, h->Xs, E, d->W, E + Hd, Ms, 4 * Hd, E, d->Gx, nullptr, 4 * Hd, P + d->b_off, 0, st);
   const size_t BHd = (size_t)Bp * Hd, BPd = (size_t)Bp * ef.ph;
-  {   // initial states of every encoder LSTM: zero, in one launch
+  const unsigned long long drop_step = (unsigned long long)h->B * H;
+  {   // initial states of every encoder LSTM (zero), and the exchange slots and tickets of the recurrences: one launch
     std::vector<FillJob> z;
     add_fill(z, ef.Hst, BPd, esz); add_fill(z, ef.Cst, BHd, 4);
     add_fill(z, eb.Hst + (size_t)S * BPd * esz, BPd, esz); add_fill(z, eb.Cst + (size_t)S * BHd, BHd, 4);
-    if (ef.fm) { add_fill(z, ef.HstF, BHd, esz); add_fill(z, eb.HstF + (size_t)S * BHd * esz, BHd, esz); }
-    for (int l = 1; l < L; ++l) {
-      add_fill(z, h->enc[l + 1].Hst, BP, esz); add_fill(z, h->enc[l + 1].Cst, BH, 4);
-      if (h->enc[l + 1].fm) add_fill(z, h->enc[l + 1].HstF, BH, esz);
-    }
+    for (int l = 1; l < L; ++l) { add_fill(z, h->enc[l + 1].Hst, BP, esz); add_fill(z, h->enc[l + 1].Cst, BH, 4); }
+    for (int l = 0; l <= L; ++l) add_empty(z, h->enc[l].X, seq_exchange_elems(S + 1, Bp, h->enc[l].Hh), esz);
+    add_fill(z, h->tickets, SEQ_TICKETS, 4);
     launch_fill_multi(z.data(), (int)z.size(), st);
   }
-  for (int k = 0; k < S; ++k) {
-    const int tf = k, tb = S - 1 - k;
-    LstmFwdDir d[2];
-    for (int i = 0; i < 2; ++i) {
-      LD& e = i ? eb : ef;
-      const int t = i ? tb : tf;
-      const int sp = i ? t + 1 : t, sn = i ? t : t + 1;
-      d[i].x = nullptr; d[i].ldx = 0; d[i].Kx = 0;
-      d[i].hprev = e.Hst + sp * BPd * esz; d[i].ldh = e.ph;
-      d[i].W = e.W; d[i].ldw = E + Hd; d[i].wx_off = 0; d[i].wh_off = E;
-      d[i].gx = e.Gx + (size_t)t * Bp * 4 * Hd; d[i].ldgx = 4 * Hd; d[i].bias = nullptr;
-      d[i].cprev = e.Cst + sp * BHd; d[i].mask = h->mask_s + (size_t)t * Bp;
-      d[i].hnext = e.Hst + sn * BPd * esz; d[i].ldhn = e.ph; d[i].cnext = e.Cst + sn * BHd;
-      d[i].gsave = e.Gs + (size_t)t * Bp * 4 * Hd;
-      d[i].ycat = h->Y0 + ((size_t)t * BH + (i ? Hd : 0)) * esz; d[i].ldy = H;
-      if (L > 1) { d[i].drop = drop_spec(h, DROP_SITE_ENC + 0, t); d[i].drop_col0 = i ? Hd : 0; }
-      if (e.fm) {
-        d[i].W_fm = e.Wfm; d[i].hprev_fm = e.HstF + sp * BHd * esz; d[i].hnext_fm = e.HstF + sn * BHd * esz;
-      }
-    }
-    launch_lstm_fwd(p, d, 2, Bp, Hd, st);
+  for (LD* d : {&ef, &eb})
+    launch_gemm_nt(p, h->Xs, E, d->W, E + Hd, Ms, 4 * Hd, E, d->Gx, nullptr, 4 * Hd, P + d->b_off, 0, st);
+  auto seq_dir = [&](LD& e) {
+    SeqFwdDir d{};
+    d.W = e.W; d.ldw = e.Kin + e.Hh; d.wh_off = e.Kin; d.gx = e.Gx; d.mask = h->mask_s; d.X = e.X;
+    d.H = e.Hst; d.ldh = e.ph; d.C = e.Cst; d.G = e.Gs;
+    return d;
+  };
+  SeqFwdArgs sa{};
+  sa.ticket = h->tickets; sa.flags = h->flags;
+  for (int i = 0; i < 2; ++i) {
+    SeqFwdDir& d = sa.d[i];
+    d = seq_dir(i ? eb : ef);
+    d.Y = h->Y0; d.ldy = H; d.y_col0 = i ? Hd : 0; d.reverse = i;
+    if (L > 1) { d.drop = drop_spec(h, DROP_SITE_ENC + 0, 0); d.drop_step = drop_step; }
   }
+  launch_lstm_seq_fwd(p, sa, 2, S, Bp, Hd, st);
   phase_mark(h, "encoder upper layers");
-  // ---- encoder layers >= 1: a wavefront over (layer, position) ------------------------------------
-  // Layer l at position t needs layer l-1 at t and itself at t-1, so all layers advance together
-  // along diagonals: one launch carries up to L-1 layer-steps (S + L - 2 launches instead of
-  // (L-1) S).  Layer 1 keeps its input part batched over all positions (the bottom layer is
-  // complete by then); layers above take [x; h] W^T per step.
-  const char* Yprev = h->Y0;                       // [S*Bp, H]
+  const char* Yprev = h->Y0;                       // [S*Bp, H] what the next layer (or the attention) reads
   int ldY = H;
-  if (L > 1) {
-    LD& e1 = h->enc[2];
-    launch_gemm_nt(p, h->Y0, H, e1.W, 2 * H, Ms, 4 * H, H, e1.Gx, nullptr, 4 * H, P + e1.b_off, 0, st);
-    for (int dg = 0; dg < S + L - 2; ++dg) {
-      LstmFwdDir dirs[STEP_MAX_INST];
-      int n = 0;
-      for (int l = 1; l < L; ++l) {
-        const int t = dg - (l - 1);
-        if (t < 0 || t >= S) continue;
-        LD& e = h->enc[l + 1];
-        LstmFwdDir& d = dirs[n++];
-        if (l == 1) {
-          d.x = nullptr; d.ldx = 0; d.Kx = 0; d.gx = e.Gx + (size_t)t * Bp * 4 * H; d.ldgx = 4 * H; d.bias = nullptr;
-        } else {
-          d.x = drop ? h->enc[l].Yd + t * BP * esz : h->enc[l].Hst + (t + 1) * BP * esz;
-          d.ldx = PH; d.Kx = H; d.gx = nullptr; d.ldgx = 0; d.bias = P + e.b_off;
-        }
-        d.hprev = e.Hst + t * BP * esz; d.ldh = e.ph;
-        d.W = e.W; d.ldw = 2 * H; d.wx_off = 0; d.wh_off = H;
-        d.cprev = e.Cst + t * BH; d.mask = h->mask_s + (size_t)t * Bp;
-        d.hnext = e.Hst + (t + 1) * BP * esz; d.ldhn = e.ph; d.cnext = e.Cst + (t + 1) * BH;
-        d.gsave = e.Gs + (size_t)t * Bp * 4 * H; d.ycat = nullptr; d.ldy = 0;
-        if (drop && l + 1 < L) {
-          d.ycat = e.Yd + t * BP * esz; d.ldy = e.ph; d.drop = drop_spec(h, DROP_SITE_ENC + l, t); d.drop_col0 = 0;
-        }
-        if (e.fm) {
-          d.W_fm = e.Wfm; d.hprev_fm = e.HstF + t * BH * esz; d.hnext_fm = e.HstF + (t + 1) * BH * esz;
-          if (l > 1) d.x_fm = drop ? h->enc[l].YdF + t * BH * esz : h->enc[l].HstF + (t + 1) * BH * esz;
-          if (d.ycat) d.ycat_fm = e.YdF + t * BH * esz;
-        }
-      }
-      launch_lstm_fwd(p, dirs, n, Bp, H, st);
+  for (int l = 1; l < L; ++l) {
+    LD& e = h->enc[l + 1];
+    launch_gemm_nt(p, Yprev, ldY, e.W, 2 * H, Ms, 4 * H, H, e.Gx, nullptr, 4 * H, P + e.b_off, 0, st);
+    sa.ticket = h->tickets + l;
+    sa.d[0] = seq_dir(e);
+    const bool dropped = drop && l + 1 < L;
+    if (dropped) {
+      sa.d[0].Y = e.Yd; sa.d[0].ldy = PH;
+      sa.d[0].drop = drop_spec(h, DROP_SITE_ENC + l, 0); sa.d[0].drop_step = drop_step;
     }
-    Yprev = h->enc[L].Hst + BP * esz; ldY = PH;
+    launch_lstm_seq_fwd(p, sa, 1, S, Bp, H, st);
+    Yprev = dropped ? e.Yd : e.Hst + BP * esz; ldY = PH;
   }
   const char* Hs = Yprev;
   const int ldHs = ldY;                          // source-side top-layer states [S, Bp, H]
@@ -787,7 +749,6 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   const char* Hs; int ldHs;                        // source-side top-layer states [S, Bp, H] and their row pitch
   enqueue_encoder(h, S, &Hs, &ldHs);
   LD& ef = h->enc[0]; LD& eb = h->enc[1];
-  const size_t BHd = (size_t)Bp * Hd;
   // ---- decoder time loop --------------------------------------------------------------------------
   // The attentional layer's pre-activation W_c [C_s; H_t] (Eq. 7) is sum_i a_i (W_c1 H_s^i) + W_c2 H_t: with the rows
   // W_c1 H_s^i made once per batch, a step needs no context before its H_o, and the W_c2 H_t sums share a launch
@@ -941,7 +902,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
         dec_att_bwd_proj(h, j, S, last);
         for (int l = L - 1; l >= 0; --l) {
           const StepBwd gl = dec_bwd_gemm(h, l, j);
-          launch_step_bwd_fused(p, &gl, 1, Bp, st);
+          launch_step_bwd_fused(p, gl, Bp, st);
         }
         continue;
       }
@@ -950,7 +911,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
         g.dg = dpre; g.lddg = PH; g.K = H; g.Wt = h->WcT; g.ldw = H;
         g.part[0].kind = BWD_EPI_STORE; g.part[0].ncols = 2 * H; g.part[0].out = h->wcp; g.part[0].ldout = 2 * H;
         g.dg_fm = dpreF; g.Wt_fm = dpreF ? h->WcTF : nullptr; g.wt_tile0 = 0;
-        launch_step_bwd_fused(p, &g, 1, Bp, st);
+        launch_step_bwd_fused(p, g, Bp, st);
         kbw = 1;
       } else {   // the same as k blocks into planes
         StepGemm g{};
@@ -968,7 +929,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
                      h->len_s, S, Bp, H, h->dots, h->att_ds + (size_t)j * Bp * S, h->dHt, st, &top);
       for (int l = L - 1; l >= 0; --l) {
         const StepBwd g = dec_bwd_gemm(h, l, j);
-        launch_step_bwd_fused(p, &g, 1, Bp, st);
+        launch_step_bwd_fused(p, g, Bp, st);
       }
     }
     for (int l = 0; l < L; ++l)
@@ -1060,110 +1021,34 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
 
   phase_mark(h, "encoder upper layers backward");
   // ---- encoder backwards ------------------------------------------------------------------------------
-  // Upper layers: the same wavefront, top layer first.  Per diagonal one pointwise launch (cell
-  // backward of every active layer-step) and one step-GEMM launch ([dx; dh_prev] = dgates [W_x; W_h]).
-  const bool upper_fused = h->bwd_fused_auto ? (double)(L - 1) * Bp * H * H <= 134217728.0 : (h->bwd_fused & 2) != 0;
-  if (L > 1 && upper_fused) {
-    // Fused form: one launch per diagonal.  The step GEMM of (layer l, position t) keeps its dh_prev half in
-    // registers and runs the cell backward of (l, t - 1) in its epilogue; its dx half is stored for the layer
-    // below (two alternating slots of bwdp per layer, Bp * H floats each).  Layer l at position t - 1 needs the
-    // dx of layer l + 1 at t - 1 from an earlier launch, so a layer runs two diagonals behind the one above:
-    // (l, t) sits on diagonal (S - 1 - t) + 2 (L - 1 - l).  The first position of a layer has no GEMM
-    // before it: its cell backward is a pointwise launch just ahead of the layer's first diagonal.
-    const size_t slot = (size_t)Bp * H;
-    auto enc_cell = [&](int l, int t) {
-      LD& e = h->enc[l + 1];
-      LstmBwdPoint q;
-      if (l == L - 1) q.dy = Planes{h->dHs + (size_t)t * Bp * H, H, 1, 0};
-      else { q.dy = Planes{h->enc[l + 2].bwdp + (size_t)(t & 1) * slot, H, 1, 0}; q.drop_dy = drop_spec(h, DROP_SITE_ENC + l, t); }
-      q.dy_col = 0;
-      q.dhrec = Planes{nullptr, 0, 0, 0}; q.dhrec_col = 0;
-      q.dh = h->dec[l].dh; q.dc = h->dec[l].dc;      // gradient of the final state = gradient of the decoder's initial state
-      q.gsave = e.Gs + (size_t)t * Bp * 4 * H;
-      q.cprev = e.Cst + t * BH; q.cnext = e.Cst + (t + 1) * BH;
-      q.mask = h->mask_s + (size_t)t * Bp;
-      q.dg = e.dG + (size_t)t * Bp * e.pg * esz; q.lddg = e.pg;
-      if (e.fmb) q.dg_fm = e.dGF + (size_t)t * Bp * 4 * H * esz;
-      return q;
-    };
-    for (int dg = 0; dg <= (S - 1) + 2 * (L - 2); ++dg) {
-      StepBwd gs[STEP_MAX_INST];
-      int ng = 0;
-      for (int l = L - 1; l >= 1; --l) {
-        const int k = dg - 2 * (L - 1 - l);
-        if (k < 0 || k >= S) continue;
-        const int t = S - 1 - k;
-        LD& e = h->enc[l + 1];
-        if (k == 0) launch_lstm_bwd_point(p, enc_cell(l, t), Bp, H, st);
-        if (l == 1 && t == 0) continue;              // the initial state is a constant, and layer 1's dx is batched below
-        StepBwd& g = gs[ng++];
-        g = StepBwd{};
-        g.dg = e.dG + (size_t)t * Bp * e.pg * esz; g.lddg = e.pg; g.K = 4 * H; g.ldw = 4 * H;
-        int np = 0;
-        if (l > 1) {
-          g.Wt = e.Wt;
-          BwdEpi& d = g.part[np++];
-          d.kind = BWD_EPI_STORE; d.ncols = H; d.hh = H; d.out = e.bwdp + (size_t)(t & 1) * slot; d.ldout = H;
-        } else {
-          g.Wt = e.Wt + (size_t)H * 4 * H * esz;
-        }
-        if (e.fmb) { g.dg_fm = e.dGF + (size_t)t * Bp * 4 * H * esz; g.Wt_fm = e.WtF; g.wt_tile0 = (l > 1 ? 0 : H) / 16; }
-        if (t > 0) {
-          BwdEpi& r = g.part[np++];
-          r.kind = BWD_EPI_CELL_REC; r.ncols = H; r.hh = H; r.cell = enc_cell(l, t - 1);
-        }
-      }
-      if (ng) launch_step_bwd_fused(p, gs, ng, Bp, st);
-    }
-    LD& e1 = h->enc[2];
-    launch_gemm_nt(p, e1.dG, e1.pg, e1.Wt, 4 * H, Ms, H, 4 * H, h->dYa, nullptr, H, nullptr, 0, st);   // layer 0's dY = dG_1 W_x
-    stream_after(h, sd, st);
-    for (int l = L - 1; l >= 1; --l) {
-      LD& e = h->enc[l + 1];
-      int ld; const char* XT = encYT(l - 1, &ld);
-      weight_grads(h, e, S, {{XT, ld}, {e.HstT, (S + 1) * Bp}}, {H, H}, sd);
-    }
-    flush_dw_group(h, sd);
-  } else if (L > 1) {
-    const int Nplan = L > 2 ? 2 * H : H;
-    const int kbE = step_kblocks(p, Nplan, 4 * H, Bp, h->kb_bwd);
-    const size_t pstrE = (size_t)Bp * 2 * H;
-    for (int dg = 0; dg < S + L - 2; ++dg) {
-      LstmBwdPoint pts[STEP_MAX_INST];
-      StepGemm gs[STEP_MAX_INST];
-      int n = 0, ng = 0;
-      for (int l = L - 1; l >= 1; --l) {
-        const int k = dg - (L - 1 - l);
-        if (k < 0 || k >= S) continue;
-        const int t = S - 1 - k;
-        LD& e = h->enc[l + 1];
-        LstmBwdPoint& q = pts[n++];
-        if (l == L - 1) q.dy = Planes{h->dHs + (size_t)t * Bp * H, H, 1, 0};
-        else { q.dy = Planes{h->enc[l + 2].bwdp, 2 * H, kbE, pstrE}; q.drop_dy = drop_spec(h, DROP_SITE_ENC + l, t); }
-        q.dy_col = 0;                                                       // dx of the layer above (its columns [0, H))
-        q.dhrec = Planes{e.bwdp, 2 * H, k == 0 ? 0 : kbE, pstrE};
-        q.dhrec_col = (l == 1) ? 0 : H;                                     // layer 1 only computes the recurrent part
-        // gradient of the final state = gradient of the decoder's initial state of the same depth
-        q.dh = h->dec[l].dh; q.dc = h->dec[l].dc;
-        q.gsave = e.Gs + (size_t)t * Bp * 4 * H;
-        q.cprev = e.Cst + t * BH; q.cnext = e.Cst + (t + 1) * BH;
-        q.mask = h->mask_s + (size_t)t * Bp;
-        q.dg = e.dG + (size_t)t * Bp * e.pg * esz; q.lddg = e.pg;
-        if (e.fmb) q.dg_fm = e.dGF + (size_t)t * Bp * 4 * H * esz;
-        if (l == 1 && k == S - 1) continue;                                 // the initial state is a constant
-        StepGemm& g = gs[ng++];
-        g = StepGemm{};
-        g.a0 = q.dg; g.lda0 = e.pg; g.K0 = 4 * H; g.w0_off = 0; g.K1 = 0;
-        g.W = e.Wt + (size_t)(l == 1 ? H : 0) * 4 * H * esz; g.ldw = 4 * H;
-        if (e.fmb) { g.W_fm = e.WtF; g.w_tile0 = (l == 1 ? H : 0) / 16; g.a0_fm = q.dg_fm; }
-        g.N = (l == 1) ? H : 2 * H; g.mode = 1; g.max_kb = h->kb_bwd;
-        g.out = e.bwdp; g.ldout = 2 * H; g.plane_stride = pstrE;
-      }
-      launch_lstm_bwd_point_multi(p, pts, n, Bp, H, st);
-      if (ng) launch_step_gemm_multi(p, gs, ng, Nplan, Bp, st);
-    }
-    LD& e1 = h->enc[2];
-    launch_gemm_nt(p, e1.dG, e1.pg, e1.Wt, 4 * H, Ms, H, 4 * H, h->dYa, nullptr, H, nullptr, 0, st);   // layer 0's dY = dG_1 W_x
+  // Per layer, top first, one launch for the whole recurrence and one GEMM for the gradient it sends to the layer below.
+  {   // the exchange slots (the tickets of the forward pass are used up: cleared as well)
+    std::vector<FillJob> z;
+    for (int l = 0; l <= L; ++l) add_empty(z, h->enc[l].XG, (size_t)Ms * 4 * h->enc[l].Hh, esz);
+    add_fill(z, h->tickets, SEQ_TICKETS, 4);
+    launch_fill_multi(z.data(), (int)z.size(), st);
+  }
+  const unsigned long long drop_step = (unsigned long long)h->B * H;
+  auto seq_bwd_dir = [&](LD& e, const float* dY) {
+    SeqBwdDir d{};
+    d.Wt = e.Wt + (size_t)e.Kin * 4 * e.Hh * esz; d.ldw = 4 * e.Hh;
+    d.dY = dY; d.lddy = H; d.mask = h->mask_s; d.G = e.Gs; d.C = e.Cst;
+    d.X = e.XG; d.dG = e.dG; d.lddg = e.pg; d.ldd0 = H;
+    return d;
+  };
+  SeqBwdArgs sb{};
+  sb.flags = h->flags;
+  for (int l = L - 1; l >= 1; --l) {
+    LD& e = h->enc[l + 1];
+    SeqBwdDir& d = sb.d[0];
+    d = seq_bwd_dir(e, l == L - 1 ? h->dHs : h->dYa);
+    if (l < L - 1) { d.drop = drop_spec(h, DROP_SITE_ENC + l, 0); d.drop_step = drop_step; }
+    d.dh0 = h->dec[l].dh; d.dc0 = h->dec[l].dc;    // gradient of the final state = that of the decoder's initial state
+    sb.ticket = h->tickets + l;
+    launch_lstm_seq_bwd(p, sb, 1, S, Bp, H, st);
+    launch_gemm_nt(p, e.dG, e.pg, e.Wt, 4 * H, Ms, H, 4 * H, h->dYa, nullptr, H, nullptr, 0, st);   // the layer below's dY = dG W_x
+  }
+  if (L > 1) {
     stream_after(h, sd, st);
     for (int l = L - 1; l >= 1; --l) {
       LD& e = h->enc[l + 1];
@@ -1173,78 +1058,17 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
     flush_dw_group(h, sd);
   }
   phase_mark(h, "encoder bottom layer backward");
-  {   // bottom layer: the two directions run in the same launches
-    const float* dY0 = L > 1 ? h->dYa : h->dHs;
+  {   // bottom layer: both directions in one launch
     LD& d0 = h->dec[0];
-    std::vector<CopyJob> cp;
-    add_copy(cp, d0.dh, H, ef.dh, Hd, Bp, Hd, 4); add_copy(cp, d0.dh + Hd, H, eb.dh, Hd, Bp, Hd, 4);
-    add_copy(cp, d0.dc, H, ef.dc, Hd, Bp, Hd, 4); add_copy(cp, d0.dc + Hd, H, eb.dc, Hd, Bp, Hd, 4);
-    launch_copy2d_multi(cp.data(), (int)cp.size(), st);
-    const int kb0 = step_kblocks(p, Hd, 4 * Hd, Bp, h->kb_bwd);
-    const size_t pstr0 = (size_t)Bp * Hd;
-    // cell backward of direction i at position t (its dy is a slice of the batched dY of the layer above)
-    auto enc0_cell = [&](int i, int t) {
-      LD& e = i ? eb : ef;
-      const int slot_prev = i ? t + 1 : t, slot_next = i ? t : t + 1;
-      LstmBwdPoint q;
-      q.dy = Planes{dY0 + (size_t)t * Bp * H, H, 1, 0}; q.dy_col = i ? Hd : 0;
-      if (L > 1) q.drop_dy = drop_spec(h, DROP_SITE_ENC + 0, t);
-      q.dhrec = Planes{nullptr, 0, 0, 0}; q.dhrec_col = 0;
-      q.dh = e.dh; q.dc = e.dc;
-      q.gsave = e.Gs + (size_t)t * Bp * 4 * Hd;
-      q.cprev = e.Cst + (size_t)slot_prev * BHd; q.cnext = e.Cst + (size_t)slot_next * BHd;
-      q.mask = h->mask_s + (size_t)t * Bp;
-      q.dg = e.dG + (size_t)t * Bp * e.pg * esz; q.lddg = e.pg;
-      if (e.fmb) q.dg_fm = e.dGF + (size_t)t * Bp * 4 * Hd * esz;
-      return q;
-    };
-    if (h->bwd_fused & 4) {
-      // one launch per position: dh_prev = dgates W_h of both directions, the cell backward of each
-      // direction's next position in the epilogue; only the very first position is a pointwise launch
-      LstmBwdPoint first[2] = {enc0_cell(0, S - 1), enc0_cell(1, 0)};
-      launch_lstm_bwd_point_multi(p, first, 2, Bp, Hd, st);
-      for (int k = 0; k + 1 < S; ++k) {
-        StepBwd gs[2];
-        for (int i = 0; i < 2; ++i) {
-          LD& e = i ? eb : ef;
-          const int t = i ? k : S - 1 - k, tn = i ? k + 1 : S - 2 - k;
-          StepBwd& g = gs[i];
-          g = StepBwd{};
-          g.dg = e.dG + (size_t)t * Bp * e.pg * esz; g.lddg = e.pg; g.K = 4 * Hd;
-          g.Wt = e.Wt + (size_t)E * 4 * Hd * esz; g.ldw = 4 * Hd;
-          if (e.fmb) { g.dg_fm = e.dGF + (size_t)t * Bp * 4 * Hd * esz; g.Wt_fm = e.WtF; g.wt_tile0 = E / 16; }
-          BwdEpi& r = g.part[0];
-          r.kind = BWD_EPI_CELL_REC; r.ncols = Hd; r.hh = Hd; r.cell = enc0_cell(i, tn);
-        }
-        launch_step_bwd_fused(p, gs, 2, Bp, st);
-      }
-    } else
-    for (int k = 0; k < S; ++k) {
-      LstmBwdPoint pts[2];
-      StepGemm gs[2];
-      for (int i = 0; i < 2; ++i) {
-        LD& e = i ? eb : ef;
-        const int t = i ? k : S - 1 - k;                                    // reverse of each direction's processing order
-        const int slot_prev = i ? t + 1 : t, slot_next = i ? t : t + 1;
-        LstmBwdPoint& q = pts[i];
-        q.dy = Planes{dY0 + (size_t)t * Bp * H, H, 1, 0}; q.dy_col = i ? Hd : 0;
-        if (L > 1) q.drop_dy = drop_spec(h, DROP_SITE_ENC + 0, t);
-        q.dhrec = Planes{e.bwdp, Hd, k == 0 ? 0 : kb0, pstr0}; q.dhrec_col = 0;
-        q.dh = e.dh; q.dc = e.dc;
-        q.gsave = e.Gs + (size_t)t * Bp * 4 * Hd;
-        q.cprev = e.Cst + (size_t)slot_prev * BHd; q.cnext = e.Cst + (size_t)slot_next * BHd;
-        q.mask = h->mask_s + (size_t)t * Bp;
-        q.dg = e.dG + (size_t)t * Bp * e.pg * esz; q.lddg = e.pg;
-        StepGemm& g = gs[i];
-        g = StepGemm{};
-        g.a0 = q.dg; g.lda0 = e.pg; g.K0 = 4 * Hd; g.w0_off = 0; g.K1 = 0;
-        g.W = e.Wt + (size_t)E * 4 * Hd * esz; g.ldw = 4 * Hd;
-        g.N = Hd; g.mode = 1; g.max_kb = h->kb_bwd;
-        g.out = e.bwdp; g.ldout = Hd; g.plane_stride = pstr0;
-      }
-      launch_lstm_bwd_point_multi(p, pts, 2, Bp, Hd, st);
-      if (k + 1 < S) launch_step_gemm_multi(p, gs, 2, Hd, Bp, st);          // the initial state is a constant
+    for (int i = 0; i < 2; ++i) {
+      SeqBwdDir& d = sb.d[i];
+      d = seq_bwd_dir(i ? eb : ef, L > 1 ? h->dYa : h->dHs);
+      d.dy_col = i ? Hd : 0; d.reverse = i;
+      if (L > 1) { d.drop = drop_spec(h, DROP_SITE_ENC + 0, 0); d.drop_step = drop_step; }
+      d.dh0 = d0.dh + (i ? Hd : 0); d.dc0 = d0.dc + (i ? Hd : 0);
     }
+    sb.ticket = h->tickets;
+    launch_lstm_seq_bwd(p, sb, 2, S, Bp, Hd, st);
     // What is left after the last recurrent kernel is shared between the two streams: the weight gradients of
     // both directions on the second one, the source-embedding gradient (dX_s, then the scatter) on the caller's.
     stream_after(h, sd, st);
@@ -1299,11 +1123,6 @@ int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* w
   h->params = (float*)params_dev; h->grads = (float*)grads_dev; h->ws = (char*)workspace_dev;
   h->Bpm = round_up(cfg->max_batch, 16);
   {
-    // k blocks of the encoder's k-split backward step GEMMs (up to L - 1 instances per launch): 2 (medium 9.72 ms
-    // per step against 9.75 with 4, 9.86 with 8 and 9.96 with 1; large 24.59 / 24.69 / 24.71 / 24.74): fewer planes
-    // for the consumer to sum weigh more than the extra workgroups, now that the operands stream fragment-major.
-    // The decoder's k-split form launches one instance at a time and keeps as many blocks as fill the chip.
-    const char* k1 = getenv("CMT_KB_BWD"); h->kb_bwd = k1 ? atoi(k1) : 2;
     const char* k1d = getenv("CMT_KB_BWD_DEC"); h->kb_bwd_dec = k1d ? atoi(k1d) : 0;
     const char* k2 = getenv("CMT_KB_WC"); h->kb_wc = k2 ? atoi(k2) : 2;
     const char* ks1 = getenv("CMT_SIDE_WGS"); h->side_wgs = ks1 ? atoi(ks1) : -1;
@@ -1312,7 +1131,7 @@ int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* w
     const char* k3 = getenv("CMT_SIDE_STREAM"); h->use_side = k3 ? atoi(k3) : 1;
     const char* k3p = getenv("CMT_ATT_PROJ"); h->att_proj = k3p ? atoi(k3p) : 1;
     const char* k4 = getenv("CMT_PHASE_TIMING"); h->phase_timing = k4 ? atoi(k4) : 0;
-    const char* k5 = getenv("CMT_BWD_FUSED"); h->bwd_fused = k5 ? atoi(k5) : 5; h->bwd_fused_auto = k5 == nullptr;
+    const char* k5 = getenv("CMT_BWD_FUSED"); h->bwd_fused = k5 ? atoi(k5) : 1;
   }
   build_table(h->cfg, h->table, h->nparams);
   h->ws_bytes = layout(h, h->ws);
@@ -1491,6 +1310,7 @@ int cmt_fetch_loss(cmt_handle* h, float* loss_host) {
     launch_fill_f32((float*)h->flags, 1, 0.f, h->st);
   }
   if (flags & 3) return fail(h, CMT_ERANGE, (flags & 1) ? "a token id is outside its vocabulary" : "a length is outside [1, padded length]");
+  if (flags & CMT_FLAG_GAVE_UP) return fail(h, CMT_EHIP, "a wait between workgroups was given up");
   if (flags & 4) return fail(h, CMT_ENONFINITE, "the loss is not finite");
   return CMT_OK;
 }
@@ -1553,7 +1373,7 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
           d.W_fm = h->Wdec0F; d.x_fm = h->xcatF; d.hprev_fm = e.HstF + j * BH * esz;
         }
       }
-      launch_lstm_fwd(p, &d, 1, Bp, H, st);
+      launch_lstm_fwd(p, d, Bp, H, st);
     }
     const char* Ht = h->dec[L - 1].Hst + (j + 1) * BP * esz;
     StepGemm g{};                                   // H_o = tanh(W_c [C_s; H_t]) straight into the next step's input
@@ -1597,6 +1417,7 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
   if (e != hipSuccess) return hip_fail(h, e, "cmt_greedy_decode");
   const int flags = *h->h_flags;
   if (flags & 3) return fail(h, CMT_ERANGE, (flags & 1) ? "a token id is outside its vocabulary" : "a length is outside [1, padded length]");
+  if (flags & CMT_FLAG_GAVE_UP) return fail(h, CMT_EHIP, "a wait between workgroups was given up");
   return CMT_OK;
 }
 
@@ -1682,7 +1503,7 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
         if (l > 0 && h->dec[l - 1].fm) { d.W_fm = e.Wfm; d.x_fm = h->dec[l - 1].HstF + 2 * slotF; d.hprev_fm = e.HstF + slotF; }
         else if (l == 0 && fm0) { d.W_fm = h->Wdec0F; d.x_fm = h->xcatF; d.hprev_fm = e.HstF + slotF; }
       }
-      launch_lstm_fwd(p, &d, 1, Rp, H, st);
+      launch_lstm_fwd(p, d, Rp, H, st);
     }
     const char* Ht = h->dec[L - 1].Hst + 2 * slotT;
     StepGemm g{};
@@ -1712,6 +1533,7 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
   if (e != hipSuccess) return hip_fail(h, e, "cmt_beam_decode");
   const int flags = *h->h_flags;
   if (flags & 3) return fail(h, CMT_ERANGE, (flags & 1) ? "a token id is outside its vocabulary" : "a length is outside [1, padded length]");
+  if (flags & CMT_FLAG_GAVE_UP) return fail(h, CMT_EHIP, "a wait between workgroups was given up");
   return CMT_OK;
 }
 
@@ -1783,7 +1605,7 @@ int cmt_time_kernel(cmt_handle* h, const char* name, int iters, float* us_per_la
                + (double)Bp * H * (4 * 4 + 2 * 4 + 2 * 4 + 2 * 4 + 4) + (double)Bp * 4 * H * esz;
     launch = [=](int i) {
       const StepBwd g = dec_bwd_gemm(h, L > 1 ? 1 + i % (L - 1) : 0, j);
-      launch_step_bwd_fused(p, &g, 1, Bp, st);
+      launch_step_bwd_fused(p, g, Bp, st);
     };
   } else if (s == "att_fwd") {
     // attention forward of one decoder step as the step launches it.  On the projected rows: scores (with the sums

@@ -80,9 +80,6 @@ void launch_ce_scale(int prec, void* ET, int pitch, int V, int Mc, const float* 
 
 // ---- step.hip ----------------------------------------------------------------------------------
 // A value delivered as `np` partial planes: v(b, c) = sum_k p[k * stride + b * ld + c]  (np = 0: zero).
-// Independent instances (layers / directions working on different time steps) that one launch of a
-// step kernel can carry.
-constexpr int STEP_MAX_INST = 8;
 struct Planes { const float* p; int ld; int np; size_t stride; };
 // Number of k-blocks (= planes written) by launch_step_gemm for N output columns, contraction
 // length K and padded batch Bp (at most 8).
@@ -95,8 +92,7 @@ int step_kblocks(int prec, int N, int K, int Bp, int max_kb = 0);
 // on = 0: identity.
 struct DropSpec { unsigned long long key0 = 0; unsigned thresh = 0; float scale = 1.f; int width = 0; int on = 0; };
 
-// One recurrent step of one LSTM layer (or of both directions of the bottom encoder layer when
-// ndir = 2): gates = Gx + [x; h_prev] W^T, then the cell, fused.
+// One recurrent step of one decoder layer: gates = Gx + [x; h_prev] W^T, then the cell, fused.
 struct LstmFwdDir {
   const void* x;  int ldx;  int Kx;     // per-step input segment (T*, [Bp, Kx]); Kx = 0 if none
   const void* hprev; int ldh;           // previous state (T*, [Bp, Hh])
@@ -130,8 +126,7 @@ void launch_fm_pack(const void* src, int ld, int rows, int cols, void* dst, hipS
 // the same for the gate rows of an LSTM weight matrix: tile T holds units 4T .. 4T+3, row m of the tile is gate m % 4
 // of unit 4T + m / 4 (rows of W are gate-major: gate * Hh + unit); columns [col0, col0 + K) of W
 void launch_fm_pack_lstm_weights(const void* W, int ldw, int col0, int K, int Hh, void* dst, hipStream_t st);
-// ndir <= STEP_MAX_INST instances of equal hidden width Hh in one launch.
-void launch_lstm_fwd(int prec, const LstmFwdDir* dirs, int ndir, int Bp, int Hh, hipStream_t st);
+void launch_lstm_fwd(int prec, const LstmFwdDir& d, int Bp, int Hh, hipStream_t st);
 
 // [a0; a1] W^T for one step.  W rows are output columns; w0_off / w1_off are the column offsets
 // inside a weight row that pair with the two activation segments.
@@ -164,10 +159,6 @@ struct StepGemm {
   const float* bias = nullptr; int32_t* best_idx = nullptr;   // mode 2
 };
 void launch_step_gemm(int prec, const StepGemm& g, int Bp, hipStream_t st);
-// n <= STEP_MAX_INST instances in one launch (mode 1 only): same K0 + K1 and max_kb, N may differ; the
-// number of planes each instance writes is step_kblocks of the widest one.
-// n_plan > 0 fixes the width the k-block plan is made for (so that it does not change from launch to launch).
-void launch_step_gemm_multi(int prec, const StepGemm* gs, int n, int n_plan, int Bp, hipStream_t st);
 
 // Cell backward for one step of one layer: builds dgates (T*) from the incoming state gradients.
 struct LstmBwdPoint {
@@ -183,7 +174,6 @@ struct LstmBwdPoint {
   void* dg_fm = nullptr;               // optional fragment-major copy of dg (16-bit types; 4Hh / 32 k steps)
 };
 void launch_lstm_bwd_point(int prec, const LstmBwdPoint& p, int Bp, int Hh, hipStream_t st);
-void launch_lstm_bwd_point_multi(int prec, const LstmBwdPoint* ps, int n, int Bp, int Hh, hipStream_t st);
 // Backward step GEMM with the whole contraction inside the workgroup and the consumer of its result fused
 // into the epilogue: out[Bp, N] = dg[Bp, K] * Wt[N, K]^T, where the N output columns come in two parts
 // (part 0 first), each with its own epilogue:
@@ -191,13 +181,11 @@ void launch_lstm_bwd_point_multi(int prec, const LstmBwdPoint* ps, int n, int Bp
 //   BWD_EPI_CELL_DY   the values are the gradient arriving at the output of the LSTM step `cell` (the layer
 //                     below, same time step: dx of this layer), added to cell.dy; the cell backward runs
 //                     in-register and writes that step's dgates;
-//   BWD_EPI_CELL_REC  the values are the recurrent part of the state gradient of the LSTM step `cell` (this
-//                     layer, the next step of the backward loop: dh_prev), added to cell.dhrec;
 //   BWD_EPI_TANH      the values are the input-feed gradient of H_o of the previous decoder step:
 //                     dpre = (dce[pos[b]] + value) * drop * (1 - Ho^2), as launch_tanh_bwd computes it.
 // ncols of part 0 is a multiple of 16; both are multiples of 4.  hh = hidden width of `cell` (CELL_*) or the
 // row width of dce (TANH).
-enum { BWD_EPI_STORE = 0, BWD_EPI_CELL_DY = 1, BWD_EPI_CELL_REC = 2, BWD_EPI_TANH = 3 };
+enum { BWD_EPI_STORE = 0, BWD_EPI_CELL_DY = 1, BWD_EPI_TANH = 2 };
 struct BwdEpi {
   int kind = BWD_EPI_STORE; int ncols = 0; int hh = 0;
   float* out = nullptr; int ldout = 0;
@@ -214,14 +202,11 @@ struct StepBwd {
   // weight matrix, of which this instance's rows start at row tile wt_tile0 (16 rows per tile)
   const void* dg_fm = nullptr; const void* Wt_fm = nullptr; int wt_tile0 = 0;
 };
-constexpr int STEP_BWD_MAX_INST = 4;
 // Attention scores that ride in a step GEMM's launch: dots[b, i] = vec[b, :] . Mat[i, b, :] for i < len[b]
 // (Mat rows [S * Bp, ldm]: T*, or float* with mat_f32 set; vec rows [Bp, ldv]: T*; dots fp32 [Bp, S])
 struct AttScores { const void* Mat; int ldm; const void* vec; int ldv; const int32_t* len; int S, H; float* dots; int mat_f32; };
-// n independent instances in one launch (more than STEP_BWD_MAX_INST are spread over several launches).
-// With `scores` (n = 1) further workgroups of the launch compute those scores; they must depend on nothing the
-// instance writes.
-void launch_step_bwd_fused(int prec, const StepBwd* gs, int n, int Bp, hipStream_t st, const AttScores* scores = nullptr);
+// With `scores` further workgroups of the launch compute those scores; they must depend on nothing the GEMM writes.
+void launch_step_bwd_fused(int prec, const StepBwd& g, int Bp, hipStream_t st, const AttScores* scores = nullptr);
 
 // out[Bp, cols] = base (or 0) + planes columns col0 + [0, cols)
 void launch_planes_add(float* out, const float* base, const Planes& p, int col0, int Bp, int cols, hipStream_t st);
@@ -276,6 +261,42 @@ void launch_att_deferred(int prec, const float* a, const float* ds, const float*
 void launch_tanh_bwd(int prec, const float* dHo_ce, const int32_t* pos, const Planes& feed, const void* Ho, int ldho, void* dpre,
                      int ldp, int Bp, int H, const DropSpec& drop, hipStream_t st, void* dpre_fm = nullptr /* fragment-major copy */);
 
+// ---- recur.hip -----------------------------------------------------------------------------------
+// Bits of the device's error word: 1 a bad token id, 2 a bad length, 4 a loss that is not finite, and
+constexpr int CMT_FLAG_GAVE_UP = 8;       // a bounded wait between workgroups was given up
+// One LSTM (layer, direction) over all L positions, its input part batched into gx.
+struct SeqFwdDir {
+  const void* W; int ldw, wh_off;         // T* [4Hh, ldw], the recurrent columns start at wh_off
+  const float* gx;                        // [L, Bp, 4Hh] input pre-activations incl. bias
+  const float* mask;                      // [L, Bp]
+  void* X;                                // exchange buffer: T, L + 1 fragment-major slots of [Bp, Hh rounded up to 32]; slots that
+                                          //   the recurrence writes are filled with 0xff bytes beforehand (seq_exchange_elems)
+  void* H; int ldh;                       // states T*: L + 1 slots of [Bp, ldh]
+  float* C;                               // cell states: L + 1 slots of [Bp, Hh]
+  float* G;                               // gate activations [L, Bp, 4Hh]
+  void* Y; int ldy, y_col0;               // optional copy of the states after dropout: T* [L, Bp, ldy], columns y_col0 + [0, Hh)
+  DropSpec drop; unsigned long long drop_step;   // dropout at position t: drop with key0 + t * drop_step
+  int reverse;                            // positions run from L - 1 to 0: position t reads slot t + 1, writes slot t
+};
+struct SeqFwdArgs { SeqFwdDir d[2]; int* ticket; int* flags; };   // ticket: zero before the launch
+constexpr int SEQ_TICKETS = 64;
+inline size_t seq_exchange_elems(int slots, int Bp, int Hh) { return (size_t)slots * Bp * ((Hh + 31) / 32 * 32); }
+// Backward of the same: builds the gate gradients of every position.
+struct SeqBwdDir {
+  const void* Wt; int ldw;                // T* [Hh, ldw]: row u = the recurrent column u of W, contiguous over the 4Hh gate rows
+  const float* dY; int lddy, dy_col;      // [L, Bp, lddy] gradient at the outputs: columns dy_col + [0, Hh)
+  DropSpec drop; unsigned long long drop_step;   // dropout between this layer and its consumer, as in SeqFwdDir
+  const float* mask; const float* G; const float* C;   // as the forward pass left them
+  const float* dh0; const float* dc0; int ldd0;  // gradient of the final state, rows [Bp, ldd0]
+  void* X;                                // exchange buffer: T, L fragment-major slots of [Bp, 4Hh], filled with 0xff bytes
+  void* dG; int lddg;                     // gate gradients T*: L slots of [Bp, lddg]
+  int reverse;                            // the direction of the forward pass
+};
+struct SeqBwdArgs { SeqBwdDir d[2]; int* ticket; int* flags; };
+void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st);
+// Forward: the initial states are zero (the slots before the first position are not read).  1 <= ndir <= 2 instances of one shape.
+void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st);
+
 // ---- misc.hip ----------------------------------------------------------------------------------
 // Embedding gather + masks + input validation (flags |= 1 bad id, |= 2 bad length).
 // ids [B, L] row-major; out[t, b, :] = table[shift ? (t == 0 ? bos : ids[b, t-1]) : ids[b, t]] as T;
@@ -293,9 +314,9 @@ void launch_cast(int prec, const float* src, void* dst, size_t n, hipStream_t st
 // 2-D copies with pitches (elements): fp32 -> fp32, T -> T.
 void launch_copy2d_f32(const float* src, int lds, float* dst, int ldd, int rows, int cols, hipStream_t st);
 // Several small zero-fills / 2-D copies in one launch each (the state initialisations of a step), in units of
-// 32-bit words: a fill clears `words` words at p; a copy moves rows x cols words with row pitches lds / ldd.
+// 32-bit words: a fill sets `words` words at p to `value`; a copy moves rows x cols words with row pitches lds / ldd.
 constexpr int MULTI_MAX_JOBS = 32;
-struct FillJob { void* p; size_t words; };
+struct FillJob { void* p; size_t words; uint32_t value = 0; };
 struct CopyJob { const void* src; int lds; void* dst; int ldd; int rows; int cols; };
 void launch_fill_multi(const FillJob* jobs, int n, hipStream_t st);
 void launch_copy2d_multi(const CopyJob* jobs, int n, hipStream_t st);

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void fill_multi_kernel(FillJobs jobs) {
   const FillJob& job = jobs.j[blockIdx.y];
   uint32_t* p = (uint32_t*)job.p;
   const size_t stride = (size_t)gridDim.x * 256;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < job.words; i += stride) p[i] = 0u;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < job.words; i += stride) p[i] = job.value;
 }
 __global__ __launch_bounds__(256) void copy2d_multi_kernel(CopyJobs jobs) {
   const CopyJob& job = jobs.j[blockIdx.y];

@@ -1,0 +1,539 @@
+// Whole recurrences in one launch: the time loop of an LSTM layer whose input part is batched over time (both
+// directions of the bottom encoder layer, the upper encoder layers), run by workgroups that stay on the chip for all
+// positions and keep their share of the recurrent weights in registers.
+//
+// Sentences do not interact, so a launch is a set of independent groups: one group = one (layer, direction) on 16 BT
+// sentences, its hidden units spread over the group's workgroups.  What a position must exchange is the new state (backward:
+// the gate gradients) of the group's sentences: every workgroup needs all units of the previous position.  It travels
+// through device memory, in the fragment-major layout the matrix cores take, one slot per position:
+//   * a slot is filled with 0xff bytes before the launch and written once, by 8-byte (fp32: 4-byte) agent-scope stores,
+//     which go to memory; the data never contains that bit pattern (NaNs are made canonical), so a reader that finds it
+//     reads again.  The data is its own flag: one store and one load per position, no fence, barrier or counter;
+//   * a reader first loads through its caches (a line that another workgroup of the same L2 has fetched complete is
+//     complete for good: nothing in a slot is written twice) and, where it finds something empty, again from memory
+//     with agent-scope loads.  It sleeps for about the time that a store takes to be visible before it looks: looking
+//     earlier costs more than it gains, since the reads then stand in the way of the stores they wait for.
+// Roles are taken from a ticket counter, in order of arrival, so that the workgroups on the chip always form complete
+// groups and at most one incomplete one per launch: as long as no more than 256 / (group size) such launches run at
+// once (a process has four hardware queues, the largest group is 64), a workgroup can always start and complete a group.
+// Every wait is bounded all the same and reports an error (recur_settle).
+//
+// What a position costs (bf16, us; before: one launch per position, 8.5 - 9, upper layers forward 5.6 of a shared one):
+// forward 1.2 (width 256, 32 sentences), 1.7 (512, 64 sentences, two directions), 2.7 (1024, 64 sentences), 3.1 (512, 128
+// sentences, two directions); backward 2.1, 3.0, 4.8 beside the second stream's GEMMs.  About 0.5 of it is the store on
+// its way to memory, 0.5 the load, the rest contraction, reduction and cell; at 128 sentences also the volume.
+#include <stdlib.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "cell.h"
+#include "common.h"
+#include "kernels.h"
+
+namespace cmt {
+
+constexpr unsigned RECUR_EMPTY = 0xffffffffu;          // a word of a slot that nobody has written
+constexpr long long RECUR_WAIT_TICKS = 1000000000ll;   // 10 s of the 100 MHz wall clock, then the wait is given up
+// s_sleep units (64 clocks) before a workgroup looks for its neighbours' results.  Measured per launch: forward, one tile of
+// sentences 14: 123 us, 20: 87, 26: 92 (width 512, 64 sentences, 50 positions); two tiles 20: 287, 28: 254, 40: 253 (128
+// sentences, 80 positions); backward 28: 262, 36: 240, 44: 225 and no change beyond (width 1024).
+constexpr int RECUR_NAP_FWD = 20, RECUR_NAP_FWD2 = 28, RECUR_NAP_BWD = 42;
+
+// one 16-byte (32-byte for float) fragment of a slot; `top` becomes RECUR_EMPTY if any of its pieces is still empty
+__device__ __forceinline__ void recur_load(const bf16_t* p, Frag<bf16_t>& f, unsigned& top) {
+  const uint64_t a = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t b = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  f.v = make_uint4((unsigned)a, (unsigned)(a >> 32), (unsigned)b, (unsigned)(b >> 32));
+  top = max(top, max(f.v.x, f.v.z));                   // pieces of 8 bytes are written whole
+}
+__device__ __forceinline__ void recur_load(const float* p, Frag<float>& f, unsigned& top) {
+  uint64_t v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p) + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  unsigned w[8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { w[2 * i] = (unsigned)v[i]; w[2 * i + 1] = (unsigned)(v[i] >> 32); }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) top = max(top, w[i]);    // pieces of 4 bytes
+  f.lo = make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), __uint_as_float(w[3]));
+  f.hi = make_float4(__uint_as_float(w[4]), __uint_as_float(w[5]), __uint_as_float(w[6]), __uint_as_float(w[7]));
+}
+
+// Where the four gate sums of (sentence, unit 4 rt + q of the workgroup) lie in a 16-byte-grained tile of partial
+// sums: written sentence by sentence, read unit by unit, both free of bank conflicts.
+__device__ __forceinline__ int recur_pos(int sentence, int q, int rt) { return q * 16 + (sentence ^ ((q + 4 * rt) & 15)); }
+// this lane's 16-bit value and its neighbour's (lane ^ 1), the even lane's in the lower half of the even lane's result
+__device__ __forceinline__ unsigned quad_pair(bf16_t v) {
+  return (unsigned)v | ((unsigned)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, true) << 16);
+}
+
+__device__ __forceinline__ unsigned recur_top(const Frag<bf16_t>& f) { return max(f.v.x, f.v.z); }
+__device__ __forceinline__ unsigned recur_top(const Frag<float>& f) {
+  unsigned t = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) t = max(t, __float_as_uint(f.get(i)));
+  return t;
+}
+// N fragments of a slot, each at a uniform base p[i] plus this lane's offset; in[i]: whether this lane has a part in it
+// (else zero).  First through the caches, which usually finds everything there (the wavefront has slept for about the
+// time that a store takes to be visible); while any piece is still empty, again from memory.  `dead`: a wait has been
+// given up before, take what there is.
+template <typename T, int N>
+__device__ __forceinline__ void recur_issue(const T* const (&p)[N], const bool (&in)[N], unsigned off, Frag<T> (&f)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    f[i].zero();
+    if (in[i]) f[i].load(p[i] + off);
+  }
+}
+template <typename T, int N>
+__device__ __forceinline__ void recur_settle(const T* const (&p)[N], const bool (&in)[N], unsigned off, Frag<T> (&f)[N], bool& dead,
+                                             int* flags) {
+  unsigned top = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) top = max(top, recur_top(f[i]));
+  if (dead || !__any(top == RECUR_EMPTY)) return;
+  long long t_end = 0;
+  for (int spin = 0;; ++spin) {
+    top = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (in[i]) recur_load(p[i] + off, f[i], top);
+    if (!__any(top == RECUR_EMPTY)) return;
+    if ((spin & 255) == 255) {
+      const long long now = wall_clock64();
+      if (t_end == 0) t_end = now + RECUR_WAIT_TICKS;
+      else if (now > t_end) {
+        dead = true;
+        if ((threadIdx.x & 63) == 0) atomicOr(flags, CMT_FLAG_GAVE_UP);
+        return;
+      }
+    }
+  }
+}
+// about n * 64 clocks
+__device__ __forceinline__ void recur_nap(int n) { for (int z = 0; z < n; ++z) __builtin_amdgcn_s_sleep(1); }
+
+// The same for the backward kernel's tiles: the sums of units 4 q .. 4 q + 3 of row tile rt for a sentence.
+__device__ __forceinline__ int recur_pos_bwd(int sentence, int q, int rt) { return q * 16 + (sentence ^ (4 * q + 2 * (rt & 1))); }
+// 4 x 4 transpose of 16-bit values over the lanes of a quad: lane j of the quad brings gates 0..3 of its unit and receives
+// gate j of the quad's four units.
+__device__ __forceinline__ uint64_t quad_transpose(bf16_t g0, bf16_t g1, bf16_t g2, bf16_t g3, int lane) {
+  const unsigned a = (unsigned)g0 | ((unsigned)g1 << 16), b = (unsigned)g2 | ((unsigned)g3 << 16);
+  const unsigned ax = __builtin_amdgcn_mov_dpp((int)a, 0xb1, 0xf, 0xf, true), bx = __builtin_amdgcn_mov_dpp((int)b, 0xb1, 0xf, 0xf, true);
+  // after the exchange with lane ^ 1: an even lane holds gates 0 and 2 of the pair's two units, an odd one gates 1 and 3
+  const bool odd = lane & 1;
+  const unsigned p = odd ? (ax >> 16) | (a & 0xffff0000u) : (a & 0xffffu) | (ax << 16);
+  const unsigned q = odd ? (bx >> 16) | (b & 0xffff0000u) : (b & 0xffffu) | (bx << 16);
+  // after the exchange with lane ^ 2: lanes 0, 1 of the quad hold gates 0, 1 of all four units, lanes 2, 3 gates 2, 3
+  const bool high = lane & 2;
+  const unsigned px = __builtin_amdgcn_mov_dpp((int)p, 0x4e, 0xf, 0xf, true), qx = __builtin_amdgcn_mov_dpp((int)q, 0x4e, 0xf, 0xf, true);
+  return high ? (uint64_t)qx | ((uint64_t)q << 32) : (uint64_t)p | ((uint64_t)px << 32);
+}
+
+template <typename T, int KS, int NK, int RT, int BT, int NE>
+__global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs args, int L, int Bp, int Hh, int ndir, int nap) {
+  __shared__ __align__(16) float red[2][KS * RT * BT * 256];
+  __shared__ int s_id;
+  if (threadIdx.x == 0) s_id = atomicAdd(args.ticket, 1);
+  __syncthreads();
+  const int nwg = (Hh + 4 * RT - 1) / (4 * RT);                  // workgroups per group
+  const int grp = s_id / nwg, u0 = (s_id - grp * nwg) * 4 * RT;
+  const SeqFwdDir d = args.d[grp % ndir];
+  const int bt0 = (grp / ndir) * BT;
+  const int nbt = min(BT, (Bp >> 4) - bt0);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nsteps = (Hh + 31) >> 5;
+  const size_t slot = (size_t)(Bp >> 4) * nsteps * 512;          // elements per slot of the exchange buffer
+  const int rev = d.reverse;
+  if (w < KS) {
+    // ---- contraction: wavefront w takes the k steps w, w + KS, ...; its weights stay in registers -----------------
+    Frag<T> wf[NK][RT];
+    bool kin[NK];
+#pragma unroll
+    for (int q = 0; q < NK; ++q) {
+      const int k = 32 * (w + KS * q) + 8 * (lane >> 4);
+      kin[q] = k < Hh;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const int m = lane & 15, u = min(u0 + 4 * rt + (m >> 2), Hh - 1);
+        if (kin[q]) wf[q][rt].load((const T*)d.W + (size_t)((m & 3) * Hh + u) * d.ldw + d.wh_off + k);
+        else wf[q][rt].zero();
+      }
+    }
+    bool dead = false;
+    for (int i = 0; i < L; ++i) {
+      if (i > 0) {
+        const T* x = (const T*)d.X + (size_t)(rev ? L - i : i) * slot + (size_t)bt0 * nsteps * 512;
+        Frag<T> fx[NK * BT];
+        const T* px[NK * BT];
+        bool in[NK * BT];
+#pragma unroll
+        for (int q = 0; q < NK; ++q)
+#pragma unroll
+          for (int b = 0; b < BT; ++b) {
+            px[q * BT + b] = x + ((size_t)b * nsteps + w + KS * q) * 512;
+            in[q * BT + b] = kin[q] && b < nbt;
+          }
+        recur_nap(nap);
+        recur_issue<T, NK * BT>(px, in, lane * 8, fx);
+        recur_settle<T, NK * BT>(px, in, lane * 8, fx, dead, args.flags);
+        v4f acc[RT][BT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int b = 0; b < BT; ++b) acc[rt][b] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < NK; ++q)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int b = 0; b < BT; ++b) mma16(acc[rt][b], wf[q][rt], fx[q * BT + b]);
+        float* r = red[i & 1];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int b = 0; b < BT; ++b) 
+            *reinterpret_cast<v4f*>(r + (((w * RT + rt) * BT + b) * 64 + recur_pos(lane & 15, lane >> 4, rt)) * 4) = acc[rt][b];
+      }
+      __syncthreads();
+    }
+    return;
+  }
+  // ---- cells: one per lane and pass; cell and hidden state stay in registers ---------------------------------------
+  // A wavefront takes all units of its workgroup for 64 / UW sentences, so that what it reads and writes per sentence is
+  // one contiguous piece (with the accumulator's own mapping, 4 units x 16 sentences, the same data is 4 times as many
+  // cache requests, and those were what a position waited for).  Addresses are a uniform base per position plus a
+  // 32-bit lane offset that never changes: the instructions of this path are on every position's critical path.
+  constexpr int UW = 4 * RT;
+  const int e = w - KS, passes = nbt * RT;
+  auto cells = [&](auto count) {
+    constexpr int NA = decltype(count)::value;
+    constexpr bool FAST = sizeof(T) == 2;
+    const int u = min(u0 + lane % UW, Hh - 1), uw = u - u0;        // (surplus lanes repeat the last unit)
+    const bool sender = !FAST || (lane % 4 == 0 && u0 + lane % UW < Hh);
+    float c[NA], hcar[NA];
+    unsigned off_r[NA], off_u[NA], off_g[NA], off_m[NA], off_x[NA], off_h[NA], off_y[NA];
+    int row[NA];
+#pragma unroll
+    for (int n = 0; n < NA; ++n) {
+      c[n] = 0.f; hcar[n] = 0.f;
+      const int b = 16 * bt0 + lane / UW + (e + NE * n) * (64 / UW), bt = (b >> 4) - bt0;
+      row[n] = b;
+      off_r[n] = (unsigned)(((uw >> 2) * BT + bt) * 1024 + recur_pos(b & 15, uw & 3, uw >> 2) * 16);
+      off_u[n] = (unsigned)(b * Hh + u) * 4u;
+      off_g[n] = (unsigned)(b * 4 * Hh + u) * 4u;
+      off_m[n] = (unsigned)b * 4u;
+      off_x[n] = (unsigned)(fm_offset(b, u, nsteps) * sizeof(T));
+      off_h[n] = (unsigned)((b * d.ldh + u) * sizeof(T));
+      off_y[n] = (unsigned)((b * d.ldy + d.y_col0 + u) * sizeof(T));
+    }
+    struct In { float g[NA][4]; float mask[NA]; };
+    auto fetch = [&](In& in, int i) {
+      const int t = rev ? L - 1 - i : i;
+      const char* g = (const char*)(d.gx + (size_t)t * Bp * 4 * Hh);
+      const char* m = (const char*)(d.mask + (size_t)t * Bp);
+#pragma unroll
+      for (int n = 0; n < NA; ++n) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) in.g[n][q] = *(const float*)(g + (size_t)q * Hh * 4 + off_g[n]);
+        in.mask[n] = *(const float*)(m + off_m[n]);
+      }
+    };
+    // The inputs of the next position are requested before this one's results are stored: loads and stores complete in
+    // order, so the other way round every position would wait until its predecessor's stores have reached memory.
+    auto step = [&](const In& in, In& next, int i) {
+      const int t = rev ? L - 1 - i : i, sn = rev ? t : t + 1;
+      char* const xs = (char*)d.X + (size_t)sn * slot * sizeof(T);
+      char* const hs = (char*)d.H + (size_t)sn * Bp * d.ldh * sizeof(T);
+      char* const cs = (char*)(d.C + (size_t)sn * Bp * Hh);
+      char* const gs = (char*)(d.G + (size_t)t * Bp * 4 * Hh);
+      char* const ys = (char*)d.Y + (size_t)t * Bp * d.ldy * sizeof(T);
+      const DropSpec drop = seq_drop(d.drop, d.drop_step, t);
+      const bool has_y = d.Y != nullptr;
+      __syncthreads();
+      fetch(next, min(i + 1, L - 1));
+      asm volatile("" ::: "memory");
+      const char* r = (const char*)red[i & 1];
+#pragma unroll
+      for (int n = 0; n < NA; ++n) {
+        v4f pre = v4f{0.f, 0.f, 0.f, 0.f};
+        if (i > 0) {
+#pragma unroll
+          for (int k = 0; k < KS; ++k) pre += *reinterpret_cast<const v4f*>(r + off_r[n] + k * RT * BT * 1024);
+        }
+        const float ig = sigm_of<FAST>(pre[0] + in.g[n][0]), fg = sigm_of<FAST>(pre[1] + in.g[n][1]);
+        const float gg = tanh_of<FAST>(pre[2] + in.g[n][2]), og = sigm_of<FAST>(pre[3] + in.g[n][3]);
+        const float cn = fg * c[n] + ig * gg;
+        const float hn = og * tanh_of<FAST>(cn);
+        if (in.mask[n] > 0.f) { c[n] = cn; hcar[n] = hn != hn ? __uint_as_float(0x7fc00000u) : hn; }
+        T hv;
+        if constexpr (FAST) {
+          hv = f2bf(hcar[n]);
+          hcar[n] = bf2f(hv);                                      // (what a masked step carries on is the stored value)
+          const unsigned p = quad_pair(hv), p2 = __builtin_amdgcn_mov_dpp(p, 0x4e, 0xf, 0xf, true);      // lanes ^ 2
+          if (sender)
+            __hip_atomic_store(reinterpret_cast<uint64_t*>(xs + off_x[n]), (uint64_t)p | ((uint64_t)p2 << 32), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+          hv = hcar[n];
+          __hip_atomic_store(reinterpret_cast<unsigned*>(xs + off_x[n]), __float_as_uint(hv), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        asm volatile("" ::: "memory");                             // (the state first: the other workgroups wait for it)
+        *(T*)(hs + off_h[n]) = hv;
+        *(float*)(cs + off_u[n]) = c[n];
+        *(float*)(gs + off_g[n]) = ig;
+        *(float*)(gs + (size_t)Hh * 4 + off_g[n]) = fg;
+        *(float*)(gs + (size_t)Hh * 8 + off_g[n]) = gg;
+        *(float*)(gs + (size_t)Hh * 12 + off_g[n]) = og;
+        if (has_y) *(T*)(ys + off_y[n]) = from_f<T>(hcar[n] * drop_factor(drop, row[n], d.y_col0 + u));
+      }
+    };
+    In in0, in1;
+    fetch(in0, 0);
+    for (int i = 0; i < L; i += 2) {                              // two positions per round: no copies between the input sets
+      step(in0, in1, i);
+      if (i + 1 < L) step(in1, in0, i + 1);
+    }
+  };
+  constexpr int NT = (RT * BT + NE - 1) / NE;                     // passes per wavefront
+  if (e >= passes) { for (int i = 0; i < L; ++i) __syncthreads(); }
+  else if (NT == 1 || e + NE >= passes) cells(std::integral_constant<int, 1>{});
+  else cells(std::integral_constant<int, NT>{});
+}
+
+// ------------------------------------------------------------------------------------------------
+// backward
+// ------------------------------------------------------------------------------------------------
+// The recurrent part of the state gradient, dG(next position) W_h, has the 4 Hh gate gradients as its contraction
+// length: a workgroup owns 16 RT units (rows of W^T), its KS wavefronts split the gate rows and keep their share of W^T
+// in registers, and what the group exchanges per position is its gate gradients.  The fragments of a position arrive CH at
+// a time, the next ones in flight while the matrix cores take the current ones.
+template <typename T, int KS, int NK, int RT, int NE>
+__global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_bwd_kernel(SeqBwdArgs args, int L, int Bp, int Hh, int ndir, int nap) {
+  constexpr int CH = NK * RT * (int)sizeof(Frag<T>) >= 512 ? (sizeof(T) == 2 ? 2 : 1) : NK < 4 ? NK : 4;   // (registers: weights and two chunks)
+  __shared__ __align__(16) float red[2][KS * RT * 256];
+  __shared__ int s_id;
+  if (threadIdx.x == 0) s_id = atomicAdd(args.ticket, 1);
+  __syncthreads();
+  const int nwg = (Hh + 16 * RT - 1) / (16 * RT);
+  const int grp = s_id / nwg, u0 = (s_id - grp * nwg) * 16 * RT;
+  const SeqBwdDir d = args.d[grp % ndir];
+  const int bt = grp / ndir;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nsteps = Hh >> 3;                                    // k steps of 32 gate rows
+  const size_t slot = (size_t)Bp * 4 * Hh;                       // elements per slot
+  const int rev = d.reverse;                                     // of the forward pass: positions run upwards here
+  if (w < KS) {
+    Frag<T> wf[NK][RT];
+#pragma unroll
+    for (int q = 0; q < NK; ++q)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const int s = w + KS * q, u = min(u0 + 16 * rt + (lane & 15), Hh - 1);
+        if (s < nsteps) wf[q][rt].load((const T*)d.Wt + (size_t)u * d.ldw + 32 * s + 8 * (lane >> 4));
+        else wf[q][rt].zero();
+      }
+    bool dead = false;
+    for (int i = 0; i < L; ++i) {
+      if (i > 0) {
+        const T* x = (const T*)d.X + (size_t)(rev ? i - 1 : L - i) * slot + (size_t)bt * nsteps * 512;
+        v4f acc[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) acc[rt] = v4f{0.f, 0.f, 0.f, 0.f};
+        recur_nap(nap);
+        Frag<T> fx[2][CH];
+        const T* p[2][CH];
+        bool in[2][CH];
+        auto issue = [&](int c) {
+#pragma unroll
+          for (int q = 0; q < CH; ++q) {
+            const int s = w + KS * (c * CH + q);
+            p[c & 1][q] = x + (size_t)s * 512;
+            in[c & 1][q] = s < nsteps;
+          }
+          recur_issue<T, CH>(p[c & 1], in[c & 1], lane * 8, fx[c & 1]);
+        };
+        issue(0);
+#pragma unroll
+        for (int c = 0; c < NK / CH; ++c) {
+          asm volatile("" ::: "memory");                         // (no more than two chunks in flight: registers)
+          if (c + 1 < NK / CH) issue(c + 1);
+          recur_settle<T, CH>(p[c & 1], in[c & 1], lane * 8, fx[c & 1], dead, args.flags);
+#pragma unroll
+          for (int q = 0; q < CH; ++q)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) mma16(acc[rt], wf[c * CH + q][rt], fx[c & 1][q]);
+        }
+        float* r = red[i & 1];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          *reinterpret_cast<v4f*>(r + ((w * RT + rt) * 64 + recur_pos_bwd(lane & 15, lane >> 4, rt)) * 4) = acc[rt];
+      }
+      __syncthreads();
+    }
+    return;
+  }
+  constexpr int UW = 16 * RT, NT = (4 * RT + NE - 1) / NE;
+  static_assert(4 * RT % NE == 0, "every cell wavefront has the same number of passes");
+  constexpr bool FAST = sizeof(T) == 2;
+  const int e = w - KS;
+  const int u = min(u0 + lane % UW, Hh - 1), uw = u - u0;          // (surplus lanes repeat the last unit)
+  const bool real = u0 + lane % UW < Hh;
+  const int gate = lane & 3, u4 = u & ~3;                        // 16-bit types: the lane stores this gate of units u4 .. u4 + 3
+  float cn[NT], dh[NT], dc[NT];
+  unsigned off_r[NT], off_u[NT], off_g[NT], off_m[NT], off_x[NT], off_d[NT], off_y[NT];
+  int row[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const int sb = lane / UW + (e + NE * n) * (64 / UW), b = 16 * bt + sb;
+    row[n] = b;
+    off_r[n] = (unsigned)((uw >> 4) * 1024 + recur_pos_bwd(sb, (uw >> 2) & 3, uw >> 4) * 16 + (uw & 3) * 4);
+    off_u[n] = (unsigned)(b * Hh + u) * 4u;
+    off_g[n] = (unsigned)(b * 4 * Hh + u) * 4u;
+    off_m[n] = (unsigned)b * 4u;
+    off_y[n] = (unsigned)(b * d.lddy + d.dy_col + u) * 4u;
+    if constexpr (FAST) {
+      off_x[n] = (unsigned)(fm_offset(b, gate * Hh + u4, nsteps) * sizeof(T));
+      off_d[n] = (unsigned)((b * d.lddg + gate * Hh + u4) * sizeof(T));
+    } else {
+      off_x[n] = (unsigned)(fm_offset(b, u, nsteps) * sizeof(T));       // gate q: Hh / 32 k steps further on, or recomputed
+      off_d[n] = (unsigned)((b * d.lddg + u) * sizeof(T));
+    }
+    cn[n] = *(const float*)((const char*)(d.C + (size_t)(rev ? 0 : L) * Bp * Hh) + off_u[n]);
+    dh[n] = d.dh0[(size_t)b * d.ldd0 + u];
+    dc[n] = d.dc0[(size_t)b * d.ldd0 + u];
+  }
+  struct In { float g[NT][4]; float cp[NT], dy[NT], mask[NT]; };
+  auto fetch = [&](In& in, int i) {
+    const int t = rev ? i : L - 1 - i;
+    const char* g = (const char*)(d.G + (size_t)t * Bp * 4 * Hh);
+    const char* c = (const char*)(d.C + (size_t)(rev ? t + 1 : t) * Bp * Hh);
+    const char* y = (const char*)(d.dY + (size_t)t * Bp * d.lddy);
+    const char* m = (const char*)(d.mask + (size_t)t * Bp);
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) in.g[n][q] = *(const float*)(g + (size_t)q * Hh * 4 + off_g[n]);
+      in.cp[n] = *(const float*)(c + off_u[n]);
+      in.dy[n] = *(const float*)(y + off_y[n]);
+      in.mask[n] = *(const float*)(m + off_m[n]);
+    }
+  };
+  auto step = [&](const In& in, In& next, int i) {
+    const int t = rev ? i : L - 1 - i;
+    char* const xs = (char*)d.X + (size_t)t * slot * sizeof(T);
+    char* const ds = (char*)d.dG + (size_t)t * Bp * d.lddg * sizeof(T);
+    const DropSpec drop = seq_drop(d.drop, d.drop_step, t);
+    // what does not wait for the recurrent part: dy's share and the factors of the cell backward
+    float dyf[NT], tc[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      dyf[n] = in.dy[n] * drop_factor(drop, row[n], d.dy_col + u);
+      tc[n] = tanh_of<FAST>(cn[n]);
+    }
+    __syncthreads();
+    fetch(next, min(i + 1, L - 1));
+    asm volatile("" ::: "memory");
+    const char* r = (const char*)red[i & 1];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      float rec = 0.f;
+      if (i > 0) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) rec += *reinterpret_cast<const float*>(r + off_r[n] + k * RT * 1024);
+      }
+      const bool valid = in.mask[n] > 0.f;
+      const float ig = in.g[n][0], fg = in.g[n][1], gg = in.g[n][2], og = in.g[n][3];
+      const float state = dh[n] + rec;
+      const float dht = state + dyf[n];
+      const float dct = dc[n] + dht * og * (1.f - tc[n] * tc[n]);
+      float o[4] = {dct * gg * ig * (1.f - ig), dct * in.cp[n] * fg * (1.f - fg), dct * ig * (1.f - gg * gg),
+                    dht * tc[n] * og * (1.f - og)};
+      dh[n] = valid ? 0.f : state;                                 // masked: the state's gradient passes through
+      dc[n] = valid ? dct * fg : dc[n];
+      cn[n] = in.cp[n];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        o[q] = valid ? o[q] : 0.f;
+        if (o[q] != o[q]) o[q] = __uint_as_float(0x7fc00000u);
+      }
+      if constexpr (FAST) {
+        const uint64_t v = quad_transpose(f2bf(o[0]), f2bf(o[1]), f2bf(o[2]), f2bf(o[3]), lane);
+        if (real) {
+          __hip_atomic_store(reinterpret_cast<uint64_t*>(xs + off_x[n]), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          *reinterpret_cast<uint64_t*>(ds + off_d[n]) = v;
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const size_t xo = fm_offset(row[n], q * Hh + u, nsteps) * sizeof(T);
+          __hip_atomic_store(reinterpret_cast<unsigned*>(xs + xo), __float_as_uint(o[q]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *(float*)(ds + (size_t)q * Hh * 4 + off_d[n]) = o[q];
+      }
+    }
+  };
+  In in0, in1;
+  fetch(in0, 0);
+  for (int i = 0; i < L; i += 2) {
+    step(in0, in1, i);
+    if (i + 1 < L) step(in1, in0, i + 1);
+  }
+}
+
+template <typename T, int KS, int NK, int RT, int NE>
+static void seq_bwd_go(const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+  const int groups = ndir * (Bp >> 4), nwg = (Hh + 16 * RT - 1) / (16 * RT);
+  hipLaunchKernelGGL((lstm_seq_bwd_kernel<T, KS, NK, RT, NE>), dim3(groups * nwg), dim3(64 * (KS + NE)), 0, st, a, L, Bp, Hh, ndir,
+                     RECUR_NAP_BWD);
+}
+template <int KS, int NK>
+static void seq_bwd_rt(int prec, const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+  const int wgs = ndir * (Bp >> 4) * ((Hh + 15) / 16);
+  if (!prec) seq_bwd_go<float, KS, NK, 1, 4>(a, ndir, L, Bp, Hh, st);
+  else if (wgs <= 128) seq_bwd_go<bf16_t, KS, NK, 1, 4>(a, ndir, L, Bp, Hh, st);
+  else seq_bwd_go<bf16_t, KS, NK, 2, (NK > 8 ? 4 : 8)>(a, ndir, L, Bp, Hh, st);
+}
+void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+  const int nsteps = Hh / 8;
+  if (nsteps <= 4) seq_bwd_rt<2, 2>(prec, a, ndir, L, Bp, Hh, st);
+  else if (nsteps <= 16) seq_bwd_rt<8, 2>(prec, a, ndir, L, Bp, Hh, st);
+  else if (nsteps <= 32) seq_bwd_rt<8, 4>(prec, a, ndir, L, Bp, Hh, st);
+  else if (nsteps <= 64) seq_bwd_rt<8, 8>(prec, a, ndir, L, Bp, Hh, st);
+  else seq_bwd_rt<8, 16>(prec, a, ndir, L, Bp, Hh, st);
+}
+
+template <typename T, int KS, int NK, int RT, int BT, int NE>
+static void seq_fwd_go(const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+  const int groups = ndir * (((Bp >> 4) + BT - 1) / BT), nwg = (Hh + 4 * RT - 1) / (4 * RT);
+  hipLaunchKernelGGL((lstm_seq_fwd_kernel<T, KS, NK, RT, BT, NE>), dim3(groups * nwg), dim3(64 * (KS + NE)), 0, st, a, L, Bp, Hh, ndir, BT == 1 ? RECUR_NAP_FWD : RECUR_NAP_FWD2);
+}
+template <typename T, int KS, int NK, int RT, int NE2>
+static void seq_fwd_bt(const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+  // one tile of sentences per group while that is one round of workgroups over the chip, else two
+  const int wgs = ndir * (Bp >> 4) * ((Hh + 4 * RT - 1) / (4 * RT));
+  if (wgs <= 256) seq_fwd_go<T, KS, NK, RT, 1, 4>(a, ndir, L, Bp, Hh, st);
+  else seq_fwd_go<T, KS, NK, RT, 2, NE2>(a, ndir, L, Bp, Hh, st);
+}
+
+void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+  const int nsteps = (Hh + 31) / 32;
+  // (registers: twice as many cell wavefronts for two tiles of sentences where 128 per lane are enough; half as many
+  // units per workgroup for long fp32 rows)
+#define GO(KS, NK, RTF, NE2)                                                    \
+  do {                                                                          \
+    if (prec) seq_fwd_bt<bf16_t, KS, NK, 4, NE2>(a, ndir, L, Bp, Hh, st);       \
+    else seq_fwd_bt<float, KS, NK, RTF, 4>(a, ndir, L, Bp, Hh, st);             \
+  } while (0)
+  if (nsteps <= 2) GO(2, 1, 4, 4);
+  else if (nsteps <= 4) GO(2, 2, 4, 4);
+  else if (nsteps <= 8) GO(8, 1, 4, 8);
+  else if (nsteps <= 16) GO(8, 2, 4, 8);
+  else GO(8, 4, 2, 4);
+#undef GO
+}
+
+}  // namespace cmt

@@ -17,7 +17,9 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <type_traits>
 
+#include "cell.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -26,8 +28,6 @@ namespace cmt {
 constexpr int STEP_MAXBT = 4;          // batch tiles (of 16 sentences) per workgroup
 
 struct StepGrid { int nx, kb, nz; };
-struct StepGemmArgs { StepGemm g[STEP_MAX_INST]; };
-struct LstmBwdPointArgs { LstmBwdPoint p[STEP_MAX_INST]; };
 __device__ __forceinline__ bool decode_block(const StepGrid& g, int& x, int& kb, int& z) {
   const int L = blockIdx.x;
   const int xcd = L & 7;
@@ -191,17 +191,6 @@ __device__ __forceinline__ void att_dots_row(const MT* __restrict__ Mat, int ldm
   if (lane == 0) dots[(size_t)b * S + i] = a;
 }
 
-// keep-and-rescale factor of element (b, col) of a dropout slice (see DropSpec)
-__device__ __forceinline__ float drop_factor(const DropSpec& d, int b, int col) {
-  if (!d.on) return 1.f;
-  unsigned long long x = d.key0 + (unsigned long long)b * (unsigned long long)d.width + (unsigned long long)col;
-  x += 0x9E3779B97F4A7C15ull;
-  x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
-  x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
-  x ^= x >> 31;
-  return (unsigned)(x >> 40) >= d.thresh ? d.scale : 0.f;
-}
-
 __device__ __forceinline__ float planes_get(const Planes& p, int b, int c) {
   float v = 0.f;
   for (int k = 0; k < p.np; ++k) v += p.p[(size_t)k * p.stride + (size_t)b * p.ld + c];
@@ -257,8 +246,6 @@ void launch_fm_pack_lstm_weights(const void* W, int ldw, int col0, int K, int Hh
 // ------------------------------------------------------------------------------------------------
 // LSTM forward step
 // ------------------------------------------------------------------------------------------------
-struct LstmFwdArgs { LstmFwdDir d[STEP_MAX_INST]; };
-
 // everything the cell update of one (sentence, unit) reads besides the GEMM result; loaded before the
 // contraction so that its latency hides behind the weight stream
 struct CellIn { float add[4]; float cp, hp, mask; };
@@ -305,37 +292,29 @@ __device__ __forceinline__ void cell_finish(const LstmFwdDir& d, int b, int u, i
 // whole k range inside the workgroup.  Per workgroup RT weight slabs and BT activation slabs cross L2:
 // for 64 sentences RT = BT = 2 moves the fewest bytes (each weight slab is then read by two workgroups,
 // which the XCD-aware numbering puts on the same L2).
-// The operand addresses of the fragment-major contraction and the grid lead the argument list (for one instance:
-// W_fm0, x_fm0, hprev_fm0, Kx0 are that instance's), so that they arrive in registers and the first loads go out
-// before the argument buffer has been read; the rest (args) is fetched behind those loads.  The grid follows from
-// Hh, Bp and the instance count as the launcher computes it.
-// nlead = how many instances the leading arguments describe: 1, or 2 when the launch's two instances have no
-// input segment (Kx = 0: the bottom encoder layer's directions) — then W_fm1 / hprev_fm1 are the second one's.
+// The operand addresses of the fragment-major contraction and the grid lead the argument list, so that they arrive in
+// registers and the first loads go out before the argument buffer has been read; the rest (d0) is fetched behind those
+// loads.  The grid follows from Hh and Bp as the launcher computes it.
 template <typename T, int RT, int KS, int U, int BT, bool FM = false>
-__global__ __launch_bounds__(64 * KS) void lstm_fwd_kernel(const void* W_fm0, const void* x_fm0, const void* hprev_fm0,
-                                                           const void* W_fm1, const void* hprev_fm1, int Kx0, int Bp, int Hh,
-                                                           int ndir_nlead, LstmFwdArgs args) {
+__global__ __launch_bounds__(64 * KS) void lstm_fwd_kernel(const void* W_fm0, const void* x_fm0, const void* hprev_fm0, int Kx0, int Bp,
+                                                           int Hh, LstmFwdDir d0) {
   __shared__ __align__(16) float red[KS * RT * BT * 256];
-  const int ndir = ndir_nlead & 0xffff, nlead = ndir_nlead >> 16;
-  const int nxd = (Hh + 4 * RT - 1) / (4 * RT);    // unit blocks per direction
-  const int nx = nxd * ndir, nz = ((Bp + 15) / 16 + BT - 1) / BT;
-  const StepGrid sg{nx, 1, nz};
+  const StepGrid sg{(Hh + 4 * RT - 1) / (4 * RT), 1, ((Bp + 15) / 16 + BT - 1) / BT};
   int x, kb, z;
   if (!decode_block(sg, x, kb, z)) return;
-  const int dir = ndir == 1 ? 0 : x / nxd;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int u0 = (x - dir * nxd) * 4 * RT;
+  const int u0 = x * 4 * RT;
   const int bt0 = z * BT;
   const int nbt = min(BT, (Bp + 15) / 16 - bt0);
   LstmFwdDir d;
   CellIn in0;
   bool have0 = false;
   auto fetch_rest = [&]() {
-    // (the instance index passes through an opaque register and a compiler barrier: otherwise the compiler moves this
-    // block, which depends on nothing before it, back in front of the contraction's loads)
-    int dsel = __builtin_amdgcn_readfirstlane(dir);
-    asm volatile("" : "+s"(dsel) : : "memory");
-    d = args.d[dsel];
+    // (an opaque offset of zero and a compiler barrier: otherwise the compiler moves this block, which depends on nothing
+    // before it, back in front of the contraction's loads)
+    int zero = 0;
+    asm volatile("" : "+s"(zero) : : "memory");
+    d = (&d0)[zero];
     // what the epilogue needs is fetched now, not behind the barrier
     CMT_PIN_UNIFORM_PTR(d.cnext); CMT_PIN_UNIFORM_PTR(d.gsave); CMT_PIN_UNIFORM_PTR(d.hnext); CMT_PIN_UNIFORM(d.ldhn);
     CMT_PIN_UNIFORM_PTR(d.ycat); CMT_PIN_UNIFORM(d.ldy); CMT_PIN_UNIFORM_PTR(d.hnext_fm); CMT_PIN_UNIFORM_PTR(d.ycat_fm);
@@ -351,18 +330,11 @@ __global__ __launch_bounds__(64 * KS) void lstm_fwd_kernel(const void* W_fm0, co
     }
   };
   if constexpr (FM) {
-    const bf16_t *Wf = (const bf16_t*)W_fm0, *xf = (const bf16_t*)x_fm0, *hf = (const bf16_t*)hprev_fm0;
-    int Kx = Kx0;
-    if (dir == 1 && nlead == 2) { Wf = (const bf16_t*)W_fm1; hf = (const bf16_t*)hprev_fm1; }
-    else if (dir >= nlead) {
-      Wf = (const bf16_t*)args.d[dir].W_fm; xf = (const bf16_t*)args.d[dir].x_fm; hf = (const bf16_t*)args.d[dir].hprev_fm;
-      Kx = args.d[dir].Kx;
-    }
-    const int ns0 = Kx >> 5, ns1 = Hh >> 5;
+    const int ns0 = Kx0 >> 5, ns1 = Hh >> 5;
     const bf16_t* wt[RT];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) wt[rt] = Wf + (size_t)((u0 >> 2) + rt) * (ns0 + ns1) * 512;
-    step_contract_fm<RT, KS, U, BT>(wt, xf, ns0, hf, ns1, bt0, nbt, red, 0, 1 << 30, fetch_rest);
+    for (int rt = 0; rt < RT; ++rt) wt[rt] = (const bf16_t*)W_fm0 + (size_t)((u0 >> 2) + rt) * (ns0 + ns1) * 512;
+    step_contract_fm<RT, KS, U, BT>(wt, (const bf16_t*)x_fm0, ns0, (const bf16_t*)hprev_fm0, ns1, bt0, nbt, red, 0, 1 << 30, fetch_rest);
   } else {
     fetch_rest();
     // row m = lane % 16 of row tile rt: gate m % 4 of unit u0 + 4 * rt + m / 4
@@ -388,22 +360,17 @@ __global__ __launch_bounds__(64 * KS) void lstm_fwd_kernel(const void* W_fm0, co
 }
 
 template <typename T, int RT, int KS, int U, int BT = STEP_MAXBT>
-static void lstm_fwd_go(const LstmFwdArgs& a, int Bp, int Hh, int ndir, hipStream_t st, bool fm = false) {
-  const int nbt = (Bp + 15) / 16;
-  StepGrid sg{((Hh + 4 * RT - 1) / (4 * RT)) * ndir, 1, (nbt + BT - 1) / BT};
-  const LstmFwdDir& d0 = a.d[0];
-  const LstmFwdDir& d1 = a.d[ndir > 1 ? 1 : 0];
-  const int nlead = (ndir == 2 && d0.Kx == 0 && d1.Kx == 0) ? 2 : 1;
-  const int ndir_nlead = ndir | (nlead << 16);
+static void lstm_fwd_go(const LstmFwdDir& d, int Bp, int Hh, hipStream_t st) {
+  const StepGrid sg{(Hh + 4 * RT - 1) / (4 * RT), 1, ((Bp + 15) / 16 + BT - 1) / BT};
   if constexpr (sizeof(T) == 2) {
-    if (fm) {
-      hipLaunchKernelGGL((lstm_fwd_kernel<T, RT, KS, U, BT, true>), dim3(step_grid_blocks(sg)), dim3(64 * KS), 0, st, d0.W_fm, d0.x_fm,
-                         d0.hprev_fm, d1.W_fm, d1.hprev_fm, d0.Kx, Bp, Hh, ndir_nlead, a);
+    if (d.W_fm) {
+      hipLaunchKernelGGL((lstm_fwd_kernel<T, RT, KS, U, BT, true>), dim3(step_grid_blocks(sg)), dim3(64 * KS), 0, st, d.W_fm, d.x_fm,
+                         d.hprev_fm, d.Kx, Bp, Hh, d);
       return;
     }
   }
-  hipLaunchKernelGGL((lstm_fwd_kernel<T, RT, KS, U, BT>), dim3(step_grid_blocks(sg)), dim3(64 * KS), 0, st, d0.W_fm, d0.x_fm, d0.hprev_fm,
-                     d1.W_fm, d1.hprev_fm, d0.Kx, Bp, Hh, ndir_nlead, a);
+  hipLaunchKernelGGL((lstm_fwd_kernel<T, RT, KS, U, BT>), dim3(step_grid_blocks(sg)), dim3(64 * KS), 0, st, d.W_fm, d.x_fm, d.hprev_fm,
+                     d.Kx, Bp, Hh, d);
 }
 
 // Shapes of the fused kernel: 16 / 32 / 64 gate rows per workgroup, with all sentences (up to 64) or
@@ -411,19 +378,11 @@ static void lstm_fwd_go(const LstmFwdArgs& a, int Bp, int Hh, int ndir, hipStrea
 // `how` (env CMT_LSTM_FWD for experiments): 0 = choose by size, 1 / 2 / 4 = that many 16-row tiles x
 // 64 sentences, 6 = 32 rows x 32 sentences.
 static int g_lstm_fwd_how = -1;
-void launch_lstm_fwd(int prec, const LstmFwdDir* dirs, int ndir, int Bp, int Hh, hipStream_t st) {
+void launch_lstm_fwd(int prec, const LstmFwdDir& d, int Bp, int Hh, hipStream_t st) {
   if (g_lstm_fwd_how < 0) {
     const char* e = getenv("CMT_LSTM_FWD");
     g_lstm_fwd_how = e ? atoi(e) : 0;
   }
-  LstmFwdArgs a;
-  int K = 0;
-  for (int i = 0; i < STEP_MAX_INST; ++i) {
-    a.d[i] = dirs[i < ndir ? i : 0];
-    if (i < ndir && dirs[i].Kx + Hh > K) K = dirs[i].Kx + Hh;      // instances may differ in their input width
-  }
-  bool fm = prec != 0;                              // fragment-major operands: every instance must bring them
-  for (int i = 0; i < ndir; ++i) fm = fm && dirs[i].W_fm != nullptr;
   int how = g_lstm_fwd_how;
   const int nbt = (Bp + 15) / 16;
   // measured (bf16, hidden 1024): 64 sentences — 32 gate rows x 32 sentences per workgroup: 9.9 us against
@@ -431,25 +390,25 @@ void launch_lstm_fwd(int prec, const LstmFwdDir* dirs, int ndir, int Bp, int Hh,
   // (32 sentences: 16 rows x 32 sentences is faster; 640 sentences, as in beam search: 64 rows x 64 sentences,
   // 65 us against 80 us; 128 sentences: 32 rows, 14.7 us against 19.7 us)
   if (how == 0) how = (Bp >= 256) ? 4 : (Bp > 64) ? 2 : (prec && nbt == 4) ? 6 : 1;
-  const int nsteps = (K / 8 + 3) / 4;
+  const int nsteps = ((d.Kx + Hh) / 8 + 3) / 4;
   if (prec) {
     if (how == 6) {
-      if (nsteps > 32) lstm_fwd_go<bf16_t, 2, 8, 4, 2>(a, Bp, Hh, ndir, st, fm);
-      else if (nsteps > 16) lstm_fwd_go<bf16_t, 2, 8, 2, 2>(a, Bp, Hh, ndir, st, fm);
-      else lstm_fwd_go<bf16_t, 2, 4, 2, 2>(a, Bp, Hh, ndir, st, fm);
+      if (nsteps > 32) lstm_fwd_go<bf16_t, 2, 8, 4, 2>(d, Bp, Hh, st);
+      else if (nsteps > 16) lstm_fwd_go<bf16_t, 2, 8, 2, 2>(d, Bp, Hh, st);
+      else lstm_fwd_go<bf16_t, 2, 4, 2, 2>(d, Bp, Hh, st);
     }
-    else if (how == 4) lstm_fwd_go<bf16_t, 4, 8, 4>(a, Bp, Hh, ndir, st, fm);
-    else if (how == 2) lstm_fwd_go<bf16_t, 2, 8, 4>(a, Bp, Hh, ndir, st, fm);
-    else if (nsteps > 32) lstm_fwd_go<bf16_t, 1, 16, 4>(a, Bp, Hh, ndir, st, fm);
-    else if (nsteps > 16) lstm_fwd_go<bf16_t, 1, 16, 2>(a, Bp, Hh, ndir, st, fm);
-    else if (nsteps > 8) lstm_fwd_go<bf16_t, 1, 8, 2>(a, Bp, Hh, ndir, st, fm);
-    else lstm_fwd_go<bf16_t, 1, 4, 2>(a, Bp, Hh, ndir, st, fm);
+    else if (how == 4) lstm_fwd_go<bf16_t, 4, 8, 4>(d, Bp, Hh, st);
+    else if (how == 2) lstm_fwd_go<bf16_t, 2, 8, 4>(d, Bp, Hh, st);
+    else if (nsteps > 32) lstm_fwd_go<bf16_t, 1, 16, 4>(d, Bp, Hh, st);
+    else if (nsteps > 16) lstm_fwd_go<bf16_t, 1, 16, 2>(d, Bp, Hh, st);
+    else if (nsteps > 8) lstm_fwd_go<bf16_t, 1, 8, 2>(d, Bp, Hh, st);
+    else lstm_fwd_go<bf16_t, 1, 4, 2>(d, Bp, Hh, st);
   } else {
-    if (how == 4) lstm_fwd_go<float, 4, 8, 2>(a, Bp, Hh, ndir, st);
-    else if (how == 2) lstm_fwd_go<float, 2, 8, 2>(a, Bp, Hh, ndir, st);
-    else if (nsteps > 16) lstm_fwd_go<float, 1, 16, 2>(a, Bp, Hh, ndir, st);
-    else if (nsteps > 8) lstm_fwd_go<float, 1, 8, 2>(a, Bp, Hh, ndir, st);
-    else lstm_fwd_go<float, 1, 4, 2>(a, Bp, Hh, ndir, st);
+    if (how == 4) lstm_fwd_go<float, 4, 8, 2>(d, Bp, Hh, st);
+    else if (how == 2) lstm_fwd_go<float, 2, 8, 2>(d, Bp, Hh, st);
+    else if (nsteps > 16) lstm_fwd_go<float, 1, 16, 2>(d, Bp, Hh, st);
+    else if (nsteps > 8) lstm_fwd_go<float, 1, 8, 2>(d, Bp, Hh, st);
+    else lstm_fwd_go<float, 1, 4, 2>(d, Bp, Hh, st);
   }
 }
 
@@ -482,12 +441,10 @@ static Step2dPlan plan2d(int prec, int N, int K, int Bp, int max_kb) {
 int step_kblocks(int prec, int N, int K, int Bp, int max_kb) { return plan2d(prec, N, K, Bp, max_kb).kb; }
 
 template <typename T, int U, bool FM = false>
-__global__ __launch_bounds__(256) void step2d_kernel(StepGemmArgs args, int Bp, StepGrid sg, int spb) {
+__global__ __launch_bounds__(256) void step2d_kernel(StepGemm g, int Bp, StepGrid sg, int spb) {
   __shared__ __align__(16) float red[4 * 16 * 64 * 4];
-  StepGemm g = args.g[blockIdx.y];
   int x, kb, z;
   if (!decode_block(sg, x, kb, z)) return;
-  if (x * 64 >= g.N) return;                       // instances of one launch may differ in N
   // what the epilogue needs is fetched now, not behind the barrier
   CMT_PIN_UNIFORM_PTR(g.bias); CMT_PIN_UNIFORM_PTR(g.best_idx);
   CMT_PIN_UNIFORM(g.N); CMT_PIN_UNIFORM(g.mode); CMT_PIN_UNIFORM_PTR(g.out); CMT_PIN_UNIFORM(g.ldout); CMT_PIN_UNIFORM(g.plane_stride);
@@ -688,32 +645,6 @@ static bool step_gemm_has_fm(const StepGemm& g) {
   return g.W_fm && (g.K0 == 0 || g.a0_fm) && (g.K1 == 0 || g.a1_fm) && g.K0 % 32 == 0 && g.K1 % 32 == 0 && g.N % 16 == 0;
 }
 
-// n instances in one launch (blockIdx.y); they share the contraction length and the k-block plan,
-// which is the plan of the widest instance.
-void launch_step_gemm_multi(int prec, const StepGemm* gs, int n, int n_plan, int Bp, hipStream_t st) {
-  const int nbt = (Bp + 15) / 16;
-  StepGemmArgs a;
-  int Nmax = 0;
-  for (int i = 0; i < STEP_MAX_INST; ++i) {
-    a.g[i] = gs[i < n ? i : 0];
-    if (i < n && gs[i].N > Nmax) Nmax = gs[i].N;
-  }
-  if (n_plan > Nmax) Nmax = n_plan;
-  const StepGemm& g = gs[0];
-  const Step2dPlan pl = plan2d(prec, Nmax, g.K0 + g.K1, Bp, g.max_kb);
-  StepGrid sg{(Nmax + 63) / 64, pl.kb, (nbt + STEP_MAXBT - 1) / STEP_MAXBT};
-  const dim3 grid(step_grid_blocks(sg), n);
-  bool fm = prec != 0;                              // fragment-major operands: every instance must bring them
-  for (int i = 0; i < n; ++i) fm = fm && step_gemm_has_fm(gs[i]);
-#define GO(TT, UU) hipLaunchKernelGGL((step2d_kernel<TT, UU>), grid, dim3(256), 0, st, a, Bp, sg, pl.steps_per_block)
-#define GOF(UU) hipLaunchKernelGGL((step2d_kernel<bf16_t, UU, true>), grid, dim3(256), 0, st, a, Bp, sg, pl.steps_per_block)
-  if (fm) { if (pl.u == 4) GOF(4); else if (pl.u == 2) GOF(2); else GOF(1); }
-  else if (prec) { if (pl.u == 4) GO(bf16_t, 4); else if (pl.u == 2) GO(bf16_t, 2); else GO(bf16_t, 1); }
-  else { if (pl.u == 2) GO(float, 2); else GO(float, 1); }
-#undef GO
-#undef GOF
-}
-
 static int g_step_tanh = -1;
 void launch_step_gemm(int prec, const StepGemm& g, int Bp, hipStream_t st) {
   const int nbt = (Bp + 15) / 16;
@@ -739,10 +670,8 @@ void launch_step_gemm(int prec, const StepGemm& g, int Bp, hipStream_t st) {
   const Step2dPlan pl = plan2d(prec, g.N, g.K0 + g.K1, Bp, g.max_kb);
   StepGrid sg{(g.N + 63) / 64, pl.kb, (nbt + STEP_MAXBT - 1) / STEP_MAXBT};
   const dim3 grid(step_grid_blocks(sg));
-  StepGemmArgs a;
-  for (int i = 0; i < STEP_MAX_INST; ++i) a.g[i] = g;
-#define GO(TT, UU) hipLaunchKernelGGL((step2d_kernel<TT, UU>), grid, dim3(256), 0, st, a, Bp, sg, pl.steps_per_block)
-#define GOF(UU) hipLaunchKernelGGL((step2d_kernel<bf16_t, UU, true>), grid, dim3(256), 0, st, a, Bp, sg, pl.steps_per_block)
+#define GO(TT, UU) hipLaunchKernelGGL((step2d_kernel<TT, UU>), grid, dim3(256), 0, st, g, Bp, sg, pl.steps_per_block)
+#define GOF(UU) hipLaunchKernelGGL((step2d_kernel<bf16_t, UU, true>), grid, dim3(256), 0, st, g, Bp, sg, pl.steps_per_block)
   if (prec && step_gemm_has_fm(g)) { if (pl.u == 4) GOF(4); else if (pl.u == 2) GOF(2); else GOF(1); }
   else if (prec) { if (pl.u == 4) GO(bf16_t, 4); else if (pl.u == 2) GO(bf16_t, 2); else GO(bf16_t, 1); }
   else { if (pl.u == 2) GO(float, 2); else GO(float, 1); }
@@ -855,8 +784,7 @@ __device__ __forceinline__ void cell_bwd_finish(const LstmBwdPoint& p, int b, in
 // of a 64-sentence x 1024-unit step spread over all CUs
 constexpr int LSTM_BWD_POINT_THREADS = 64;
 template <typename T>
-__global__ __launch_bounds__(LSTM_BWD_POINT_THREADS) void lstm_bwd_point_kernel(LstmBwdPointArgs args, int Bp, int Hh) {
-  const LstmBwdPoint& p = args.p[blockIdx.y];
+__global__ __launch_bounds__(LSTM_BWD_POINT_THREADS) void lstm_bwd_point_kernel(LstmBwdPoint p, int Bp, int Hh) {
   const int idx4 = blockIdx.x * LSTM_BWD_POINT_THREADS + threadIdx.x;
   const int hq = Hh >> 2;
   if (idx4 >= Bp * hq) return;
@@ -867,16 +795,11 @@ __global__ __launch_bounds__(LSTM_BWD_POINT_THREADS) void lstm_bwd_point_kernel(
   cell_bwd_finish<T>(p, b, u, Hh, cell_bwd_load(p, b, u, Hh), zero, zero);
 }
 
-void launch_lstm_bwd_point_multi(int prec, const LstmBwdPoint* ps, int n, int Bp, int Hh, hipStream_t st) {
-  LstmBwdPointArgs a;
-  for (int i = 0; i < STEP_MAX_INST; ++i) a.p[i] = ps[i < n ? i : 0];
-  const int cnt = Bp * (Hh >> 2);
-  const dim3 grid((cnt + LSTM_BWD_POINT_THREADS - 1) / LSTM_BWD_POINT_THREADS, n);
-  if (prec) hipLaunchKernelGGL(lstm_bwd_point_kernel<bf16_t>, grid, dim3(LSTM_BWD_POINT_THREADS), 0, st, a, Bp, Hh);
-  else hipLaunchKernelGGL(lstm_bwd_point_kernel<float>, grid, dim3(LSTM_BWD_POINT_THREADS), 0, st, a, Bp, Hh);
-}
 void launch_lstm_bwd_point(int prec, const LstmBwdPoint& p, int Bp, int Hh, hipStream_t st) {
-  launch_lstm_bwd_point_multi(prec, &p, 1, Bp, Hh, st);
+  const int cnt = Bp * (Hh >> 2);
+  const dim3 grid((cnt + LSTM_BWD_POINT_THREADS - 1) / LSTM_BWD_POINT_THREADS);
+  if (prec) hipLaunchKernelGGL(lstm_bwd_point_kernel<bf16_t>, grid, dim3(LSTM_BWD_POINT_THREADS), 0, st, p, Bp, Hh);
+  else hipLaunchKernelGGL(lstm_bwd_point_kernel<float>, grid, dim3(LSTM_BWD_POINT_THREADS), 0, st, p, Bp, Hh);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -887,20 +810,16 @@ void launch_lstm_bwd_point(int prec, const LstmBwdPoint& p, int Bp, int Hh, hipS
 // of one sentence — for the cell backward that is 4 consecutive hidden units, the same unit of work a
 // thread of the pointwise kernel has — so the consumer runs in registers and neither the planes nor a
 // second launch exist.  The epilogue's operands are fetched before the contraction starts.
-struct StepBwdArgs { StepBwd g[STEP_BWD_MAX_INST]; };
 
-// What the fragment-major contraction of an instance needs before its first load, as leading kernel arguments
-// (they arrive in registers): the operands, the contraction length and the column counts.  `on` = 0: read the
-// instance's own fields instead (further instances of a launch).
-struct StepBwdLead { const void* Wt_fm; const void* dg_fm; int K, wt_tile0, N, ncols0, on; };   // (on: see step_bwd_fused_kernel)
+// What the fragment-major contraction needs before its first load, as leading kernel arguments (they arrive in
+// registers): the operands, the contraction length and the column counts.
+struct StepBwdLead { const void* Wt_fm; const void* dg_fm; int K, wt_tile0, N, ncols0; };
 template <typename T, int KS, int U, int BT, bool FM>
 __device__ __forceinline__ void step_bwd_body(const StepBwdLead& ld, const StepBwd& g, int Bp, const StepGrid& sg, float* red) {
   int x, kb, z;
   if (!decode_block(sg, x, kb, z)) return;
-  const int ncols0 = ld.on ? ld.ncols0 : g.part[0].ncols;
-  const int N = ld.on ? ld.N : g.part[0].ncols + g.part[1].ncols;
+  const int ncols0 = ld.ncols0, N = ld.N;
   const int n0 = x * 16;
-  if (n0 >= N) return;                              // instances of one launch may differ in N
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int which = n0 >= ncols0 ? 1 : 0;
   const int c0 = n0 - (which ? ncols0 : 0);
@@ -927,7 +846,7 @@ __device__ __forceinline__ void step_bwd_body(const StepBwdLead& ld, const StepB
     CMT_PIN_UNIFORM_PTR(e.cell.dh); CMT_PIN_UNIFORM(e.cell.drop_dy.on); CMT_PIN_UNIFORM(e.cell.dy_col);
     mine = w < nbt && b < Bp && c < e.ncols;
     if (mine) {
-      if (e.kind == BWD_EPI_CELL_DY || e.kind == BWD_EPI_CELL_REC) cin = cell_bwd_load(e.cell, b, c, e.hh);
+      if (e.kind == BWD_EPI_CELL_DY) cin = cell_bwd_load(e.cell, b, c, e.hh);
       else if (e.kind == BWD_EPI_TANH) {
         const int r = e.pos ? e.pos[b] : b;
         if (r >= 0) tce = *reinterpret_cast<const float4*>(e.dce + (size_t)r * e.hh + c);
@@ -937,10 +856,9 @@ __device__ __forceinline__ void step_bwd_body(const StepBwdLead& ld, const StepB
     }
   };
   if constexpr (FM) {
-    const int ns = (ld.on ? ld.K : g.K) >> 5;
-    const bf16_t* Wf = (const bf16_t*)(ld.on ? ld.Wt_fm : g.Wt_fm);
-    const bf16_t* wt[1] = {Wf + (size_t)((ld.on ? ld.wt_tile0 : g.wt_tile0) + x) * ns * 512};
-    step_contract_fm<1, KS, U, BT, decltype(fetch_rest), KS == 16>(wt, (const bf16_t*)(ld.on ? ld.dg_fm : g.dg_fm), ns, nullptr, 0, bt0, nbt,
+    const int ns = ld.K >> 5;
+    const bf16_t* wt[1] = {(const bf16_t*)ld.Wt_fm + (size_t)(ld.wt_tile0 + x) * ns * 512};
+    step_contract_fm<1, KS, U, BT, decltype(fetch_rest), KS == 16>(wt, (const bf16_t*)ld.dg_fm, ns, nullptr, 0, bt0, nbt,
                                                                    red, 0, 1 << 30, fetch_rest);
   } else {
     fetch_rest();
@@ -955,8 +873,6 @@ __device__ __forceinline__ void step_bwd_body(const StepBwdLead& ld, const StepB
     store4<float>(e.out + (size_t)b * e.ldout + c, v);
   } else if (e.kind == BWD_EPI_CELL_DY) {
     cell_bwd_finish<T>(e.cell, b, c, e.hh, cin, v, zero);
-  } else if (e.kind == BWD_EPI_CELL_REC) {
-    cell_bwd_finish<T>(e.cell, b, c, e.hh, cin, zero, v);
   } else {
     float o[4];
 #pragma unroll
@@ -965,19 +881,14 @@ __device__ __forceinline__ void step_bwd_body(const StepBwdLead& ld, const StepB
     if (sizeof(T) == 2 && e.dpre_fm) store4<T>((T*)e.dpre_fm + fm_offset(b, c, e.hh >> 5), o);
   }
 }
-// The leading arguments describe instance 0 and, with nlead = 2, instance 1 (same shape, its own operands: the
-// bottom encoder layer's two directions).  nx = the launch's column tiles (of its widest instance).
 template <typename T, int KS, int U, int BT, bool FM = false>
-__global__ __launch_bounds__(64 * KS) void step_bwd_fused_kernel(const void* Wt_fm0, const void* dg_fm0, const void* Wt_fm1,
-                                                                 const void* dg_fm1, int K0, int wt_tile00, int N0, int ncols00, int Bp,
-                                                                 int nx_nlead, StepBwdArgs args) {
+__global__ __launch_bounds__(64 * KS) void step_bwd_fused_kernel(const void* Wt_fm0, const void* dg_fm0, int K0, int wt_tile00, int N0,
+                                                                 int ncols00, int Bp, StepBwd g) {
   __shared__ __align__(16) float red[KS * BT * 256];
-  const int nx = nx_nlead & 0xffff, nlead = nx_nlead >> 16;
-  const int inst = blockIdx.y;
-  const StepBwdLead ld{inst == 1 ? Wt_fm1 : Wt_fm0, inst == 1 ? dg_fm1 : dg_fm0, K0, wt_tile00, N0, ncols00, inst < nlead ? 1 : 0};
-  step_bwd_body<T, KS, U, BT, FM>(ld, args.g[inst], Bp, StepGrid{nx, 1, ((Bp + 15) / 16 + BT - 1) / BT}, red);
+  const StepBwdLead ld{Wt_fm0, dg_fm0, K0, wt_tile00, N0, ncols00};
+  step_bwd_body<T, KS, U, BT, FM>(ld, g, Bp, StepGrid{(N0 + 15) / 16, 1, ((Bp + 15) / 16 + BT - 1) / BT}, red);
 }
-// One instance and, in further workgroups of the same launch, attention scores that depend on the same input
+// The same and, in further workgroups of the launch, attention scores that depend on the same input
 // alone (block n_gemm + ig * Bp + b: positions ig * KS + wavefront of sentence b).
 template <typename T, int KS, int U, int BT, bool FM = false>
 __global__ __launch_bounds__(64 * KS) void step_bwd_scores_kernel(const void* Wt_fm0, const void* dg_fm0, int K0, int wt_tile00, int N0,
@@ -993,76 +904,47 @@ __global__ __launch_bounds__(64 * KS) void step_bwd_scores_kernel(const void* Wt
     else att_dots_row<T, T>((const T*)d.Mat, d.ldm, (const T*)d.vec, d.ldv, d.len, d.S, Bp, d.H, d.dots, i, b);
     return;
   }
-  const StepBwdLead ld{Wt_fm0, dg_fm0, K0, wt_tile00, N0, ncols00, 1};
+  const StepBwdLead ld{Wt_fm0, dg_fm0, K0, wt_tile00, N0, ncols00};
   step_bwd_body<T, KS, U, BT, FM>(ld, g, Bp, sg, red);
 }
 
 template <typename T, int KS, int U, int BT>
-static void step_bwd_go(const StepBwdArgs& a, int n, int Nmax, int Bp, hipStream_t st, bool fm, const AttScores* sc) {
-  const int nbt = (Bp + 15) / 16;
-  StepGrid sg{(Nmax + 15) / 16, 1, (nbt + BT - 1) / BT};
-  const StepBwd& g0 = a.g[0];
-  const int N0 = g0.part[0].ncols + g0.part[1].ncols;
-  if (sc) {                                        // (one instance) the scores ride in the same launch
-    const int n_gemm = step_grid_blocks(sg);
-    const dim3 grid(n_gemm + ((sc->S + KS - 1) / KS) * Bp);
-    if constexpr (sizeof(T) == 2) {
-      if (fm) {
-        hipLaunchKernelGGL((step_bwd_scores_kernel<T, KS, U, BT, true>), grid, dim3(64 * KS), 0, st, g0.Wt_fm, g0.dg_fm, g0.K, g0.wt_tile0,
-                           N0, g0.part[0].ncols, Bp, sg.nx, sg.nz, n_gemm, g0, *sc);
-        return;
-      }
-    }
-    hipLaunchKernelGGL((step_bwd_scores_kernel<T, KS, U, BT>), grid, dim3(64 * KS), 0, st, g0.Wt_fm, g0.dg_fm, g0.K, g0.wt_tile0, N0,
-                       g0.part[0].ncols, Bp, sg.nx, sg.nz, n_gemm, g0, *sc);
-    return;
-  }
-  const StepBwd& g1 = a.g[n > 1 ? 1 : 0];
-  const bool same = n > 1 && g1.K == g0.K && g1.wt_tile0 == g0.wt_tile0 && g1.part[0].ncols == g0.part[0].ncols &&
-                    g1.part[1].ncols == g0.part[1].ncols;
-  const int nx_nlead = sg.nx | ((same ? 2 : 1) << 16);
+static void step_bwd_go(const StepBwd& g, int Bp, hipStream_t st, const AttScores* sc) {
+  const int N = g.part[0].ncols + g.part[1].ncols;
+  const StepGrid sg{(N + 15) / 16, 1, ((Bp + 15) / 16 + BT - 1) / BT};
+  const int n_gemm = step_grid_blocks(sg);
+  const dim3 grid(n_gemm + (sc ? ((sc->S + KS - 1) / KS) * Bp : 0));    // (the scores ride in the same launch)
+  auto go = [&](auto fm) {
+    constexpr bool FM = decltype(fm)::value;
+    if (sc)
+      hipLaunchKernelGGL((step_bwd_scores_kernel<T, KS, U, BT, FM>), grid, dim3(64 * KS), 0, st, g.Wt_fm, g.dg_fm, g.K, g.wt_tile0, N,
+                         g.part[0].ncols, Bp, sg.nx, sg.nz, n_gemm, g, *sc);
+    else
+      hipLaunchKernelGGL((step_bwd_fused_kernel<T, KS, U, BT, FM>), grid, dim3(64 * KS), 0, st, g.Wt_fm, g.dg_fm, g.K, g.wt_tile0, N,
+                         g.part[0].ncols, Bp, g);
+  };
   if constexpr (sizeof(T) == 2) {
-    if (fm) {
-      hipLaunchKernelGGL((step_bwd_fused_kernel<T, KS, U, BT, true>), dim3(step_grid_blocks(sg), n), dim3(64 * KS), 0, st, g0.Wt_fm,
-                         g0.dg_fm, g1.Wt_fm, g1.dg_fm, g0.K, g0.wt_tile0, N0, g0.part[0].ncols, Bp, nx_nlead, a);
-      return;
-    }
+    if (g.dg_fm && g.Wt_fm) { go(std::true_type{}); return; }
   }
-  hipLaunchKernelGGL((step_bwd_fused_kernel<T, KS, U, BT>), dim3(step_grid_blocks(sg), n), dim3(64 * KS), 0, st, g0.Wt_fm, g0.dg_fm,
-                     g1.Wt_fm, g1.dg_fm, g0.K, g0.wt_tile0, N0, g0.part[0].ncols, Bp, nx_nlead, a);
+  go(std::false_type{});
 }
 
-void launch_step_bwd_fused(int prec, const StepBwd* gs, int n, int Bp, hipStream_t st, const AttScores* scores) {
-  if (scores && n != 1) scores = nullptr;            // (callers pass one instance with scores)
-  for (int base = 0; base < n; base += STEP_BWD_MAX_INST) {
-    const int m = n - base < STEP_BWD_MAX_INST ? n - base : STEP_BWD_MAX_INST;
-    StepBwdArgs a;
-    int Nmax = 0, Kmax = 0;
-    bool fm = prec != 0;                           // fragment-major operands: every instance must bring them
-    for (int i = 0; i < STEP_BWD_MAX_INST; ++i) {
-      a.g[i] = gs[base + (i < m ? i : 0)];
-      if (i < m) {
-        fm = fm && a.g[i].dg_fm && a.g[i].Wt_fm;
-        Nmax = std::max(Nmax, a.g[i].part[0].ncols + a.g[i].part[1].ncols);
-        Kmax = std::max(Kmax, a.g[i].K);
-      }
-    }
-    const int nsteps = (Kmax / 8 + 3) / 4;
-    const int wgs = ((Nmax + 15) / 16) * (((Bp + 15) / 16 + 1) / 2) * m;
-    // 16 columns x 32 sentences per workgroup.  (64 sentences per workgroup halves the number of workgroups
-    // and was measured at twice the time: 25.6 against 12.9 us for 64 sentences, 26.2 against 21.8 us for 128.)
-#define GO(TT, KS, UU) step_bwd_go<TT, KS, UU, 2>(a, m, Nmax, Bp, st, fm, scores)
-    if (prec) {
-      // a long k range is split over 16 wavefronts while the launch is one round of workgroups; with more than 256
-      // workgroups (128 sentences) 8 wavefronts, so that two workgroups share a CU instead of taking turns
-      // (decoder layer at 128 sentences: 12.4 against 14.5 us; at 64 sentences: 10.2 against 9.1 us)
-      if (nsteps > 64 && wgs > 256) GO(bf16_t, 8, 2); else
-      if (nsteps > 64) GO(bf16_t, 16, 4); else if (nsteps > 32) GO(bf16_t, 8, 4); else if (nsteps > 16) GO(bf16_t, 8, 2); else GO(bf16_t, 4, 2);
-    } else {
-      if (nsteps > 32) GO(float, 16, 2); else if (nsteps > 16) GO(float, 8, 2); else GO(float, 4, 2);
-    }
-#undef GO
+void launch_step_bwd_fused(int prec, const StepBwd& g, int Bp, hipStream_t st, const AttScores* scores) {
+  const int nsteps = (g.K / 8 + 3) / 4;
+  const int wgs = ((g.part[0].ncols + g.part[1].ncols + 15) / 16) * (((Bp + 15) / 16 + 1) / 2);
+  // 16 columns x 32 sentences per workgroup.  (64 sentences per workgroup halves the number of workgroups
+  // and was measured at twice the time: 25.6 against 12.9 us for 64 sentences, 26.2 against 21.8 us for 128.)
+#define GO(TT, KS, UU) step_bwd_go<TT, KS, UU, 2>(g, Bp, st, scores)
+  if (prec) {
+    // a long k range is split over 16 wavefronts while the launch is one round of workgroups; with more than 256
+    // workgroups (128 sentences) 8 wavefronts, so that two workgroups share a CU instead of taking turns
+    // (decoder layer at 128 sentences: 12.4 against 14.5 us; at 64 sentences: 10.2 against 9.1 us)
+    if (nsteps > 64 && wgs > 256) GO(bf16_t, 8, 2); else
+    if (nsteps > 64) GO(bf16_t, 16, 4); else if (nsteps > 32) GO(bf16_t, 8, 4); else if (nsteps > 16) GO(bf16_t, 8, 2); else GO(bf16_t, 4, 2);
+  } else {
+    if (nsteps > 32) GO(float, 16, 2); else if (nsteps > 16) GO(float, 8, 2); else GO(float, 4, 2);
   }
+#undef GO
 }
 
 // out[b, c] = base[b, c] + sum of planes (plain fp32 [Bp, cols])

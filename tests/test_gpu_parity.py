@@ -970,3 +970,65 @@ def test_small_config_fp32_full_size():
     loss, oloss, worst, tr = run_case(cfg, I.make_params(cfg, c["seed"]), I.make_batch(c), prec=0, check_inter=False)
     tr.close()
     print("small fp32: loss", loss, "oracle", oloss, "worst rel L2", max(worst.values()))
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("B,S,H,E,L,reg", [(16, 2, 16, 8, 2, None), (17, 3, 48, 24, 2, (0.2, 0.1, 5)), (33, 9, 144, 16, 3, (0.3, 0.0, 6)),
+                                           (48, 5, 336, 40, 2, None), (65, 4, 528, 16, 2, (0.2, 0.0, 7)), (129, 3, 512, 16, 2, None),
+                                           (150, 2, 1024, 16, 2, (0.2, 0.0, 8))])
+def test_encoder_recurrences_at_tile_edges(prec, B, S, H, E, L, reg):
+    """The encoder's recurrences run as one launch each, on groups of 16 or 32 sentences whose workgroups hold 16 units
+    (8 for wide fp32 layers) forwards and 16 or 32 backwards and exchange states and gate gradients through memory: batches
+    around the sentence tiles (the last tile of a pair missing; one and two tiles per group; more workgroups than CUs),
+    widths whose units do not fill the last workgroup (bottom layer 8, 24, 72, 168, 264) and every split of the
+    contraction, with and without the dropped copies.  All intermediates and gradients at the usual bars, bf16
+    gradients' relative L2 within max(2e-2, 2 s) with s = what rounding the operands moves the exact gradient (on sources of two or
+    three tokens W_a's, the difference of nearly equal terms, moves by more than the plain bar)."""
+    cfg = dict(src_vocab=104, tgt_vocab=136, emb=E, hidden=H, layers=L)
+    rng = np.random.default_rng(1100 + B)
+    params = I.make_params(cfg, seed=B, scale=0.3 if H <= 128 else 0.05)
+    batch = ragged_batch(rng, B, S, 2, cfg["src_vocab"], cfg["tgt_vocab"])
+    relax = {}
+    if prec:
+        sens = oracle_sensitivity(cfg, params, batch, reg)
+        relax = dict(l2_override={k: max(2e-2, SWEEP_SENS_C * v) for k, v in sens.items()})
+    loss, oloss, worst, tr = run_case(cfg, params, batch, prec, reg=reg, **relax)
+    tr.close()
+
+
+def test_recurrences_of_several_streams_at_once():
+    """Four handles on four streams, driven by four threads: their recurrences share the chip, and every step's gradients
+    are those of the handle alone, bit for bit."""
+    import threading
+
+    import torch
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=104, tgt_vocab=136, emb=64, hidden=512, layers=2)
+    params = I.flatten(I.make_params(cfg, seed=3, scale=0.05), cfg)
+    rng = np.random.default_rng(77)
+    batches = [ragged_batch(rng, B, 30, 3, cfg["src_vocab"], cfg["tgt_vocab"]) for B in (64, 40, 64, 17)]
+    trainers, alone, devs = [], [], []
+    for batch in batches:
+        with torch.cuda.stream(torch.cuda.Stream()):
+            tr = binding.Trainer(cfg, *batch[0].shape, batch[2].shape[1], precision=1)
+            tr.set_params(params)
+        dev = tr.upload_batch(*batch)
+        torch.cuda.synchronize()
+        tr.train_step(dev)
+        trainers.append(tr)
+        devs.append(dev)
+        alone.append(tr.get_grads())
+    got = [None] * len(batches)
+
+    def work(k):
+        for _ in range(5):
+            trainers[k].train_step(devs[k])
+        got[k] = trainers[k].get_grads()
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(batches))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k, tr in enumerate(trainers):
+        assert np.array_equal(got[k], alone[k]), k
+        tr.close()
