@@ -1364,7 +1364,7 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
       d.hprev = e.Hst + j * BP * esz; d.ldh = e.ph; d.W = e.W;
       d.cprev = e.Cst + j * BH; d.mask = h->dec_mask;
       d.hnext = e.Hst + (j + 1) * BP * esz; d.ldhn = e.ph; d.cnext = e.Cst + (j + 1) * BH;
-      d.gsave = e.Gs + (size_t)j * Bp * 4 * H; d.ycat = nullptr; d.ldy = 0;
+      d.gsave = nullptr; d.ycat = nullptr; d.ldy = 0;
       if (e.fm) {
         d.hnext_fm = e.HstF + (j + 1) * BH * esz;
         if (l > 0 && h->dec[l - 1].fm) {
@@ -1497,7 +1497,7 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
       d.hprev = e.Hst + slotT; d.ldh = e.ph; d.W = e.W;
       d.cprev = (const float*)((char*)e.Cst + slotC); d.mask = bs.mask;
       d.hnext = e.Hst + 2 * slotT; d.ldhn = e.ph; d.cnext = (float*)((char*)e.Cst + 2 * slotC);
-      d.gsave = e.Gs; d.ycat = nullptr; d.ldy = 0;
+      d.gsave = nullptr; d.ycat = nullptr; d.ldy = 0;
       if (e.fm) {                                    // as in greedy decoding: the layers above the bottom one
         d.hnext_fm = e.HstF + 2 * slotF;
         if (l > 0 && h->dec[l - 1].fm) { d.W_fm = e.Wfm; d.x_fm = h->dec[l - 1].HstF + 2 * slotF; d.hprev_fm = e.HstF + slotF; }

@@ -102,7 +102,7 @@ struct LstmFwdDir {
   const float* cprev;                   // [Bp, Hh]
   const float* mask;                    // [Bp] 1 = valid step
   void* hnext; int ldhn; float* cnext;  // next state (T*, row pitch ldhn); cell state [Bp, Hh]
-  float* gsave;                         // [Bp, 4Hh] gate activations kept for the backward pass
+  float* gsave;                         // [Bp, 4Hh] gate activations kept for the backward pass, or null
   void* ycat; int ldy;                  // optional second copy of h (T*, row pitch ldy), or null:
   DropSpec drop{}; int drop_col0 = 0;   //   the layer's output as the layer above sees it, i.e. after
                                         //   dropout (columns drop_col0 + [0, Hh) of the site)

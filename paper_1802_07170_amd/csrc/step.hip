@@ -273,8 +273,10 @@ __device__ __forceinline__ void cell_finish(const LstmFwdDir& d, int b, int u, i
   const float hn = og * tcn;
   const bool valid = in.mask > 0.f;
   d.cnext[(size_t)b * Hh + u] = valid ? cn : in.cp;
-  float* gs = d.gsave + (size_t)b * 4 * Hh + u;
-  gs[0] = ig; gs[Hh] = fg; gs[2 * Hh] = gg; gs[3 * Hh] = og;
+  if (d.gsave) {                                           // (decoding keeps no gates)
+    float* gs = d.gsave + (size_t)b * 4 * Hh + u;
+    gs[0] = ig; gs[Hh] = fg; gs[2 * Hh] = gg; gs[3 * Hh] = og;
+  }
   const float hv = valid ? hn : in.hp;
   const float yv = d.ycat ? hv * drop_factor(d.drop, b, d.drop_col0 + u) : 0.f;
   if (is_bf16) {
@@ -359,10 +361,135 @@ __global__ __launch_bounds__(64 * KS) void lstm_fwd_kernel(const void* W_fm0, co
   }
 }
 
+// The same step for 256 rows and more (beam search: beam x batch rows; wide training batches), fragment-major operands.
+// There the step is a product of some size (640 rows, width 1024: 10.7 GFLOP), and what bounds it is the traffic from L2
+// into the CUs and its latency: a workgroup owns 8 row tiles (32 units x 4 gates) x BT tiles of sentences, takes their
+// blocks straight into LDS (a block is the register image of a fragment, so neither padding nor swizzle is needed), three
+// stages of WIDE_SK k steps in flight while the fourth feeds the matrix cores.  Per CU at 640 rows 852 KB cross L2 (the
+// kernel above with 4 x 4 tiles per workgroup: 1.3 MB, and every round of its loads was waited for): 48 -> 23 us
+// a launch.  Below 256 rows there are too few such tiles to fill the chip.
+// The 8 wavefronts are 4 pairs of row tiles x the two k steps of a stage; the two partial sums meet in LDS, and there
+// the cells change hands: a lane takes one unit for one sentence of each tile, so that 32 lanes touch 128 contiguous bytes.
+constexpr int WIDE_RT = 8, WIDE_SK = 2, WIDE_STAGES = 4;
+// completion of this wavefront's transfers but the last n (n is 0 or one of the few counts that the stages make)
+template <int N> __device__ __forceinline__ void wide_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// where the four gate sums of (sentence, unit 4 rt + q) lie in a tile of partial sums: no bank conflicts written sentence by
+// sentence nor read unit by unit
+__device__ __forceinline__ int wide_pos(int sentence, int q, int rt) { return q * 16 + (sentence ^ ((q + 4 * rt) & 15)); }
+
+template <int BT>
+__global__ __launch_bounds__(512) void lstm_fwd_wide_kernel(LstmFwdDir d, int Bp, int Hh) {
+  constexpr int BLOCKS = WIDE_SK * (WIDE_RT + BT);                 // 1 KB blocks of a stage
+  constexpr int FEW = BLOCKS / 8, MORE = BLOCKS % 8;               // a wavefront's share: the first MORE take one more
+  constexpr int STAGE = BLOCKS * 1024;
+  constexpr int RED = 2 * WIDE_RT * BT * 1024;
+  __shared__ __align__(16) char smem[WIDE_STAGES * STAGE > RED ? WIDE_STAGES * STAGE : RED];
+  const int nbt_all = (Bp + 15) >> 4;
+  const StepGrid sg{(Hh + 4 * WIDE_RT - 1) / (4 * WIDE_RT), 1, (nbt_all + BT - 1) / BT};
+  int x, kb, z;
+  if (!decode_block(sg, x, kb, z)) return;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int u0 = x * 4 * WIDE_RT, bt0 = z * BT, nbt = min(BT, nbt_all - bt0);
+  const int ns0 = d.Kx >> 5, ns1 = Hh >> 5, ns = ns0 + ns1, nstage = (ns + WIDE_SK - 1) / WIDE_SK;
+  const unsigned lane16 = (unsigned)lane * 16u;
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) const char*)smem;
+  // block q of stage i: k step WIDE_SK i + q / (WIDE_RT + BT); first the row tiles, then the tiles of sentences (those
+  // beyond the last one, and k steps beyond the end, repeat the last: never used)
+  auto issue = [&](int i) {
+#pragma unroll
+    for (int n = 0; n <= FEW; ++n) {
+      if (n == FEW && w >= MORE) break;
+      const int q = w + 8 * n, kk = q / (WIDE_RT + BT), r = q - kk * (WIDE_RT + BT);
+      const int s = min(WIDE_SK * i + kk, ns - 1);
+      const bf16_t* src;
+      if (r < WIDE_RT) src = (const bf16_t*)d.W_fm + ((size_t)((u0 >> 2) + r) * ns + s) * 512;
+      else {
+        const int b = min(bt0 + r - WIDE_RT, nbt_all - 1);
+        src = s < ns0 ? (const bf16_t*)d.x_fm + ((size_t)b * ns0 + s) * 512 : (const bf16_t*)d.hprev_fm + ((size_t)b * ns1 + (s - ns0)) * 512;
+      }
+      const unsigned dst = lds0 + (unsigned)((i % WIDE_STAGES) * STAGE + q * 1024);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane16), "s"(src) : "memory");
+    }
+  };
+  v4f acc[2][BT];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < BT; ++b) acc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
+  const int rp = w & 3, kk = w >> 2;                               // this wavefront's pair of row tiles and k step of a stage
+#pragma unroll
+  for (int i = 0; i < WIDE_STAGES - 1; ++i)
+    if (i < nstage) issue(i);
+  for (int i = 0; i < nstage; ++i) {
+    // stage i has arrived when no more than the later ones in flight are outstanding
+    const int later = min(WIDE_STAGES - 2, nstage - 1 - i);
+    static_assert(WIDE_STAGES == 4, "the waits below count up to two later stages");
+    if (w < MORE) { if (later == 2) wide_wait<2 * (FEW + 1)>(); else if (later == 1) wide_wait<FEW + 1>(); else wide_wait<0>(); }
+    else          { if (later == 2) wide_wait<2 * FEW>(); else if (later == 1) wide_wait<FEW>(); else wide_wait<0>(); }
+    __builtin_amdgcn_s_barrier();                                  // every wavefront's share is there, and stage i - 1 is read
+    asm volatile("" ::: "memory");
+    if (i + WIDE_STAGES - 1 < nstage) issue(i + WIDE_STAGES - 1);  // (into the buffer of stage i - 1)
+    if (WIDE_SK * i + kk < ns) {
+      const char* st = smem + (i % WIDE_STAGES) * STAGE + kk * (WIDE_RT + BT) * 1024 + lane16;
+      Frag<bf16_t> fw[2], fx[BT];
+#pragma unroll
+      for (int a = 0; a < 2; ++a) fw[a].load(reinterpret_cast<const bf16_t*>(st + (2 * rp + a) * 1024));
+#pragma unroll
+      for (int b = 0; b < BT; ++b) fx[b].load(reinterpret_cast<const bf16_t*>(st + (WIDE_RT + b) * 1024));
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < BT; ++b) mma16(acc[a][b], fw[a], fx[b]);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // (this wavefront's reads of the stage are done before the next barrier)
+  }
+  // cell inputs: unit u of sentence 16 (bt0 + b) + sl, requested before the sums are exchanged
+  const int uw = threadIdx.x & 31, sl = threadIdx.x >> 5, u = u0 + uw;
+  CellIn in[BT];
+#pragma unroll
+  for (int b = 0; b < BT; ++b) in[b] = cell_load(d, 16 * min(bt0 + b, nbt_all - 1) + sl, u, Hh, true);
+  __syncthreads();
+  float* red = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < BT; ++b)
+      *reinterpret_cast<v4f*>(red + (((kk * WIDE_RT + 2 * rp + a) * BT + b) * 64 + wide_pos(lane & 15, lane >> 4, 2 * rp + a)) * 4) = acc[a][b];
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < BT; ++b) {
+    if (b >= nbt) break;
+    const int rt = uw >> 2, pos = wide_pos(sl, uw & 3, rt);
+    const v4f s0 = *reinterpret_cast<const v4f*>(red + ((rt * BT + b) * 64 + pos) * 4);
+    const v4f s1 = *reinterpret_cast<const v4f*>(red + (((WIDE_RT + rt) * BT + b) * 64 + pos) * 4);
+    const float p[4] = {s0[0] + s1[0], s0[1] + s1[1], s0[2] + s1[2], s0[3] + s1[3]};
+    cell_finish(d, 16 * (bt0 + b) + sl, u, Hh, p, in[b], true);
+  }
+}
+// Tiles of sentences per workgroup: rounds of workgroups over the chip's 256 CUs times the tiles that each takes in.
+static int wide_plan(int Bp, int Hh) {
+  int best = 8; long cost = 0;
+  for (int bt : {8, 6, 5, 4}) {
+    const long wgs = (long)(Hh / (4 * WIDE_RT)) * ((Bp / 16 + bt - 1) / bt);
+    const long c = (wgs + 255) / 256 * (WIDE_RT + bt);
+    if (cost == 0 || c < cost) { cost = c; best = bt; }
+  }
+  return best;
+}
+static void lstm_fwd_wide_go(const LstmFwdDir& d, int Bp, int Hh, hipStream_t st) {
+  const int bt = wide_plan(Bp, Hh);
+  const StepGrid sg{Hh / (4 * WIDE_RT), 1, (Bp / 16 + bt - 1) / bt};
+  const dim3 grid(step_grid_blocks(sg)), block(512);
+  if (bt == 8) hipLaunchKernelGGL(lstm_fwd_wide_kernel<8>, grid, block, 0, st, d, Bp, Hh);
+  else if (bt == 6) hipLaunchKernelGGL(lstm_fwd_wide_kernel<6>, grid, block, 0, st, d, Bp, Hh);
+  else if (bt == 5) hipLaunchKernelGGL(lstm_fwd_wide_kernel<5>, grid, block, 0, st, d, Bp, Hh);
+  else hipLaunchKernelGGL(lstm_fwd_wide_kernel<4>, grid, block, 0, st, d, Bp, Hh);
+}
+
 template <typename T, int RT, int KS, int U, int BT = STEP_MAXBT>
 static void lstm_fwd_go(const LstmFwdDir& d, int Bp, int Hh, hipStream_t st) {
   const StepGrid sg{(Hh + 4 * RT - 1) / (4 * RT), 1, ((Bp + 15) / 16 + BT - 1) / BT};
-  if constexpr (sizeof(T) == 2) {
+  if constexpr (sizeof(T) == 2 && RT < 4) {          // (four row tiles: the kernel for wide batches takes these operands)
     if (d.W_fm) {
       hipLaunchKernelGGL((lstm_fwd_kernel<T, RT, KS, U, BT, true>), dim3(step_grid_blocks(sg)), dim3(64 * KS), 0, st, d.W_fm, d.x_fm,
                          d.hprev_fm, d.Kx, Bp, Hh, d);
@@ -387,10 +514,11 @@ void launch_lstm_fwd(int prec, const LstmFwdDir& d, int Bp, int Hh, hipStream_t 
   const int nbt = (Bp + 15) / 16;
   // measured (bf16, hidden 1024): 64 sentences — 32 gate rows x 32 sentences per workgroup: 9.9 us against
   // 11.3 us for 16 rows x 64 sentences; more than 64 sentences — 32 rows x 64 sentences
-  // (32 sentences: 16 rows x 32 sentences is faster; 640 sentences, as in beam search: 64 rows x 64 sentences,
-  // 65 us against 80 us; 128 sentences: 32 rows, 14.7 us against 19.7 us)
+  // (32 sentences: 16 rows x 32 sentences is faster; 128 sentences: 32 rows, 14.7 us against 19.7 us; 640 sentences, as in
+  // beam search: 64 rows, 65 us against 80 us, and with fragment-major operands the kernel for wide batches, 23 against 48)
   if (how == 0) how = (Bp >= 256) ? 4 : (Bp > 64) ? 2 : (prec && nbt == 4) ? 6 : 1;
   const int nsteps = ((d.Kx + Hh) / 8 + 3) / 4;
+  if (prec && how == 4 && d.W_fm) { lstm_fwd_wide_go(d, Bp, Hh, st); return; }
   if (prec) {
     if (how == 6) {
       if (nsteps > 32) lstm_fwd_go<bf16_t, 2, 8, 4, 2>(d, Bp, Hh, st);

@@ -1032,3 +1032,20 @@ def test_recurrences_of_several_streams_at_once():
     for k, tr in enumerate(trainers):
         assert np.array_equal(got[k], alone[k]), k
         tr.close()
+
+
+@pytest.mark.parametrize("B,T,H,E,L,reg", [(241, 3, 32, 16, 3, (0.2, 0.1, 9)), (265, 2, 96, 32, 2, None), (530, 2, 1024, 32, 1, None),
+                                           (660, 2, 1024, 32, 2, (0.2, 0.0, 4)), (800, 2, 1024, 32, 1, None)])
+def test_decoder_steps_of_wide_batches(B, T, H, E, L, reg):
+    """From 256 rows a decoder step with 16-bit operands runs on 32 units and 4, 5, 6 or 8 tiles of 16 sentences per
+    workgroup: every one of these, batches that fill neither their last tile nor their last workgroup, an odd number of k
+    steps, the bottom layer (input part added) and the upper ones (bias), with and without the dropped copies.  All
+    intermediates and gradients at the usual bars, gradients' relative L2 within max(2e-2, 2 s) with s = what rounding
+    the operands moves the exact gradient."""
+    cfg = dict(src_vocab=104, tgt_vocab=136, emb=E, hidden=H, layers=L)
+    rng = np.random.default_rng(1300 + B)
+    params = I.make_params(cfg, seed=B, scale=0.3 if H <= 128 else 0.05)
+    batch = ragged_batch(rng, B, 2, T, cfg["src_vocab"], cfg["tgt_vocab"])
+    sens = oracle_sensitivity(cfg, params, batch, reg)
+    loss, oloss, worst, tr = run_case(cfg, params, batch, 1, reg=reg, l2_override={k: max(2e-2, SWEEP_SENS_C * v) for k, v in sens.items()})
+    tr.close()
