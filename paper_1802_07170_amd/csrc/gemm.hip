@@ -6,25 +6,36 @@
 #include "kernels.h"
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 #include <vector>
 
 namespace cmt {
 
-// Dispatch thresholds, from measurements on MI355X (bf16, k = 1024 .. 4096): with 208 tiles of
-// 256 x 256 the big tile already wins (628 against 546 TFLOP/s), with 128 it loses.
+// Dispatch thresholds, from measurements on MI355X, us (256 x 256 | 128 x 128 | 64 x 64).
+// bf16: 160 big tiles (10240 x 1024, k 1024) 30 | 43 | 38, 104 (3200 x 2048, k 1024) 29 | 26 | 27: big from 144 up.  Below
+// that the medium tile only with a round of workgroups and a k to spread its prologue and store over: 200 medium tiles
+// 25.8 | 27.3 (k 1024; 1472 x 2048, k 512: 16.5 | 9.9), 100 (3200 x 1024, k 1024) 21.5 | 15.3, (1472 x 1024, k 512) 16.1 | 7.6,
+// one or two tiles 11 | 5; rows or columns that fit a small tile (16 x 32000, k 1024) 17.5 | 12.3.
+// fp32 (matrix-core bound, the shape hardly matters once the chip is full): 400 medium tiles 78 | 76, 200 (3200 x 1024, k 512)
+// 48 | 46, 100 46 | 24, two 21 | 7.7.
 static int env_int(const char* name, int dflt) {
   const char* e = getenv(name);
   return e && *e ? atoi(e) : dflt;
 }
-static const int GEMM_BIG_MIN_TILES = env_int("CMT_GEMM_BIG_MIN_TILES", 192);
-static const int GEMM_SPLIT_BELOW = env_int("CMT_GEMM_SPLIT_BELOW", 129);
-static const int GEMM_SPLIT_TARGET = env_int("CMT_GEMM_SPLIT_TARGET", 512);
+static const int GEMM_BIG_MIN_TILES = env_int("CMT_GEMM_BIG_MIN_TILES", 144);
+static const int GEMM_SPLIT_BELOW = env_int("CMT_GEMM_SPLIT_BELOW", 257);       // small tiles
+static const int GEMM_SPLIT_TARGET = env_int("CMT_GEMM_SPLIT_TARGET", 1024);
 static const int GEMM_SPLIT_MAX = env_int("CMT_GEMM_SPLIT_MAX", 16);
 static const int GEMM_BIGSPLIT_MIN_K = env_int("CMT_GEMM_BIGSPLIT_MIN_K", 8192);
 // beyond this many big tiles (by the host's row count) the small tile without a split measured faster (large
 // workload: 160 tiles, 3.15 against 3.57 ms for the output layer)
 static const int GEMM_BIGSPLIT_MAX_TILES = env_int("CMT_GEMM_BIGSPLIT_MAX_TILES", 96);
 
+// the 64 x 64 tile instead of the 128 x 128 one, of which there would be `tiles`
+static bool gemm_small_tile(int prec, long tiles, int M, int N, int K) {
+  if (!prec) return tiles < 512;
+  return tiles < 192 || K < 1024 || M <= GemmSmall::BM || N <= GemmSmall::BN;
+}
 
 // Number of k splits when the row count is known to the device alone: as many as make one round of workgroups
 // over the chip's 256 CUs out of the tiles that exist, at most the launched number.  The kernel and the plane
@@ -176,7 +187,9 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
   if (M <= 0 || N <= 0) return;
   // enough 256 x 256 tiles to fill the chip: the big tile (half the L2 traffic per flop)
   const int ntm_b = (M + GemmBig::BM - 1) / GemmBig::BM, ntn_b = (N + GemmBig::BN - 1) / GemmBig::BN;
-  if (ntm_b * ntn_b >= GEMM_BIG_MIN_TILES) {
+  // (of rows that only the device counts, the valid target positions, some 60 - 75 % exist)
+  const bool counted = lim.n && lim_kind == 1;
+  if (ntm_b * ntn_b >= (counted ? GEMM_BIG_MIN_TILES * 5 / 3 : GEMM_BIG_MIN_TILES)) {
     const int grid = ((ntm_b * ntn_b + 7) / 8) * 8;
     if (prec) gemm_go<bf16_t, 4, 4, 2, 2>(dim3(grid, 1), st, A, lda, B, ldb, M, N, K, Cf, Ct, ldc, bias, accumulate, ntn_b, K, 0, lim, lim_kind, 0, wg_cap);
     else gemm_go<float, 4, 4, 2, 2>(dim3(grid, 1), st, A, lda, B, ldb, M, N, K, Cf, Ct, ldc, bias, accumulate, ntn_b, K, 0, lim, lim_kind, 0, wg_cap);
@@ -186,7 +199,7 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
   // planes.  With a device-side row limit the kernel picks the number of splits itself (gemm_dyn_splits) out of
   // the launched maximum; otherwise the host aims at about one and a half rounds of workgroups.
   if (split_scratch && Cf && !Ct && K >= GEMM_BIGSPLIT_MIN_K && ntm_b * ntn_b <= GEMM_BIGSPLIT_MAX_TILES) {
-    const bool dyn = lim.n && lim_kind == 1;
+    const bool dyn = counted;
     int ks = dyn ? GEMM_SPLIT_MAX : (384 + ntm_b * ntn_b - 1) / (ntm_b * ntn_b);
     if (ks > GEMM_SPLIT_MAX) ks = GEMM_SPLIT_MAX;
     while (ks > 1 && ((size_t)ks * M * N > split_scratch_floats || K / ks < 2048)) --ks;
@@ -202,15 +215,17 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
       return;
     }
   }
-  using G = GemmSmall;
-  const int ntm = (M + G::BM - 1) / G::BM, ntn = (N + G::BN - 1) / G::BN;
+  const auto medium = [&](int d) { return (d + GemmMedium::BM - 1) / GemmMedium::BM; };
+  const bool small = gemm_small_tile(prec, (long)medium(M) * medium(N), M, N, K);
+  const int bm = small ? GemmSmall::BM : GemmMedium::BM;
+  const int ntm = (M + bm - 1) / bm, ntn = (N + bm - 1) / bm;
   const int nb = ntm * ntn;
   const int grid = ((nb + 7) / 8) * 8;
   const int esz = prec ? 2 : 4;
   const int bk = 128 / esz;
-  // few output tiles but a long contraction: split k over workgroups (two workgroups per CU wanted)
+  // few output tiles but a long contraction: split k over workgroups (four small workgroups per CU wanted)
   int ks = 1;
-  if (split_scratch && Cf && !Ct && nb < GEMM_SPLIT_BELOW && K >= 16 * bk) {
+  if (split_scratch && Cf && !Ct && small && nb < GEMM_SPLIT_BELOW && K >= 16 * bk) {
     ks = (GEMM_SPLIT_TARGET + nb - 1) / nb;
     if (ks > GEMM_SPLIT_MAX) ks = GEMM_SPLIT_MAX;
     while (ks > 1 && ((size_t)ks * M * N > split_scratch_floats || K / ks < 4 * bk)) --ks;
@@ -223,8 +238,18 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
   const int oldc = nks > 1 ? N : ldc;
   const float* obias = nks > 1 ? nullptr : bias;
   const int oacc = nks > 1 ? 0 : accumulate;
-  if (prec) gemm_go<bf16_t, 2, 2, 2, 2>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, wg_cap);
-  else gemm_go<float, 2, 2, 2, 2>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, wg_cap);
+  const int cap = small ? 4 * wg_cap : wg_cap;
+  auto go = [&](auto type, auto shape) {
+    using T = decltype(type);
+    if constexpr (decltype(shape)::value == 1)
+      gemm_go<T, 2, 2, 1, 1>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, cap);
+    else
+      gemm_go<T, 2, 2, 2, 2>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, cap);
+  };
+  using One = std::integral_constant<int, 1>;
+  using Two = std::integral_constant<int, 2>;
+  if (prec) { if (small) go(bf16_t{}, One{}); else go(bf16_t{}, Two{}); }
+  else { if (small) go(float{}, One{}); else go(float{}, Two{}); }
   if (nks > 1) launch_planes_sum(split_scratch, nks, pstride, Cf, M, N, ldc, bias, accumulate, lim_kind == 1 ? lim : RowLimit{}, st);
 }
 
@@ -305,16 +330,18 @@ void launch_gemm_nt_group(int prec, const GemmProb* probs, int n, hipStream_t st
     return;
   }
   std::vector<GemmProb> live;
-  long big = 0;
+  long big = 0, medium = 0;
   for (int i = 0; i < n; ++i) {
     if (probs[i].M <= 0 || probs[i].N <= 0) continue;
     live.push_back(probs[i]);
     big += (long)((probs[i].M + GemmBig::BM - 1) / GemmBig::BM) * ((probs[i].N + GemmBig::BN - 1) / GemmBig::BN);
+    medium += (long)((probs[i].M + GemmMedium::BM - 1) / GemmMedium::BM) * ((probs[i].N + GemmMedium::BN - 1) / GemmMedium::BN);
   }
   if (live.empty()) return;
-  // enough 256 x 256 tiles over the whole group to fill the chip: the big tile, else the small one
+  // the tile by the number of them over the whole group (k is the batch's positions: long)
   if (big >= GEMM_BIG_MIN_TILES) gemm_group_go<bf16_t, 4, 4, 2, 2>(live.data(), (int)live.size(), st, wg_cap);
-  else gemm_group_go<bf16_t, 2, 2, 2, 2>(live.data(), (int)live.size(), st, wg_cap);
+  else if (medium >= 192) gemm_group_go<bf16_t, 2, 2, 2, 2>(live.data(), (int)live.size(), st, wg_cap);
+  else gemm_group_go<bf16_t, 2, 2, 1, 1>(live.data(), (int)live.size(), st, 4 * wg_cap);
 }
 
 // Measurement aid: nothing but matrix-core instructions (4 independent 32x32x16 bf16 accumulator chains per

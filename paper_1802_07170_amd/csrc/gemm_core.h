@@ -1,12 +1,15 @@
 // LDS-tiled matrix-core main loop for C = A * B^T with both operands k-contiguous (the paper's
 // LinearLayer forward GEMM form; every batched-over-time contraction of the step is brought to
 // this form).  WM x WN wavefronts; each wavefront owns TA x TB MFMA 32x32 tiles, so the workgroup
-// tile is (32 TA WM) x (32 TB WN).  Two shapes are used:
+// tile is (32 TA WM) x (32 TB WN).  Three shapes are used:
+//   * 2x2 wavefronts, one tile each: 64 x 64, 256 threads, 36 KB of LDS, four workgroups per CU: for the many
+//     products of a small network or batch that are a few dozen tiles of the next size, where what a launch takes is
+//     the chain prologue - contraction - store of one workgroup (16 stores a lane instead of 64).
 //   * 2x2 wavefronts, 2x2 tiles each: 128 x 128, 256 threads, 72 KB of LDS, two workgroups per CU
 //     hiding each other's barriers.  Needs 32 KB from L2 per 2 x 128 x 128 x 64 flops.
 //   * 4x4 wavefronts, 2x2 tiles each: 256 x 256, 1024 threads, 144 KB of LDS, one workgroup per CU.
 //     Half the L2 traffic per flop (64 KB per k tile): 1.3 PFLOP/s on large problems, and faster than the
-//     small tile whenever there are about 200 or more tiles.
+//     others from about 150 tiles up.
 // What bounds both is the rate at which a CU takes data from L2: about 49 GB/s per CU measured with the main
 // loop's loads alone (12.6 TB/s over the chip), i.e. at most 1.6 PFLOP/s for the big tile and 0.8 for the small.
 // Tiles of KB bytes of k per row are double-buffered in LDS; the next tile's global loads are in
@@ -28,7 +31,8 @@ template <int WM, int WN, int TA, int TB, int KB = 128> struct GemmTile {
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   static constexpr int SMEM_BYTES = 2 * STAGE_BYTES;
 };
-using GemmSmall = GemmTile<2, 2, 2, 2, 128>;               // 128 x 128, 256 threads
+using GemmSmall = GemmTile<2, 2, 1, 1, 128>;               // 64 x 64, 256 threads
+using GemmMedium = GemmTile<2, 2, 2, 2, 128>;              // 128 x 128, 256 threads
 using GemmBig = GemmTile<4, 4, 2, 2, 128>;                 // 256 x 256, 1024 threads
 
 // Workgroup id -> output tile.  Consecutive workgroup ids go round-robin to the 8 XCDs (each with

@@ -1049,3 +1049,21 @@ def test_decoder_steps_of_wide_batches(B, T, H, E, L, reg):
     sens = oracle_sensitivity(cfg, params, batch, reg)
     loss, oloss, worst, tr = run_case(cfg, params, batch, 1, reg=reg, l2_override={k: max(2e-2, SWEEP_SENS_C * v) for k, v in sens.items()})
     tr.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("B,S,T,H,E,L,V", [(33, 31, 2, 64, 72, 1, 72), (65, 33, 3, 112, 40, 2, 200), (16, 4, 70, 32, 64, 1, 4104),
+                                           (128, 12, 2, 256, 1032, 1, 136)])
+def test_batched_products_at_the_edges_of_their_tiles(prec, B, S, T, H, E, L, V):
+    """The products over all positions on 64 x 64 tiles and with the contraction split: one row or column more than a
+    whole number of tiles, contractions that end inside a k tile (72, 40, 1032), a split whose last part is shorter."""
+    cfg = dict(src_vocab=104, tgt_vocab=V, emb=E, hidden=H, layers=L)
+    rng = np.random.default_rng(1500 + B)
+    params = I.make_params(cfg, seed=B, scale=0.3 if H <= 128 else 0.1)
+    batch = ragged_batch(rng, B, S, T, cfg["src_vocab"], V)
+    relax = {}
+    if prec:
+        sens = oracle_sensitivity(cfg, params, batch, None)
+        relax = dict(l2_override={k: max(2e-2, SWEEP_SENS_C * v) for k, v in sens.items()})
+    loss, oloss, worst, tr = run_case(cfg, params, batch, prec, **relax)
+    tr.close()
