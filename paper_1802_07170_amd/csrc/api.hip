@@ -1486,8 +1486,9 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
   ro.ldh = PH;
   ro.ho_src = h->HoBuf; ro.ldho_src = PH; ro.ho_dst = h->xcat + (size_t)E * esz; ro.ldho_dst = h->ldxcat;
   if (fm0) { ro.ho_dst_fm = h->xcatF; ro.ho_fm_nsteps = (E + H) >> 5; ro.ho_fm_k0 = E; }
-  for (int j = 0; j < max_len; ++j) {
-    launch_dec_embed(p, h->Pw(h->off_Etgt), E, bs.tok, R, Rp, h->xcat, h->ldxcat, st, fm0 ? h->xcatF : nullptr, (E + H) >> 5);
+  ro.table = h->Pw(h->off_Etgt); ro.E = E; ro.x = h->xcat;
+  launch_dec_embed(p, h->Pw(h->off_Etgt), E, bs.tok, R, Rp, h->xcat, h->ldxcat, st, fm0 ? h->xcatF : nullptr, (E + H) >> 5);
+  for (int j = 0; j < max_len; ++j) {                  // (the later steps' embeddings come with the reorder)
     for (int l = 0; l < L; ++l) {
       LD& e = h->dec[l];
       LstmFwdDir d;

@@ -375,6 +375,8 @@ struct BeamReorder {
   const void* ho_src; int ldho_src; void* ho_dst; int ldho_dst;   // H_o of the step -> input feed of the next
   void* ho_dst_fm = nullptr; int ho_fm_nsteps = 0, ho_fm_k0 = 0;  // optional fragment-major copy: columns [k0, k0 + H) of a
                                                                   //   matrix of ho_fm_nsteps k steps (16-bit types)
+  const void* table = nullptr; int E = 0; void* x = nullptr;      // embeddings of the new tokens -> x[r, 0:E] (pitch ldho_dst),
+                                                                  //   and columns [0, E) of ho_dst_fm
 };
 // dst[i, r, 0:cols] = src[i, r / K, 0:cols] (r < R), zero rows up to Rp; elem_bytes 2 or 4.
 void launch_beam_expand(int elem_bytes, const void* src, int ld_src, int rows_src, void* dst, int ld_dst, int n_outer, int R, int Rp,

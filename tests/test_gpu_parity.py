@@ -611,6 +611,29 @@ def test_beam_search_with_massively_tied_logits():
     tr.close()
 
 
+@pytest.mark.parametrize("B,V", [(3, 1000), (3, 8192), (3, 8200), (3, 32768), (3, 32776), (25, 8200), (26, 8192), (26, 8200)])
+def test_beam_search_at_the_edges_of_the_row_sizes(B, V):
+    """The per-row selection keeps a row in the registers of 256 or 512 threads or reads it again, by its length and the
+    number of rows (256): both sides of every line, fp32, against the oracle.  The best tokens' biases sit at the row's
+    ends, so that a piece that a form leaves out changes the result."""
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=104, tgt_vocab=V, emb=24, hidden=32, layers=2)
+    rng = np.random.default_rng(B + V)
+    params = I.make_params(cfg, seed=4, scale=0.5)
+    params["B_o"] = rng.uniform(-1.0, 1.0, V).astype(params["B_o"].dtype)
+    params["B_o"][[4, V // 2, V - 8, V - 3, V - 1]] += 2.0
+    src, sl, _, _ = ragged_batch(rng, B, 4, 5, 104, V)
+    tr = binding.Trainer(cfg, B * 10, 4, 8, precision=0)
+    tr.set_params(I.flatten(params, cfg))
+    ids, lens, score = tr.beam_decode(src, sl, 6, beam=10, length_penalty=0.6, eos_id=3)
+    oids, olens, oscore, margins = O.beam_decode(cfg, params, src, sl, 6, 10, 0.6, bos_id=2, eos_id=3)
+    assert np.allclose(score, oscore, rtol=1e-4)         # the edge cases' bar; a near tie shares its score
+    for b in range(B):
+        if margins[b] > 1e-3:
+            assert np.array_equal(ids[b], oids[b]) and lens[b] == olens[b], (B, V, b, ids[b], oids[b])
+    tr.close()
+
+
 def test_beam_search_edge_cases():
     """A beam wider than the number of candidates of the first steps (vocabulary 8, beam 16), a single
     step, and the argument checks."""
