@@ -27,7 +27,7 @@ HBM_PEAK_GBS = 8000.0
 # profiles/ gives the commands and the figures.  Valid for the workload and the kernel source it was
 # measured with: (workload, first 12 hex digits of the sha256 of csrc/step.hip + csrc/common.h) -> bytes;
 # with another source the figure is stale and reported as null.
-MEASURED_TRAFFIC_BYTES = {("medium", "22155112665a"): 22882304}      # profiles/step_kernels_medium_bf16_memory_counters.md
+MEASURED_TRAFFIC_BYTES = {("medium", "a9575a67abc7"): 22864896}      # profiles/step_kernels_medium_bf16_memory_counters.md
 
 
 def step_kernel_source_tag():
@@ -160,7 +160,7 @@ def main():
     tr.set_regularization(0.0, 0.0, 0)
     tr.train_step_async(dev)
     torch.cuda.synchronize()
-    # dominant kernel of the step (largest share of kernel time in the rocprofv3 trace under
+    # one of the two dominant kernels of the step (each a tenth of the kernel time in the rocprofv3 trace under
     # profiles/): the fused decoder LSTM step.  HBM carries its weights once; what it waits for is the
     # L2 -> CU traffic of weights plus re-read activations (see the summaries under profiles/).
     us, nbytes = tr.time_kernel("lstm_fwd_dec", 400)
