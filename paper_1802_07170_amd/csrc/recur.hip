@@ -267,17 +267,18 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs
         const float gg = tanh_of<FAST>(pre[2] + in.g[n][2]), og = sigm_of<FAST>(pre[3] + in.g[n][3]);
         const float cn = fg * c[n] + ig * gg;
         const float hn = og * tanh_of<FAST>(cn);
-        if (in.mask[n] > 0.f) { c[n] = cn; hcar[n] = hn != hn ? __uint_as_float(0x7fc00000u) : hn; }
+        float state = hcar[n];                                     // (a masked step carries on the stored value)
+        if (in.mask[n] > 0.f) { c[n] = cn; state = hn != hn ? __uint_as_float(0x7fc00000u) : hn; }
         T hv;
         if constexpr (FAST) {
-          hv = f2bf(hcar[n]);
-          hcar[n] = bf2f(hv);                                      // (what a masked step carries on is the stored value)
+          hv = f2bf(state);
+          hcar[n] = bf2f(hv);
           const unsigned p = quad_pair(hv), p2 = __builtin_amdgcn_mov_dpp(p, 0x4e, 0xf, 0xf, true);      // lanes ^ 2
           if (sender)
             __hip_atomic_store(reinterpret_cast<uint64_t*>(xs + off_x[n]), (uint64_t)p | ((uint64_t)p2 << 32), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         } else {
-          hv = hcar[n];
+          hv = hcar[n] = state;
           __hip_atomic_store(reinterpret_cast<unsigned*>(xs + off_x[n]), __float_as_uint(hv), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         asm volatile("" ::: "memory");                             // (the state first: the other workgroups wait for it)
@@ -287,7 +288,8 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs
         *(float*)(gs + (size_t)Hh * 4 + off_g[n]) = fg;
         *(float*)(gs + (size_t)Hh * 8 + off_g[n]) = gg;
         *(float*)(gs + (size_t)Hh * 12 + off_g[n]) = og;
-        if (has_y) *(T*)(ys + off_y[n]) = from_f<T>(hcar[n] * drop_factor(drop, row[n], d.y_col0 + u));
+        // (the copy after dropout is rounded once, from the state as computed)
+        if (has_y) *(T*)(ys + off_y[n]) = from_f<T>(state * drop_factor(drop, row[n], d.y_col0 + u));
       }
     };
     In in0, in1;

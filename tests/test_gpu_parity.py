@@ -433,6 +433,47 @@ def test_dropout_and_label_smoothing(prec, B, S, T, H, E, L):
     tr.close()
 
 
+def test_dropped_encoder_outputs_are_rounded_once():
+    """With 16-bit operands the copy of a layer's states that the next layer reads is the fp32 state times its dropout factor,
+    rounded once (rounding the state first changes a quarter of the kept values).  The layers above the bottom one get
+    weights that show what they read: cell gate u = tanh(input u), all else zero, so that artanh of that gate is the input;
+    what it has to be follows from the fetched output gates and cell states of the layer below.  Those are good to about 1e-6
+    and a bfloat16 interval is at least 2^-8 wide, both relative, so fewer than 1e-3 of the values can fall to the other side of
+    a rounding boundary: at most 1 % may differ."""
+    from paper_1802_07170_amd import binding
+    p, seed, B, S, H, L = 0.2, 77, 19, 7, 64, 4
+    cfg = dict(src_vocab=104, tgt_vocab=136, emb=16, hidden=H, layers=L)
+    rng = np.random.default_rng(21)
+    params = I.make_params(cfg, seed=5, scale=0.3)
+    for l in range(1, L):
+        params[f"enc.l{l}.W"][:] = 0
+        params[f"enc.l{l}.W"][2 * H + np.arange(H), np.arange(H)] = 1.0
+        params[f"enc.l{l}.b"][:] = 0
+    batch = ragged_batch(rng, B, S, 3, cfg["src_vocab"], cfg["tgt_vocab"])
+    tr = binding.Trainer(cfg, B, S, 3, precision=1)
+    try:
+        tr.set_params(I.flatten(params, cfg))
+        tr.set_regularization(p, 0.0, seed)
+        tr.train_step(tr.upload_batch(*batch))
+        Bp = tr.padded_batch()
+        valid = np.arange(S)[:, None] < batch[1][None, :]
+
+        def fetch(name, width):
+            return tr.debug_fetch(name, (S, Bp, width))[:, :B].astype(np.float64)
+
+        def state(name, width):
+            return fetch(f"{name}.gates", 4 * width)[:, :, 3 * width:] * np.tanh(fetch(f"{name}.c", width))
+        for l in range(L - 1):                                  # the top layer's output is not dropped
+            below = np.concatenate([state("enc.l0.fwd", H // 2), state("enc.l0.bwd", H // 2)], -1) if l == 0 else state(f"enc.l{l}", H)
+            want = bf16_round(below * O.dropout_mask(seed, O.DROPOUT_SITE_ENC + l, S, B, H, p))[valid]
+            got = np.arctanh(fetch(f"enc.l{l + 1}.gates", 4 * H)[:, :, 2 * H:3 * H])[valid]
+            assert np.count_nonzero(want) > want.size // 2
+            off = np.abs(got - want) > 2.0 ** -10 * np.abs(want) + 1e-6
+            assert off.mean() <= 0.01, (l, off.mean())
+    finally:
+        tr.close()
+
+
 def test_label_smoothing_alone_and_dropout_alone():
     cfg = dict(src_vocab=104, tgt_vocab=328, emb=16, hidden=48, layers=2)
     rng = np.random.default_rng(17)
