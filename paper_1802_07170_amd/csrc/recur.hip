@@ -14,8 +14,8 @@
 //     with agent-scope loads.  It sleeps for about the time that a store takes to be visible before it looks: looking
 //     earlier costs more than it gains, since the reads then stand in the way of the stores they wait for.
 // Roles are taken from a ticket counter, in order of arrival, so that the workgroups on the chip always form complete
-// groups and at most one incomplete one per launch: as long as no more than 256 / (group size) such launches run at
-// once (a process has four hardware queues, the largest group is 64), a workgroup can always start and complete a group.
+// groups and at most one incomplete one per launch.  Groups have at most 64 workgroups (recur_plan.h), so the four launches
+// that a process's hardware queues can run at once leave a CU free for one of them to complete its group.
 // Every wait is bounded all the same and reports an error (recur_settle).
 //
 // What a position costs (bf16, us; before: one launch per position, 8.5 - 9, upper layers forward 5.6 of a shared one):
@@ -30,6 +30,7 @@
 #include "cell.h"
 #include "common.h"
 #include "kernels.h"
+#include "recur_plan.h"
 
 namespace cmt {
 
@@ -132,9 +133,10 @@ __device__ __forceinline__ uint64_t quad_transpose(bf16_t g0, bf16_t g1, bf16_t 
   return high ? (uint64_t)qx | ((uint64_t)q << 32) : (uint64_t)p | ((uint64_t)px << 32);
 }
 
-template <typename T, int KS, int NK, int RT, int BT, int NE>
+template <typename T, int KS, int NK, int LK, int RT, int BT, int NE>
 __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs args, int L, int Bp, int Hh, int ndir, int nap) {
   __shared__ __align__(16) float red[2][KS * RT * BT * 256];
+  __shared__ Frag<T> wlds[LK ? KS * LK * RT * 64 : 1];           // the last LK k steps' weights, read by the wavefront that put them there
   __shared__ int s_id;
   if (threadIdx.x == 0) s_id = atomicAdd(args.ticket, 1);
   __syncthreads();
@@ -148,8 +150,9 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs
   const size_t slot = (size_t)(Bp >> 4) * nsteps * 512;          // elements per slot of the exchange buffer
   const int rev = d.reverse;
   if (w < KS) {
-    // ---- contraction: wavefront w takes the k steps w, w + KS, ...; its weights stay in registers -----------------
-    Frag<T> wf[NK][RT];
+    // ---- contraction: wavefront w takes the k steps w, w + KS, ...; its weights stay in registers (and LDS) ---------
+    Frag<T> wf[NK - LK][RT];
+    Frag<T>* const wl = wlds + w * LK * RT * 64 + lane;
     bool kin[NK];
 #pragma unroll
     for (int q = 0; q < NK; ++q) {
@@ -158,8 +161,11 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         const int m = lane & 15, u = min(u0 + 4 * rt + (m >> 2), Hh - 1);
-        if (kin[q]) wf[q][rt].load((const T*)d.W + (size_t)((m & 3) * Hh + u) * d.ldw + d.wh_off + k);
-        else wf[q][rt].zero();
+        Frag<T> f;
+        if (kin[q]) f.load((const T*)d.W + (size_t)((m & 3) * Hh + u) * d.ldw + d.wh_off + k);
+        else f.zero();
+        if (q < NK - LK) wf[q][rt] = f;
+        else wl[((q - (NK - LK)) * RT + rt) * 64] = f;
       }
     }
     bool dead = false;
@@ -187,9 +193,11 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs
 #pragma unroll
         for (int q = 0; q < NK; ++q)
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
+          for (int rt = 0; rt < RT; ++rt) {
+            const Frag<T> f = q < NK - LK ? wf[q < NK - LK ? q : 0][rt] : wl[((q - (NK - LK)) * RT + rt) * 64];
 #pragma unroll
-            for (int b = 0; b < BT; ++b) mma16(acc[rt][b], wf[q][rt], fx[q * BT + b]);
+            for (int b = 0; b < BT; ++b) mma16(acc[rt][b], f, fx[q * BT + b]);
+          }
         float* r = red[i & 1];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
@@ -487,54 +495,45 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_bwd_kernel(SeqBwdArgs
 }
 
 template <typename T, int KS, int NK, int RT, int NE>
-static void seq_bwd_go(const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
-  const int groups = ndir * (Bp >> 4), nwg = (Hh + 16 * RT - 1) / (16 * RT);
-  hipLaunchKernelGGL((lstm_seq_bwd_kernel<T, KS, NK, RT, NE>), dim3(groups * nwg), dim3(64 * (KS + NE)), 0, st, a, L, Bp, Hh, ndir,
+static void seq_bwd_go(const SeqPlan& p, const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+  hipLaunchKernelGGL((lstm_seq_bwd_kernel<T, KS, NK, RT, NE>), dim3(p.groups * p.group), dim3(64 * (KS + NE)), 0, st, a, L, Bp, Hh, ndir,
                      RECUR_NAP_BWD);
 }
-template <int KS, int NK>
-static void seq_bwd_rt(int prec, const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
-  const int wgs = ndir * (Bp >> 4) * ((Hh + 15) / 16);
-  if (!prec) seq_bwd_go<float, KS, NK, 1, 4>(a, ndir, L, Bp, Hh, st);
-  else if (wgs <= 128) seq_bwd_go<bf16_t, KS, NK, 1, 4>(a, ndir, L, Bp, Hh, st);
-  else seq_bwd_go<bf16_t, KS, NK, 2, (NK > 8 ? 4 : 8)>(a, ndir, L, Bp, Hh, st);
-}
 void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
-  const int nsteps = Hh / 8;
-  if (nsteps <= 4) seq_bwd_rt<2, 2>(prec, a, ndir, L, Bp, Hh, st);
-  else if (nsteps <= 16) seq_bwd_rt<8, 2>(prec, a, ndir, L, Bp, Hh, st);
-  else if (nsteps <= 32) seq_bwd_rt<8, 4>(prec, a, ndir, L, Bp, Hh, st);
-  else if (nsteps <= 64) seq_bwd_rt<8, 8>(prec, a, ndir, L, Bp, Hh, st);
-  else seq_bwd_rt<8, 16>(prec, a, ndir, L, Bp, Hh, st);
-}
-
-template <typename T, int KS, int NK, int RT, int BT, int NE>
-static void seq_fwd_go(const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
-  const int groups = ndir * (((Bp >> 4) + BT - 1) / BT), nwg = (Hh + 4 * RT - 1) / (4 * RT);
-  hipLaunchKernelGGL((lstm_seq_fwd_kernel<T, KS, NK, RT, BT, NE>), dim3(groups * nwg), dim3(64 * (KS + NE)), 0, st, a, L, Bp, Hh, ndir, BT == 1 ? RECUR_NAP_FWD : RECUR_NAP_FWD2);
-}
-template <typename T, int KS, int NK, int RT, int NE2>
-static void seq_fwd_bt(const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
-  // one tile of sentences per group while that is one round of workgroups over the chip, else two
-  const int wgs = ndir * (Bp >> 4) * ((Hh + 4 * RT - 1) / (4 * RT));
-  if (wgs <= 256) seq_fwd_go<T, KS, NK, RT, 1, 4>(a, ndir, L, Bp, Hh, st);
-  else seq_fwd_go<T, KS, NK, RT, 2, NE2>(a, ndir, L, Bp, Hh, st);
-}
-
-void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
-  const int nsteps = (Hh + 31) / 32;
-  // (registers: twice as many cell wavefronts for two tiles of sentences where 128 per lane are enough; half as many
-  // units per workgroup for long fp32 rows)
-#define GO(KS, NK, RTF, NE2)                                                    \
-  do {                                                                          \
-    if (prec) seq_fwd_bt<bf16_t, KS, NK, 4, NE2>(a, ndir, L, Bp, Hh, st);       \
-    else seq_fwd_bt<float, KS, NK, RTF, 4>(a, ndir, L, Bp, Hh, st);             \
+  const SeqPlan p = seq_bwd_plan(prec, ndir, Bp, Hh);
+#define GO(KS, NK)                                                                                   \
+  do {                                                                                               \
+    if (!prec) seq_bwd_go<float, KS, NK, 1, 4>(p, a, ndir, L, Bp, Hh, st);                           \
+    else if (p.rt == 1) seq_bwd_go<bf16_t, KS, NK, 1, 4>(p, a, ndir, L, Bp, Hh, st);                 \
+    else seq_bwd_go<bf16_t, KS, NK, 2, (NK > 8 ? 4 : 8)>(p, a, ndir, L, Bp, Hh, st);                 \
   } while (0)
-  if (nsteps <= 2) GO(2, 1, 4, 4);
-  else if (nsteps <= 4) GO(2, 2, 4, 4);
-  else if (nsteps <= 8) GO(8, 1, 4, 8);
-  else if (nsteps <= 16) GO(8, 2, 4, 8);
-  else GO(8, 4, 2, 4);
+  if (p.ks == 2) GO(2, 2);
+  else if (p.nk == 2) GO(8, 2);
+  else if (p.nk == 4) GO(8, 4);
+  else if (p.nk == 8) GO(8, 8);
+  else GO(8, 16);
+#undef GO
+}
+
+template <typename T, int KS, int NK, int LK, int BT, int NE>
+static void seq_fwd_go(const SeqPlan& p, const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+  hipLaunchKernelGGL((lstm_seq_fwd_kernel<T, KS, NK, LK, 4, BT, NE>), dim3(p.groups * p.group), dim3(64 * (KS + NE)), 0, st, a, L, Bp, Hh,
+                     ndir, BT == 1 ? RECUR_NAP_FWD : RECUR_NAP_FWD2);
+}
+void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+  const SeqPlan p = seq_fwd_plan(prec, ndir, Bp, Hh);
+#define GO(KS, NK, NE2)                                                                              \
+  do {                                                                                               \
+    if (prec && p.bt == 1) seq_fwd_go<bf16_t, KS, NK, 0, 1, 4>(p, a, ndir, L, Bp, Hh, st);           \
+    else if (prec) seq_fwd_go<bf16_t, KS, NK, 0, 2, NE2>(p, a, ndir, L, Bp, Hh, st);                 \
+    else if (p.bt == 1) seq_fwd_go<float, KS, NK, NK == 4, 1, 4>(p, a, ndir, L, Bp, Hh, st);         \
+    else if constexpr (NK < 4) seq_fwd_go<float, KS, NK, 0, 2, 4>(p, a, ndir, L, Bp, Hh, st);        \
+  } while (0)
+  if (p.ks == 2 && p.nk == 1) GO(2, 1, 4);
+  else if (p.ks == 2) GO(2, 2, 4);
+  else if (p.nk == 1) GO(8, 1, 8);
+  else if (p.nk == 2) GO(8, 2, 8);
+  else GO(8, 4, 4);
 #undef GO
 }
 

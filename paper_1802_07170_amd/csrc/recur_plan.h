@@ -1,0 +1,49 @@
+// Shapes of the whole-recurrence kernels (recur.hip): which workgroups form a group that waits for one another.  No
+// device code, so that the rules can be checked with a host compiler.
+#pragma once
+
+namespace cmt {
+
+// A launch starts its workgroups group by group, so of its groups at most one is incomplete.  SEQ_QUEUES such launches run at
+// once in a process (its hardware queues).  With one workgroup per CU they can all be stuck only if their incomplete groups,
+// one workgroup short each, take every CU: not while SEQ_QUEUES * (group - 1) < CUs, i.e. 4 x 63 < 256.
+constexpr int SEQ_QUEUES = 4, SEQ_MAX_GROUP = 64;
+
+// ks wavefronts split the contraction, nk k steps of 32 each, of which the weights of lk stay in LDS and the others in
+// registers; rt row tiles (forward 4 units x 4 gates, backward 16 units) x bt tiles of 16 sentences per workgroup; ne
+// wavefronts for the cells.
+struct SeqPlan { int ks, nk, lk, rt, bt, ne, group, groups; };
+
+inline SeqPlan seq_fwd_plan(int prec, int ndir, int Bp, int Hh) {
+  const int nsteps = (Hh + 31) / 32;
+  SeqPlan p{};
+  p.ks = nsteps <= 4 ? 2 : 8;
+  p.nk = nsteps <= 2 ? 1 : nsteps <= 4 ? 2 : nsteps <= 8 ? 1 : nsteps <= 16 ? 2 : 4;
+  p.rt = 4;
+  p.group = (Hh + 4 * p.rt - 1) / (4 * p.rt);
+  // Long fp32 rows: 16 units are 256 KB of weights.  A quarter of them in LDS leaves room for one tile of sentences in the
+  // registers.  (8 units per workgroup fit the registers alone, but in groups of up to 128, too many to wait for one
+  // another; the times agree within 1 %, e.g. a step of 2 layers of 1024 units, 64 sentences 8.80 | 8.74 ms.)
+  p.lk = !prec && p.nk == 4 ? 1 : 0;
+  // one tile of sentences per group while that is one round of workgroups over the chip, else two
+  p.bt = p.lk || ndir * (Bp >> 4) * p.group <= 256 ? 1 : 2;
+  // (registers: twice as many cell wavefronts for two tiles of sentences where 128 per lane are enough)
+  p.ne = prec && p.bt == 2 && (nsteps > 4 && nsteps <= 16) ? 8 : 4;
+  p.groups = ndir * (((Bp >> 4) + p.bt - 1) / p.bt);
+  return p;
+}
+
+inline SeqPlan seq_bwd_plan(int prec, int ndir, int Bp, int Hh) {
+  const int nsteps = Hh / 8;                           // k steps of 32 gate rows
+  SeqPlan p{};
+  p.ks = nsteps <= 4 ? 2 : 8;
+  p.nk = nsteps <= 16 ? 2 : nsteps <= 32 ? 4 : nsteps <= 64 ? 8 : 16;
+  p.bt = 1;
+  p.groups = ndir * (Bp >> 4);
+  p.rt = prec && p.groups * ((Hh + 15) / 16) > 128 ? 2 : 1;
+  p.ne = p.rt == 2 && p.nk <= 8 ? 8 : 4;
+  p.group = (Hh + 16 * p.rt - 1) / (16 * p.rt);
+  return p;
+}
+
+}  // namespace cmt

@@ -1042,7 +1042,7 @@ def test_small_config_fp32_full_size():
                                            (150, 2, 1024, 16, 2, (0.2, 0.0, 8))])
 def test_encoder_recurrences_at_tile_edges(prec, B, S, H, E, L, reg):
     """The encoder's recurrences run as one launch each, on groups of 16 or 32 sentences whose workgroups hold 16 units
-    (8 for wide fp32 layers) forwards and 16 or 32 backwards and exchange states and gate gradients through memory: batches
+    forwards and 16 or 32 backwards and exchange states and gate gradients through memory: batches
     around the sentence tiles (the last tile of a pair missing; one and two tiles per group; more workgroups than CUs),
     widths whose units do not fill the last workgroup (bottom layer 8, 24, 72, 168, 264) and every split of the
     contraction, with and without the dropped copies.  All intermediates and gradients at the usual bars, bf16
