@@ -62,7 +62,12 @@ int cmt_query_sizes(const cmt_config* cfg, size_t* param_bytes, size_t* grad_byt
 
 /* Binds caller-owned device buffers (each 256-byte aligned, sizes from cmt_query_sizes) and a
  * HIP stream (hipStream_t passed as void*; NULL = the default stream).  The buffers must stay
- * alive until cmt_destroy.  Parameters are uninitialised until cmt_init_params / cmt_set_params. */
+ * alive until cmt_destroy.  Parameters are uninitialised until cmt_init_params / cmt_set_params.
+ * Handles are independent of one another: any number may be at work on a device, on streams and in threads of
+ * their own (one call at a time per handle) and beside other processes.  The encoder's recurrences are made by workgroups
+ * that wait for one another; with up to four such launches at once on 256 CUs, what a process's hardware queues allow by
+ * default, they always get on.  Where they do not, a recurrence gives up its waits after 50 ms and is made again
+ * without any: the call is late, by some tens of milliseconds per layer, and its results are sound. */
 int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* workspace_dev,
                void* hip_stream, cmt_handle** out);
 /* Releases the handle, its pinned host memory, its internal stream and events (it waits for the

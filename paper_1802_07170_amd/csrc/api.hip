@@ -136,7 +136,8 @@ struct cmt_handle {
   int32_t *ce_pos = nullptr, *ce_row = nullptr, *ce_nvalid = nullptr, *labels_c = nullptr;
   char* Hoc = nullptr; char* HocT = nullptr;   // H_o (as the output layer sees it) of the valid positions, and its transpose
   float* loss = nullptr; int* flags = nullptr; float* colscr = nullptr;
-  int* tickets = nullptr;               // SEQ_TICKETS counters, one per recurrence launch of a pass (layers <= 8)
+  int* tickets = nullptr;               // SEQ_TICKETS words, two per recurrence launch of a pass (layers <= 8)
+  SeqRun seq{};                         // how the recurrences run (env CMT_RECUR)
   char* dzs = nullptr; char* dzTs = nullptr; float* dbo_parts = nullptr;
   std::vector<GemmProb> dw_group;       // weight-gradient GEMMs collected for one grouped launch (flush_dw_group)
   int ce_rows = 0, ce_pitch = 0;        // row capacity of an output-layer slab and the row pitch of its buffers
@@ -657,28 +658,28 @@ void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
     return d;
   };
   SeqFwdArgs sa{};
-  sa.ticket = h->tickets; sa.flags = h->flags;
+  sa.ticket = h->tickets;
   for (int i = 0; i < 2; ++i) {
     SeqFwdDir& d = sa.d[i];
     d = seq_dir(i ? eb : ef);
     d.Y = h->Y0; d.ldy = H; d.y_col0 = i ? Hd : 0; d.reverse = i;
     if (L > 1) { d.drop = drop_spec(h, DROP_SITE_ENC + 0, 0); d.drop_step = drop_step; }
   }
-  launch_lstm_seq_fwd(p, sa, 2, S, Bp, Hd, st);
+  launch_lstm_seq_fwd(p, sa, 2, S, Bp, Hd, h->seq, st);
   phase_mark(h, "encoder upper layers");
   const char* Yprev = h->Y0;                       // [S*Bp, H] what the next layer (or the attention) reads
   int ldY = H;
   for (int l = 1; l < L; ++l) {
     LD& e = h->enc[l + 1];
     launch_gemm_nt(p, Yprev, ldY, e.W, 2 * H, Ms, 4 * H, H, e.Gx, nullptr, 4 * H, P + e.b_off, 0, st);
-    sa.ticket = h->tickets + l;
+    sa.ticket = h->tickets + 2 * l;
     sa.d[0] = seq_dir(e);
     const bool dropped = drop && l + 1 < L;
     if (dropped) {
       sa.d[0].Y = e.Yd; sa.d[0].ldy = PH;
       sa.d[0].drop = drop_spec(h, DROP_SITE_ENC + l, 0); sa.d[0].drop_step = drop_step;
     }
-    launch_lstm_seq_fwd(p, sa, 1, S, Bp, H, st);
+    launch_lstm_seq_fwd(p, sa, 1, S, Bp, H, h->seq, st);
     Yprev = dropped ? e.Yd : e.Hst + BP * esz; ldY = PH;
   }
   const char* Hs = Yprev;
@@ -1037,15 +1038,14 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
     return d;
   };
   SeqBwdArgs sb{};
-  sb.flags = h->flags;
   for (int l = L - 1; l >= 1; --l) {
     LD& e = h->enc[l + 1];
     SeqBwdDir& d = sb.d[0];
     d = seq_bwd_dir(e, l == L - 1 ? h->dHs : h->dYa);
     if (l < L - 1) { d.drop = drop_spec(h, DROP_SITE_ENC + l, 0); d.drop_step = drop_step; }
     d.dh0 = h->dec[l].dh; d.dc0 = h->dec[l].dc;    // gradient of the final state = that of the decoder's initial state
-    sb.ticket = h->tickets + l;
-    launch_lstm_seq_bwd(p, sb, 1, S, Bp, H, st);
+    sb.ticket = h->tickets + 2 * l;
+    launch_lstm_seq_bwd(p, sb, 1, S, Bp, H, h->seq, st);
     launch_gemm_nt(p, e.dG, e.pg, e.Wt, 4 * H, Ms, H, 4 * H, h->dYa, nullptr, H, nullptr, 0, st);   // the layer below's dY = dG W_x
   }
   if (L > 1) {
@@ -1068,7 +1068,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
       d.dh0 = d0.dh + (i ? Hd : 0); d.dc0 = d0.dc + (i ? Hd : 0);
     }
     sb.ticket = h->tickets;
-    launch_lstm_seq_bwd(p, sb, 2, S, Bp, Hd, st);
+    launch_lstm_seq_bwd(p, sb, 2, S, Bp, Hd, h->seq, st);
     // What is left after the last recurrent kernel is shared between the two streams: the weight gradients of
     // both directions on the second one, the source-embedding gradient (dX_s, then the scatter) on the caller's.
     stream_after(h, sd, st);
@@ -1132,10 +1132,16 @@ int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* w
     const char* k3p = getenv("CMT_ATT_PROJ"); h->att_proj = k3p ? atoi(k3p) : 1;
     const char* k4 = getenv("CMT_PHASE_TIMING"); h->phase_timing = k4 ? atoi(k4) : 0;
     const char* k5 = getenv("CMT_BWD_FUSED"); h->bwd_fused = k5 ? atoi(k5) : 1;
+    const char* k6 = getenv("CMT_RECUR"); h->seq.mode = k6 ? atoi(k6) : SEQ_RUN_TOGETHER;
   }
   build_table(h->cfg, h->table, h->nparams);
   h->ws_bytes = layout(h, h->ws);
   bind_params(h);
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&h->seq.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+    cmt_destroy(h);
+    return CMT_EHIP;
+  }
   hipError_t e = hipHostMalloc((void**)&h->h_loss, 256, hipHostMallocDefault);
   if (e != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
   // second stream at the default priority, and a pool of events for the hand-offs between the two
@@ -1310,7 +1316,6 @@ int cmt_fetch_loss(cmt_handle* h, float* loss_host) {
     launch_fill_f32((float*)h->flags, 1, 0.f, h->st);
   }
   if (flags & 3) return fail(h, CMT_ERANGE, (flags & 1) ? "a token id is outside its vocabulary" : "a length is outside [1, padded length]");
-  if (flags & CMT_FLAG_GAVE_UP) return fail(h, CMT_EHIP, "a wait between workgroups was given up");
   if (flags & 4) return fail(h, CMT_ENONFINITE, "the loss is not finite");
   return CMT_OK;
 }
@@ -1417,7 +1422,6 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
   if (e != hipSuccess) return hip_fail(h, e, "cmt_greedy_decode");
   const int flags = *h->h_flags;
   if (flags & 3) return fail(h, CMT_ERANGE, (flags & 1) ? "a token id is outside its vocabulary" : "a length is outside [1, padded length]");
-  if (flags & CMT_FLAG_GAVE_UP) return fail(h, CMT_EHIP, "a wait between workgroups was given up");
   return CMT_OK;
 }
 
@@ -1534,7 +1538,6 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
   if (e != hipSuccess) return hip_fail(h, e, "cmt_beam_decode");
   const int flags = *h->h_flags;
   if (flags & 3) return fail(h, CMT_ERANGE, (flags & 1) ? "a token id is outside its vocabulary" : "a length is outside [1, padded length]");
-  if (flags & CMT_FLAG_GAVE_UP) return fail(h, CMT_EHIP, "a wait between workgroups was given up");
   return CMT_OK;
 }
 

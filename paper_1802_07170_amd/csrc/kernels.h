@@ -262,8 +262,10 @@ void launch_tanh_bwd(int prec, const float* dHo_ce, const int32_t* pos, const Pl
                      int ldp, int Bp, int H, const DropSpec& drop, hipStream_t st, void* dpre_fm = nullptr /* fragment-major copy */);
 
 // ---- recur.hip -----------------------------------------------------------------------------------
-// Bits of the device's error word: 1 a bad token id, 2 a bad length, 4 a loss that is not finite, and
-constexpr int CMT_FLAG_GAVE_UP = 8;       // a bounded wait between workgroups was given up
+// How a recurrence runs on a device of `cus` CUs: its workgroups waiting for one another, with a second launch that makes it again
+// without waits if one had to be given up; without waits at once; or every wait given up (for tests of the second launch).
+enum { SEQ_RUN_ALONE = 0, SEQ_RUN_TOGETHER = 1, SEQ_RUN_GIVE_UP = 2 };
+struct SeqRun { int cus = 0; int mode = SEQ_RUN_TOGETHER; };
 // One LSTM (layer, direction) over all L positions, its input part batched into gx.
 struct SeqFwdDir {
   const void* W; int ldw, wh_off;         // T* [4Hh, ldw], the recurrent columns start at wh_off
@@ -278,7 +280,8 @@ struct SeqFwdDir {
   DropSpec drop; unsigned long long drop_step;   // dropout at position t: drop with key0 + t * drop_step
   int reverse;                            // positions run from L - 1 to 0: position t reads slot t + 1, writes slot t
 };
-struct SeqFwdArgs { SeqFwdDir d[2]; int* ticket; int* flags; };   // ticket: zero before the launch
+// ticket: two words, zero before the launch (roles taken; whether a wait was given up); wait_ticks is set by the launcher
+struct SeqFwdArgs { SeqFwdDir d[2]; int* ticket; int wait_ticks; };
 constexpr int SEQ_TICKETS = 64;
 inline size_t seq_exchange_elems(int slots, int Bp, int Hh) { return (size_t)slots * Bp * ((Hh + 31) / 32 * 32); }
 // Backward of the same: builds the gate gradients of every position.
@@ -292,10 +295,10 @@ struct SeqBwdDir {
   void* dG; int lddg;                     // gate gradients T*: L slots of [Bp, lddg]
   int reverse;                            // the direction of the forward pass
 };
-struct SeqBwdArgs { SeqBwdDir d[2]; int* ticket; int* flags; };
-void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st);
+struct SeqBwdArgs { SeqBwdDir d[2]; int* ticket; int wait_ticks; };
+void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& args, int ndir, int L, int Bp, int Hh, const SeqRun& run, hipStream_t st);
 // Forward: the initial states are zero (the slots before the first position are not read).  1 <= ndir <= 2 instances of one shape.
-void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st);
+void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& args, int ndir, int L, int Bp, int Hh, const SeqRun& run, hipStream_t st);
 
 // ---- misc.hip ----------------------------------------------------------------------------------
 // Embedding gather + masks + input validation (flags |= 1 bad id, |= 2 bad length).

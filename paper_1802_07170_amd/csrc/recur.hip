@@ -15,8 +15,11 @@
 //     earlier costs more than it gains, since the reads then stand in the way of the stores they wait for.
 // Roles are taken from a ticket counter, in order of arrival, so that the workgroups on the chip always form complete
 // groups and at most one incomplete one per launch.  Groups have at most 64 workgroups (recur_plan.h), so the four launches
-// that a process's hardware queues can run at once leave a CU free for one of them to complete its group.
-// Every wait is bounded all the same and reports an error (recur_settle).
+// that a process's hardware queues can run at once leave a CU free for one of them to complete its group.  Nothing rests on
+// that but speed: more queues, other processes or a stream confined to a few CUs may stop a group from forming.  Every wait
+// is bounded, a workgroup that gives up says so and finishes without waiting, the others of the launch follow, and a second
+// launch (2 us where there is nothing to do) makes the recurrence again without waits, one workgroup per 16 sentences:
+// some hundred us a position at width 1024.  That form also serves devices too small for the groups.
 //
 // What a position costs (bf16, us; before: one launch per position, 8.5 - 9, upper layers forward 5.6 of a shared one):
 // forward 1.2 (width 256, 32 sentences), 1.7 (512, 64 sentences, two directions), 2.7 (1024, 64 sentences), 3.1 (512, 128
@@ -35,7 +38,7 @@
 namespace cmt {
 
 constexpr unsigned RECUR_EMPTY = 0xffffffffu;          // a word of a slot that nobody has written
-constexpr long long RECUR_WAIT_TICKS = 1000000000ll;   // 10 s of the 100 MHz wall clock, then the wait is given up
+constexpr int RECUR_WAIT_TICKS = 5000000;              // 50 ms of the 100 MHz wall clock, then a wait is given up
 // s_sleep units (64 clocks) before a workgroup looks for its neighbours' results.  Measured per launch: forward, one tile of
 // sentences 14: 123 us, 20: 87, 26: 92 (width 512, 64 sentences, 50 positions); two tiles 20: 287, 28: 254, 40: 253 (128
 // sentences, 80 positions); backward 28: 262, 36: 240, 44: 225 and no change beyond (width 1024).
@@ -78,8 +81,8 @@ __device__ __forceinline__ unsigned recur_top(const Frag<float>& f) {
 }
 // N fragments of a slot, each at a uniform base p[i] plus this lane's offset; in[i]: whether this lane has a part in it
 // (else zero).  First through the caches, which usually finds everything there (the wavefront has slept for about the
-// time that a store takes to be visible); while any piece is still empty, again from memory.  `dead`: a wait has been
-// given up before, take what there is.
+// time that a store takes to be visible); while any piece is still empty, again from memory.  `dead`: this workgroup or
+// another one of the launch has given up (*gave_up), take what there is.
 template <typename T, int N>
 __device__ __forceinline__ void recur_issue(const T* const (&p)[N], const bool (&in)[N], unsigned off, Frag<T> (&f)[N]) {
 #pragma unroll
@@ -90,7 +93,7 @@ __device__ __forceinline__ void recur_issue(const T* const (&p)[N], const bool (
 }
 template <typename T, int N>
 __device__ __forceinline__ void recur_settle(const T* const (&p)[N], const bool (&in)[N], unsigned off, Frag<T> (&f)[N], bool& dead,
-                                             int* flags) {
+                                             int* gave_up, int wait_ticks) {
   unsigned top = 0;
 #pragma unroll
   for (int i = 0; i < N; ++i) top = max(top, recur_top(f[i]));
@@ -102,12 +105,12 @@ __device__ __forceinline__ void recur_settle(const T* const (&p)[N], const bool 
     for (int i = 0; i < N; ++i)
       if (in[i]) recur_load(p[i] + off, f[i], top);
     if (!__any(top == RECUR_EMPTY)) return;
-    if ((spin & 255) == 255) {
+    if ((spin & 15) == 15) {
       const long long now = wall_clock64();
-      if (t_end == 0) t_end = now + RECUR_WAIT_TICKS;
-      else if (now > t_end) {
+      if (t_end == 0) t_end = now + wait_ticks;
+      else if (now > t_end || __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
         dead = true;
-        if ((threadIdx.x & 63) == 0) atomicOr(flags, CMT_FLAG_GAVE_UP);
+        if ((threadIdx.x & 63) == 0) atomicOr(gave_up, 1);
         return;
       }
     }
@@ -133,15 +136,64 @@ __device__ __forceinline__ uint64_t quad_transpose(bf16_t g0, bf16_t g1, bf16_t 
   return high ? (uint64_t)qx | ((uint64_t)q << 32) : (uint64_t)p | ((uint64_t)px << 32);
 }
 
+// The role of this workgroup (its number in order of arrival), and whether the launch has given up already; ticket as in
+// SeqFwdArgs.  With wait_ticks = 0 every wait is given up beforehand.
+__device__ __forceinline__ int recur_role(int* ticket, int wait_ticks, int (&s_role)[2], bool& dead) {
+  if (threadIdx.x == 0) {
+    if (wait_ticks == 0) atomicOr(ticket + 1, 1);
+    s_role[1] = __hip_atomic_load(ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_role[0] = atomicAdd(ticket, 1);
+  }
+  __syncthreads();
+  dead = s_role[1] != 0;
+  return s_role[0];
+}
+
+// The cell of one sentence and unit: recurrent part `pre` and input part `gx` of its four gates, cell state c (in and out), h
+// = the stored state that a masked step carries on.  Returns the new state as computed, NaN in its canonical form.
+template <bool FAST>
+__device__ __forceinline__ float seq_cell(const v4f& pre, const float (&gx)[4], float mask, float h, float& c, float (&g)[4]) {
+  g[0] = sigm_of<FAST>(pre[0] + gx[0]);
+  g[1] = sigm_of<FAST>(pre[1] + gx[1]);
+  g[2] = tanh_of<FAST>(pre[2] + gx[2]);
+  g[3] = sigm_of<FAST>(pre[3] + gx[3]);
+  const float cn = g[1] * c + g[0] * g[2];
+  const float hn = g[3] * tanh_of<FAST>(cn);
+  if (!(mask > 0.f)) return h;
+  c = cn;
+  return hn != hn ? __uint_as_float(0x7fc00000u) : hn;
+}
+// Its backward: gate activations g, the cell state before (cp) and the tanh of the one after (tc), the gradient dy at its
+// output and the recurrent part rec; dh, dc = the state's gradients that pass by (in and out), o = the gate gradients.
+__device__ __forceinline__ void seq_cell_bwd(const float (&g)[4], float cp, float tc, float dy, float rec, float mask, float& dh, float& dc,
+                                             float (&o)[4]) {
+  const bool valid = mask > 0.f;
+  const float ig = g[0], fg = g[1], gg = g[2], og = g[3];
+  const float state = dh + rec;
+  const float dht = state + dy;
+  const float dct = dc + dht * og * (1.f - tc * tc);
+  o[0] = dct * gg * ig * (1.f - ig);
+  o[1] = dct * cp * fg * (1.f - fg);
+  o[2] = dct * ig * (1.f - gg * gg);
+  o[3] = dht * tc * og * (1.f - og);
+  dh = valid ? 0.f : state;                                        // masked: the state's gradient passes through
+  dc = valid ? dct * fg : dc;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    o[q] = valid ? o[q] : 0.f;
+    if (o[q] != o[q]) o[q] = __uint_as_float(0x7fc00000u);
+  }
+}
+
 template <typename T, int KS, int NK, int LK, int RT, int BT, int NE>
 __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs args, int L, int Bp, int Hh, int ndir, int nap) {
   __shared__ __align__(16) float red[2][KS * RT * BT * 256];
   __shared__ Frag<T> wlds[LK ? KS * LK * RT * 64 : 1];           // the last LK k steps' weights, read by the wavefront that put them there
-  __shared__ int s_id;
-  if (threadIdx.x == 0) s_id = atomicAdd(args.ticket, 1);
-  __syncthreads();
+  __shared__ int s_role[2];
+  bool dead;
+  const int id = recur_role(args.ticket, args.wait_ticks, s_role, dead);
   const int nwg = (Hh + 4 * RT - 1) / (4 * RT);                  // workgroups per group
-  const int grp = s_id / nwg, u0 = (s_id - grp * nwg) * 4 * RT;
+  const int grp = id / nwg, u0 = (id - grp * nwg) * 4 * RT;
   const SeqFwdDir d = args.d[grp % ndir];
   const int bt0 = (grp / ndir) * BT;
   const int nbt = min(BT, (Bp >> 4) - bt0);
@@ -168,7 +220,6 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs
         else wl[((q - (NK - LK)) * RT + rt) * 64] = f;
       }
     }
-    bool dead = false;
     for (int i = 0; i < L; ++i) {
       if (i > 0) {
         const T* x = (const T*)d.X + (size_t)(rev ? L - i : i) * slot + (size_t)bt0 * nsteps * 512;
@@ -184,7 +235,7 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs
           }
         recur_nap(nap);
         recur_issue<T, NK * BT>(px, in, lane * 8, fx);
-        recur_settle<T, NK * BT>(px, in, lane * 8, fx, dead, args.flags);
+        recur_settle<T, NK * BT>(px, in, lane * 8, fx, dead, args.ticket + 1, args.wait_ticks);
         v4f acc[RT][BT];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
@@ -271,12 +322,8 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs
 #pragma unroll
           for (int k = 0; k < KS; ++k) pre += *reinterpret_cast<const v4f*>(r + off_r[n] + k * RT * BT * 1024);
         }
-        const float ig = sigm_of<FAST>(pre[0] + in.g[n][0]), fg = sigm_of<FAST>(pre[1] + in.g[n][1]);
-        const float gg = tanh_of<FAST>(pre[2] + in.g[n][2]), og = sigm_of<FAST>(pre[3] + in.g[n][3]);
-        const float cn = fg * c[n] + ig * gg;
-        const float hn = og * tanh_of<FAST>(cn);
-        float state = hcar[n];                                     // (a masked step carries on the stored value)
-        if (in.mask[n] > 0.f) { c[n] = cn; state = hn != hn ? __uint_as_float(0x7fc00000u) : hn; }
+        float g[4];
+        const float state = seq_cell<FAST>(pre, in.g[n], in.mask[n], hcar[n], c[n], g);
         T hv;
         if constexpr (FAST) {
           hv = f2bf(state);
@@ -292,10 +339,8 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_fwd_kernel(SeqFwdArgs
         asm volatile("" ::: "memory");                             // (the state first: the other workgroups wait for it)
         *(T*)(hs + off_h[n]) = hv;
         *(float*)(cs + off_u[n]) = c[n];
-        *(float*)(gs + off_g[n]) = ig;
-        *(float*)(gs + (size_t)Hh * 4 + off_g[n]) = fg;
-        *(float*)(gs + (size_t)Hh * 8 + off_g[n]) = gg;
-        *(float*)(gs + (size_t)Hh * 12 + off_g[n]) = og;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *(float*)(gs + (size_t)q * Hh * 4 + off_g[n]) = g[q];
         // (the copy after dropout is rounded once, from the state as computed)
         if (has_y) *(T*)(ys + off_y[n]) = from_f<T>(state * drop_factor(drop, row[n], d.y_col0 + u));
       }
@@ -324,11 +369,11 @@ template <typename T, int KS, int NK, int RT, int NE>
 __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_bwd_kernel(SeqBwdArgs args, int L, int Bp, int Hh, int ndir, int nap) {
   constexpr int CH = NK * RT * (int)sizeof(Frag<T>) >= 512 ? (sizeof(T) == 2 ? 2 : 1) : NK < 4 ? NK : 4;   // (registers: weights and two chunks)
   __shared__ __align__(16) float red[2][KS * RT * 256];
-  __shared__ int s_id;
-  if (threadIdx.x == 0) s_id = atomicAdd(args.ticket, 1);
-  __syncthreads();
+  __shared__ int s_role[2];
+  bool dead;
+  const int id = recur_role(args.ticket, args.wait_ticks, s_role, dead);
   const int nwg = (Hh + 16 * RT - 1) / (16 * RT);
-  const int grp = s_id / nwg, u0 = (s_id - grp * nwg) * 16 * RT;
+  const int grp = id / nwg, u0 = (id - grp * nwg) * 16 * RT;
   const SeqBwdDir d = args.d[grp % ndir];
   const int bt = grp / ndir;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -345,7 +390,6 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_bwd_kernel(SeqBwdArgs
         if (s < nsteps) wf[q][rt].load((const T*)d.Wt + (size_t)u * d.ldw + 32 * s + 8 * (lane >> 4));
         else wf[q][rt].zero();
       }
-    bool dead = false;
     for (int i = 0; i < L; ++i) {
       if (i > 0) {
         const T* x = (const T*)d.X + (size_t)(rev ? i - 1 : L - i) * slot + (size_t)bt * nsteps * 512;
@@ -370,7 +414,7 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_bwd_kernel(SeqBwdArgs
         for (int c = 0; c < NK / CH; ++c) {
           asm volatile("" ::: "memory");                         // (no more than two chunks in flight: registers)
           if (c + 1 < NK / CH) issue(c + 1);
-          recur_settle<T, CH>(p[c & 1], in[c & 1], lane * 8, fx[c & 1], dead, args.flags);
+          recur_settle<T, CH>(p[c & 1], in[c & 1], lane * 8, fx[c & 1], dead, args.ticket + 1, args.wait_ticks);
 #pragma unroll
           for (int q = 0; q < CH; ++q)
 #pragma unroll
@@ -454,21 +498,9 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_bwd_kernel(SeqBwdArgs
 #pragma unroll
         for (int k = 0; k < KS; ++k) rec += *reinterpret_cast<const float*>(r + off_r[n] + k * RT * 1024);
       }
-      const bool valid = in.mask[n] > 0.f;
-      const float ig = in.g[n][0], fg = in.g[n][1], gg = in.g[n][2], og = in.g[n][3];
-      const float state = dh[n] + rec;
-      const float dht = state + dyf[n];
-      const float dct = dc[n] + dht * og * (1.f - tc[n] * tc[n]);
-      float o[4] = {dct * gg * ig * (1.f - ig), dct * in.cp[n] * fg * (1.f - fg), dct * ig * (1.f - gg * gg),
-                    dht * tc[n] * og * (1.f - og)};
-      dh[n] = valid ? 0.f : state;                                 // masked: the state's gradient passes through
-      dc[n] = valid ? dct * fg : dc[n];
+      float o[4];
+      seq_cell_bwd(in.g[n], in.cp[n], tc[n], dyf[n], rec, in.mask[n], dh[n], dc[n], o);
       cn[n] = in.cp[n];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        o[q] = valid ? o[q] : 0.f;
-        if (o[q] != o[q]) o[q] = __uint_as_float(0x7fc00000u);
-      }
       if constexpr (FAST) {
         const uint64_t v = quad_transpose(f2bf(o[0]), f2bf(o[1]), f2bf(o[2]), f2bf(o[3]), lane);
         if (real) {
@@ -494,25 +526,139 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_bwd_kernel(SeqBwdArgs
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// without waits
+// ------------------------------------------------------------------------------------------------
+// The same recurrences by one workgroup per (direction, 16 sentences), which needs no other: it reads the recurrent weights
+// at every position, and that (from L2, at some 50 GB/s per CU) is what a position costs.  gave_up (may be null): nothing is
+// to be done while it is zero.  States and gate gradients are read back through memory, written by the same workgroup before
+// a barrier; everything else of a (sentence, unit) stays with one lane.  Few registers and half the wavefronts that fit: a
+// launch with nothing to do is to start and end beside other kernels' workgroups.
+constexpr int SOLO_WAVES = 8;
+
+template <typename T>
+__global__ __launch_bounds__(64 * SOLO_WAVES) void lstm_seq_fwd_solo_kernel(SeqFwdArgs args, const int* gave_up, int L, int Bp, int Hh, int ndir) {
+  if (gave_up && *gave_up == 0) return;
+  constexpr bool FAST = sizeof(T) == 2;
+  const SeqFwdDir d = args.d[blockIdx.x % ndir];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int sentence = 16 * (blockIdx.x / ndir) + (lane & 15);
+  for (int i = 0; i < L; ++i) {
+    const int t = d.reverse ? L - 1 - i : i, sp = d.reverse ? t + 1 : t, sn = d.reverse ? t : t + 1;
+    const T* hp = (const T*)d.H + ((size_t)sp * Bp + sentence) * d.ldh;
+    const float mask = d.mask[(size_t)t * Bp + sentence];
+    const DropSpec drop = seq_drop(d.drop, d.drop_step, t);
+    for (int rt = w; rt < Hh >> 2; rt += SOLO_WAVES) {             // tiles of 4 units x 4 gates
+      v4f pre = v4f{0.f, 0.f, 0.f, 0.f};
+      if (i > 0) {
+        const int m = lane & 15;
+        const T* wr = (const T*)d.W + (size_t)((m & 3) * Hh + 4 * rt + (m >> 2)) * d.ldw + d.wh_off;
+        for (int k0 = 0; k0 < Hh; k0 += 32) {
+          const int k = k0 + 8 * (lane >> 4);
+          Frag<T> fw, fx;
+          fw.zero(); fx.zero();
+          if (k < Hh) { fw.load(wr + k); fx.load(hp + k); }
+          mma16(pre, fw, fx);
+        }
+      }
+      const int u = 4 * rt + (lane >> 4);
+      const size_t at = (size_t)t * Bp + sentence, next = (size_t)sn * Bp + sentence;
+      float gx[4], g[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) gx[q] = d.gx[at * 4 * Hh + (size_t)q * Hh + u];
+      float c = i > 0 ? d.C[((size_t)sp * Bp + sentence) * Hh + u] : 0.f;
+      const float state = seq_cell<FAST>(pre, gx, mask, i > 0 ? to_f<T>(hp[u]) : 0.f, c, g);
+      ((T*)d.H)[next * d.ldh + u] = from_f<T>(state);
+      d.C[next * Hh + u] = c;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) d.G[at * 4 * Hh + (size_t)q * Hh + u] = g[q];
+      if (d.Y) ((T*)d.Y)[at * d.ldy + d.y_col0 + u] = from_f<T>(state * drop_factor(drop, sentence, d.y_col0 + u));
+    }
+    __syncthreads();
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(64 * SOLO_WAVES) void lstm_seq_bwd_solo_kernel(SeqBwdArgs args, const int* gave_up, int L, int Bp, int Hh, int ndir) {
+  if (gave_up && *gave_up == 0) return;
+  constexpr bool FAST = sizeof(T) == 2;
+  const SeqBwdDir d = args.d[blockIdx.x % ndir];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int sentence = 16 * (blockIdx.x / ndir) + (lane & 15);
+  // the gradients that pass by are kept in the exchange buffer, which nobody else uses now: [2, Bp, Hh] floats
+  float* const keep = (float*)d.X + (size_t)sentence * Hh;
+  const size_t plane = (size_t)Bp * Hh;
+  for (int i = 0; i < L; ++i) {
+    const int t = d.reverse ? i : L - 1 - i, sp = d.reverse ? t + 1 : t, sn = d.reverse ? t : t + 1;   // slots before and after the position
+    const T* gp = (const T*)d.dG + ((size_t)(d.reverse ? t - 1 : t + 1) * Bp + sentence) * d.lddg;     // (of the position that came before here)
+    const float mask = d.mask[(size_t)t * Bp + sentence];
+    const DropSpec drop = seq_drop(d.drop, d.drop_step, t);
+    const size_t at = (size_t)t * Bp + sentence;
+    for (int u16 = 16 * w; u16 < Hh; u16 += 16 * SOLO_WAVES) {
+      v4f rec = v4f{0.f, 0.f, 0.f, 0.f};
+      if (i > 0) {
+        const T* wr = (const T*)d.Wt + (size_t)min(u16 + (lane & 15), Hh - 1) * d.ldw;
+        for (int k = 8 * (lane >> 4); k < 4 * Hh; k += 32) {       // (4 Hh is a multiple of 32)
+          Frag<T> fw, fx;
+          fw.load(wr + k); fx.load(gp + k);
+          mma16(rec, fw, fx);
+        }
+      }
+      for (int k = 0; k < 4; ++k) {
+        const int u = u16 + 4 * (lane >> 4) + k;
+        if (u >= Hh) break;
+        const float r = k == 0 ? rec[0] : k == 1 ? rec[1] : k == 2 ? rec[2] : rec[3];
+        float dh = i > 0 ? keep[u] : d.dh0[(size_t)sentence * d.ldd0 + u], dc = i > 0 ? keep[plane + u] : d.dc0[(size_t)sentence * d.ldd0 + u];
+        float g[4], o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[q] = d.G[at * 4 * Hh + (size_t)q * Hh + u];
+        const float cp = d.C[((size_t)sp * Bp + sentence) * Hh + u], cn = d.C[((size_t)sn * Bp + sentence) * Hh + u];
+        const float dy = d.dY[at * d.lddy + d.dy_col + u] * drop_factor(drop, sentence, d.dy_col + u);
+        seq_cell_bwd(g, cp, tanh_of<FAST>(cn), dy, r, mask, dh, dc, o);
+        keep[u] = dh; keep[plane + u] = dc;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ((T*)d.dG)[at * d.lddg + (size_t)q * Hh + u] = from_f<T>(o[q]);
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// launches
+// ------------------------------------------------------------------------------------------------
+// Groups that wait only where as many launches as a process runs at once fit the device (recur_plan.h).
+static bool seq_together(const SeqPlan& p, const SeqRun& run) { return run.mode != SEQ_RUN_ALONE && SEQ_QUEUES * (p.group - 1) < run.cus; }
+static int seq_wait(const SeqRun& run) { return run.mode == SEQ_RUN_GIVE_UP ? 0 : RECUR_WAIT_TICKS; }
+
 template <typename T, int KS, int NK, int RT, int NE>
 static void seq_bwd_go(const SeqPlan& p, const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
   hipLaunchKernelGGL((lstm_seq_bwd_kernel<T, KS, NK, RT, NE>), dim3(p.groups * p.group), dim3(64 * (KS + NE)), 0, st, a, L, Bp, Hh, ndir,
                      RECUR_NAP_BWD);
 }
-void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& args, int ndir, int L, int Bp, int Hh, const SeqRun& run, hipStream_t st) {
   const SeqPlan p = seq_bwd_plan(prec, ndir, Bp, Hh);
+  const bool together = seq_together(p, run);
+  SeqBwdArgs a = args;
+  a.wait_ticks = seq_wait(run);
 #define GO(KS, NK)                                                                                   \
   do {                                                                                               \
     if (!prec) seq_bwd_go<float, KS, NK, 1, 4>(p, a, ndir, L, Bp, Hh, st);                           \
     else if (p.rt == 1) seq_bwd_go<bf16_t, KS, NK, 1, 4>(p, a, ndir, L, Bp, Hh, st);                 \
     else seq_bwd_go<bf16_t, KS, NK, 2, (NK > 8 ? 4 : 8)>(p, a, ndir, L, Bp, Hh, st);                 \
   } while (0)
-  if (p.ks == 2) GO(2, 2);
+  if (!together) {}
+  else if (p.ks == 2) GO(2, 2);
   else if (p.nk == 2) GO(8, 2);
   else if (p.nk == 4) GO(8, 4);
   else if (p.nk == 8) GO(8, 8);
   else GO(8, 16);
 #undef GO
+  if (together && (L == 1 || p.group == 1)) return;  // (nothing to wait for)
+  const int* gave_up = together ? a.ticket + 1 : nullptr;
+  const dim3 grid(ndir * (Bp >> 4)), block(64 * SOLO_WAVES);
+  if (prec) hipLaunchKernelGGL(lstm_seq_bwd_solo_kernel<bf16_t>, grid, block, 0, st, a, gave_up, L, Bp, Hh, ndir);
+  else hipLaunchKernelGGL(lstm_seq_bwd_solo_kernel<float>, grid, block, 0, st, a, gave_up, L, Bp, Hh, ndir);
 }
 
 template <typename T, int KS, int NK, int LK, int BT, int NE>
@@ -520,8 +666,11 @@ static void seq_fwd_go(const SeqPlan& p, const SeqFwdArgs& a, int ndir, int L, i
   hipLaunchKernelGGL((lstm_seq_fwd_kernel<T, KS, NK, LK, 4, BT, NE>), dim3(p.groups * p.group), dim3(64 * (KS + NE)), 0, st, a, L, Bp, Hh,
                      ndir, BT == 1 ? RECUR_NAP_FWD : RECUR_NAP_FWD2);
 }
-void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
+void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& args, int ndir, int L, int Bp, int Hh, const SeqRun& run, hipStream_t st) {
   const SeqPlan p = seq_fwd_plan(prec, ndir, Bp, Hh);
+  const bool together = seq_together(p, run);
+  SeqFwdArgs a = args;
+  a.wait_ticks = seq_wait(run);
 #define GO(KS, NK, NE2)                                                                              \
   do {                                                                                               \
     if (prec && p.bt == 1) seq_fwd_go<bf16_t, KS, NK, 0, 1, 4>(p, a, ndir, L, Bp, Hh, st);           \
@@ -529,12 +678,18 @@ void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& a, int ndir, int L, int Bp,
     else if (p.bt == 1) seq_fwd_go<float, KS, NK, NK == 4, 1, 4>(p, a, ndir, L, Bp, Hh, st);         \
     else if constexpr (NK < 4) seq_fwd_go<float, KS, NK, 0, 2, 4>(p, a, ndir, L, Bp, Hh, st);        \
   } while (0)
-  if (p.ks == 2 && p.nk == 1) GO(2, 1, 4);
+  if (!together) {}
+  else if (p.ks == 2 && p.nk == 1) GO(2, 1, 4);
   else if (p.ks == 2) GO(2, 2, 4);
   else if (p.nk == 1) GO(8, 1, 8);
   else if (p.nk == 2) GO(8, 2, 8);
   else GO(8, 4, 4);
 #undef GO
+  if (together && (L == 1 || p.group == 1)) return;  // (nothing to wait for)
+  const int* gave_up = together ? a.ticket + 1 : nullptr;
+  const dim3 grid(ndir * (Bp >> 4)), block(64 * SOLO_WAVES);
+  if (prec) hipLaunchKernelGGL(lstm_seq_fwd_solo_kernel<bf16_t>, grid, block, 0, st, a, gave_up, L, Bp, Hh, ndir);
+  else hipLaunchKernelGGL(lstm_seq_fwd_solo_kernel<float>, grid, block, 0, st, a, gave_up, L, Bp, Hh, ndir);
 }
 
 }  // namespace cmt

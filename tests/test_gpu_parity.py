@@ -1060,21 +1060,52 @@ def test_encoder_recurrences_at_tile_edges(prec, B, S, H, E, L, reg):
     tr.close()
 
 
-def test_recurrences_of_several_streams_at_once():
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("how", ["0", "2"])
+@pytest.mark.parametrize("B,S,H,E,L,reg", [(5, 4, 16, 8, 1, None), (33, 9, 144, 16, 3, (0.3, 0.0, 6)), (48, 5, 336, 40, 2, None),
+                                           (17, 3, 1024, 16, 2, (0.2, 0.0, 8))])
+def test_encoder_recurrences_without_waits(prec, how, B, S, H, E, L, reg, monkeypatch):
+    """Where the workgroups of a recurrence cannot all be on the chip, it is made by workgroups that wait for none: at once on a small
+    device (CMT_RECUR=0, read when the handle is created), or by a second launch after one whose waits were given up (2: all of them,
+    beforehand).  All intermediates and gradients at the usual bars (bf16 as in the test before), gradients equal to
+    the usual form's to rounding order, and the handle's later calls are sound: evaluation and greedy decoding."""
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=104, tgt_vocab=136, emb=E, hidden=H, layers=L)
+    rng = np.random.default_rng(1200 + B)
+    params = I.make_params(cfg, seed=B, scale=0.3 if H <= 128 else 0.05)
+    batch = ragged_batch(rng, B, S, 3, cfg["src_vocab"], cfg["tgt_vocab"])
+    relax = {}
+    if prec:
+        sens = oracle_sensitivity(cfg, params, batch, reg)
+        relax = dict(l2_override={k: max(2e-2, SWEEP_SENS_C * v) for k, v in sens.items()})
+    got = []
+    for mode in (how, "1"):
+        monkeypatch.setenv("CMT_RECUR", mode)
+        loss, oloss, worst, tr = run_case(cfg, params, batch, prec, reg=reg, check_inter=mode == how, **relax)
+        got.append((tr.get_grads(), tr.eval_loss(tr.upload_batch(*batch))[0], tr.greedy_decode(batch[0], batch[1], 3)))
+        tr.close()
+    assert np.linalg.norm(got[0][0] - got[1][0]) <= (1e-5 if prec == 0 else 1e-2) * np.linalg.norm(got[1][0])
+    assert abs(got[0][1] - got[1][1]) <= (1e-5 if prec == 0 else 1e-2) * got[1][1]
+    if prec == 0:                                             # (16-bit operands: a near tie may go either way)
+        assert np.array_equal(got[0][2][0], got[1][2][0])
+
+
+@pytest.mark.parametrize("prec,H,lengths", [(1, 512, 30), (1, 1024, 20), (0, 1024, 12)])
+def test_recurrences_of_several_streams_at_once(prec, H, lengths):
     """Four handles on four streams, driven by four threads: their recurrences share the chip, and every step's gradients
-    are those of the handle alone, bit for bit."""
+    are those of the handle alone, bit for bit.  Width 1024: groups of 64 workgroups that wait for one another, the largest."""
     import threading
 
     import torch
     from paper_1802_07170_amd import binding
-    cfg = dict(src_vocab=104, tgt_vocab=136, emb=64, hidden=512, layers=2)
+    cfg = dict(src_vocab=104, tgt_vocab=136, emb=64, hidden=H, layers=2)
     params = I.flatten(I.make_params(cfg, seed=3, scale=0.05), cfg)
     rng = np.random.default_rng(77)
-    batches = [ragged_batch(rng, B, 30, 3, cfg["src_vocab"], cfg["tgt_vocab"]) for B in (64, 40, 64, 17)]
+    batches = [ragged_batch(rng, B, lengths, 3, cfg["src_vocab"], cfg["tgt_vocab"]) for B in (64, 40, 64, 17)]
     trainers, alone, devs = [], [], []
     for batch in batches:
         with torch.cuda.stream(torch.cuda.Stream()):
-            tr = binding.Trainer(cfg, *batch[0].shape, batch[2].shape[1], precision=1)
+            tr = binding.Trainer(cfg, *batch[0].shape, batch[2].shape[1], precision=prec)
             tr.set_params(params)
         dev = tr.upload_batch(*batch)
         torch.cuda.synchronize()
