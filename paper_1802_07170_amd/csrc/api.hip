@@ -49,15 +49,16 @@ struct LD {
   char* HstT = nullptr;              // T [Hh, (Lmax+1)*Bp]
   char* Yd = nullptr;                // T [Lmax, Bp, Hh] the layer's output after dropout (row pitch ph) ...
   char* YdT = nullptr;               // ... and its transpose [Hh, L*Bp]; used only while dropout is on
-  float* dh = nullptr; float* dc = nullptr;   // [Bp, Hh]
-  float* bwdp = nullptr;             // [8][Bp][2Hh] backward step-GEMM planes
+  float* dh = nullptr; float* dc = nullptr;   // decoder: [Bp, Hh]
+  float* bwdp = nullptr;             // decoder: [8][Bp][2Hh] backward step-GEMM planes
   // decoder: fragment-major copies read by the per-step kernels (bf16 path, Hh a multiple of 32; see fm_offset)
   int Kstep = 0;                     // width of the per-step input segment: the x columns [Kin - Kstep, Kin) of W
   char* Wfm = nullptr;               // gate rows of W, columns [Kin - Kstep, Kin + Hh)
   char* HstF = nullptr;              // [(Lmax+1)] slots of [Bp, Hh]
   char* YdF = nullptr;               // [Lmax] slots of [Bp, Hh] (the layer's output after dropout)
   bool fm = false;
-  // encoder: exchange slots of the whole-recurrence kernels, for the states and for the gate gradients (recur.hip)
+  // encoder: exchange slots of the whole-recurrence kernels, for the states and for the gate gradients (recur.hip); they
+  // share the memory of dGT and Gx
   char* X = nullptr; char* XG = nullptr;
   char* WtF = nullptr;               // W^T [Kin+Hh, 4Hh] (backward step GEMMs; needs Kin a multiple of 16)
   char* dGF = nullptr;               // [Lmax] slots of [Bp, 4Hh]
@@ -266,18 +267,23 @@ size_t layout(cmt_handle* h, char* base) {
       d.WtF = a.take((size_t)(Kin + Hh) * 4 * Hh * esz);
       d.dGF = a.take(M * 4 * Hh * esz);
     }
-    if (encoder) { d.X = a.take(seq_exchange_elems(Lm + 1, Bp, Hh) * esz); d.XG = a.take(M * 4 * Hh * esz); }
     d.Wt = a.take((size_t)(Kin + Hh) * 4 * Hh * esz);
     d.Hst = a.take((M + Bp) * d.ph * esz);
     d.Cst = (float*)a.take((M + Bp) * Hh * 4);
     d.Gs = (float*)a.take(M * 4 * Hh * 4);
     d.Gx = gx ? (float*)a.take(M * 4 * Hh * 4) : nullptr;
     d.dG = a.take(M * d.pg * esz);
-    d.dGT = a.take(M * 4 * Hh * esz);
+    // The recurrences' exchange slots are filled afresh by every pass and take no memory of their own: the states' lie
+    // where the gate gradients are transposed to after the backward pass, the gate gradients' where the forward pass had
+    // its input parts.
+    d.dGT = a.take(std::max(M * 4 * Hh, encoder ? seq_exchange_elems(Lm + 1, Bp, Hh) : 0) * esz);
+    if (encoder) { d.X = d.dGT; d.XG = (char*)d.Gx; }
     d.HstT = a.take((M + Bp) * Hh * esz);
-    d.dh = (float*)a.take((size_t)Bp * Hh * 4);
-    d.dc = (float*)a.take((size_t)Bp * Hh * 4);
-    d.bwdp = (float*)a.take((size_t)8 * Bp * 2 * Hh * 4);
+    if (!encoder) {
+      d.dh = (float*)a.take((size_t)Bp * Hh * 4);
+      d.dc = (float*)a.take((size_t)Bp * Hh * 4);
+      d.bwdp = (float*)a.take((size_t)8 * Bp * 2 * Hh * 4);
+    }
     d.Yd = a.take(M * d.ph * esz);                 // the layer's output after dropout, and its transpose
     d.YdT = a.take(M * Hh * esz);
   };

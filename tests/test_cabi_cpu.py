@@ -43,6 +43,17 @@ def test_query_sizes_for_the_five_workloads(lib):
         assert wb < 64 * 2 ** 30, (name, wb)            # far below the 288 GB of one MI355X
 
 
+@pytest.mark.parametrize("H,E,L,length,prec", [(64, 64, 2, 45, 0), (128, 64, 2, 20, 0), (96, 96, 2, 30, 0), (48, 40, 3, 70, 1), (80, 64, 4, 36, 1)])
+def test_the_static_evaluation_s_array_holds_these_shapes(lib, H, E, L, length, prec):
+    """cmt_eval_loss_static lays a workspace of exactly the call's shape into an array of CMT_STATIC_SCRATCH_BYTES: 16
+    sentences of these lengths just fit (vocabulary 1000), and a workspace that grows refuses them."""
+    with open(os.path.join(ROOT, "include", "cytonmt_hip.h")) as f:
+        mb = int(re.search(r"CMT_STATIC_SCRATCH_BYTES \((\d+)u << 20\)", f.read()).group(1))
+    cfg = dict(src_vocab=1000, tgt_vocab=1000, emb=E, hidden=H, layers=L)
+    sizes = [binding.query_sizes(binding.make_config(cfg, 16, n, n, prec))[2] for n in (length, 2 * length)]
+    assert sizes[0] <= mb << 20 < sizes[1]
+
+
 def test_unsupported_configurations_are_rejected(lib):
     good = dict(src_vocab=1000, tgt_vocab=1000, emb=64, hidden=64, layers=1)
     def rc(cfg=good, **kw):

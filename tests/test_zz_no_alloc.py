@@ -51,6 +51,20 @@ def test_static_eval_matches_workspace_eval_bf16():
     _case(1)
 
 
+@pytest.mark.parametrize("H,E,L,length,prec", [(64, 64, 2, 45, 0), (80, 64, 4, 36, 1)])
+def test_static_eval_takes_shapes_that_just_fit(H, E, L, length, prec):
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=1000, tgt_vocab=1000, emb=E, hidden=H, layers=L)
+    batch = I.make_batch(dict(cfg, ids="zipf", batch=16, len_range=(length, length), seed=4))
+    tr = binding.Trainer(cfg, 16, length, length, precision=prec)
+    try:
+        tr.init_params(1, 0.1)
+        dev = tr.upload_batch(*batch)
+        assert tr.eval_loss_static(dev) == tr.eval_loss(dev)
+    finally:
+        tr.close()
+
+
 def test_static_eval_refuses_a_shape_beyond_the_array():
     from paper_1802_07170_amd import binding
     c = I.CONFIGS["small"]                                       # vocabulary 32000: the slab buffers alone exceed the array
