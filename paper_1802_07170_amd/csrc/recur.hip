@@ -654,7 +654,7 @@ void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& args, int ndir, int L, int 
   else if (p.nk == 8) GO(8, 8);
   else GO(8, 16);
 #undef GO
-  if (together && (L == 1 || p.group == 1)) return;  // (nothing to wait for)
+  if (together && L == 1) return;                    // (nothing to wait for)
   const int* gave_up = together ? a.ticket + 1 : nullptr;
   const dim3 grid(ndir * (Bp >> 4)), block(64 * SOLO_WAVES);
   if (prec) hipLaunchKernelGGL(lstm_seq_bwd_solo_kernel<bf16_t>, grid, block, 0, st, a, gave_up, L, Bp, Hh, ndir);
@@ -685,7 +685,7 @@ void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& args, int ndir, int L, int 
   else if (p.nk == 2) GO(8, 2, 8);
   else GO(8, 4, 4);
 #undef GO
-  if (together && (L == 1 || p.group == 1)) return;  // (nothing to wait for)
+  if (together && L == 1) return;                    // (nothing to wait for)
   const int* gave_up = together ? a.ticket + 1 : nullptr;
   const dim3 grid(ndir * (Bp >> 4)), block(64 * SOLO_WAVES);
   if (prec) hipLaunchKernelGGL(lstm_seq_fwd_solo_kernel<bf16_t>, grid, block, 0, st, a, gave_up, L, Bp, Hh, ndir);
