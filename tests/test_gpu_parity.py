@@ -198,33 +198,29 @@ def test_vocabulary_long_enough_for_the_k_split_of_the_output_gradient(prec, B, 
 
 
 @pytest.mark.parametrize("prec", [0, 1])
-@pytest.mark.parametrize("forms", ["0", "0 uncapped k blocks", "2", "7", "7 k-split W_c"])
+@pytest.mark.parametrize("forms", [dict(CMT_BWD_FUSED="0"), dict(CMT_BWD_FUSED="0", CMT_KB_BWD_DEC="2"),
+                                   dict(CMT_BWD_FUSED="0", CMT_KB_WC="1"), dict(CMT_WC_WHOLE_K="0"),
+                                   dict(CMT_WC_WHOLE_K="0", CMT_KB_WC="1")], ids=lambda f: " ".join(f"{k[4:]}={v}" for k, v in f.items()))
 @pytest.mark.parametrize("B,S,T,H,E,L", [(19, 9, 8, 80, 40, 3), (64, 6, 7, 256, 64, 2), (70, 5, 4, 48, 16, 2), (130, 3, 4, 64, 32, 2)])
 def test_every_form_of_the_backward_loops(prec, forms, B, S, T, H, E, L, monkeypatch):
-    """The three backward loops (decoder, upper encoder layers, bottom encoder layer) each exist as a
-    step GEMM with its consumer in the epilogue and as a k-split GEMM followed by a pointwise kernel; the
-    library picks per loop and batch width.  CMT_BWD_FUSED (read when the handle is created) forces the
-    choice: all three pointwise (0), the upper encoder fused alone (2), all three fused (7, the decoder
-    only up to 128 sentences).  Inside the fused decoder loop the product dpre W_c runs with the whole k
-    range per workgroup by default and as k blocks into planes with CMT_WC_WHOLE_K=0; the k-split GEMMs write
-    two planes by default and up to eight with CMT_KB_BWD=0.  Every form meets the
-    same bars against the oracle, and the gradients of the forms agree with each other to rounding order
+    """The decoder's backward loop exists as a step GEMM with its consumer in the epilogue (the default up to 128
+    sentences) and as a k-split GEMM followed by a pointwise kernel (CMT_BWD_FUSED=0, read when the handle is
+    created, and wider batches); the k-split GEMMs of the layers write up to eight planes by default and at most two with
+    CMT_KB_BWD_DEC=2.  The product dpre W_c runs with the whole k range per workgroup in the fused loop by default, and as k
+    blocks into planes with CMT_WC_WHOLE_K=0 and in the other loop: two of them where H is 256, one with CMT_KB_WC=1.  Every form meets the
+    same bars against the oracle, and its gradients agree with the default's to rounding order
     (same products, different summation order)."""
     cfg = dict(src_vocab=104, tgt_vocab=136, emb=E, hidden=H, layers=L)
     rng = np.random.default_rng(700 + B)
     params = I.make_params(cfg, seed=B + 1, scale=0.3 if H <= 128 else 0.05)
     batch = ragged_batch(rng, B, S, T, cfg["src_vocab"], cfg["tgt_vocab"])
-    monkeypatch.setenv("CMT_BWD_FUSED", forms.split()[0])
-    if "k-split W_c" in forms:
-        monkeypatch.setenv("CMT_WC_WHOLE_K", "0")
-    if "uncapped k blocks" in forms:
-        monkeypatch.setenv("CMT_KB_BWD", "0")
+    for name, value in forms.items():
+        monkeypatch.setenv(name, value)
     loss, oloss, worst, tr = run_case(cfg, params, batch, prec)
     g = tr.get_grads().copy()
     tr.close()
-    monkeypatch.delenv("CMT_BWD_FUSED")
-    monkeypatch.delenv("CMT_WC_WHOLE_K", raising=False)
-    monkeypatch.delenv("CMT_KB_BWD", raising=False)
+    for name in forms:
+        monkeypatch.delenv(name)
     loss0, _, _, tr0 = run_case(cfg, params, batch, prec, check_inter=False)
     g0 = tr0.get_grads().copy()
     tr0.close()
