@@ -25,15 +25,17 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of the timed kernel from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE),
 # scaled by what the same counters read for a plain 256 MiB copy (x2 and x1): the summary under
 # profiles/ gives the commands and the figures.  Valid for the workload and the kernel source it was
-# measured with: (workload, first 12 hex digits of the sha256 of csrc/step.hip + csrc/common.h) -> bytes;
+# measured with: (workload, first 12 hex digits of the sha256 of STEP_KERNEL_SOURCES) -> bytes;
 # with another source the figure is stale and reported as null.
-MEASURED_TRAFFIC_BYTES = {("medium", "a9575a67abc7"): 22864896}      # profiles/step_kernels_medium_bf16_memory_counters.md
+MEASURED_TRAFFIC_BYTES = {("medium", "e675f64d3e81"): 22864896}      # profiles/step_kernels_medium_bf16_memory_counters.md
+
+STEP_KERNEL_SOURCES = ("step.hip", "cell.h", "common.h", "kernels.h")   # the timed kernel's file and what it includes
 
 
 def step_kernel_source_tag():
     import hashlib
     h = hashlib.sha256()
-    for f in ("step.hip", "common.h"):
+    for f in STEP_KERNEL_SOURCES:
         h.update(open(os.path.join(ROOT, "paper_1802_07170_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:12]
 MFMA_BF16_PEAK_TFLOPS = 2500.0

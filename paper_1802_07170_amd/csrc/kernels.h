@@ -24,7 +24,8 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
                     float* split_scratch = nullptr, size_t split_scratch_floats = 0, RowLimit limit = RowLimit{},
                     int limit_kind = 0, int wg_cap = 0);
 // wg_cap > 0: at most that many workgroups (rounded up to a multiple of 8) walk the tiles — for a GEMM on a second
-// stream that is to leave part of the chip to the kernels of the first.
+// stream that is to leave part of the chip to the kernels of the first.  The cap counts workgroups of the two larger tiles; of
+// the 64 x 64 tile, which fits a CU four times, four times as many are launched.
 // Matrix-core issue-rate probe: `blocks` workgroups of 4 wavefronts, each `iters` x 4 bf16 32x32x16 MFMAs on
 // registers; out needs blocks * 256 floats.  Returns the flops of the launch.
 // Several independent C (+)= A * B^T problems (fp32 C, no bias) as one launch: the tiles of all problems form one
@@ -33,7 +34,7 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
 struct GemmProb { const void* A; const void* B; float* C; int lda, ldb, ldc, M, N, K, accumulate; };
 // split_scratch: planes for the fp32 path, which launches the problems one by one (see launch_gemm_nt).
 void launch_gemm_nt_group(int prec, const GemmProb* probs, int n, hipStream_t st, float* split_scratch, size_t split_scratch_floats,
-                          int wg_cap = 0);
+                          int wg_cap = 0);         // (wg_cap as above)
 double launch_mfma_rate(float* out, int blocks, int iters, hipStream_t st);
 // out[C,R] = in[R,C]^T for T matrices (ldin, ldout in elements).
 void launch_transpose(int prec, const void* in, int ldin, void* out, int ldout, int R, int C, hipStream_t st);
