@@ -18,13 +18,16 @@
 // that a process's hardware queues can run at once leave a CU free for one of them to complete its group.  Nothing rests on
 // that but speed: more queues, other processes or a stream confined to a few CUs may stop a group from forming.  Every wait
 // is bounded, a workgroup that gives up says so and finishes without waiting, the others of the launch follow, and a second
-// launch (2 us where there is nothing to do) makes the recurrence again without waits, one workgroup per 16 sentences:
-// some hundred us a position at width 1024.  That form also serves devices too small for the groups.
+// launch (about 5 us where there is nothing to do) makes the recurrence again without waits, one workgroup per 16 sentences:
+// 0.4 ms a position at width 1024.  That form also serves devices too small for the groups.
 //
-// What a position costs (bf16, us; before: one launch per position, 8.5 - 9, upper layers forward 5.6 of a shared one):
-// forward 1.2 (width 256, 32 sentences), 1.7 (512, 64 sentences, two directions), 2.7 (1024, 64 sentences), 3.1 (512, 128
-// sentences, two directions); backward 2.1, 3.0, 4.8 beside the second stream's GEMMs.  About 0.5 of it is the store on
-// its way to memory, 0.5 the load, the rest contraction, reduction and cell; at 128 sentences also the volume.
+// What a position costs within a training step (bf16, us; a launch per position cost 8.5 - 9, upper layers forward 5.6 of a
+// shared one).  Forward: width 256 x two directions, 32 sentences 1.2; 512, 32 sentences 1.4; 512 x two directions, 64 and 128
+// sentences 1.9 and 3.3; 1024, 64 and 128 sentences 3.0 and 6.3.  Backward, beside the second stream's GEMMs: 256 x two
+// directions, 32 sentences 2.2; 512, 32 sentences 2.7; 512 x two directions, 64 and 128 sentences 6.4 and 10.0; 1024, 64
+// sentences 3.6 - 4.8, 128 sentences 4.8 - 14.6 (median 5.6; the first of a step's layers, which runs beside the decoder's
+// weight gradients, takes longest).  About 0.5 of it is the store on its way to memory, 0.5 the load, the rest contraction,
+// reduction and cell; at 128 sentences also the volume.
 #include <stdlib.h>
 
 #include <algorithm>
@@ -39,9 +42,12 @@ namespace cmt {
 
 constexpr unsigned RECUR_EMPTY = 0xffffffffu;          // a word of a slot that nobody has written
 constexpr int RECUR_WAIT_TICKS = 5000000;              // 50 ms of the 100 MHz wall clock, then a wait is given up
-// s_sleep units (64 clocks) before a workgroup looks for its neighbours' results.  Measured per launch: forward, one tile of
-// sentences 14: 123 us, 20: 87, 26: 92 (width 512, 64 sentences, 50 positions); two tiles 20: 287, 28: 254, 40: 253 (128
-// sentences, 80 positions); backward 28: 262, 36: 240, 44: 225 and no change beyond (width 1024).
+// s_sleep units (64 clocks) before a workgroup looks for its neighbours' results: one value each for every width.  Whole passes
+// over 150 positions x 3 layers, us, with 16 | 20 | 28 | 36 units forward (evaluation; bf16, 64 sentences): hidden size 64
+// 581 | 624 | 715 | 800, 128 654 | 663 | 764 | 855, 512 1208 | 1041 | 996 | 1087, 1024 1871 | 1814 | 1595 | 1492; fp32, 512
+// 3054 | 2988 | 2493 | 2541; two tiles of sentences (128), 512 1565 | 1409 | 1261 | 1292, 1024 3870 | 3510 | 3393 | 2933.  24 | 36 |
+// 42 | 50 units backward (training step): 64 1475 | 1598 | 1675 | 1786, 256 (32 sentences) 1925 | 1762 | 1822 | 1923, 512
+// 3285 | 3039 | 2901 | 2913, 1024 5439 | 5054 | 4869 | 4847.  So the best value grows with the width.
 constexpr int RECUR_NAP_FWD = 20, RECUR_NAP_FWD2 = 28, RECUR_NAP_BWD = 42;
 
 // one 16-byte (32-byte for float) fragment of a slot; `top` becomes RECUR_EMPTY if any of its pieces is still empty
@@ -452,7 +458,7 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_bwd_kernel(SeqBwdArgs
       off_x[n] = (unsigned)(fm_offset(b, gate * Hh + u4, nsteps) * sizeof(T));
       off_d[n] = (unsigned)((b * d.lddg + gate * Hh + u4) * sizeof(T));
     } else {
-      off_x[n] = (unsigned)(fm_offset(b, u, nsteps) * sizeof(T));       // gate q: Hh / 32 k steps further on, or recomputed
+      off_x[n] = 0;                                                // (the four gates' places are worked out where they are stored)
       off_d[n] = (unsigned)((b * d.lddg + u) * sizeof(T));
     }
     cn[n] = *(const float*)((const char*)(d.C + (size_t)(rev ? 0 : L) * Bp * Hh) + off_u[n]);
@@ -537,7 +543,8 @@ __global__ __launch_bounds__(64 * (KS + NE)) void lstm_seq_bwd_kernel(SeqBwdArgs
 constexpr int SOLO_WAVES = 8;
 
 template <typename T>
-__global__ __launch_bounds__(64 * SOLO_WAVES) void lstm_seq_fwd_solo_kernel(SeqFwdArgs args, const int* gave_up, int L, int Bp, int Hh, int ndir) {
+__global__ __launch_bounds__(64 * SOLO_WAVES) void lstm_seq_fwd_solo_kernel(const int* gave_up, int L, int Bp, int Hh, int ndir,
+                                                                             SeqFwdArgs args) {
   if (gave_up && *gave_up == 0) return;
   constexpr bool FAST = sizeof(T) == 2;
   const SeqFwdDir d = args.d[blockIdx.x % ndir];
@@ -579,7 +586,8 @@ __global__ __launch_bounds__(64 * SOLO_WAVES) void lstm_seq_fwd_solo_kernel(SeqF
 }
 
 template <typename T>
-__global__ __launch_bounds__(64 * SOLO_WAVES) void lstm_seq_bwd_solo_kernel(SeqBwdArgs args, const int* gave_up, int L, int Bp, int Hh, int ndir) {
+__global__ __launch_bounds__(64 * SOLO_WAVES) void lstm_seq_bwd_solo_kernel(const int* gave_up, int L, int Bp, int Hh, int ndir,
+                                                                             SeqBwdArgs args) {
   if (gave_up && *gave_up == 0) return;
   constexpr bool FAST = sizeof(T) == 2;
   const SeqBwdDir d = args.d[blockIdx.x % ndir];
@@ -657,8 +665,8 @@ void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& args, int ndir, int L, int 
   if (together && L == 1) return;                    // (nothing to wait for)
   const int* gave_up = together ? a.ticket + 1 : nullptr;
   const dim3 grid(ndir * (Bp >> 4)), block(64 * SOLO_WAVES);
-  if (prec) hipLaunchKernelGGL(lstm_seq_bwd_solo_kernel<bf16_t>, grid, block, 0, st, a, gave_up, L, Bp, Hh, ndir);
-  else hipLaunchKernelGGL(lstm_seq_bwd_solo_kernel<float>, grid, block, 0, st, a, gave_up, L, Bp, Hh, ndir);
+  if (prec) hipLaunchKernelGGL(lstm_seq_bwd_solo_kernel<bf16_t>, grid, block, 0, st, gave_up, L, Bp, Hh, ndir, a);
+  else hipLaunchKernelGGL(lstm_seq_bwd_solo_kernel<float>, grid, block, 0, st, gave_up, L, Bp, Hh, ndir, a);
 }
 
 template <typename T, int KS, int NK, int LK, int BT, int NE>
@@ -688,8 +696,8 @@ void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& args, int ndir, int L, int 
   if (together && L == 1) return;                    // (nothing to wait for)
   const int* gave_up = together ? a.ticket + 1 : nullptr;
   const dim3 grid(ndir * (Bp >> 4)), block(64 * SOLO_WAVES);
-  if (prec) hipLaunchKernelGGL(lstm_seq_fwd_solo_kernel<bf16_t>, grid, block, 0, st, a, gave_up, L, Bp, Hh, ndir);
-  else hipLaunchKernelGGL(lstm_seq_fwd_solo_kernel<float>, grid, block, 0, st, a, gave_up, L, Bp, Hh, ndir);
+  if (prec) hipLaunchKernelGGL(lstm_seq_fwd_solo_kernel<bf16_t>, grid, block, 0, st, gave_up, L, Bp, Hh, ndir, a);
+  else hipLaunchKernelGGL(lstm_seq_fwd_solo_kernel<float>, grid, block, 0, st, gave_up, L, Bp, Hh, ndir, a);
 }
 
 }  // namespace cmt
