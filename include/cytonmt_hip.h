@@ -133,7 +133,7 @@ int cmt_eval_loss(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* src_
  * workspace, its last step's intermediates and the gradient buffer are untouched.  The call allocates
  * and frees nothing.  A shape whose intermediates do not fit is refused with CMT_EINVAL (cmt_last_error
  * names both sizes): the tiny configuration (hidden 64, vocabulary 1000, 8 x 10 tokens) needs about
- * 20 MB.  Each GPU holds one such array until the process ends, shared by all handles; it keeps the last
+ * 9 MB.  Each GPU holds one such array until the process ends, shared by all handles; it keeps the last
  * call's contents and is cleared at the start of each call.  Calls that overlap on one GPU — from
  * several handles, streams or threads — race on it: serialise them.  Like cmt_eval_loss it leaves its
  * own loss in the handle's pinned read-back slot (what a later cmt_fetch_loss returns). */

@@ -159,10 +159,11 @@ struct cmt_handle {
   int kb_wc = 0;                        // caps on the k blocks of the decoder's k-split step GEMMs (0 = default): dpre W_c, and
   int kb_bwd_dec = 0;                   // the layers' backward GEMMs
   // Workgroup caps of the second stream's GEMMs (weight gradients; dW_o), 0 = none, -1 = by batch width: with all
-  // 256 CUs taken by 256 x 256 tiles for tens of microseconds at a time, the recurrences' kernels on the caller's
-  // stream queue behind them; capped at 128 workgroups the GEMMs take twice as long (still hidden) and leave half the
-  // chip free.  Step time capped / uncapped, ms: medium 9.83 / 9.96, attn 11.03 / 11.12, small (fp32) 10.57 / 10.90;
-  // at 128 sentences (large) 24.82 / 24.73, so the caps apply up to 64 sentences.  Env CMT_SIDE_WGS, CMT_SIDE_WGS_WO.
+  // 256 CUs taken by 256 x 256 tiles for tens of microseconds at a time, the kernels on the caller's stream queue behind
+  // them; capped at 128 workgroups (512 of the 64 x 64 tile, see launch_gemm_nt) the GEMMs take twice as long (still
+  // hidden) and leave half the chip free.  Step time capped / uncapped, ms: small (fp32) 8.53 / 8.93, attn 7.45 / 7.51,
+  // paper_512x2 3.31 / 3.35, medium 8.21 / 8.18 (within its runs); at 128 sentences (large) 21.96 / 21.40, so the caps
+  // apply up to 64 sentences.  Env CMT_SIDE_WGS, CMT_SIDE_WGS_WO.
   int side_wgs = -1, side_wgs_wo = -1;
   int side_cap(int v) const { return v >= 0 ? v : (Bp <= 64 ? 128 : 0); }
   int wc_whole_k = 1;                   // fused decoder loop: dpre W_c with the whole k range per workgroup (env CMT_WC_WHOLE_K)
