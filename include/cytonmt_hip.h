@@ -67,7 +67,8 @@ int cmt_query_sizes(const cmt_config* cfg, size_t* param_bytes, size_t* grad_byt
  * their own (one call at a time per handle) and beside other processes.  The encoder's recurrences are made by workgroups
  * that wait for one another; with up to four such launches at once on 256 CUs, what a process's hardware queues allow by
  * default, they always get on.  Where they do not, a recurrence gives up its waits after 50 ms and is made again
- * without any: the call is late, by some tens of milliseconds per layer, and its results are sound. */
+ * without any: the call is late, by some tens of milliseconds per layer, and its
+ * results are sound (sums in another order, so equal to the usual ones but for rounding). */
 int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* workspace_dev,
                void* hip_stream, cmt_handle** out);
 /* Releases the handle, its pinned host memory, its internal stream and events (it waits for the
