@@ -18,7 +18,7 @@
 // that a process's hardware queues can run at once leave a CU free for one of them to complete its group.  Nothing rests on
 // that but speed: more queues, other processes or a stream confined to a few CUs may stop a group from forming.  Every wait
 // is bounded, a workgroup that gives up says so and finishes without waiting, the others of the launch follow, and a second
-// launch (about 5 us where there is nothing to do) makes the recurrence again without waits, one workgroup per 16 sentences:
+// launch (2 - 4 us of a step where there is nothing to do) makes the recurrence again without waits, one workgroup per 16 sentences:
 // 0.4 ms a position at width 1024.  That form also serves devices too small for the groups.
 //
 // What a position costs within a training step (bf16, us; a launch per position cost 8.5 - 9, upper layers forward 5.6 of a
