@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <functional>
 #include <chrono>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -56,6 +57,8 @@ struct LD {
   char* Wfm = nullptr;               // gate rows of W, columns [Kin - Kstep, Kin + Hh)
   char* HstF = nullptr;              // [(Lmax+1)] slots of [Bp, Hh]
   char* YdF = nullptr;               // [Lmax] slots of [Bp, Hh] (the layer's output after dropout)
+  char* XH = nullptr; char* XY = nullptr; char* XD = nullptr;   // decoder: the whole loop's slots (states, after dropout, gate
+                                     // gradients): the copies above and dGF where there are such
   bool fm = false;
   // encoder: exchange slots of the whole-recurrence kernels, for the states and for the gate gradients (recur.hip); they
   // share the memory of dGT and Gx
@@ -139,6 +142,10 @@ struct cmt_handle {
   float* loss = nullptr; int* flags = nullptr; float* colscr = nullptr;
   int* tickets = nullptr;               // SEQ_TICKETS words, two per recurrence launch of a pass (layers <= 8)
   SeqRun seq{};                         // how the recurrences run (env CMT_RECUR)
+  int loop = 1;                         // the decoder's loops as one launch each (env CMT_DEC_LOOP); its slots, where the
+                                        // layers have no fragment-major copies that can serve (LD::HstF, YdF, dGF)
+  char* HoFeedX = nullptr; char* dPreX = nullptr;
+  bool capturing = false;               // the pass being enqueued is captured into a graph
   char* dzs = nullptr; char* dzTs = nullptr; float* dbo_parts = nullptr;
   std::vector<GemmProb> dw_group;       // weight-gradient GEMMs collected for one grouped launch (flush_dw_group)
   int ce_rows = 0, ce_pitch = 0;        // row capacity of an output-layer slab and the row pitch of its buffers
@@ -253,6 +260,9 @@ size_t layout(cmt_handle* h, char* base) {
   h->PH = H + ACT_PAD;
   const size_t PH = h->PH;
   h->Pc = c.precision ? a.take(h->nparams * esz) : (char*)h->params;
+  // (the whole loops take batches up to LOOP_MAX_BATCH; Bl: the rows of their slots)
+  const bool loops = h->loop && L <= LOOP_MAX_LAYERS;
+  const size_t Bl = std::min(Bp, LOOP_MAX_BATCH);
   auto ld_alloc = [&](LD& d, int Kin, int Hh, int Lm, bool gx, int Kstep, bool encoder) {
     d.Kin = Kin; d.Hh = Hh; d.ph = Hh + ACT_PAD; d.pg = 4 * Hh + ACT_PAD;
     const size_t M = (size_t)Lm * Bp;
@@ -277,8 +287,16 @@ size_t layout(cmt_handle* h, char* base) {
     // The recurrences' exchange slots are filled afresh by every pass and take no memory of their own: the states' lie
     // where the gate gradients are transposed to after the backward pass, the gate gradients' where the forward pass had
     // its input parts.
-    d.dGT = a.take(std::max(M * 4 * Hh, encoder ? seq_exchange_elems(Lm + 1, Bp, Hh) : 0) * esz);
+    // (The decoder's whole loops likewise, where there are no fragment-major copies that can serve.)
+    const size_t row = loop_slot_elems(1, Hh), Ml = (size_t)Lm * Bl;
+    const size_t slots = encoder ? seq_exchange_elems(Lm + 1, Bp, Hh) : !loops ? 0 : std::max(d.fm ? 0 : (2 * Ml + Bl) * row, d.fmb ? 0 : Ml * 4 * row);
+    d.dGT = a.take(std::max(M * 4 * Hh, slots) * esz);
     if (encoder) { d.X = d.dGT; d.XG = (char*)d.Gx; }
+    else if (loops) {
+      d.XH = d.fm ? d.HstF : d.dGT;
+      d.XY = d.fm ? d.YdF : d.dGT + (base ? (Ml + Bl) * row * esz : 0);
+      d.XD = d.fmb ? d.dGF : d.dGT;
+    }
     d.HstT = a.take((M + Bp) * Hh * esz);
     if (!encoder) {
       d.dh = (float*)a.take((size_t)Bp * Hh * 4);
@@ -313,13 +331,17 @@ size_t layout(cmt_handle* h, char* base) {
   h->Y0 = a.take(Ms * H * esz); h->Y0T = a.take(Ms * H * esz); h->Kmat = a.take(Ms * H * esz);
   h->Pmat = (float*)a.take(Ms * H * 4); h->PmatT = a.take(Ms * H * esz);
   h->dHs = (float*)a.take(Ms * H * 4); h->dK = a.take(Ms * H * esz); h->dKT = a.take(Ms * H * esz);
-  h->dYa = (float*)a.take(Ms * H * 4);
+  // (until the encoder's backward pass the decoder's backward loop exchanges its scores there, in dYa and on into dXs)
+  const size_t loop_scores = loops ? (size_t)Tm * Bl * std::min(Sm, LOOP_MAX_SRC) : 0;
+  h->dYa = (float*)a.take(std::max(Ms * H, loop_scores > Ms * E ? loop_scores - Ms * E : 0) * 4);
   h->dXs = (float*)a.take(Ms * E * 4);
   // target side
   h->Xt = a.take(Mt * E * esz); h->XtT = a.take(Mt * E * esz);
   h->mask_t = (float*)a.take(Mt * 4); h->tok_t = (int32_t*)a.take(Mt * 4); h->labels = (int32_t*)a.take(Mt * 4);
   h->len_t = (int32_t*)a.take((size_t)Bp * 4);
-  h->HoBuf = a.take((Mt + Bp) * PH * esz); h->HoBufT = a.take((Mt + Bp) * H * esz);
+  const size_t loop_row = loops ? loop_slot_elems(1, H) * esz : 0;     // bytes of a row in a loop's slots
+  h->HoBuf = a.take((Mt + Bp) * PH * esz); h->HoBufT = a.take(std::max((Mt + Bp) * H * esz, ((size_t)Tm + 1) * Bl * loop_row));
+  h->HoFeedX = !loops ? nullptr : h->HoFeedF ? h->HoFeedF : h->HoBufT;   // (transposed after the forward loop)
   h->HoDrop = a.take((Mt + Bp) * PH * esz);
   h->ldxcat = E + H + ACT_PAD;
   h->xcat = a.take((size_t)Bp * h->ldxcat * esz);
@@ -342,7 +364,8 @@ size_t layout(cmt_handle* h, char* base) {
   }
   h->Cs = a.take(Mt * PH * esz); h->CsT = a.take(Mt * H * esz);
   h->att_a = (float*)a.take(Mt * Sm * 4); h->att_ds = (float*)a.take(Mt * Sm * 4);
-  h->dCs = (float*)a.take(Mt * H * 4);
+  h->dCs = (float*)a.take(std::max(Mt * H * 4, (size_t)Tm * Bl * loop_row));
+  h->dPreX = !loops ? nullptr : h->dPreF ? h->dPreF : (char*)h->dCs;     // (dC_s is made after the backward loop)
   h->dots = (float*)a.take((size_t)Bp * Sm * 4);
   h->att_s = (float*)a.take(Mt * Sm * 4);
   h->dPre = a.take(Mt * PH * esz); h->dPreT = a.take(Mt * H * esz);
@@ -715,6 +738,118 @@ void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
   }
 }
 
+// A loop takes every CU there is and its workgroups wait for one another, as the encoder's recurrences' do: if parts of two such
+// launches were on the chip at once, neither might get on until its waits are given up.  Those of one stream follow each other
+// anyway; the sections of a pass that hold them are kept apart across the streams of a process by an event per device: a section
+// on another stream than the last one waits for the last one's end.  (The mutex is held while a section is enqueued.)  Nothing of
+// the kind under capture, where an event from outside must not be waited for; loops are not captured.
+struct WideGate { std::mutex mu; hipEvent_t ev = nullptr; hipStream_t last = nullptr; bool used = false; };
+WideGate g_wide_gate[64];
+class WideSection {
+ public:
+  explicit WideSection(cmt_handle* h) : h_(h) {}
+  ~WideSection() { close(); }
+  WideSection(const WideSection&) = delete;
+  WideSection& operator=(const WideSection&) = delete;
+  void open() {
+    int dev = -1;
+    if (gate_ || h_->capturing || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return;
+    WideGate* g = &g_wide_gate[dev];
+    g->mu.lock();
+    if (!g->ev && hipEventCreateWithFlags(&g->ev, hipEventDisableTiming) != hipSuccess) { g->ev = nullptr; g->mu.unlock(); return; }
+    gate_ = g;
+    if (g->used && g->last != h_->st) (void)hipStreamWaitEvent(h_->st, g->ev, 0);
+  }
+  void close() {
+    if (!gate_) return;
+    gate_->used = hipEventRecord(gate_->ev, h_->st) == hipSuccess;
+    gate_->last = h_->st;
+    gate_->mu.unlock();
+    gate_ = nullptr;
+  }
+ private:
+  cmt_handle* h_;
+  WideGate* gate_ = nullptr;
+};
+void note_capture(cmt_handle* h) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  h->capturing = hipStreamIsCapturing(h->st, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
+}
+
+// Whether the decoder's loops run as one launch each.
+bool dec_loop(const cmt_handle* h, int S) {
+  return h->loop && !h->capturing && h->att_proj == 1 && h->HoFeedX &&
+         loop_fits(h->prec, h->cfg.layers, h->Bp, h->cfg.hidden, S, h->seq);
+}
+// All target positions of the forward pass, on the projected source rows.
+void enqueue_dec_loop_fwd(cmt_handle* h, int S, int T) {
+  const cmt_config& c = h->cfg;
+  const int p = h->prec, E = c.emb_dim, H = c.hidden, L = c.layers, Bp = h->Bp;
+  const size_t esz = h->esz, slot = loop_slot_elems(Bp, H);
+  const bool drop = h->drop_p > 0.f;
+  hipStream_t st = h->st;
+  LoopFwdArgs a{};
+  std::vector<FillJob> z;
+  for (int l = 0; l < L; ++l) {
+    LD& e = h->dec[l];
+    LoopFwdLayer& d = a.l[l];
+    d.W = e.W; d.ldw = e.Kin + H; d.wx_off = l == 0 ? E : 0; d.wh_off = e.Kin; d.bias = l > 0 ? h->params + e.b_off : nullptr;
+    d.H = e.Hst; d.ldh = e.ph; d.C = e.Cst; d.G = e.Gs; d.X = e.XH;
+    if (drop && l + 1 < L) { d.Y = e.Yd; d.XY = e.XY; d.drop = drop_spec(h, DROP_SITE_DEC + l, 0); add_empty(z, e.XY, T * slot, esz); }
+    add_empty(z, e.XH, (T + 1) * slot, esz);
+  }
+  a.gx = h->dec[0].Gx; a.mask = h->mask_t; a.len = h->len_s;
+  a.Wc = h->Pw(h->off_Wc) + (size_t)H * esz; a.ldwc = 2 * H;
+  a.K = h->Kmat; a.P = h->PmatT; a.Pg = h->dK;     // (dK is made after the backward loop)
+  a.scores = h->att_s; a.a = h->att_a;
+  a.Ho = h->HoBuf; a.HoD = drop ? h->HoDrop : nullptr; a.ldho = h->PH; a.XO = h->HoFeedX;
+  if (drop) a.drop_o = drop_spec(h, DROP_SITE_HO, 0);
+  a.drop_step = (unsigned long long)h->B * H;
+  a.ticket = h->tickets + LOOP_TICKET_FWD;
+  add_empty(z, h->HoFeedX + slot * esz, T * slot, esz);
+  add_empty(z, h->att_s, (size_t)T * Bp * S, 4);
+  // (slot 0 of the bottom layer's input, H_o^{<-1>} = 0)
+  add_fill(z, h->HoFeedX, slot, esz);
+  launch_fill_multi(z.data(), (int)z.size(), st);
+  launch_loop_columns(p, h->PmatT, h->dK, S, Bp, H, st);
+  launch_loop_fwd(p, a, L, T, Bp, H, S, h->seq, st);
+}
+
+// All target positions of the backward pass.
+void enqueue_dec_loop_bwd(cmt_handle* h, int S, int T) {
+  const cmt_config& c = h->cfg;
+  const int p = h->prec, E = c.emb_dim, H = c.hidden, L = c.layers, Bp = h->Bp;
+  const size_t esz = h->esz, slot = loop_slot_elems(Bp, H);
+  const bool drop = h->drop_p > 0.f;
+  hipStream_t st = h->st;
+  LoopBwdArgs a{};
+  std::vector<FillJob> z;
+  for (int l = 0; l < L; ++l) {
+    LD& e = h->dec[l];
+    LoopBwdLayer& d = a.l[l];
+    d.Wt = e.Wt; d.ldw = 4 * H; d.x_row = l == 0 ? E : 0; d.h_row = e.Kin;
+    d.C = e.Cst; d.G = e.Gs; d.dG = e.dG; d.lddg = e.pg; d.X = e.XD; d.part = e.bwdp; d.dh = e.dh; d.dc = e.dc;
+    if (drop && l + 1 < L) d.drop = drop_spec(h, DROP_SITE_DEC + l, 0);
+    add_empty(z, e.XD, T * 4 * slot, esz);
+    add_empty(z, e.bwdp, (size_t)16 * Bp * H, 4);
+  }
+  a.mask = h->mask_t; a.len = h->len_s; a.Wct = h->WcT + (size_t)H * H * esz;
+  a.K = h->Kmat; a.Kg = h->dKT; a.P = h->Pmat;     // (dKT is made after the loop)
+  a.a = h->att_a; a.da = h->dYa; a.ds = h->att_ds;
+  a.dce = h->dHoCE; a.pos = h->ce_pos; a.Ho = h->HoBuf; a.ldho = h->PH;
+  a.dPre = h->dPre; a.ldp = h->PH; a.XP = h->dPreX;
+  if (drop) a.drop_o = drop_spec(h, DROP_SITE_HO, 0);
+  a.drop_step = (unsigned long long)h->B * H;
+  a.ticket = h->tickets + LOOP_TICKET_BWD;
+  add_empty(z, h->dPreX, T * slot, esz);
+  add_empty(z, h->dYa, (size_t)T * Bp * S, 4);
+  launch_fill_multi(z.data(), (int)z.size(), st);
+  launch_loop_columns(p, h->Kmat, h->dKT, S, Bp, H, st);
+  launch_loop_bwd(p, a, L, T, Bp, H, S, h->seq, st);
+  // dC_s of all positions (the deferred gradients read it): dpre W_c1
+  launch_gemm_nt(p, h->dPre, h->PH, h->WcT, H, T * Bp, H, H, h->dCs, nullptr, H, nullptr, 0, st);
+}
+
 int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, const int32_t* tgt_ids,
                  const int32_t* tgt_len, int B, int S, int T, bool forward_only) {
   const cmt_config& c = h->cfg;
@@ -755,6 +890,9 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   launch_ce_compact(h->mask_t, h->labels, Mt, h->ce_pos, h->ce_row, h->labels_c, h->rowscale, h->ce_nvalid, h->loss, st);
 
   const char* Hs; int ldHs;                        // source-side top-layer states [S, Bp, H] and their row pitch
+  note_capture(h);
+  WideSection wide(h);
+  wide.open();
   enqueue_encoder(h, S, &Hs, &ldHs);
   LD& ef = h->enc[0]; LD& eb = h->enc[1];
   // ---- decoder time loop --------------------------------------------------------------------------
@@ -763,12 +901,15 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   // with the scores (both wait for the top layer's state alone) — two dependent launches per step instead of three.
   // The contexts themselves (the weight gradient of W_c needs them) are made for all steps at once afterwards.
   const bool proj = h->att_proj && Bp < 256;
+  const bool loop = dec_loop(h, S);                // the whole loop as one launch
   {
     LD& d0 = h->dec[0];
     launch_gemm_nt(p, h->Xt, E, d0.W, E + 2 * H, Mt, 4 * H, E, d0.Gx, nullptr, 4 * H, P + d0.b_off, 0, st);
     if (proj) launch_gemm_nt(p, Hs, ldHs, h->Pw(h->off_Wc), 2 * H, Ms, H, H, h->Pmat, h->PmatT, H, nullptr, 0, st);
     phase_mark(h, "decoder forward loop");
-    for (int j = 0; j < T; ++j) {
+    if (loop) enqueue_dec_loop_fwd(h, S, T);
+    wide.close();
+    for (int j = loop ? T : 0; j < T; ++j) {
       for (int l = 0; l < L; ++l) dec_lstm_fwd(h, l, j);
       const char* Ht = h->dec[L - 1].Hst + (j + 1) * BP * esz;
       if (proj) { dec_att_fwd_proj(h, j, S, h->att_s + (size_t)j * Bp * S); continue; }
@@ -896,7 +1037,10 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   const int kbd = step_kblocks(p, 2 * H, 4 * H, Bp, h->kb_bwd_dec);       // planes written by a decoder layer's backward GEMM
   const size_t pstr = (size_t)Bp * 2 * H;
   const Planes no_planes{nullptr, 0, 0, 0};
-  if ((h->bwd_fused & 1) && Bp <= 128) {            // (measured at 128 sentences: 8.1 against 8.7 ms for the k-split form)
+  wide.open();
+  if (loop && (h->bwd_fused & 1) && h->wc_whole_k) {
+    enqueue_dec_loop_bwd(h, S, T);
+  } else if ((h->bwd_fused & 1) && Bp <= 128) {            // (measured at 128 sentences: 8.1 against 8.7 ms for the k-split form)
     // one launch per layer and step (dec_bwd_gemm): no pointwise launches, no planes
     for (int j = T - 1; j >= 0; --j) {
       char* dpre = h->dPre + j * BP * esz;
@@ -1076,6 +1220,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
     }
     sb.ticket = h->tickets;
     launch_lstm_seq_bwd(p, sb, 2, S, Bp, Hd, h->seq, st);
+    wide.close();
     // What is left after the last recurrent kernel is shared between the two streams: the weight gradients of
     // both directions on the second one, the source-embedding gradient (dX_s, then the scatter) on the caller's.
     stream_after(h, sd, st);
@@ -1108,6 +1253,7 @@ int cmt_query_sizes(const cmt_config* cfg, size_t* param_bytes, size_t* grad_byt
   cmt_handle tmp;
   tmp.cfg = *cfg; tmp.prec = cfg->precision; tmp.esz = cfg->precision ? 2 : 4;
   tmp.Bpm = round_up(cfg->max_batch, 16);
+  { const char* e = getenv("CMT_DEC_LOOP"); tmp.loop = e ? atoi(e) : 1; }
   build_table(tmp.cfg, tmp.table, tmp.nparams);
   const size_t ws = layout(&tmp, nullptr);
   if (param_bytes) *param_bytes = tmp.nparams * 4;
@@ -1139,6 +1285,7 @@ int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* w
     const char* k3p = getenv("CMT_ATT_PROJ"); h->att_proj = k3p ? atoi(k3p) : 1;
     const char* k4 = getenv("CMT_PHASE_TIMING"); h->phase_timing = k4 ? atoi(k4) : 0;
     const char* k5 = getenv("CMT_BWD_FUSED"); h->bwd_fused = k5 ? atoi(k5) : 1;
+    const char* k7 = getenv("CMT_DEC_LOOP"); h->loop = k7 ? atoi(k7) : 1;
     const char* k6 = getenv("CMT_RECUR"); h->seq.mode = k6 ? atoi(k6) : SEQ_RUN_TOGETHER;
   }
   build_table(h->cfg, h->table, h->nparams);
@@ -1274,6 +1421,7 @@ int cmt_eval_loss_static(cmt_handle* h, const int32_t* src_ids_dev, const int32_
   cmt_handle v = *h;
   v.cfg.max_batch = B; v.cfg.max_src_len = S; v.cfg.max_tgt_len = T;
   v.Bpm = round_up(B, 16);
+  v.loop = 0;                                        // (their slots would take room here, and the call may be under capture)
   v.phase_timing = 0; v.phase_ev.clear(); v.phase_name.clear();
   const size_t need = layout(&v, nullptr);
   if (need > (size_t)CMT_STATIC_SCRATCH_BYTES) {
@@ -1357,7 +1505,11 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
   launch_gather(p, h->Pw(h->off_Esrc), c.src_vocab, E, src_ids_dev, src_len_dev, B, Bp, S, 0, 0, h->Xs, h->mask_s, h->tok_s,
                 nullptr, h->len_s, h->flags, st);
   const char* Hs; int ldHs;
+  note_capture(h);
+  WideSection wide(h);
+  wide.open();
   enqueue_encoder(h, S, &Hs, &ldHs);
+  wide.close();
   const bool proj = h->att_proj && Bp < 256;
   if (proj) launch_gemm_nt(p, Hs, ldHs, h->Pw(h->off_Wc), 2 * H, S * Bp, H, H, nullptr, h->PmatT, H, nullptr, 0, st);
   launch_dec_init(B, Bp, max_len, c.bos_id, c.pad_id, h->dec_tok, h->dec_done, out_ids_dev, out_len_dev, h->dec_mask, st);
@@ -1460,7 +1612,11 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
   launch_gather(p, h->Pw(h->off_Esrc), c.src_vocab, E, src_ids_dev, src_len_dev, B, BpE, S, 0, 0, h->Xs, h->mask_s, h->tok_s,
                 nullptr, h->len_s, h->flags, st);
   const char* Hs; int ldHs;
-  enqueue_encoder(h, S, &Hs, &ldHs);                 // also leaves the decoder's initial states in slot 0 (BpE rows)
+  note_capture(h);
+  WideSection wide(h);
+  wide.open();
+  enqueue_encoder(h, S, &Hs, &ldHs);
+  wide.close();                 // also leaves the decoder's initial states in slot 0 (BpE rows)
   h->drop_p = keep_p;
   // one decoder row per hypothesis: encoder outputs, keys, lengths and initial states repeated K times
   BeamState& bs = h->beam;

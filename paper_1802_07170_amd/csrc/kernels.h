@@ -283,7 +283,8 @@ struct SeqFwdDir {
 };
 // ticket: two words, zero before the launch (roles taken; whether a wait was given up); wait_ticks is set by the launcher
 struct SeqFwdArgs { SeqFwdDir d[2]; int* ticket; int wait_ticks; };
-constexpr int SEQ_TICKETS = 64;
+constexpr int SEQ_TICKETS = 64;           // two words per launch: 18 for the encoder's recurrences, then the decoder's loops
+constexpr int LOOP_TICKET_FWD = 32, LOOP_TICKET_BWD = 34;
 inline size_t seq_exchange_elems(int slots, int Bp, int Hh) { return (size_t)slots * Bp * ((Hh + 31) / 32 * 32); }
 // Backward of the same: builds the gate gradients of every position.
 struct SeqBwdDir {
@@ -300,6 +301,64 @@ struct SeqBwdArgs { SeqBwdDir d[2]; int* ticket; int wait_ticks; };
 void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& args, int ndir, int L, int Bp, int Hh, const SeqRun& run, hipStream_t st);
 // Forward: the initial states are zero (the slots before the first position are not read).  1 <= ndir <= 2 instances of one shape.
 void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& args, int ndir, int L, int Bp, int Hh, const SeqRun& run, hipStream_t st);
+
+// ---- loop.hip --------------------------------------------------------------------------------------
+// The decoder's time loop in one launch (see there).  Slots hold T elements in fragment-major tiles, rows of `width` units
+// rounded up to 32; what the loop writes is filled with 0xff bytes beforehand, and so are `scores` / `da`.
+constexpr int LOOP_MAX_LAYERS = 4, LOOP_MAX_BATCH = 128, LOOP_MAX_SRC = 128;
+inline size_t loop_slot_elems(int Bp, int H) { return (size_t)Bp * ((H + 31) / 32 * 32); }
+struct LoopFwdLayer {
+  const void* W; int ldw, wx_off, wh_off;  // T* [4H, ldw]: the per-step input's columns and the recurrent ones
+  const float* bias;                       // [4H] (layer 0: not used, gx holds it)
+  void* H; int ldh; float* C; float* G;    // states T* [T + 1, Bp, ldh], cell states [T + 1, Bp, H], gate activations [T, Bp, 4H]
+  void* X;                                 // T + 1 slots of states
+  void* Y; void* XY;                       // the states after dropout, rows [T, Bp, ldh] and T slots; null: none
+  DropSpec drop;                           // position 0 (see drop_step)
+};
+struct LoopFwdArgs {
+  LoopFwdLayer l[LOOP_MAX_LAYERS];
+  const float* gx;                         // [T, Bp, 4H] the bottom layer's batched input part
+  const float* mask;                       // [T, Bp]
+  const int32_t* len;                      // [Bp] source lengths
+  const void* Wc; int ldwc;                // T* [H, ldwc]: the H_t half of W_c
+  const void* K; const void* P;            // T* [S, Bp, H] keys and projected source rows
+  void* Pg;                                // the same rows as [H / 4, Bp, S, 4]
+  float* scores; float* a;                 // [T, Bp, S]
+  void* Ho; void* HoD; int ldho;           // H_o T* [T + 1, Bp, ldho], and after dropout (null: none)
+  void* XO;                                // T + 1 slots of H_o as fed; slot 0 is not read
+  DropSpec drop_o; unsigned long long drop_step;
+  int* ticket; int wait_ticks;             // as in SeqFwdArgs (the first word is not used)
+};
+struct LoopBwdLayer {
+  const void* Wt; int ldw, x_row, h_row;   // T* [.., ldw], rows = input columns of W, contiguous over the 4H gate rows: the first
+                                           //   of the per-step input's H rows and of the recurrent ones
+  const float* C; const float* G;          // as the forward pass left them
+  void* dG; int lddg;                      // gate gradients T* [T, Bp, lddg]
+  void* X;                                 // T slots of gate gradients: per tile of 16 sentences the four gates' rows
+  float* part;                             // 16 Bp H floats, filled with 0xff bytes: partial sums on their way (two positions x
+                                           //   input and recurrent part x the gate that they come from)
+  float* dh; float* dc;                    // out: gradient of the initial states [Bp, H]
+  DropSpec drop;                           // dropout between this layer and the one above, position 0
+};
+struct LoopBwdArgs {
+  LoopBwdLayer l[LOOP_MAX_LAYERS];
+  const float* mask; const int32_t* len;
+  const void* Wct;                         // T* [H, H]: row c = column c of W_c's H_t half
+  const void* K; void* Kg;                 // T* [S, Bp, H] keys, and as [H / 4, Bp, S, 4]
+  const float* P;                          // projected source rows, fp32 [S, Bp, H]
+  const float* a; float* da; float* ds;    // [T, Bp, S]: attention weights; dpre . P_i (filled with 0xff bytes); the scores' gradients
+  const float* dce; const int32_t* pos;    // output layer's gradient at H_o: rows by pos [T, Bp] (< 0: none)
+  const void* Ho; int ldho;                // T* [T + 1, Bp, ldho] before dropout
+  void* dPre; int ldp; void* XP;           // dpre T* [T, Bp, ldp], and its T slots
+  DropSpec drop_o; unsigned long long drop_step;
+  int* ticket; int wait_ticks;
+};
+// Whether the loop runs as one launch on this device.
+bool loop_fits(int prec, int L, int Bp, int H, int S, const SeqRun& run);
+// dst [H / 4, Bp, S, 4] <- src [S, Bp, H]
+void launch_loop_columns(int prec, const void* src, void* dst, int S, int Bp, int H, hipStream_t st);
+void launch_loop_bwd(int prec, const LoopBwdArgs& args, int L, int T, int Bp, int H, int S, const SeqRun& run, hipStream_t st);
+void launch_loop_fwd(int prec, const LoopFwdArgs& args, int L, int T, int Bp, int H, int S, const SeqRun& run, hipStream_t st);
 
 // ---- misc.hip ----------------------------------------------------------------------------------
 // Embedding gather + masks + input validation (flags |= 1 bad id, |= 2 bad length).

@@ -46,4 +46,28 @@ inline SeqPlan seq_bwd_plan(int prec, int ndir, int Bp, int Hh) {
   return p;
 }
 
+// The decoder's whole loop: a group = up to 128 sentences, its H / 4 workgroups own four units of every layer.  All layers'
+// weights stay on the chip, so a group is as large as the widest network needs (256 workgroups at width 1024) and a launch
+// takes every CU there is.  Launches of that kind and the recurrences above run one after the other in a process (see
+// wide_section in api.hip).
+struct LoopPlan { bool ok; int nk, nwg, bt, nch, groups, tiles; };   // nk k steps per wavefront; bt tiles of 16 sentences at a time, nch
+                                                                     // times; tiles = the most a group has
+inline LoopPlan loop_plan(int prec, int L, int Bp, int H, int S, int cus) {
+  LoopPlan p{};
+  const int nt = Bp / 16, nsteps = (H + 31) / 32;
+  p.nwg = H / 4;
+  p.nk = nsteps <= 8 ? 1 : nsteps <= 16 ? 2 : 4;
+  // (fp32 wider than 512: twice the weights, more than a CU's registers and LDS hold)
+  if (L > 4 || nt > 8 || S > 128 || p.nwg > cus || nsteps > 32 || (!prec && p.nk > 2)) return p;
+  p.groups = nt < cus / p.nwg ? nt : cus / p.nwg;
+  p.tiles = (nt + p.groups - 1) / p.groups;
+  p.groups = (nt + p.tiles - 1) / p.tiles;
+  // a chunk's fragments are in flight at once: 4 tiles of them, or 2 where twice 4 tiles' sums take the registers (3 run as 4)
+  p.bt = p.tiles < 3 || p.tiles > 4 ? (p.tiles < 2 ? 1 : 2) : 4;
+  p.nch = p.tiles > 4 ? 4 : 1;
+  if ((p.nch > 1 && !(prec && p.nk == 4)) || (p.nk == 1 && p.bt > 2)) return p;
+  p.ok = true;
+  return p;
+}
+
 }  // namespace cmt
