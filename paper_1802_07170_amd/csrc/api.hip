@@ -165,14 +165,11 @@ struct cmt_handle {
   char* Wdec0F = nullptr; char* xcatF = nullptr;
   int kb_wc = 0;                        // caps on the k blocks of the decoder's k-split step GEMMs (0 = default): dpre W_c, and
   int kb_bwd_dec = 0;                   // the layers' backward GEMMs
-  // Workgroup caps of the second stream's GEMMs (weight gradients; dW_o), 0 = none, -1 = by batch width: with all
-  // 256 CUs taken by 256 x 256 tiles for tens of microseconds at a time, the kernels on the caller's stream queue behind
-  // them; capped at 128 workgroups (512 of the 64 x 64 tile, see launch_gemm_nt) the GEMMs take twice as long (still
-  // hidden) and leave half the chip free.  Step time capped / uncapped, ms: small (fp32) 8.53 / 8.93, attn 7.45 / 7.51,
-  // paper_512x2 3.31 / 3.35, medium 8.21 / 8.18 (within its runs); at 128 sentences (large) 21.96 / 21.40, so the caps
-  // apply up to 64 sentences.  Env CMT_SIDE_WGS, CMT_SIDE_WGS_WO.
-  int side_wgs = -1, side_wgs_wo = -1;
-  int side_cap(int v) const { return v >= 0 ? v : (Bp <= 64 ? 128 : 0); }
+  // Workgroup caps of the second stream's GEMMs (weight gradients; dW_o), 0 = none (env CMT_SIDE_WGS, CMT_SIDE_WGS_WO).  A cap leaves
+  // part of the chip to the kernels of the caller's stream, which paid while the decoder's loops were chains of short launches
+  // beside them; a loop that takes the whole chip waits for them instead.  Step time with a cap of 128 / without, ms: medium 6.68 /
+  // 6.54, attn 5.42 / 5.29, paper_512x2 2.64 / 2.57, small (fp32) 4.52 / 4.52; at 128 sentences (large) 20.7 / 20.2.
+  int side_wgs = 0, side_wgs_wo = 0;
   int wc_whole_k = 1;                   // fused decoder loop: dpre W_c with the whole k range per workgroup (env CMT_WC_WHOLE_K)
   // decoder's backward loop with the whole-k step GEMM and the consumer in its epilogue (env CMT_BWD_FUSED, bit 1), up
   // to 128 sentences: 8.1 against 8.7 ms for the large workload's loop; wider batches keep the k-split GEMM +
@@ -482,7 +479,7 @@ void weight_grads(cmt_handle* h, LD& d, int Lsteps, const std::vector<std::pair<
 // launches what weight_grads (and the callers that add W_c / W_a problems) have collected, as one queue of tiles
 void flush_dw_group(cmt_handle* h, hipStream_t st) {
   launch_gemm_nt_group(h->prec, h->dw_group.data(), (int)h->dw_group.size(), st, h->gsplit2, h->gsplit2_floats,
-                       st != h->st ? h->side_cap(h->side_wgs) : 0);
+                       st != h->st ? h->side_wgs : 0);
   h->dw_group.clear();
 }
 
@@ -1021,7 +1018,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
                      h->gsplit_floats, lim, 1);                           // dH_o[slab] = dz W_o
       // dW_o (+)= dz^T H_o[slab]; the first slab always holds a row, so W_o's gradient is always written
       launch_gemm_nt(p, dzT, h->ce_pitch, h->HocT + (size_t)m0 * esz, Mt, V, H, Mc, G + h->off_Wo, nullptr, H, nullptr, sl > 0,
-                     sd, nullptr, 0, lim, 2, sd != st ? h->side_cap(h->side_wgs_wo) : 0);
+                     sd, nullptr, 0, lim, 2, sd != st ? h->side_wgs_wo : 0);
       if (sd != st) {
         done[sl] = h->ev[h->ev_next++ % h->ev.size()];
         (void)hipEventRecord(done[sl], sd);
@@ -1278,8 +1275,8 @@ int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* w
   {
     const char* k1d = getenv("CMT_KB_BWD_DEC"); h->kb_bwd_dec = k1d ? atoi(k1d) : 0;
     const char* k2 = getenv("CMT_KB_WC"); h->kb_wc = k2 ? atoi(k2) : 2;
-    const char* ks1 = getenv("CMT_SIDE_WGS"); h->side_wgs = ks1 ? atoi(ks1) : -1;
-    const char* ks2 = getenv("CMT_SIDE_WGS_WO"); h->side_wgs_wo = ks2 ? atoi(ks2) : -1;
+    const char* ks1 = getenv("CMT_SIDE_WGS"); h->side_wgs = ks1 ? atoi(ks1) : 0;
+    const char* ks2 = getenv("CMT_SIDE_WGS_WO"); h->side_wgs_wo = ks2 ? atoi(ks2) : 0;
     const char* kw = getenv("CMT_WC_WHOLE_K"); h->wc_whole_k = kw ? atoi(kw) : 1;
     const char* k3 = getenv("CMT_SIDE_STREAM"); h->use_side = k3 ? atoi(k3) : 1;
     const char* k3p = getenv("CMT_ATT_PROJ"); h->att_proj = k3p ? atoi(k3p) : 1;
