@@ -147,7 +147,9 @@ struct cmt_handle {
   char* HoFeedX = nullptr; char* dPreX = nullptr;
   bool capturing = false;               // the pass being enqueued is captured into a graph
   char* dzs = nullptr; char* dzTs = nullptr; float* dbo_parts = nullptr;
-  std::vector<GemmProb> dw_group;       // weight-gradient GEMMs collected for one grouped launch (flush_dw_group)
+  std::vector<GemmProb> dw_group;       // weight-gradient GEMMs collected for one grouped launch (flush_dw_group), the transposes
+  std::vector<TransposeJob> dw_tr;      // of their operands and the sums for the biases that come with those
+  std::vector<SumPartsJob> dw_sums;
   int ce_rows = 0, ce_pitch = 0;        // row capacity of an output-layer slab and the row pitch of its buffers
   int ce_cap = ce_cap_env();            // upper bound of ce_rows
   float* gsplit = nullptr; size_t gsplit_floats = 0;   // split-k planes of dH_o = dz W_o (also the probes' scratch)
@@ -425,22 +427,25 @@ void refresh_params(cmt_handle* h, bool cast = true) {
   const int H = c.hidden, p = h->prec;
   hipStream_t st = h->st;
   if (p && cast) launch_cast(1, h->params, h->Pc, h->nparams, st);
+  std::vector<TransposeJob> t;
+  for (auto* v : {&h->enc, &h->dec})
+    for (auto& d : *v) t.push_back({d.W, d.Kin + d.Hh, d.Wt, 4 * d.Hh, 4 * d.Hh, d.Kin + d.Hh});
+  t.push_back({h->Pw(h->off_Wa), H, h->WaT, H, H, H});
+  t.push_back({h->Pw(h->off_Wc), 2 * H, h->WcT, H, H, 2 * H});
+  t.push_back({h->Pw(h->off_Wo), H, h->WoT, c.tgt_vocab, c.tgt_vocab, H});
+  launch_transpose_multi(p, t.data(), (int)t.size(), st);
   auto tr = [&](LD& d) {
-    launch_transpose(p, d.W, d.Kin + d.Hh, d.Wt, 4 * d.Hh, 4 * d.Hh, d.Kin + d.Hh, st);
     if (d.fm) launch_fm_pack_lstm_weights(d.W, d.Kin + d.Hh, d.Kin - d.Kstep, d.Kstep + d.Hh, d.Hh, d.Wfm, st);
     if (d.fmb) launch_fm_pack(d.Wt, 4 * d.Hh, d.Kin + d.Hh, 4 * d.Hh, d.WtF, st);
   };
   for (auto& d : h->enc) tr(d);
   for (auto& d : h->dec) tr(d);
-  launch_transpose(p, h->Pw(h->off_Wa), H, h->WaT, H, H, H, st);
-  launch_transpose(p, h->Pw(h->off_Wc), 2 * H, h->WcT, H, H, 2 * H, st);
   if (h->WcF) {
     launch_fm_pack(h->Pw(h->off_Wc), 2 * H, H, 2 * H, h->WcF, st);
     launch_fm_pack(h->WcT, H, 2 * H, H, h->WcTF, st);
     if (h->WoF) launch_fm_pack(h->Pw(h->off_Wo), H, c.tgt_vocab, H, h->WoF, st);
     if (h->Wdec0F) launch_fm_pack_lstm_weights(h->dec[0].W, c.emb_dim + 2 * H, 0, c.emb_dim + 2 * H, H, h->Wdec0F, st);
   }
-  launch_transpose(p, h->Pw(h->off_Wo), H, h->WoT, c.tgt_vocab, c.tgt_vocab, H, st);
 }
 
 int fail(cmt_handle* h, int code, const std::string& msg) {
@@ -465,19 +470,25 @@ void stream_after(cmt_handle* h, hipStream_t to, hipStream_t from) {
 void weight_grads(cmt_handle* h, LD& d, int Lsteps, const std::vector<std::pair<const char*, int>>& segs /* (XT ptr, ld) */,
                   const std::vector<int>& seg_k, hipStream_t st) {
   // dW[:, segment] = dG^T * X_segment as one GEMM with k = Lsteps * Bp; db = column sums of dG
-  const int p = h->prec, Bp = h->Bp, Hh = d.Hh;
+  const int Bp = h->Bp, Hh = d.Hh;
   const int M = Lsteps * Bp;
-  launch_transpose(p, d.dG, d.pg, d.dGT, M, M, 4 * Hh, st);
+  // (the partial sums' places: the backward loop's partial sums of some decoder layer are used up)
+  const size_t k = h->dw_sums.size();
+  float* const parts = k == 0 ? h->colscr : (int)k < h->cfg.layers ? h->dec[k].bwdp : h->wcp;
+  h->dw_tr.push_back({d.dG, d.pg, d.dGT, M, M, 4 * Hh, parts});
+  h->dw_sums.push_back({parts, (size_t)4 * Hh, h->grads + d.b_off});
   float* dW = h->grads + d.w_off;
   int col = 0;
   for (size_t i = 0; i < segs.size(); ++i) {
     h->dw_group.push_back(GemmProb{d.dGT, segs[i].first, dW + col, M, segs[i].second, d.Kin + Hh, 4 * Hh, seg_k[i], M, 0});
     col += seg_k[i];
   }
-  launch_colsum(p, d.dG, d.pg, M, 4 * Hh, h->colscr, h->grads + d.b_off, st);
 }
 // launches what weight_grads (and the callers that add W_c / W_a problems) have collected, as one queue of tiles
 void flush_dw_group(cmt_handle* h, hipStream_t st) {
+  launch_transpose_multi(h->prec, h->dw_tr.data(), (int)h->dw_tr.size(), st);
+  launch_sum_parts_multi(h->dw_sums.data(), (int)h->dw_sums.size(), TRANSPOSE_SPLITS, st);
+  h->dw_tr.clear(); h->dw_sums.clear();
   launch_gemm_nt_group(h->prec, h->dw_group.data(), (int)h->dw_group.size(), st, h->gsplit2, h->gsplit2_floats,
                        st != h->st ? h->side_wgs : 0);
   h->dw_group.clear();
@@ -963,9 +974,6 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   }
   hipStream_t sd = h->use_side ? h->side : st;
   const int ldHoT = Mt + Bp;
-  auto transpose_states = [&](LD& d, int Lsteps) {
-    launch_transpose(p, d.Hst, d.ph, d.HstT, (Lsteps + 1) * Bp, (Lsteps + 1) * Bp, d.Hh, sd);
-  };
   stream_after(h, sd, st);
   // the dense embedding gradients start from zero: cleared now, while the second stream has little to do
   launch_fill_f32(G + h->off_Esrc, (size_t)c.src_vocab * E, 0.f, sd);
@@ -975,19 +983,26 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
     esrc_cleared = h->ev[h->ev_next++ % h->ev.size()];
     (void)hipEventRecord(esrc_cleared, sd);
   }
-  launch_transpose(p, h->Hoc, PH, h->HocT, Mt, Mt, H, sd);           // dense H_o rows, for dW_o
-  launch_transpose(p, HoFeed, PH, h->HoBufT, ldHoT, Mt + Bp, H, sd);
-  for (auto& d : h->enc) transpose_states(d, S);
-  for (auto& d : h->dec) transpose_states(d, T);
-  if (drop) {                                      // inputs of the layers above, as they saw them
-    for (int l = 1; l + 1 < L; ++l) launch_transpose(p, h->enc[l + 1].Yd, PH, h->enc[l + 1].YdT, Ms, Ms, H, sd);
-    for (int l = 0; l + 1 < L; ++l) launch_transpose(p, h->dec[l].Yd, PH, h->dec[l].YdT, Mt, Mt, H, sd);
+  {
+    std::vector<TransposeJob> t;
+    t.push_back({h->Hoc, PH, h->HocT, Mt, Mt, H});                   // dense H_o rows, for dW_o
+    t.push_back({HoFeed, PH, h->HoBufT, ldHoT, Mt + Bp, H});
+    for (auto& d : h->enc) t.push_back({d.Hst, d.ph, d.HstT, (S + 1) * Bp, (S + 1) * Bp, d.Hh});
+    for (auto& d : h->dec) t.push_back({d.Hst, d.ph, d.HstT, (T + 1) * Bp, (T + 1) * Bp, d.Hh});
+    if (drop) {                                    // inputs of the layers above, as they saw them
+      for (int l = 1; l + 1 < L; ++l) t.push_back({h->enc[l + 1].Yd, PH, h->enc[l + 1].YdT, Ms, Ms, H});
+      for (int l = 0; l + 1 < L; ++l) t.push_back({h->dec[l].Yd, PH, h->dec[l].YdT, Mt, Mt, H});
+    }
+    t.push_back({h->Y0, H, h->Y0T, Ms, Ms, H});
+    t.push_back({h->Xs, E, h->XsT, Ms, Ms, E});
+    t.push_back({h->Xt, E, h->XtT, Mt, Mt, E});
+    launch_transpose_multi(p, t.data(), (int)t.size(), sd);
   }
-  launch_transpose(p, h->Y0, H, h->Y0T, Ms, Ms, H, sd);
-  launch_transpose(p, h->Xs, E, h->XsT, Ms, Ms, E, sd);
-  launch_transpose(p, h->Xt, E, h->XtT, Mt, Mt, E, sd);
   if (proj) launch_att_context(p, Hs, ldHs, h->att_a, h->len_s, S, T, Bp, H, h->Cs, PH, sd);
-  launch_transpose(p, h->Cs, PH, h->CsT, Mt, Mt, H, sd);
+  {
+    const TransposeJob t{h->Cs, PH, h->CsT, Mt, Mt, H};
+    launch_transpose_multi(p, &t, 1, sd);
+  }
   {
     // Full slabs of the slab capacity and one remainder (one slab whenever the batch fits), two slab buffer pairs, over the dense rows of
     // the valid target positions.  The host sizes the slabs for all T * Bp rows; every kernel gets the
@@ -1133,7 +1148,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   phase_mark(h, "deferred attention gradients");
   // ---- second stream: everything that only needed the decoder's dgates and dpre -----------------------
   stream_after(h, sd, st);
-  launch_transpose(p, h->dPre, PH, h->dPreT, Mt, Mt, H, sd);
+  h->dw_tr.push_back({h->dPre, PH, h->dPreT, Mt, Mt, H});
   // encoder layer outputs, transposed: layer 0 -> Y0T (ld Ms); layer l >= 1 -> HstT + Bp (ld (S+1)Bp)
   auto encYT = [&](int l, int* ld) -> const char* {
     if (l == 0) { *ld = Ms; return h->Y0T; }
@@ -1161,7 +1176,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   launch_att_deferred(p, h->att_a, h->att_ds, h->dCs, H, HtAll, PH, S, T, Bp, H, h->dHs, h->dK, st);
   launch_gemm_nt(p, h->dK, H, h->Pw(h->off_Wa), H, Ms, H, H, h->dHs, nullptr, H, nullptr, 1, st);   // dHs += dK W_a^T
   stream_after(h, sd, st);
-  launch_transpose(p, h->dK, H, h->dKT, Ms, Ms, H, sd);
+  h->dw_tr.push_back({h->dK, H, h->dKT, Ms, Ms, H});
   {   // dW_a[r,c] = sum_i H_s[i,r] dK[i,c]
     int ld; const char* HsT = encYT(L - 1, &ld);
     h->dw_group.push_back(GemmProb{HsT, h->dKT, G + h->off_Wa, ld, Ms, H, H, H, Ms, 0});

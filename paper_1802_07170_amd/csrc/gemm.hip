@@ -372,7 +372,78 @@ double launch_mfma_rate(float* out, int blocks, int iters, hipStream_t st) {
   return (double)blocks * 4 /*wavefronts*/ * iters * 4.0 * (2.0 * 32 * 32 * 16);
 }
 
-// 64x64 tiles through LDS; reads and writes are both row-contiguous.
+// Several transposes in one launch.  A lane takes a block of 8 x 8 16-bit (4 x 4 32-bit) elements: it reads 16 bytes of each of its
+// rows, turns the block over in registers and writes 16 bytes of each column, so that 8 neighbouring lanes read 128
+// contiguous bytes and 8 others write such, with no LDS in between.  A wavefront takes 8 x 8 such blocks.  With `parts` the
+// column sums come along (a bias' gradient: the matrix is read once instead of twice): the rows go in TRANSPOSE_SPLITS shares, each
+// with its partial sums.  Memory-bound: four [3200, 4096] bf16 matrices with
+// their sums and a [3200, 1024] one 52 us (4.3 TB/s) + 5; one element per lane through LDS, a pass of its own for the sums and a
+// launch for each took 230 us.
+struct TransposeJobD { const void* in; void* out; float* parts; int ldin, ldout, R, C, nx, blocks, tpb; };
+struct TransposeJobs { TransposeJobD j[TRANSPOSE_MAX_JOBS]; };
+template <typename T>
+__global__ __launch_bounds__(256) void transpose_multi_kernel(TransposeJobs jobs) {
+  constexpr int NB = 16 / sizeof(T);                      // elements per side of a lane's block
+  constexpr int TILE = 8 * NB;
+  __shared__ float s_sum[4][TILE];
+  int blk = blockIdx.x, k = 0;
+  while (blk >= jobs.j[k].blocks) blk -= jobs.j[k++].blocks;
+  const TransposeJobD& job = jobs.j[k];
+  const int by = blk / job.nx, bx = blk - by * job.nx;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, rb = lane >> 3, cb = lane & 7;
+  const int c = bx * TILE + cb * NB;
+  const T* const in = (const T*)job.in;
+  T* const out = (T*)job.out;
+  float sum[NB];
+#pragma unroll
+  for (int e = 0; e < NB; ++e) sum[e] = 0.f;
+  for (int t = w; t < job.tpb; t += 4) {
+    const int r = (by * job.tpb + t) * TILE + rb * NB;
+    if (r >= job.R || c >= job.C) continue;               // (both are multiples of NB)
+    uint4 v[NB], o[NB];
+#pragma unroll
+    for (int e = 0; e < NB; ++e) v[e] = *reinterpret_cast<const uint4*>(in + (size_t)(r + e) * job.ldin + c);
+    if constexpr (NB == 8) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)                         // words of the rows: columns 2q, 2q + 1
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          const uint32_t a = (&v[2 * m].x)[q], b = (&v[2 * m + 1].x)[q];
+          (&o[2 * q].x)[m] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+          (&o[2 * q + 1].x)[m] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+        }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = make_uint4((&v[0].x)[q], (&v[1].x)[q], (&v[2].x)[q], (&v[3].x)[q]);
+    }
+#pragma unroll
+    for (int e = 0; e < NB; ++e) *reinterpret_cast<uint4*>(out + (size_t)(c + e) * job.ldout + r) = o[e];
+    if (job.parts) {
+#pragma unroll
+      for (int e = 0; e < NB; ++e)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t x = (&o[e].x)[q];
+          if constexpr (NB == 8) sum[e] += __uint_as_float(x << 16) + __uint_as_float(x & 0xffff0000u);
+          else sum[e] += __uint_as_float(x);
+        }
+    }
+  }
+  if (!job.parts) return;
+#pragma unroll
+  for (int e = 0; e < NB; ++e) {
+    float x = sum[e];
+#pragma unroll
+    for (int d = 8; d < 64; d <<= 1) x += __shfl_xor(x, d, 64);
+    if (rb == 0) s_sum[w][cb * NB + e] = x;
+  }
+  __syncthreads();
+  if (threadIdx.x < TILE && bx * TILE + (int)threadIdx.x < job.C)
+    job.parts[(size_t)by * job.C + bx * TILE + threadIdx.x] = (s_sum[0][threadIdx.x] + s_sum[1][threadIdx.x]) +
+                                                              (s_sum[2][threadIdx.x] + s_sum[3][threadIdx.x]);
+}
+
+// 64x64 tiles through LDS: sizes, pitches or addresses that 16-byte pieces do not fit.
 template <typename T>
 __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in, int ldin, T* __restrict__ out, int ldout,
                                                         int R, int C) {
@@ -392,13 +463,40 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
   }
 }
 
-void launch_transpose(int prec, const void* in, int ldin, void* out, int ldout, int R, int C, hipStream_t st) {
-  if (R <= 0 || C <= 0) return;
-  dim3 grid((C + 63) / 64, (R + 63) / 64);
+static void transpose_one(int prec, const TransposeJob& j, hipStream_t st) {
+  const dim3 grid((j.C + 63) / 64, (j.R + 63) / 64);
   if (prec)
-    hipLaunchKernelGGL(transpose_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)in, ldin, (bf16_t*)out, ldout, R, C);
+    hipLaunchKernelGGL(transpose_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)j.in, j.ldin, (bf16_t*)j.out, j.ldout, j.R, j.C);
   else
-    hipLaunchKernelGGL(transpose_kernel<float>, grid, dim3(256), 0, st, (const float*)in, ldin, (float*)out, ldout, R, C);
+    hipLaunchKernelGGL(transpose_kernel<float>, grid, dim3(256), 0, st, (const float*)j.in, j.ldin, (float*)j.out, j.ldout, j.R, j.C);
+}
+void launch_transpose_multi(int prec, const TransposeJob* jobs, int n, hipStream_t st) {
+  const int nb = prec ? 8 : 4, tile = 8 * nb;
+  TransposeJobs a;
+  int m = 0, blocks = 0;
+  auto go = [&]() {
+    if (m == 0) return;
+    for (int k = m; k < TRANSPOSE_MAX_JOBS; ++k) a.j[k] = TransposeJobD{nullptr, nullptr, nullptr, 0, 0, 0, 0, 1, 0, 0};
+    if (prec) hipLaunchKernelGGL(transpose_multi_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(transpose_multi_kernel<float>, dim3(blocks), dim3(256), 0, st, a);
+    m = 0; blocks = 0;
+  };
+  for (int k = 0; k < n; ++k) {
+    const TransposeJob& j = jobs[k];
+    if (j.R <= 0 || j.C <= 0) continue;
+    const bool pieces = ((uintptr_t)j.in | (uintptr_t)j.out) % 16 == 0 && (j.ldin | j.ldout | j.R | j.C) % nb == 0;
+    if (!pieces) {
+      transpose_one(prec, j, st);
+      if (j.parts) launch_colsum_parts(prec, j.in, j.ldin, j.R, j.C, j.parts, st);
+      continue;
+    }
+    const int tiles = (j.R + tile - 1) / tile, tpb = j.parts ? (tiles + TRANSPOSE_SPLITS - 1) / TRANSPOSE_SPLITS : 4;
+    const int nx = (j.C + tile - 1) / tile, ny = j.parts ? TRANSPOSE_SPLITS : (tiles + tpb - 1) / tpb;
+    a.j[m++] = TransposeJobD{j.in, j.out, j.parts, j.ldin, j.ldout, j.R, j.C, nx, nx * ny, tpb};
+    blocks += nx * ny;
+    if (m == TRANSPOSE_MAX_JOBS) go();
+  }
+  go();
 }
 
 }  // namespace cmt

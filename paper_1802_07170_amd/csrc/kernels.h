@@ -36,8 +36,11 @@ struct GemmProb { const void* A; const void* B; float* C; int lda, ldb, ldc, M, 
 void launch_gemm_nt_group(int prec, const GemmProb* probs, int n, hipStream_t st, float* split_scratch, size_t split_scratch_floats,
                           int wg_cap = 0);         // (wg_cap as above)
 double launch_mfma_rate(float* out, int blocks, int iters, hipStream_t st);
-// out[C,R] = in[R,C]^T for T matrices (ldin, ldout in elements).
-void launch_transpose(int prec, const void* in, int ldin, void* out, int ldout, int R, int C, hipStream_t st);
+// out[C,R] = in[R,C]^T for T matrices (ldin, ldout in elements); with parts (TRANSPOSE_SPLITS rows of C floats) also partial sums
+// of the columns of `in`.  Any number of them.
+struct TransposeJob { const void* in; int ldin; void* out; int ldout; int R, C; float* parts = nullptr; };
+constexpr int TRANSPOSE_MAX_JOBS = 24, TRANSPOSE_SPLITS = 16;
+void launch_transpose_multi(int prec, const TransposeJob* jobs, int n, hipStream_t st);
 
 // ---- ce.hip ------------------------------------------------------------------------------------
 // Eq. 1 for a slab of M <= pitch rows (all row pointers at the slab's first row; pitch = row capacity of the
@@ -386,8 +389,12 @@ void launch_copy2d_multi(const CopyJob* jobs, int n, hipStream_t st);
 void launch_copy2d_T(int prec, const void* src, int lds, void* dst, int ldd, int rows, int cols, hipStream_t st);
 void launch_add_f32(float* dst, const float* src, size_t n, hipStream_t st);          // dst += src
 void launch_sum_parts(const float* parts, int nparts, size_t n, float* out, hipStream_t st);
-// db[n] = sum_m dG[m, n] over M rows of a T matrix [M, N].
-void launch_colsum(int prec, const void* dG, int ld, int M, int N, float* scratch /*[16*N]*/, float* db, hipStream_t st);
+// Several of these, nparts rows each, in one launch (at most SUM_PARTS_MAX_JOBS).
+struct SumPartsJob { const float* parts; size_t n; float* out; };
+constexpr int SUM_PARTS_MAX_JOBS = 16;
+void launch_sum_parts_multi(const SumPartsJob* jobs, int n, int nparts, hipStream_t st);
+// Partial column sums of a T matrix [M, N]: TRANSPOSE_SPLITS rows of N floats.
+void launch_colsum_parts(int prec, const void* dG, int ld, int M, int N, float* parts, hipStream_t st);
 // p <- p - lr g; skipped entirely while *flags != 0 (flags may be null)
 // bf16_copy (may be null): the bf16 working copy of p, rewritten in the same pass
 void launch_sgd(float* p, const float* g, size_t n, float lr, const int* flags, void* bf16_copy, hipStream_t st);
