@@ -8,7 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcytonmt_hip.so")
-SOURCES = ["api.hip", "gemm.hip", "ce.hip", "step.hip", "recur.hip", "loop.hip", "misc.hip", "beam.hip"]
+SOURCES = ["api.hip", "gemm.hip", "ce.hip", "step.hip", "recur.hip", "loop.hip", "loop_dec.hip", "misc.hip", "beam.hip"]
 # -amdgpu-kernarg-preload-count: the leading kernel arguments (as many as fit into the user SGPRs, at most 14
 # dwords) are delivered in registers at wavefront start instead of being fetched from the argument buffer, which
 # takes about 0.6 us off the head of every kernel of the recurrences' launch chains.  Kernels keep the ordinary

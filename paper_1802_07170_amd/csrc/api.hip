@@ -823,6 +823,39 @@ void enqueue_dec_loop_fwd(cmt_handle* h, int S, int T) {
   launch_loop_fwd(p, a, L, T, Bp, H, S, h->seq, st);
 }
 
+// All steps of greedy decoding, on the projected source rows.
+void enqueue_greedy_loop(cmt_handle* h, int B, int S, int T, int eos, int32_t* out_ids, int32_t* out_len) {
+  const cmt_config& c = h->cfg;
+  const int p = h->prec, E = c.emb_dim, H = c.hidden, L = c.layers, Bp = h->Bp;
+  const size_t esz = h->esz, slot = loop_slot_elems(Bp, H);
+  hipStream_t st = h->st;
+  LoopFwdArgs a{};
+  std::vector<FillJob> z;
+  for (int l = 0; l < L; ++l) {
+    LD& e = h->dec[l];
+    LoopFwdLayer& d = a.l[l];
+    d.W = e.W; d.ldw = e.Kin + H; d.wx_off = l == 0 ? E : 0; d.wh_off = e.Kin; d.bias = h->params + e.b_off;
+    d.H = e.Hst; d.ldh = e.ph; d.C = e.Cst; d.X = e.XH;
+    add_empty(z, e.XH, (T + 1) * slot, esz);
+  }
+  a.len = h->len_s; a.Wc = h->Pw(h->off_Wc) + (size_t)H * esz; a.ldwc = 2 * H;
+  a.K = h->Kmat; a.P = h->PmatT; a.Pg = h->dK; a.scores = h->att_s;
+  a.Ho = h->HoBuf; a.ldho = h->PH; a.XO = h->HoFeedX;
+  a.ticket = h->tickets + LOOP_TICKET_FWD;
+  LoopTokens& t = a.t;
+  t.table = h->Pw(h->off_Etgt); t.emb = E; t.fm = h->WoF ? 1 : 0; t.Wo = h->WoF ? h->WoF : h->Pw(h->off_Wo);
+  t.Bo = h->params + h->off_Bo; t.V = c.tgt_vocab;
+  t.part = (uint64_t*)h->wcp; t.tok = (int*)((char*)h->wcp + (size_t)4 * H * Bp);   // (of 64 H Bp bytes)
+  t.B = B; t.bos = c.bos_id; t.eos = eos; t.pad = c.pad_id; t.out_ids = out_ids; t.out_len = out_len;
+  add_empty(z, h->HoFeedX + slot * esz, T * slot, esz);
+  add_empty(z, h->att_s, (size_t)T * Bp * S, 4);
+  add_empty(z, h->wcp, (size_t)H * Bp + 4 * Bp, 4);
+  add_fill(z, h->HoBuf, (size_t)Bp * h->PH, esz);              // (H_o before the first step, for the form without waits)
+  launch_fill_multi(z.data(), (int)z.size(), st);
+  launch_loop_columns(p, h->PmatT, h->dK, S, Bp, H, st);
+  launch_loop_decode(p, a, L, T, Bp, H, S, h->seq, st);
+}
+
 // All target positions of the backward pass.
 void enqueue_dec_loop_bwd(cmt_handle* h, int S, int T) {
   const cmt_config& c = h->cfg;
@@ -1521,16 +1554,20 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
   WideSection wide(h);
   wide.open();
   enqueue_encoder(h, S, &Hs, &ldHs);
-  wide.close();
   const bool proj = h->att_proj && Bp < 256;
   if (proj) launch_gemm_nt(p, Hs, ldHs, h->Pw(h->off_Wc), 2 * H, S * Bp, H, H, nullptr, h->PmatT, H, nullptr, 0, st);
   launch_dec_init(B, Bp, max_len, c.bos_id, c.pad_id, h->dec_tok, h->dec_done, out_ids_dev, out_len_dev, h->dec_mask, st);
-  launch_fill_T(p, h->xcat, (size_t)Bp * h->ldxcat, st);              // H_o^{<-1>} = 0
+  const bool loop = proj && dec_loop(h, S) && loop_decode_fits(p, L, Bp, H, S, V, h->seq);
+  if (loop) enqueue_greedy_loop(h, B, S, max_len, eos_id, out_ids_dev, out_len_dev);
+  wide.close();
   const bool fm0 = h->xcatF && h->dec[0].fm;                          // bottom layer on fragment-major operands
-  if (fm0) launch_fill_T(p, h->xcatF, (size_t)Bp * (E + H), st);
-  // the first step's input embedding; every later one is written by the arg-max kernel of the step before
-  launch_dec_embed(p, h->Pw(h->off_Etgt), E, h->dec_tok, B, Bp, h->xcat, h->ldxcat, st, fm0 ? h->xcatF : nullptr, (E + H) >> 5);
-  for (int j = 0; j < max_len; ++j) {
+  if (!loop) {
+    launch_fill_T(p, h->xcat, (size_t)Bp * h->ldxcat, st);            // H_o^{<-1>} = 0
+    if (fm0) launch_fill_T(p, h->xcatF, (size_t)Bp * (E + H), st);
+    // the first step's input embedding; every later one is written by the arg-max kernel of the step before
+    launch_dec_embed(p, h->Pw(h->off_Etgt), E, h->dec_tok, B, Bp, h->xcat, h->ldxcat, st, fm0 ? h->xcatF : nullptr, (E + H) >> 5);
+  }
+  for (int j = loop ? max_len : 0; j < max_len; ++j) {
     for (int l = 0; l < L; ++l) {
       LD& e = h->dec[l];
       LstmFwdDir d;

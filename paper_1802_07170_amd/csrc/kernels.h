@@ -318,6 +318,17 @@ struct LoopFwdLayer {
   void* Y; void* XY;                       // the states after dropout, rows [T, Bp, ldh] and T slots; null: none
   DropSpec drop;                           // position 0 (see drop_step)
 };
+// Greedy decoding by the same loop: the bottom layer contracts the token's embedding as well (the first `emb` columns of its
+// weights; its bias is set, gx is not used, and neither are G, Y, HoD and `a`), and the best token of a step feeds the next one.
+struct LoopTokens {
+  const void* table; int emb;              // T* [V, emb]
+  const void* Wo;                          // T*: rows [V, H], or fragment-major (fm_offset) with fm set
+  int fm; const float* Bo; int V;
+  uint64_t* part;                          // [2, H / 4, Bp] (value, token), filled with 0xff bytes
+  int* tok;                                // [4, Bp] tokens of the positions, filled with 0xff bytes
+  int B, bos, eos, pad;
+  int32_t* out_ids; int32_t* out_len;      // [B, T], [B]: filled with pad and 0
+};
 struct LoopFwdArgs {
   LoopFwdLayer l[LOOP_MAX_LAYERS];
   const float* gx;                         // [T, Bp, 4H] the bottom layer's batched input part
@@ -331,6 +342,7 @@ struct LoopFwdArgs {
   void* XO;                                // T + 1 slots of H_o as fed; slot 0 is not read
   DropSpec drop_o; unsigned long long drop_step;
   int* ticket; int wait_ticks;             // as in SeqFwdArgs (the first word is not used)
+  LoopTokens t;
 };
 struct LoopBwdLayer {
   const void* Wt; int ldw, x_row, h_row;   // T* [.., ldw], rows = input columns of W, contiguous over the 4H gate rows: the first
@@ -358,6 +370,9 @@ struct LoopBwdArgs {
 };
 // Whether the loop runs as one launch on this device.
 bool loop_fits(int prec, int L, int Bp, int H, int S, const SeqRun& run);
+// Whether greedy decoding does: not for more than 4 tiles of sentences per group, nor for vocabularies that are long for the width.
+bool loop_decode_fits(int prec, int L, int Bp, int H, int S, int V, const SeqRun& run);
+void launch_loop_decode(int prec, const LoopFwdArgs& args, int L, int T, int Bp, int H, int S, const SeqRun& run, hipStream_t st);
 // dst [H / 4, Bp, S, 4] <- src [S, Bp, H]
 void launch_loop_columns(int prec, const void* src, void* dst, int S, int Bp, int H, hipStream_t st);
 void launch_loop_bwd(int prec, const LoopBwdArgs& args, int L, int T, int Bp, int H, int S, const SeqRun& run, hipStream_t st);

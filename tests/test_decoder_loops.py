@@ -178,3 +178,39 @@ def test_loops_of_several_streams_and_threads():
         np.testing.assert_array_equal(g, want)
     for tr, _ in trainers:
         tr.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec,B,S,T,H,E,L,V", [(0, 1, 5, 7, 64, 40, 1, 1000), (0, 40, 9, 6, 336, 72, 3, 136), (0, 64, 20, 9, 256, 256, 2, 5000),
+                                                (0, 128, 12, 5, 512, 16, 4, 2056), (1, 17, 9, 9, 48, 24, 2, 136), (1, 64, 30, 8, 1024, 1160, 4, 1016),
+                                                (1, 3, 9, 8, 528, 2048, 2, 8008), (1, 100, 9, 8, 512, 512, 1, 2000), (0, 5, 9, 8, 16, 8, 1, 16000)])
+@pytest.mark.parametrize("give_up", [False, True], ids=["together", "waits given up"])
+def test_greedy_loop_gives_the_tokens_of_the_launches(prec, B, S, T, H, E, L, V, give_up, monkeypatch):
+    """The whole search in one launch against a launch per layer and step (CMT_DEC_LOOP=0); the last shape's vocabulary is too long
+    for its width and takes the launches both times.  Weights of twice a layer's usual scale make the tokens vary (27 - 572 different
+    ones over these shapes); the end token is one that ends some sentences early.  In fp32 all tokens agree; with 16-bit operands a
+    near tie may turn, and with it the rest of that sentence.  The two differ in the order of 32-bit sums and in the few 16-bit roundings
+    that this turns, so fewer sentences may part than 16-bit operands make part from 32-bit ones."""
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=128, tgt_vocab=V, emb=E, hidden=H, layers=L)
+    params = I.make_params(cfg, 11, 3.4 / np.sqrt(H))
+    params["E_tgt"] *= np.sqrt(H) / 2
+    params["E_src"] *= np.sqrt(H) / 2
+    src, src_len, _, _ = _batch(cfg, B, S, T, seed=B)
+    res, eos = {}, 3
+    for mode in ("any end", "fp32", "0", "1"):
+        monkeypatch.setenv("CMT_DEC_LOOP", "1" if mode == "1" else "0")
+        if mode == "1" and give_up:
+            monkeypatch.setenv("CMT_RECUR", "2")
+        tr = binding.Trainer(cfg, B, S, T, precision=0 if mode == "fp32" else prec)
+        tr.set_params(I.flatten(params, cfg))
+        for _ in range(2):                                # (the second time on the memory that the first left behind)
+            ids, lens = tr.greedy_decode(src, src_len, T, eos_id=eos)
+            res[mode] = np.array(ids), np.array(lens)
+        tr.close()
+        if mode == "any end":
+            eos = int(np.array(ids)[0, 2])
+    same, near = ((res["0"][0] == res[m][0]).all(axis=1) for m in ("1", "fp32"))
+    assert (~same).sum() <= (~near).sum()
+    np.testing.assert_array_equal(res["0"][1][same], res["1"][1][same])
+    assert len(np.unique(res["0"][0])) > 2 and (res["0"][1] < T).any()
