@@ -888,7 +888,11 @@ void enqueue_dec_loop_bwd(cmt_handle* h, int S, int T) {
   launch_loop_columns(p, h->Kmat, h->dKT, S, Bp, H, st);
   launch_loop_bwd(p, a, L, T, Bp, H, S, h->seq, st);
   // dC_s of all positions (the deferred gradients read it): dpre W_c1
-  launch_gemm_nt(p, h->dPre, h->PH, h->WcT, H, T * Bp, H, H, h->dCs, nullptr, H, nullptr, 0, st);
+  // (fp32: a quarter of k at a time.  Summed up in one go it made the encoder's gradients 10 - 30 % worse against 64 bits than the launch per
+  // position, whose wavefronts share k, did: 512 units, 2 layers, error of the upper encoder layer's dW 5.0e-7 instead of 3.9e-7, 3.8e-7 so)
+  for (int k = 0, kc = p ? H : std::max(round_up(H, 64) / 4, 32); k < H; k += kc)
+    launch_gemm_nt(p, (const char*)h->dPre + k * esz, h->PH, (const char*)h->WcT + k * esz, H, T * Bp, H, std::min(kc, H - k), h->dCs, nullptr, H,
+                   nullptr, k > 0, st);
 }
 
 int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, const int32_t* tgt_ids,
