@@ -41,13 +41,15 @@
 
 namespace cmt {
 
-// s_sleep units (64 clocks) before a workgroup looks for its neighbours' results: one value each for every width.  Whole passes
-// over 150 positions x 3 layers, us, with 16 | 20 | 28 | 36 units forward (evaluation; bf16, 64 sentences): hidden size 64
-// 581 | 624 | 715 | 800, 128 654 | 663 | 764 | 855, 512 1208 | 1041 | 996 | 1087, 1024 1871 | 1814 | 1595 | 1492; fp32, 512
-// 3054 | 2988 | 2493 | 2541; two tiles of sentences (128), 512 1565 | 1409 | 1261 | 1292, 1024 3870 | 3510 | 3393 | 2933.  24 | 36 |
-// 42 | 50 units backward (training step): 64 1475 | 1598 | 1675 | 1786, 256 (32 sentences) 1925 | 1762 | 1822 | 1923, 512
-// 3285 | 3039 | 2901 | 2913, 1024 5439 | 5054 | 4869 | 4847.  So the best value grows with the width.
-constexpr int RECUR_NAP_FWD = 20, RECUR_NAP_FWD2 = 28, RECUR_NAP_BWD = 42;
+// s_sleep units (64 clocks) before a workgroup looks for its neighbours' results.  They come the later the more bytes of state
+// a workgroup has to read and multiply, and a look that comes too early fetches lines that it has to fetch again.  Whole passes
+// over 150 positions x 3 layers, us, with 16 | 20 | 24 | 28 | 36 units forward (evaluation; bf16, 64 sentences): hidden size 64
+// 581 | 624 | 658 | 715 | 800, 128 654 | 663 | 711 | 764 | 855, 512 1208 | 1041 | 963 | 996 | 1087, 1024 1871 | 1814 | 1745 | 1595 | 1492; fp32, 64
+// (8 sentences) 1023 | 909 | 889 | 918 | 1013, 512 3054 | 2988 | 2739 | 2493 | 2541; two tiles of sentences (128), 512 1565 | 1409 | 1316 | 1261 | 1292,
+// 1024 3870 | 3510 | 3373 | 3393 | 2933.  24 | 36 | 42 | 50 units backward (training step): 64 1475 | 1598 | 1675 | 1786, 256 (32
+// sentences) 1925 | 1762 | 1822 | 1923, 512 3285 | 3039 | 2901 | 2913, 1024 5439 | 5054 | 4869 | 4847.  The lines below follow these minima.
+static int recur_nap_fwd(int elem, int bt, int Hh) { return elem * bt == 2 ? 16 + std::min(Hh, 1024) * 20 / 1024 : 20 + std::min(Hh, 1024) * 16 / 1024; }
+static int recur_nap_bwd(int Hh) { return 24 + std::min(Hh, 512) * 24 / 512; }
 
 // Where the four gate sums of (sentence, unit 4 rt + q of the workgroup) lie in a 16-byte-grained tile of partial
 // sums: written sentence by sentence, read unit by unit, both free of bank conflicts.
@@ -518,7 +520,7 @@ static int seq_wait(const SeqRun& run) { return run.mode == SEQ_RUN_GIVE_UP ? 0 
 template <typename T, int KS, int NK, int RT, int NE>
 static void seq_bwd_go(const SeqPlan& p, const SeqBwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
   hipLaunchKernelGGL((lstm_seq_bwd_kernel<T, KS, NK, RT, NE>), dim3(p.groups * p.group), dim3(64 * (KS + NE)), 0, st, a, L, Bp, Hh, ndir,
-                     RECUR_NAP_BWD);
+                     recur_nap_bwd(Hh));
 }
 void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& args, int ndir, int L, int Bp, int Hh, const SeqRun& run, hipStream_t st) {
   const SeqPlan p = seq_bwd_plan(prec, ndir, Bp, Hh);
@@ -548,7 +550,7 @@ void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& args, int ndir, int L, int 
 template <typename T, int KS, int NK, int LK, int BT, int NE>
 static void seq_fwd_go(const SeqPlan& p, const SeqFwdArgs& a, int ndir, int L, int Bp, int Hh, hipStream_t st) {
   hipLaunchKernelGGL((lstm_seq_fwd_kernel<T, KS, NK, LK, 4, BT, NE>), dim3(p.groups * p.group), dim3(64 * (KS + NE)), 0, st, a, L, Bp, Hh,
-                     ndir, BT == 1 ? RECUR_NAP_FWD : RECUR_NAP_FWD2);
+                     ndir, recur_nap_fwd(sizeof(T), BT, Hh));
 }
 void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& args, int ndir, int L, int Bp, int Hh, const SeqRun& run, hipStream_t st) {
   const SeqPlan p = seq_fwd_plan(prec, ndir, Bp, Hh);
