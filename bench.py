@@ -3,7 +3,7 @@
 python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload medium] [--no-cpu-baseline]
 
 Prints ONE JSON line: target tokens/s of the whole step with inputs resident in HBM, the roofline
-figures of the dominant kernel (measured live with HIP events), and the CPU oracle timed on a
+figures of the decoder's layer step kernel (measured live with HIP events), and the CPU oracle timed on a
 bounded sample of the same workload."""
 from __future__ import annotations
 
@@ -162,9 +162,10 @@ def main():
     tr.set_regularization(0.0, 0.0, 0)
     tr.train_step_async(dev)
     torch.cuda.synchronize()
-    # one of the two dominant kernels of the step (each a tenth of the kernel time in the rocprofv3 trace under
-    # profiles/): the fused decoder LSTM step.  HBM carries its weights once; what it waits for is the
-    # L2 -> CU traffic of weights plus re-read activations (see the summaries under profiles/).
+    # the decoder layer step of the launch-per-position form, replayed alone: what the timed step runs where its shapes are beyond
+    # the one-launch loops (loop_fwd_kernel, loop_bwd_kernel, which wait for exchanges between workgroups, not for HBM, and which
+    # the traces under profiles/ hold).  HBM carries its weights once; what it waits for is the L2 -> CU traffic of weights plus
+    # re-read activations (see the summaries under profiles/).
     us, nbytes = tr.time_kernel("lstm_fwd_dec", 400)
     achieved = nbytes / (us * 1e-6) / 1e9
     out["roofline"] = {"kernel": "lstm_fwd_kernel (decoder layer step: gate GEMM + fused cell)", "bound": "hbm",

@@ -12,8 +12,8 @@
 // 3.7: its state and its input are 128 KB each that every CU reads through its L1 at no more than 64 bytes a clock (1.0 - 1.6 us each
 // measured, 0.85 at that rate), then 0.65 until the sums have met, 0.5 the cells, 0.7 until a store can be seen.  So the recurrent
 // half is read while the layer below is still being exchanged.  Narrow layers are bound by the exchange alone: width 512, 2 layers,
-// 32 sentences 9 us a position (21).  Backward 38 us (54) and 15 us (24): a layer is two exchanges there.
-// Whole steps, launch per step | one launch, ms: medium 8.33 | 6.45, attn 7.68 | 5.10, small (fp32) 8.99 | 6.45, 336 units x 3 layers, 23
+// 32 sentences 9 us a position (21).  Backward 36 us (54) and 15 us (24): a layer is two exchanges there.
+// Whole steps with everything else alike, launch per step | one launch, ms: medium 8.33 | 6.45, attn 7.68 | 5.10, small (fp32) 8.99 | 6.45, 336 units x 3 layers, 23
 // sentences 2.99 | 1.92, large 21.9 | 20.3; forward-only evaluation of medium 3.17 | 2.20.
 //
 // The waits are bounded, and a launch behind each loop makes it again without waits where one was given up, as the encoder's

@@ -23,9 +23,9 @@
 //
 // What a position costs within a training step (bf16, us; a launch per position cost 8.5 - 9, upper layers forward 5.6 of a
 // shared one).  Forward: width 256 x two directions, 32 sentences 1.2; 512, 32 sentences 1.4; 512 x two directions, 64 and 128
-// sentences 1.9 and 3.3; 1024, 64 and 128 sentences 3.0 and 6.3.  Backward, beside the second stream's GEMMs: 256 x two
-// directions, 32 sentences 2.2; 512, 32 sentences 2.7; 512 x two directions, 64 and 128 sentences 6.4 and 10.0; 1024, 64
-// sentences 3.6 - 4.8, 128 sentences 4.8 - 14.6 (median 5.6; the first of a step's layers, which runs beside the decoder's
+// sentences 1.6 and 3.4; 1024, 64 and 128 sentences 2.1 and 4.7.  Backward, beside the second stream's GEMMs: 256 x two
+// directions, 32 sentences 2.0; 512, 32 sentences 2.5; 512 x two directions, 64 and 128 sentences 3.6 and 4.0; 1024, 64
+// sentences 3.6 - 5.3 (median 3.7), 128 sentences 4.0 - 12 (median 4.7; the first of a step's layers, which runs beside the decoder's
 // weight gradients, takes longest).  About 0.5 of it is the store on its way to memory, 0.5 the load, the rest contraction,
 // reduction and cell; at 128 sentences also the volume.
 #include <stdlib.h>
