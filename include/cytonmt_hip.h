@@ -128,7 +128,8 @@ int cmt_eval_loss(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* src_
 
 /* cmt_eval_loss for callers that cannot provide (or allocate) a workspace for the call: code under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation.  Same arguments, same result
- * (the same kernels in the same order), but every intermediate — including the working copies of the
+ * (the same kernels in the same order; only a shape of 16 units or of one position that misses the array's
+ * size by a few KB otherwise takes kernels that add in another order), but every intermediate — including the working copies of the
  * parameters, which are rebuilt on each call — lives in one array of CMT_STATIC_SCRATCH_BYTES that is
  * part of the library's device code, laid out for exactly this call's B, S and T; the handle's
  * workspace, its last step's intermediates and the gradient buffer are untouched.  The call allocates

@@ -32,6 +32,9 @@ using namespace cmt;
 
 namespace {
 
+// Which of the decoder's whole loops a workspace has slots for: none, the forward one without dropout (an evaluation), all.
+enum { LOOP_SLOTS_NONE = 0, LOOP_SLOTS_EVAL = 1, LOOP_SLOTS_ALL = 2 };
+
 struct ParamInfo { std::string name; int64_t rows, cols; size_t off; };
 
 // one LSTM (layer, direction)
@@ -145,6 +148,7 @@ struct cmt_handle {
   int loop = 1;                         // the decoder's loops as one launch each (env CMT_DEC_LOOP); its slots, where the
                                         // layers have no fragment-major copies that can serve (LD::HstF, YdF, dGF)
   char* HoFeedX = nullptr; char* dPreX = nullptr;
+  int loop_slots = LOOP_SLOTS_ALL;      // what the layout holds for them
   bool capturing = false;               // the pass being enqueued is captured into a graph
   char* dzs = nullptr; char* dzTs = nullptr; float* dbo_parts = nullptr;
   std::vector<GemmProb> dw_group;       // weight-gradient GEMMs collected for one grouped launch (flush_dw_group), the transposes
@@ -260,7 +264,8 @@ size_t layout(cmt_handle* h, char* base) {
   const size_t PH = h->PH;
   h->Pc = c.precision ? a.take(h->nparams * esz) : (char*)h->params;
   // (the whole loops take batches up to LOOP_MAX_BATCH; Bl: the rows of their slots)
-  const bool loops = h->loop && L <= LOOP_MAX_LAYERS;
+  const bool loops = h->loop && h->loop_slots != LOOP_SLOTS_NONE && L <= LOOP_MAX_LAYERS;
+  const bool loop_all = loops && h->loop_slots == LOOP_SLOTS_ALL;
   const size_t Bl = std::min(Bp, LOOP_MAX_BATCH);
   auto ld_alloc = [&](LD& d, int Kin, int Hh, int Lm, bool gx, int Kstep, bool encoder) {
     d.Kin = Kin; d.Hh = Hh; d.ph = Hh + ACT_PAD; d.pg = 4 * Hh + ACT_PAD;
@@ -286,15 +291,21 @@ size_t layout(cmt_handle* h, char* base) {
     // The recurrences' exchange slots are filled afresh by every pass and take no memory of their own: the states' lie
     // where the gate gradients are transposed to after the backward pass, the gate gradients' where the forward pass had
     // its input parts.
-    // (The decoder's whole loops likewise, where there are no fragment-major copies that can serve.)
+    // (The decoder's whole loops likewise, where there are no fragment-major copies that can serve.  An evaluation's has no use
+    // for the second half, and the bottom layer's takes the fed H_o.)
     const size_t row = loop_slot_elems(1, Hh), Ml = (size_t)Lm * Bl;
-    const size_t slots = encoder ? seq_exchange_elems(Lm + 1, Bp, Hh) : !loops ? 0 : std::max(d.fm ? 0 : (2 * Ml + Bl) * row, d.fmb ? 0 : Ml * 4 * row);
+    const bool eval_feed = !loop_all && &d == &h->dec[0];
+    const size_t fwd_slots = d.fm ? 0 : loop_all ? (2 * Ml + Bl) * row : (eval_feed ? 2 : 1) * (Ml + Bl) * row;
+    const size_t slots = encoder ? seq_exchange_elems(Lm + 1, Bp, Hh) : !loops ? 0 : std::max(fwd_slots, d.fmb || !loop_all ? 0 : Ml * 4 * row);
     d.dGT = a.take(std::max(M * 4 * Hh, slots) * esz);
     if (encoder) { d.X = d.dGT; d.XG = (char*)d.Gx; }
     else if (loops) {
+      char* const second = d.dGT + (base ? (Ml + Bl) * row * esz : 0);
       d.XH = d.fm ? d.HstF : d.dGT;
-      d.XY = d.fm ? d.YdF : d.dGT + (base ? (Ml + Bl) * row * esz : 0);
-      d.XD = d.fmb ? d.dGF : d.dGT;
+      if (loop_all) {
+        d.XY = d.fm ? d.YdF : second;
+        d.XD = d.fmb ? d.dGF : d.dGT;
+      } else if (eval_feed) h->HoFeedX = second;
     }
     d.HstT = a.take((M + Bp) * Hh * esz);
     if (!encoder) {
@@ -331,16 +342,18 @@ size_t layout(cmt_handle* h, char* base) {
   h->Pmat = (float*)a.take(Ms * H * 4); h->PmatT = a.take(Ms * H * esz);
   h->dHs = (float*)a.take(Ms * H * 4); h->dK = a.take(Ms * H * esz); h->dKT = a.take(Ms * H * esz);
   // (until the encoder's backward pass the decoder's backward loop exchanges its scores there, in dYa and on into dXs)
-  const size_t loop_scores = loops ? (size_t)Tm * Bl * std::min(Sm, LOOP_MAX_SRC) : 0;
+  const size_t loop_scores = loop_all ? (size_t)Tm * Bl * std::min(Sm, LOOP_MAX_SRC) : 0;
   h->dYa = (float*)a.take(std::max(Ms * H, loop_scores > Ms * E ? loop_scores - Ms * E : 0) * 4);
   h->dXs = (float*)a.take(Ms * E * 4);
   // target side
   h->Xt = a.take(Mt * E * esz); h->XtT = a.take(Mt * E * esz);
   h->mask_t = (float*)a.take(Mt * 4); h->tok_t = (int32_t*)a.take(Mt * 4); h->labels = (int32_t*)a.take(Mt * 4);
   h->len_t = (int32_t*)a.take((size_t)Bp * 4);
-  const size_t loop_row = loops ? loop_slot_elems(1, H) * esz : 0;     // bytes of a row in a loop's slots
+  const size_t loop_row = loop_all ? loop_slot_elems(1, H) * esz : 0;  // bytes of a row in a loop's slots
   h->HoBuf = a.take((Mt + Bp) * PH * esz); h->HoBufT = a.take(std::max((Mt + Bp) * H * esz, ((size_t)Tm + 1) * Bl * loop_row));
-  h->HoFeedX = !loops ? nullptr : h->HoFeedF ? h->HoFeedF : h->HoBufT;   // (transposed after the forward loop)
+  if (!loops) h->HoFeedX = nullptr;
+  else if (h->HoFeedF) h->HoFeedX = h->HoFeedF;
+  else if (loop_all) h->HoFeedX = h->HoBufT;                             // (transposed after the forward loop)
   h->HoDrop = a.take((Mt + Bp) * PH * esz);
   h->ldxcat = E + H + ACT_PAD;
   h->xcat = a.take((size_t)Bp * h->ldxcat * esz);
@@ -364,7 +377,7 @@ size_t layout(cmt_handle* h, char* base) {
   h->Cs = a.take(Mt * PH * esz); h->CsT = a.take(Mt * H * esz);
   h->att_a = (float*)a.take(Mt * Sm * 4); h->att_ds = (float*)a.take(Mt * Sm * 4);
   h->dCs = (float*)a.take(std::max(Mt * H * 4, (size_t)Tm * Bl * loop_row));
-  h->dPreX = !loops ? nullptr : h->dPreF ? h->dPreF : (char*)h->dCs;     // (dC_s is made after the backward loop)
+  h->dPreX = !loop_all ? nullptr : h->dPreF ? h->dPreF : (char*)h->dCs;  // (dC_s is made after the backward loop)
   h->dots = (float*)a.take((size_t)Bp * Sm * 4);
   h->att_s = (float*)a.take(Mt * Sm * 4);
   h->dPre = a.take(Mt * PH * esz); h->dPreT = a.take(Mt * H * esz);
@@ -1470,9 +1483,16 @@ int cmt_eval_loss_static(cmt_handle* h, const int32_t* src_ids_dev, const int32_
   cmt_handle v = *h;
   v.cfg.max_batch = B; v.cfg.max_src_len = S; v.cfg.max_tgt_len = T;
   v.Bpm = round_up(B, 16);
-  v.loop = 0;                                        // (their slots would take room here, and the call may be under capture)
   v.phase_timing = 0; v.phase_ev.clear(); v.phase_name.clear();
-  const size_t need = layout(&v, nullptr);
+  // The kernels of cmt_eval_loss in their order, so that the losses are equal bit by bit.  (The decoder's loop has its slots in
+  // buffers that are there already; for one position, or 16 units, one of them is a few KB larger, and a shape that just fits
+  // without those gets the launches per position.)
+  v.loop_slots = LOOP_SLOTS_EVAL;
+  size_t need = layout(&v, nullptr);
+  if (need > (size_t)CMT_STATIC_SCRATCH_BYTES) {
+    v.loop_slots = LOOP_SLOTS_NONE;
+    need = layout(&v, nullptr);
+  }
   if (need > (size_t)CMT_STATIC_SCRATCH_BYTES) {
     char msg[160];
     snprintf(msg, sizeof msg, "this shape needs %zu bytes of scratch, the static buffer holds %zu", need,

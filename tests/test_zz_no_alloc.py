@@ -65,6 +65,25 @@ def test_static_eval_takes_shapes_that_just_fit(H, E, L, length, prec):
         tr.close()
 
 
+@pytest.mark.parametrize("H,E,L,B,S,T", [(128, 64, 2, 20, 12, 9), (80, 64, 3, 40, 9, 6), (48, 24, 4, 17, 20, 5), (256, 64, 1, 16, 6, 3),
+                                         (16, 8, 2, 33, 7, 7), (64, 32, 2, 70, 5, 1)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_static_eval_is_the_workspace_eval_bit_by_bit(H, E, L, B, S, T, prec):
+    """Several networks per shape, at weights of a scale where another order of the sums shows in the loss."""
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=504, tgt_vocab=504, emb=E, hidden=H, layers=L)
+    recipe = dict(cfg, ids="zipf", batch=B, seed=H)
+    batch = I.make_batch(recipe, len_range=(max(1, S // 2), S))[:2] + I.make_batch(recipe, len_range=(max(1, T // 2), T))[2:]
+    tr = binding.Trainer(cfg, B, S, T, precision=prec)
+    try:
+        dev = tr.upload_batch(*batch)
+        for seed in range(6):
+            tr.init_params(seed, 4.0 / H ** 0.5)
+            assert tr.eval_loss_static(dev) == tr.eval_loss(dev), seed
+    finally:
+        tr.close()
+
+
 def test_static_eval_refuses_a_shape_beyond_the_array():
     from paper_1802_07170_amd import binding
     c = I.CONFIGS["small"]                                       # vocabulary 32000: the slab buffers alone exceed the array
