@@ -263,8 +263,9 @@ size_t layout(cmt_handle* h, char* base) {
   h->PH = H + ACT_PAD;
   const size_t PH = h->PH;
   h->Pc = c.precision ? a.take(h->nparams * esz) : (char*)h->params;
-  // (the whole loops take batches up to LOOP_MAX_BATCH; Bl: the rows of their slots)
-  const bool loops = h->loop && h->loop_slots != LOOP_SLOTS_NONE && L <= LOOP_MAX_LAYERS;
+  // (The whole loops take batches up to LOOP_MAX_BATCH; Bl: the rows of their slots.  The slots are there whether or not
+  // CMT_DEC_LOOP asks for the loops: the size that a caller was told holds for every handle.)
+  const bool loops = h->loop_slots != LOOP_SLOTS_NONE && L <= LOOP_MAX_LAYERS;
   const bool loop_all = loops && h->loop_slots == LOOP_SLOTS_ALL;
   const size_t Bl = std::min(Bp, LOOP_MAX_BATCH);
   auto ld_alloc = [&](LD& d, int Kin, int Hh, int Lm, bool gx, int Kstep, bool encoder) {
@@ -1315,7 +1316,6 @@ int cmt_query_sizes(const cmt_config* cfg, size_t* param_bytes, size_t* grad_byt
   cmt_handle tmp;
   tmp.cfg = *cfg; tmp.prec = cfg->precision; tmp.esz = cfg->precision ? 2 : 4;
   tmp.Bpm = round_up(cfg->max_batch, 16);
-  { const char* e = getenv("CMT_DEC_LOOP"); tmp.loop = e ? atoi(e) : 1; }
   build_table(tmp.cfg, tmp.table, tmp.nparams);
   const size_t ws = layout(&tmp, nullptr);
   if (param_bytes) *param_bytes = tmp.nparams * 4;

@@ -54,6 +54,19 @@ def test_the_static_evaluation_s_array_holds_these_shapes(lib, H, E, L, length, 
     assert sizes[0] <= mb << 20 < sizes[1]
 
 
+@pytest.mark.parametrize("H,L,prec", [(16, 1, 0), (80, 3, 1), (48, 4, 0), (64, 2, 1), (512, 5, 1)])
+def test_the_workspace_does_not_depend_on_switches_read_at_create(lib, H, L, prec, monkeypatch):
+    """A size asked for with the decoder's loops off must hold for a handle that is created with them on."""
+    cfg = dict(src_vocab=1000, tgt_vocab=1000, emb=32, hidden=H, layers=L)
+    sizes = set()
+    for mode in (None, "0", "1"):
+        monkeypatch.delenv("CMT_DEC_LOOP", raising=False)
+        if mode is not None:
+            monkeypatch.setenv("CMT_DEC_LOOP", mode)
+        sizes.add(binding.query_sizes(binding.make_config(cfg, 20, 100, 40, prec)))
+    assert len(sizes) == 1
+
+
 def test_unsupported_configurations_are_rejected(lib):
     good = dict(src_vocab=1000, tgt_vocab=1000, emb=64, hidden=64, layers=1)
     def rc(cfg=good, **kw):
