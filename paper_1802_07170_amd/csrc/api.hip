@@ -21,12 +21,12 @@
 #include <algorithm>
 #include <functional>
 #include <chrono>
-#include <mutex>
 #include <string>
 #include <vector>
 
 #include "../../include/cytonmt_hip.h"
 #include "kernels.h"
+#include "section_gate.h"
 
 using namespace cmt;
 
@@ -96,6 +96,18 @@ struct Bump {
   }
 };
 
+// how the gate that keeps sections of several streams apart talks to the device
+struct GateRt {
+  using Event = hipEvent_t;
+  using Stream = hipStream_t;
+  static bool record(Event e, Stream st) { return hipEventRecord(e, st) == hipSuccess; }
+  static void wait(Stream st, Event e) { (void)hipStreamWaitEvent(st, e, 0); }
+  static void finish(Event e) { if (e) (void)hipEventSynchronize(e); }
+};
+using Gate = SectionGate<GateRt>;
+constexpr int GATES = 64;
+Gate g_gates[GATES];                    // by device
+
 }  // namespace
 
 struct cmt_handle {
@@ -150,6 +162,7 @@ struct cmt_handle {
   char* HoFeedX = nullptr; char* dPreX = nullptr;
   int loop_slots = LOOP_SLOTS_ALL;      // what the layout holds for them
   bool capturing = false;               // the pass being enqueued is captured into a graph
+  Gate* gate = nullptr; Gate::Client* section = nullptr;   // the device's gate, and this handle's place in it
   char* dzs = nullptr; char* dzTs = nullptr; float* dbo_parts = nullptr;
   std::vector<GemmProb> dw_group;       // weight-gradient GEMMs collected for one grouped launch (flush_dw_group), the transposes
   std::vector<TransposeJob> dw_tr;      // of their operands and the sums for the biases that come with those
@@ -761,12 +774,9 @@ void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
 }
 
 // A loop takes every CU there is and its workgroups wait for one another, as the encoder's recurrences' do: if parts of two such
-// launches were on the chip at once, neither might get on until its waits are given up.  Those of one stream follow each other
-// anyway; the sections of a pass that hold them are kept apart across the streams of a process by an event per device: a section
-// on another stream than the last one waits for the last one's end.  (The mutex is held while a section is enqueued.)  Nothing of
-// the kind under capture, where an event from outside must not be waited for; loops are not captured.
-struct WideGate { std::mutex mu; hipEvent_t ev = nullptr; hipStream_t last = nullptr; bool used = false; };
-WideGate g_wide_gate[64];
+// launches were on the chip at once, neither might get on until its waits are given up.  The sections of a pass that hold them
+// are kept apart across the streams of a process (section_gate.h).  Nothing of the kind under capture, where an event from
+// outside must not be waited for; loops are not captured.
 class WideSection {
  public:
   explicit WideSection(cmt_handle* h) : h_(h) {}
@@ -774,24 +784,17 @@ class WideSection {
   WideSection(const WideSection&) = delete;
   WideSection& operator=(const WideSection&) = delete;
   void open() {
-    int dev = -1;
-    if (gate_ || h_->capturing || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return;
-    WideGate* g = &g_wide_gate[dev];
-    g->mu.lock();
-    if (!g->ev && hipEventCreateWithFlags(&g->ev, hipEventDisableTiming) != hipSuccess) { g->ev = nullptr; g->mu.unlock(); return; }
-    gate_ = g;
-    if (g->used && g->last != h_->st) (void)hipStreamWaitEvent(h_->st, g->ev, 0);
+    if (open_ || h_->capturing) return;
+    h_->gate->enter(*h_->section, h_->st);
+    open_ = true;
   }
   void close() {
-    if (!gate_) return;
-    gate_->used = hipEventRecord(gate_->ev, h_->st) == hipSuccess;
-    gate_->last = h_->st;
-    gate_->mu.unlock();
-    gate_ = nullptr;
+    if (open_) h_->gate->leave(*h_->section, h_->st);
+    open_ = false;
   }
  private:
   cmt_handle* h_;
-  WideGate* gate_ = nullptr;
+  bool open_ = false;
 };
 void note_capture(cmt_handle* h) {
   hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
@@ -1360,6 +1363,9 @@ int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* w
   }
   hipError_t e = hipHostMalloc((void**)&h->h_loss, 256, hipHostMallocDefault);
   if (e != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
+  h->gate = &g_gates[dev % GATES];
+  h->section = new Gate::Client();
+  if (hipEventCreateWithFlags(&h->section->end, hipEventDisableTiming) != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
   // second stream at the default priority, and a pool of events for the hand-offs between the two
   if (hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking) != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
   h->ev.assign(512, nullptr);
@@ -1376,6 +1382,11 @@ void cmt_destroy(cmt_handle* h) {
   if (!h) return;
   if (h->h_loss) (void)hipHostFree(h->h_loss);
   if (h->side) (void)hipStreamSynchronize(h->side);
+  if (h->section) {
+    h->gate->remove(*h->section);
+    if (h->section->end) (void)hipEventDestroy(h->section->end);
+    delete h->section;
+  }
   for (auto ev : h->ev) if (ev) (void)hipEventDestroy(ev);
   for (auto ev : h->phase_ev) if (ev) (void)hipEventDestroy(ev);
   if (h->side) (void)hipStreamDestroy(h->side);

@@ -17,7 +17,7 @@
 // sentences 2.99 | 1.92, large 21.9 | 20.3; forward-only evaluation of medium 3.17 | 2.20.
 //
 // The waits are bounded, and a launch behind each loop makes it again without waits where one was given up, as the encoder's
-// recurrences have it; loops of several streams take turns (WideSection in api.hip).
+// recurrences have it; loops of several streams take turns (section_gate.h).
 #include <algorithm>
 #include <type_traits>
 

@@ -48,8 +48,9 @@ inline SeqPlan seq_bwd_plan(int prec, int ndir, int Bp, int Hh) {
 
 // The decoder's whole loop: a group = up to 128 sentences, its H / 4 workgroups own four units of every layer.  All layers'
 // weights stay on the chip, so a group is as large as the widest network needs (256 workgroups at width 1024) and a launch
-// takes every CU there is.  Launches of that kind and the recurrences above run one after the other in a process (see
-// wide_section in api.hip).
+// takes every CU there is.  The sections of a pass that hold launches of that kind, and the recurrences above, run one after the
+// other in a process (section_gate.h).  Nothing keeps them apart from another process, or from the recurrences of a graph that is
+// replayed on another stream: waits may be given up there.
 struct LoopPlan { bool ok; int nk, nwg, bt, nch, groups, tiles; };   // nk k steps per wavefront; bt tiles of 16 sentences at a time, nch
                                                                      // times; tiles = the most a group has
 inline LoopPlan loop_plan(int prec, int L, int Bp, int H, int S, int cus) {
