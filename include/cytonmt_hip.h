@@ -64,10 +64,13 @@ int cmt_query_sizes(const cmt_config* cfg, size_t* param_bytes, size_t* grad_byt
  * HIP stream (hipStream_t passed as void*; NULL = the default stream).  The buffers must stay
  * alive until cmt_destroy.  Parameters are uninitialised until cmt_init_params / cmt_set_params.
  * Handles are independent of one another: any number may be at work on a device, on streams and in threads of
- * their own (one call at a time per handle) and beside other processes.  The encoder's recurrences are made by workgroups
- * that wait for one another; with up to four such launches at once on 256 CUs, what a process's hardware queues allow by
- * default, they always get on.  Where they do not, a recurrence gives up its waits after 50 ms and is made again
- * without any: the call is late, by some tens of milliseconds per layer, and its
+ * their own (one call at a time per handle) and beside other processes.  The encoder's recurrences and the decoder's loops are
+ * made by workgroups that wait for one another; the library keeps those of one process apart where they would not get on
+ * side by side (a loop of more than 64 workgroups waits, on its stream, for such launches of other handles, and they for it;
+ * a host thread may wait while another one enqueues such a part).  It cannot keep them apart from another process on the device, from the
+ * recurrences of a captured step that is replayed beside them, or where more than four hardware queues run such launches.  If
+ * they hold each other up there, or a foreign kernel keeps CUs for as long, a launch gives up its waits after 50 ms and is
+ * made again without any: the call is late, by some tens to hundreds of milliseconds per launch, and its
  * results are sound (sums in another order, so equal to the usual ones but for rounding). */
 int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* workspace_dev,
                void* hip_stream, cmt_handle** out);

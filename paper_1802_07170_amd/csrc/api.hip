@@ -773,28 +773,32 @@ void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
   }
 }
 
-// A loop takes every CU there is and its workgroups wait for one another, as the encoder's recurrences' do: if parts of two such
-// launches were on the chip at once, neither might get on until its waits are given up.  The sections of a pass that hold them
-// are kept apart across the streams of a process (section_gate.h).  Nothing of the kind under capture, where an event from
-// outside must not be waited for; loops are not captured.
-class WideSection {
+// The parts of a pass whose workgroups wait for one another, the encoder's recurrences and the decoder's loops, as sections of
+// the device's gate (section_gate.h): a loop may take every CU there is, and if parts of two such launches were on the chip
+// at once, neither might get on until its waits are given up.  Nothing of the kind under capture, where an event from outside
+// must not be waited for; loops are not captured.
+// A loop that runs alone shares its section with the encoder's recurrences beside it while this is the device's only handle (each
+// section's end costs an event, 5 us of a step), and has one of its own otherwise: steps of three handles on their streams, 512 units,
+// 32 sentences 3.88 | 3.68 ms a round, 256 units, 64 sentences 3.50 | 3.23.
+class Section {
  public:
-  explicit WideSection(cmt_handle* h) : h_(h) {}
-  ~WideSection() { close(); }
-  WideSection(const WideSection&) = delete;
-  WideSection& operator=(const WideSection&) = delete;
-  void open() {
-    if (open_ || h_->capturing) return;
-    h_->gate->enter(*h_->section, h_->st);
+  explicit Section(cmt_handle* h) : h_(h) {}
+  ~Section() { close(); }
+  Section(const Section&) = delete;
+  Section& operator=(const Section&) = delete;
+  void open(bool alone) {
+    if (open_ || h_->capturing || h_->seq.mode == SEQ_RUN_ALONE) return;
+    alone_ = alone;
+    h_->gate->enter(*h_->section, h_->st, alone_);
     open_ = true;
   }
   void close() {
-    if (open_) h_->gate->leave(*h_->section, h_->st);
+    if (open_) h_->gate->leave(*h_->section, h_->st, alone_);
     open_ = false;
   }
  private:
   cmt_handle* h_;
-  bool open_ = false;
+  bool open_ = false, alone_ = false;
 };
 void note_capture(cmt_handle* h) {
   hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
@@ -953,9 +957,13 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
 
   const char* Hs; int ldHs;                        // source-side top-layer states [S, Bp, H] and their row pitch
   note_capture(h);
-  WideSection wide(h);
-  wide.open();
+  const bool loop = dec_loop(h, S);                // the whole decoder loop as one launch
+  const bool alone = loop && loop_runs_alone(p, L, Bp, H, S, h->seq);
+  const bool split = alone && h->gate->crowded();
+  Section sec(h);
+  sec.open(alone && !split);
   enqueue_encoder(h, S, &Hs, &ldHs);
+  if (!loop || split) sec.close();
   LD& ef = h->enc[0]; LD& eb = h->enc[1];
   // ---- decoder time loop --------------------------------------------------------------------------
   // The attentional layer's pre-activation W_c [C_s; H_t] (Eq. 7) is sum_i a_i (W_c1 H_s^i) + W_c2 H_t: with the rows
@@ -963,14 +971,16 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   // with the scores (both wait for the top layer's state alone) — two dependent launches per step instead of three.
   // The contexts themselves (the weight gradient of W_c needs them) are made for all steps at once afterwards.
   const bool proj = h->att_proj && Bp < 256;
-  const bool loop = dec_loop(h, S);                // the whole loop as one launch
   {
     LD& d0 = h->dec[0];
     launch_gemm_nt(p, h->Xt, E, d0.W, E + 2 * H, Mt, 4 * H, E, d0.Gx, nullptr, 4 * H, P + d0.b_off, 0, st);
     if (proj) launch_gemm_nt(p, Hs, ldHs, h->Pw(h->off_Wc), 2 * H, Ms, H, H, h->Pmat, h->PmatT, H, nullptr, 0, st);
     phase_mark(h, "decoder forward loop");
-    if (loop) enqueue_dec_loop_fwd(h, S, T);
-    wide.close();
+    if (loop) {
+      sec.open(alone);
+      enqueue_dec_loop_fwd(h, S, T);
+      sec.close();
+    }
     for (int j = loop ? T : 0; j < T; ++j) {
       for (int l = 0; l < L; ++l) dec_lstm_fwd(h, l, j);
       const char* Ht = h->dec[L - 1].Hst + (j + 1) * BP * esz;
@@ -1103,9 +1113,10 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   const int kbd = step_kblocks(p, 2 * H, 4 * H, Bp, h->kb_bwd_dec);       // planes written by a decoder layer's backward GEMM
   const size_t pstr = (size_t)Bp * 2 * H;
   const Planes no_planes{nullptr, 0, 0, 0};
-  wide.open();
   if (loop && (h->bwd_fused & 1) && h->wc_whole_k) {
+    sec.open(alone);
     enqueue_dec_loop_bwd(h, S, T);
+    if (split) sec.close();
   } else if ((h->bwd_fused & 1) && Bp <= 128) {            // (measured at 128 sentences: 8.1 against 8.7 ms for the k-split form)
     // one launch per layer and step (dec_bwd_gemm): no pointwise launches, no planes
     for (int j = T - 1; j >= 0; --j) {
@@ -1255,6 +1266,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
     return d;
   };
   SeqBwdArgs sb{};
+  sec.open(false);
   for (int l = L - 1; l >= 1; --l) {
     LD& e = h->enc[l + 1];
     SeqBwdDir& d = sb.d[0];
@@ -1286,7 +1298,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
     }
     sb.ticket = h->tickets;
     launch_lstm_seq_bwd(p, sb, 2, S, Bp, Hd, h->seq, st);
-    wide.close();
+    sec.close();
     // What is left after the last recurrent kernel is shared between the two streams: the weight gradients of
     // both directions on the second one, the source-embedding gradient (dX_s, then the scatter) on the caller's.
     stream_after(h, sd, st);
@@ -1365,7 +1377,9 @@ int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* w
   if (e != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
   h->gate = &g_gates[dev % GATES];
   h->section = new Gate::Client();
-  if (hipEventCreateWithFlags(&h->section->end, hipEventDisableTiming) != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
+  h->gate->add(*h->section);
+  for (hipEvent_t* ev : {&h->section->shared, &h->section->alone})
+    if (hipEventCreateWithFlags(ev, hipEventDisableTiming) != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
   // second stream at the default priority, and a pool of events for the hand-offs between the two
   if (hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking) != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
   h->ev.assign(512, nullptr);
@@ -1384,7 +1398,7 @@ void cmt_destroy(cmt_handle* h) {
   if (h->side) (void)hipStreamSynchronize(h->side);
   if (h->section) {
     h->gate->remove(*h->section);
-    if (h->section->end) (void)hipEventDestroy(h->section->end);
+    for (hipEvent_t ev : {h->section->shared, h->section->alone}) if (ev) (void)hipEventDestroy(ev);
     delete h->section;
   }
   for (auto ev : h->ev) if (ev) (void)hipEventDestroy(ev);
@@ -1586,15 +1600,21 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
                 nullptr, h->len_s, h->flags, st);
   const char* Hs; int ldHs;
   note_capture(h);
-  WideSection wide(h);
-  wide.open();
-  enqueue_encoder(h, S, &Hs, &ldHs);
   const bool proj = h->att_proj && Bp < 256;
+  const bool loop = proj && dec_loop(h, S) && loop_decode_fits(p, L, Bp, H, S, V, h->seq);
+  const bool alone = loop && loop_runs_alone(p, L, Bp, H, S, h->seq);
+  const bool split = alone && h->gate->crowded();
+  Section sec(h);
+  sec.open(alone && !split);
+  enqueue_encoder(h, S, &Hs, &ldHs);
+  if (!loop || split) sec.close();
   if (proj) launch_gemm_nt(p, Hs, ldHs, h->Pw(h->off_Wc), 2 * H, S * Bp, H, H, nullptr, h->PmatT, H, nullptr, 0, st);
   launch_dec_init(B, Bp, max_len, c.bos_id, c.pad_id, h->dec_tok, h->dec_done, out_ids_dev, out_len_dev, h->dec_mask, st);
-  const bool loop = proj && dec_loop(h, S) && loop_decode_fits(p, L, Bp, H, S, V, h->seq);
-  if (loop) enqueue_greedy_loop(h, B, S, max_len, eos_id, out_ids_dev, out_len_dev);
-  wide.close();
+  if (loop) {
+    sec.open(alone);
+    enqueue_greedy_loop(h, B, S, max_len, eos_id, out_ids_dev, out_len_dev);
+    sec.close();
+  }
   const bool fm0 = h->xcatF && h->dec[0].fm;                          // bottom layer on fragment-major operands
   if (!loop) {
     launch_fill_T(p, h->xcat, (size_t)Bp * h->ldxcat, st);            // H_o^{<-1>} = 0
@@ -1697,10 +1717,10 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
                 nullptr, h->len_s, h->flags, st);
   const char* Hs; int ldHs;
   note_capture(h);
-  WideSection wide(h);
-  wide.open();
-  enqueue_encoder(h, S, &Hs, &ldHs);
-  wide.close();                 // also leaves the decoder's initial states in slot 0 (BpE rows)
+  Section sec(h);
+  sec.open(false);
+  enqueue_encoder(h, S, &Hs, &ldHs);                 // also leaves the decoder's initial states in slot 0 (BpE rows)
+  sec.close();
   h->drop_p = keep_p;
   // one decoder row per hypothesis: encoder outputs, keys, lengths and initial states repeated K times
   BeamState& bs = h->beam;

@@ -370,6 +370,8 @@ struct LoopBwdArgs {
 };
 // Whether the loop runs as one launch on this device.
 bool loop_fits(int prec, int L, int Bp, int H, int S, const SeqRun& run);
+// Whether a loop that fits has more workgroups than a recurrence's group may have: nothing else that waits may run beside it.
+bool loop_runs_alone(int prec, int L, int Bp, int H, int S, const SeqRun& run);
 // Whether greedy decoding does: not for more than 4 tiles of sentences per group, nor for vocabularies that are long for the width.
 bool loop_decode_fits(int prec, int L, int Bp, int H, int S, int V, const SeqRun& run);
 void launch_loop_decode(int prec, const LoopFwdArgs& args, int L, int T, int Bp, int H, int S, const SeqRun& run, hipStream_t st);

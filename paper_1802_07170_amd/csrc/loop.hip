@@ -17,7 +17,7 @@
 // sentences 2.99 | 1.92, large 21.9 | 20.3; forward-only evaluation of medium 3.17 | 2.20.
 //
 // The waits are bounded, and a launch behind each loop makes it again without waits where one was given up, as the encoder's
-// recurrences have it; loops of several streams take turns (section_gate.h).
+// recurrences have it; loops of several streams are kept apart (section_gate.h).
 #include <algorithm>
 #include <type_traits>
 
@@ -663,6 +663,10 @@ void launch_loop_columns(int prec, const void* src, void* dst, int S, int Bp, in
 
 bool loop_fits(int prec, int L, int Bp, int H, int S, const SeqRun& run) {
   return run.mode != SEQ_RUN_ALONE && loop_plan(prec, L, Bp, H, S, std::min(run.cus, 256)).ok;
+}
+
+bool loop_runs_alone(int prec, int L, int Bp, int H, int S, const SeqRun& run) {
+  return loop_runs_alone(loop_plan(prec, L, Bp, H, S, std::min(run.cus, 256)));
 }
 
 void launch_loop_fwd(int prec, const LoopFwdArgs& args, int L, int T, int Bp, int H, int S, const SeqRun& run, hipStream_t st) {

@@ -48,9 +48,10 @@ inline SeqPlan seq_bwd_plan(int prec, int ndir, int Bp, int Hh) {
 
 // The decoder's whole loop: a group = up to 128 sentences, its H / 4 workgroups own four units of every layer.  All layers'
 // weights stay on the chip, so a group is as large as the widest network needs (256 workgroups at width 1024) and a launch
-// takes every CU there is.  The sections of a pass that hold launches of that kind, and the recurrences above, run one after the
-// other in a process (section_gate.h).  Nothing keeps them apart from another process, or from the recurrences of a graph that is
-// replayed on another stream: waits may be given up there.
+// may take every CU there is.  One of at most SEQ_MAX_GROUP workgroups counts as a group of the recurrences above (its workgroups
+// start in any order, so at worst all but one of the whole launch wait); a larger one has nothing beside it on the chip that
+// waits, in this process (section_gate.h).  Nothing keeps it apart from another process, or from the recurrences of a graph that
+// is replayed on another stream: waits may be given up there, and what was given up is made again without them.
 struct LoopPlan { bool ok; int nk, nwg, bt, nch, groups, tiles; };   // nk k steps per wavefront; bt tiles of 16 sentences at a time, nch
                                                                      // times; tiles = the most a group has
 inline LoopPlan loop_plan(int prec, int L, int Bp, int H, int S, int cus) {
@@ -70,5 +71,7 @@ inline LoopPlan loop_plan(int prec, int L, int Bp, int H, int S, int cus) {
   p.ok = true;
   return p;
 }
+
+inline bool loop_runs_alone(const LoopPlan& p) { return p.groups * p.nwg > SEQ_MAX_GROUP; }
 
 }  // namespace cmt

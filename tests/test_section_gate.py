@@ -9,13 +9,16 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r"""
 #include <stdio.h>
-#include <string.h>
+#include <atomic>
+#include <chrono>
 #include <string>
+#include <thread>
 #include "paper_1802_07170_amd/csrc/section_gate.h"
-static std::string said;
+static std::string said, order = "..";
+static bool broken = false;
 struct Rt {
   using Event = int; using Stream = int;
-  static bool record(Event e, Stream st) { said += "R" + std::to_string(st) + "." + std::to_string(e) + " "; return true; }
+  static bool record(Event e, Stream st) { if (broken) return false; said += "R" + std::to_string(st) + "." + std::to_string(e) + " "; return true; }
   static void wait(Stream st, Event e) { said += "W" + std::to_string(st) + "." + std::to_string(e) + " "; }
   static void finish(Event e) { said += "F" + std::to_string(e) + " "; }
 };
@@ -28,7 +31,9 @@ static int check(const char* what, const char* want) {
 }
 int main(int argc, char** argv) {
   Gate g;
-  Gate::Client a{1}, b{2};
+  Gate::Client a, b, c, d;
+  a.alone = 1; a.shared = 2; b.alone = 3; b.shared = 4; c.alone = 5; c.shared = 6; d.alone = 7; d.shared = 8;
+  auto in = [&](Gate::Client& who, int stream, bool alone) { g.enter(who, stream, alone); g.leave(who, stream, alone); };
   const std::string what = argv[1];
   %s
   printf("no such case\n");
@@ -38,12 +43,32 @@ int main(int argc, char** argv) {
 
 CASES = {
     # one client's sections follow each other on its stream
-    "alone": ("g.enter(a, 7); g.leave(a, 7); g.enter(a, 7); g.leave(a, 7);", "R7.1 R7.1 "),
-    "two streams": ("g.enter(a, 7); g.leave(a, 7); g.enter(b, 8); g.leave(b, 8); g.enter(a, 7); g.leave(a, 7);", "R7.1 W8.1 R8.2 W7.2 R7.1 "),
+    "one client": ("in(a, 7, 1); in(a, 7, 0); in(a, 7, 1);", "R7.1 R7.2 R7.1 "),
+    "two streams": ("in(a, 7, 1); in(b, 8, 1); in(a, 7, 1);", "R7.1 W8.1 R8.3 W7.3 R7.1 "),
     # one value for two streams: hipStreamPerThread of two threads, or a new stream in a destroyed one's place
-    "one handle value": ("g.enter(a, 7); g.leave(a, 7); g.enter(b, 7); g.leave(b, 7);", "R7.1 W7.1 R7.2 "),
+    "one handle value": ("in(a, 7, 1); in(b, 7, 1);", "R7.1 W7.1 R7.3 "),
+    # sections that may share the chip do not wait for one another ...
+    "shared": ("in(a, 7, 0); in(b, 8, 0); in(c, 9, 0); in(a, 7, 0);", "R7.2 R8.4 R9.6 R7.2 "),
+    # ... but for the last one that ran alone, and the next one alone waits for each of them, once
+    "shared after alone": ("in(a, 7, 1); in(b, 8, 0); in(c, 9, 0);", "R7.1 W8.1 R8.4 W9.1 R9.6 "),
+    "alone after shared": ("in(a, 7, 0); in(b, 8, 0); in(a, 7, 0); in(c, 9, 1); in(d, 6, 1);", "R7.2 R8.4 R7.2 W9.2 W9.4 R9.5 W6.5 R6.7 "),
+    "own shared one before alone": ("in(a, 7, 0); in(b, 8, 0); in(a, 7, 1); in(b, 8, 0);", "R7.2 R8.4 W7.4 R7.1 W8.1 R8.4 "),
+    # an end that could not be recorded: the ones before it are still waited for
+    "not recorded": ("in(a, 7, 0); broken = true; in(b, 8, 1); broken = false; in(c, 9, 1);", "R7.2 W8.2 W9.2 R9.5 "),
     # a client that goes is waited for, and then by nobody
-    "gone": ("g.enter(a, 7); g.leave(a, 7); g.remove(a); g.enter(b, 7); g.leave(b, 7);", "R7.1 F1 R7.2 "),
+    "gone": ("in(a, 7, 1); in(a, 7, 0); g.add(a); g.add(b); if (g.crowded()) g.remove(a); if (!g.crowded()) in(b, 7, 1);", "R7.1 R7.2 F2 F1 R7.3 "),
+    # on the host: two shared sections open at once; one alone is enqueued when both are closed, and before a third
+    "order on the host": ("""
+      g.enter(a, 7, false); g.enter(b, 8, false);
+      std::atomic<int> n{0};
+      std::thread t1([&] { g.enter(c, 9, true); order[n++] = 'C'; g.leave(c, 9, true); });
+      std::this_thread::sleep_for(std::chrono::milliseconds(100));
+      std::thread t2([&] { g.enter(d, 6, false); order[n++] = 'D'; g.leave(d, 6, false); });
+      std::this_thread::sleep_for(std::chrono::milliseconds(100));
+      if (n != 0) { printf("not kept out\\n"); return 1; }
+      g.leave(a, 7, false); g.leave(b, 8, false);
+      t1.join(); t2.join();
+      said = order;""", "CD"),
 }
 
 
