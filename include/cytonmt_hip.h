@@ -243,6 +243,12 @@ int cmt_padded_batch(const cmt_handle* h);
  * state they reach; the next step re-initialises them.  Synchronises the stream. */
 int cmt_time_kernel(cmt_handle* h, const char* name, int iters, float* us_per_launch, double* algo_work);
 
+/* How the passes of this handle have run since cmt_create: *loops = the decoder loops that went out as one launch (a training
+ * step has a forward and a backward one, an evaluation or a greedy decode one; 0 where a shape takes a launch per layer
+ * and position), *again = the launches, of these and of the encoder's recurrences, that gave up a wait and were made
+ * again without any (see cmt_create: late, not wrong).  Either may be NULL.  Synchronises the stream. */
+int cmt_wait_counts(cmt_handle* h, int64_t* loops, int64_t* again);
+
 const char* cmt_last_error(const cmt_handle* h);
 
 #ifdef __cplusplus

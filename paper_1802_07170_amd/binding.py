@@ -18,7 +18,7 @@ EXPORTS = [
     "cmt_init_params", "cmt_set_params", "cmt_get_params", "cmt_train_step", "cmt_train_step_async",
     "cmt_fetch_loss", "cmt_get_grads", "cmt_sgd_update", "cmt_debug_fetch", "cmt_padded_batch",
     "cmt_time_kernel", "cmt_last_error", "cmt_set_regularization", "cmt_greedy_decode", "cmt_beam_decode",
-    "cmt_eval_loss", "cmt_eval_loss_static",
+    "cmt_eval_loss", "cmt_eval_loss_static", "cmt_wait_counts",
 ]
 
 
@@ -72,6 +72,7 @@ def load_library():
     lib.cmt_debug_fetch.argtypes = [vp, C.c_char_p, vp, sz]
     lib.cmt_padded_batch.argtypes = [vp]
     lib.cmt_time_kernel.argtypes = [vp, C.c_char_p, C.c_int, C.POINTER(C.c_float), C.POINTER(C.c_double)]
+    lib.cmt_wait_counts.argtypes = [vp, C.POINTER(C.c_int64), C.POINTER(C.c_int64)]
     lib.cmt_last_error.argtypes = [vp]
     lib.cmt_last_error.restype = C.c_char_p
     for name in EXPORTS:
@@ -239,6 +240,12 @@ class Trainer:
         us, nbytes = C.c_float(), C.c_double()
         self._check(self.lib.cmt_time_kernel(self.h, name.encode(), iters, C.byref(us), C.byref(nbytes)))
         return us.value, nbytes.value
+
+    def wait_counts(self):
+        """(decoder loops that went out as one launch, launches that gave up a wait and were made again), since creation."""
+        loops, again = C.c_int64(), C.c_int64()
+        self._check(self.lib.cmt_wait_counts(self.h, C.byref(loops), C.byref(again)))
+        return loops.value, again.value
 
     def padded_batch(self):
         return self.lib.cmt_padded_batch(self.h)

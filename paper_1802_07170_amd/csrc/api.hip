@@ -161,6 +161,8 @@ struct cmt_handle {
                                         // layers have no fragment-major copies that can serve (LD::HstF, YdF, dGF)
   char* HoFeedX = nullptr; char* dPreX = nullptr;
   int loop_slots = LOOP_SLOTS_ALL;      // what the layout holds for them
+  int* again = nullptr;                 // launches made again after a wait that was given up, counted on the device
+  int64_t n_loops = 0;                  // decoder loops enqueued as one launch
   bool capturing = false;               // the pass being enqueued is captured into a graph
   Gate* gate = nullptr; Gate::Client* section = nullptr;   // the device's gate, and this handle's place in it
   char* dzs = nullptr; char* dzTs = nullptr; float* dbo_parts = nullptr;
@@ -723,7 +725,7 @@ void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
     return d;
   };
   SeqFwdArgs sa{};
-  sa.ticket = h->tickets;
+  sa.ticket = h->tickets; sa.again = h->again;
   for (int i = 0; i < 2; ++i) {
     SeqFwdDir& d = sa.d[i];
     d = seq_dir(i ? eb : ef);
@@ -834,7 +836,8 @@ void enqueue_dec_loop_fwd(cmt_handle* h, int S, int T) {
   a.Ho = h->HoBuf; a.HoD = drop ? h->HoDrop : nullptr; a.ldho = h->PH; a.XO = h->HoFeedX;
   if (drop) a.drop_o = drop_spec(h, DROP_SITE_HO, 0);
   a.drop_step = (unsigned long long)h->B * H;
-  a.ticket = h->tickets + LOOP_TICKET_FWD;
+  a.ticket = h->tickets + LOOP_TICKET_FWD; a.again = h->again;
+  h->n_loops++;
   add_empty(z, h->HoFeedX + slot * esz, T * slot, esz);
   add_empty(z, h->att_s, (size_t)T * Bp * S, 4);
   // (slot 0 of the bottom layer's input, H_o^{<-1>} = 0)
@@ -862,7 +865,8 @@ void enqueue_greedy_loop(cmt_handle* h, int B, int S, int T, int eos, int32_t* o
   a.len = h->len_s; a.Wc = h->Pw(h->off_Wc) + (size_t)H * esz; a.ldwc = 2 * H;
   a.K = h->Kmat; a.P = h->PmatT; a.Pg = h->dK; a.scores = h->att_s;
   a.Ho = h->HoBuf; a.ldho = h->PH; a.XO = h->HoFeedX;
-  a.ticket = h->tickets + LOOP_TICKET_FWD;
+  a.ticket = h->tickets + LOOP_TICKET_FWD; a.again = h->again;
+  h->n_loops++;
   LoopTokens& t = a.t;
   t.table = h->Pw(h->off_Etgt); t.emb = E; t.fm = h->WoF ? 1 : 0; t.Wo = h->WoF ? h->WoF : h->Pw(h->off_Wo);
   t.Bo = h->params + h->off_Bo; t.V = c.tgt_vocab;
@@ -902,7 +906,8 @@ void enqueue_dec_loop_bwd(cmt_handle* h, int S, int T) {
   a.dPre = h->dPre; a.ldp = h->PH; a.XP = h->dPreX;
   if (drop) a.drop_o = drop_spec(h, DROP_SITE_HO, 0);
   a.drop_step = (unsigned long long)h->B * H;
-  a.ticket = h->tickets + LOOP_TICKET_BWD;
+  a.ticket = h->tickets + LOOP_TICKET_BWD; a.again = h->again;
+  h->n_loops++;
   add_empty(z, h->dPreX, T * slot, esz);
   add_empty(z, h->dYa, (size_t)T * Bp * S, 4);
   launch_fill_multi(z.data(), (int)z.size(), st);
@@ -1266,6 +1271,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
     return d;
   };
   SeqBwdArgs sb{};
+  sb.again = h->again;
   sec.open(false);
   for (int l = L - 1; l >= 1; --l) {
     LD& e = h->enc[l + 1];
@@ -1387,7 +1393,8 @@ int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* w
     if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
   h->h_flags = (int*)(h->h_loss + 8);
   h->h_loss[0] = 0.f; h->h_loss[1] = 0.f; *h->h_flags = 0;
-  launch_fill_f32((float*)h->flags, 1, 0.f, h->st);  // the workspace may hold anything
+  h->again = h->flags + 1;
+  launch_fill_f32((float*)h->flags, 2, 0.f, h->st);  // the workspace may hold anything
   *out = h;
   return CMT_OK;
 }
@@ -1539,6 +1546,7 @@ int cmt_eval_loss_static(cmt_handle* h, const int32_t* src_ids_dev, const int32_
   if (rc != CMT_OK) { h->err = v.err; return rc; }
   if (n_tok_host) *n_tok_host = v.h_loss[1];
   h->ev_next = v.ev_next;
+  h->n_loops = v.n_loops;
   return CMT_OK;
 }
 
@@ -1566,6 +1574,17 @@ int cmt_fetch_loss(cmt_handle* h, float* loss_host) {
   }
   if (flags & 3) return fail(h, CMT_ERANGE, (flags & 1) ? "a token id is outside its vocabulary" : "a length is outside [1, padded length]");
   if (flags & 4) return fail(h, CMT_ENONFINITE, "the loss is not finite");
+  return CMT_OK;
+}
+
+int cmt_wait_counts(cmt_handle* h, int64_t* loops, int64_t* again) {
+  if (!h) return CMT_EINVAL;
+  int n = 0;
+  hipError_t e = hipMemcpyAsync(&n, h->again, sizeof n, hipMemcpyDeviceToHost, h->st);
+  if (e == hipSuccess) e = hipStreamSynchronize(h->st);
+  if (e != hipSuccess) return hip_fail(h, e, "cmt_wait_counts");
+  if (loops) *loops = h->n_loops;
+  if (again) *again = n;
   return CMT_OK;
 }
 

@@ -284,8 +284,9 @@ struct SeqFwdDir {
   DropSpec drop; unsigned long long drop_step;   // dropout at position t: drop with key0 + t * drop_step
   int reverse;                            // positions run from L - 1 to 0: position t reads slot t + 1, writes slot t
 };
-// ticket: two words, zero before the launch (roles taken; whether a wait was given up); wait_ticks is set by the launcher
-struct SeqFwdArgs { SeqFwdDir d[2]; int* ticket; int wait_ticks; };
+// ticket: two words, zero before the launch (roles taken; whether a wait was given up); wait_ticks is set by the launcher;
+// *again counts the launches that were made again because of that
+struct SeqFwdArgs { SeqFwdDir d[2]; int* ticket; int wait_ticks; int* again; };
 constexpr int SEQ_TICKETS = 64;           // two words per launch: 18 for the encoder's recurrences, then the decoder's loops
 constexpr int LOOP_TICKET_FWD = 32, LOOP_TICKET_BWD = 34;
 inline size_t seq_exchange_elems(int slots, int Bp, int Hh) { return (size_t)slots * Bp * ((Hh + 31) / 32 * 32); }
@@ -300,7 +301,7 @@ struct SeqBwdDir {
   void* dG; int lddg;                     // gate gradients T*: L slots of [Bp, lddg]
   int reverse;                            // the direction of the forward pass
 };
-struct SeqBwdArgs { SeqBwdDir d[2]; int* ticket; int wait_ticks; };
+struct SeqBwdArgs { SeqBwdDir d[2]; int* ticket; int wait_ticks; int* again; };
 void launch_lstm_seq_bwd(int prec, const SeqBwdArgs& args, int ndir, int L, int Bp, int Hh, const SeqRun& run, hipStream_t st);
 // Forward: the initial states are zero (the slots before the first position are not read).  1 <= ndir <= 2 instances of one shape.
 void launch_lstm_seq_fwd(int prec, const SeqFwdArgs& args, int ndir, int L, int Bp, int Hh, const SeqRun& run, hipStream_t st);
@@ -341,7 +342,7 @@ struct LoopFwdArgs {
   void* Ho; void* HoD; int ldho;           // H_o T* [T + 1, Bp, ldho], and after dropout (null: none)
   void* XO;                                // T + 1 slots of H_o as fed; slot 0 is not read
   DropSpec drop_o; unsigned long long drop_step;
-  int* ticket; int wait_ticks;             // as in SeqFwdArgs (the first word is not used)
+  int* ticket; int wait_ticks; int* again; // as in SeqFwdArgs (the ticket's first word is not used)
   LoopTokens t;
 };
 struct LoopBwdLayer {
@@ -366,7 +367,7 @@ struct LoopBwdArgs {
   const void* Ho; int ldho;                // T* [T + 1, Bp, ldho] before dropout
   void* dPre; int ldp; void* XP;           // dpre T* [T, Bp, ldp], and its T slots
   DropSpec drop_o; unsigned long long drop_step;
-  int* ticket; int wait_ticks;
+  int* ticket; int wait_ticks; int* again;
 };
 // Whether the loop runs as one launch on this device.
 bool loop_fits(int prec, int L, int Bp, int H, int S, const SeqRun& run);

@@ -525,7 +525,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_bwd_kernel(LoopBwdArgs a
 // kept where the other form has its partial sums: per layer [dh | dc | recurrent part | feed] of [Bp, H].
 template <typename T>
 __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_bwd_solo_kernel(const int* gave_up, int L, int Tn, int Bp, int H, int S, LoopBwdArgs args) {
-  if (gave_up && *gave_up == 0) return;
+  if (!recur_again(gave_up, args.again)) return;
   constexpr bool FAST = sizeof(T) == 2;
   __shared__ float s_d[16][LOOP_MAX_SRC];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, b0 = 16 * blockIdx.x, b = b0 + (lane & 15), kl = 8 * (lane >> 4);

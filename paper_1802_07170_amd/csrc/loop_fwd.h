@@ -630,7 +630,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_kernel(LoopFwdArgs a
 // launch above that gave up a wait, and nothing to do otherwise.
 template <typename T, bool DEC>
 __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_solo_kernel(const int* gave_up, int L, int Tn, int Bp, int H, int S, LoopFwdArgs args) {
-  if (gave_up && *gave_up == 0) return;
+  if (!recur_again(gave_up, args.again)) return;
   constexpr bool FAST = sizeof(T) == 2;
   __shared__ float s_a[16][LOOP_MAX_SRC];
   __shared__ float s_bv[LOOP_WAVES][16];

@@ -423,7 +423,7 @@ constexpr int SOLO_WAVES = 8;
 template <typename T>
 __global__ __launch_bounds__(64 * SOLO_WAVES) void lstm_seq_fwd_solo_kernel(const int* gave_up, int L, int Bp, int Hh, int ndir,
                                                                              SeqFwdArgs args) {
-  if (gave_up && *gave_up == 0) return;
+  if (!recur_again(gave_up, args.again)) return;
   constexpr bool FAST = sizeof(T) == 2;
   const SeqFwdDir d = args.d[blockIdx.x % ndir];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(64 * SOLO_WAVES) void lstm_seq_fwd_solo_kernel(cons
 template <typename T>
 __global__ __launch_bounds__(64 * SOLO_WAVES) void lstm_seq_bwd_solo_kernel(const int* gave_up, int L, int Bp, int Hh, int ndir,
                                                                              SeqBwdArgs args) {
-  if (gave_up && *gave_up == 0) return;
+  if (!recur_again(gave_up, args.again)) return;
   constexpr bool FAST = sizeof(T) == 2;
   const SeqBwdDir d = args.d[blockIdx.x % ndir];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;

@@ -79,6 +79,14 @@ __device__ __forceinline__ void recur_settle(const T* const (&p)[N], const bool 
     }
   }
 }
+// For the launch behind one whose waits may have been given up (null: behind none): whether there is anything to do, and if so it
+// is counted.
+__device__ __forceinline__ bool recur_again(const int* gave_up, int* again) {
+  if (!gave_up) return true;
+  if (*gave_up == 0) return false;
+  if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(again, 1);
+  return true;
+}
 // about n * 64 clocks
 __device__ __forceinline__ void recur_nap(int n) { for (int z = 0; z < n; ++z) __builtin_amdgcn_s_sleep(1); }
 
