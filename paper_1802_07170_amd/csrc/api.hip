@@ -157,8 +157,9 @@ struct cmt_handle {
   float* loss = nullptr; int* flags = nullptr; float* colscr = nullptr;
   int* tickets = nullptr;               // SEQ_TICKETS words, two per recurrence launch of a pass (layers <= 8)
   SeqRun seq{};                         // how the recurrences run (env CMT_RECUR)
-  int loop = 1;                         // the decoder's loops as one launch each (env CMT_DEC_LOOP); its slots, where the
-                                        // layers have no fragment-major copies that can serve (LD::HstF, YdF, dGF)
+  int loop = 1;                         // the decoder's loops as one launch each: 0 never, 1 where that is faster, 2 where it
+                                        // fits (env CMT_DEC_LOOP); its slots, where the layers have no fragment-major copies
+                                        // that can serve (LD::HstF, YdF, dGF)
   char* HoFeedX = nullptr; char* dPreX = nullptr;
   int loop_slots = LOOP_SLOTS_ALL;      // what the layout holds for them
   int* again = nullptr;                 // launches made again after a wait that was given up, counted on the device
@@ -807,10 +808,9 @@ void note_capture(cmt_handle* h) {
   h->capturing = hipStreamIsCapturing(h->st, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
 }
 
-// Whether the decoder's loops run as one launch each.
-bool dec_loop(const cmt_handle* h, int S) {
-  return h->loop && !h->capturing && h->att_proj == 1 && h->HoFeedX &&
-         loop_fits(h->prec, h->cfg.layers, h->Bp, h->cfg.hidden, S, h->seq);
+// Whether the decoder's loops run as one launch each, given what the plan of their workgroups says.
+bool dec_loop(const cmt_handle* h, const LoopFit& f) {
+  return h->loop && !h->capturing && h->att_proj == 1 && h->HoFeedX && f.fits && (f.pays || h->loop == 2);
 }
 // All target positions of the forward pass, on the projected source rows.
 void enqueue_dec_loop_fwd(cmt_handle* h, int S, int T) {
@@ -962,8 +962,8 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
 
   const char* Hs; int ldHs;                        // source-side top-layer states [S, Bp, H] and their row pitch
   note_capture(h);
-  const bool loop = dec_loop(h, S);                // the whole decoder loop as one launch
-  const bool alone = loop && loop_runs_alone(p, L, Bp, H, S, h->seq);
+  const LoopFit fit = loop_fits(p, L, Bp, H, S, T, h->seq);
+  const bool loop = dec_loop(h, fit), alone = loop && fit.alone;   // the whole decoder loop as one launch
   const bool split = alone && h->gate->crowded();
   Section sec(h);
   sec.open(alone && !split);
@@ -1620,8 +1620,8 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
   const char* Hs; int ldHs;
   note_capture(h);
   const bool proj = h->att_proj && Bp < 256;
-  const bool loop = proj && dec_loop(h, S) && loop_decode_fits(p, L, Bp, H, S, V, h->seq);
-  const bool alone = loop && loop_runs_alone(p, L, Bp, H, S, h->seq);
+  const LoopFit fit = loop_decode_fits(p, L, Bp, H, S, V, h->seq);
+  const bool loop = proj && dec_loop(h, fit), alone = loop && fit.alone;
   const bool split = alone && h->gate->crowded();
   Section sec(h);
   sec.open(alone && !split);

@@ -369,12 +369,12 @@ struct LoopBwdArgs {
   DropSpec drop_o; unsigned long long drop_step;
   int* ticket; int wait_ticks; int* again;
 };
-// Whether the loop runs as one launch on this device.
-bool loop_fits(int prec, int L, int Bp, int H, int S, const SeqRun& run);
-// Whether a loop that fits has more workgroups than a recurrence's group may have: nothing else that waits may run beside it.
-bool loop_runs_alone(int prec, int L, int Bp, int H, int S, const SeqRun& run);
-// Whether greedy decoding does: not for more than 4 tiles of sentences per group, nor for vocabularies that are long for the width.
-bool loop_decode_fits(int prec, int L, int Bp, int H, int S, int V, const SeqRun& run);
+// Whether the loops of a step of T positions run as one launch each on this device, whether that is the faster form, and whether
+// nothing that waits may run beside them (recur_plan.h); the same for greedy decoding, which has no form for more than 4
+// tiles of sentences per group.
+struct LoopFit { bool fits, pays, alone; };
+LoopFit loop_fits(int prec, int L, int Bp, int H, int S, int T, const SeqRun& run);
+LoopFit loop_decode_fits(int prec, int L, int Bp, int H, int S, int V, const SeqRun& run);
 void launch_loop_decode(int prec, const LoopFwdArgs& args, int L, int T, int Bp, int H, int S, const SeqRun& run, hipStream_t st);
 // dst [H / 4, Bp, S, 4] <- src [S, Bp, H]
 void launch_loop_columns(int prec, const void* src, void* dst, int S, int Bp, int H, hipStream_t st);

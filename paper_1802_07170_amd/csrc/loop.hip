@@ -661,12 +661,10 @@ void launch_loop_columns(int prec, const void* src, void* dst, int S, int Bp, in
   else hipLaunchKernelGGL(loop_columns_kernel<float>, grid, dim3(64), 0, st, (const float*)src, (float*)dst, S, Bp, H);
 }
 
-bool loop_fits(int prec, int L, int Bp, int H, int S, const SeqRun& run) {
-  return run.mode != SEQ_RUN_ALONE && loop_plan(prec, L, Bp, H, S, std::min(run.cus, 256)).ok;
-}
-
-bool loop_runs_alone(int prec, int L, int Bp, int H, int S, const SeqRun& run) {
-  return loop_runs_alone(loop_plan(prec, L, Bp, H, S, std::min(run.cus, 256)));
+LoopFit loop_fits(int prec, int L, int Bp, int H, int S, int T, const SeqRun& run) {
+  const LoopPlan p = loop_plan(prec, L, Bp, H, S, std::min(run.cus, 256));
+  const bool fits = run.mode != SEQ_RUN_ALONE && p.ok;
+  return LoopFit{fits, fits && loop_pays(p, L, T), loop_runs_alone(p)};
 }
 
 void launch_loop_fwd(int prec, const LoopFwdArgs& args, int L, int T, int Bp, int H, int S, const SeqRun& run, hipStream_t st) {

@@ -52,14 +52,15 @@ inline SeqPlan seq_bwd_plan(int prec, int ndir, int Bp, int Hh) {
 // start in any order, so at worst all but one of the whole launch wait); a larger one has nothing beside it on the chip that
 // waits, in this process (section_gate.h).  Nothing keeps it apart from another process, or from the recurrences of a graph that
 // is replayed on another stream: waits may be given up there, and what was given up is made again without them.
-struct LoopPlan { bool ok; int nk, nwg, bt, nch, groups, tiles; };   // nk k steps per wavefront; bt tiles of 16 sentences at a time, nch
-                                                                     // times; tiles = the most a group has
+// nk k steps per wavefront; bt tiles of 16 sentences at a time, nch times; tiles = the most a group has; rows = source rows that a
+// wavefront scores per position
+struct LoopPlan { bool ok; int nk, nwg, bt, nch, groups, tiles, rows; };
 inline LoopPlan loop_plan(int prec, int L, int Bp, int H, int S, int cus) {
   LoopPlan p{};
   const int nt = Bp / 16, nsteps = (H + 31) / 32;
   p.nwg = H / 4;
   p.nk = nsteps <= 8 ? 1 : nsteps <= 16 ? 2 : 4;
-  // (fp32 wider than 512: twice the weights, more than a CU's registers and LDS hold)
+  // (fp32 wider than 512: the weights of four layers are more than a CU's registers and LDS hold, and there is no form for fewer)
   if (L > 4 || nt > 8 || S > 128 || p.nwg > cus || nsteps > 32 || (!prec && p.nk > 2)) return p;
   p.groups = nt < cus / p.nwg ? nt : cus / p.nwg;
   p.tiles = (nt + p.groups - 1) / p.groups;
@@ -68,8 +69,33 @@ inline LoopPlan loop_plan(int prec, int L, int Bp, int H, int S, int cus) {
   p.bt = p.tiles < 3 || p.tiles > 4 ? (p.tiles < 2 ? 1 : 2) : 4;
   p.nch = p.tiles > 4 ? 4 : 1;
   if ((p.nch > 1 && !(prec && p.nk == 4)) || (p.nk == 1 && p.bt > 2)) return p;
+  const int waves = 8 * p.nwg, sentences = 16 * p.tiles, share = waves > sentences ? waves / sentences : 1;   // wavefronts per sentence
+  p.rows = (sentences * share + waves - 1) / waves * ((S + share - 1) / share);
   p.ok = true;
   return p;
+}
+
+// Whether the loops of a step or an evaluation, where they fit, are faster than launches.  Not for narrow layers with long sources,
+// whose rows H / 4 workgroups score: evaluations of 40 positions, bf16, one layer, one group of sentences are so many times as fast with
+// the loop at 20 | 32 | 64 rows per wavefront: width 16 1.11 | 0.87 | 0.67; at 16 | 24 | 32, width 32 1.08 | 0.99 | 0.90.  Two layers, 32 | 48
+// rows 1.00 | 0.89, three, 48 rows 0.96.  Groups of sentences run side by side: with 8, one layer, 32 | 48 rows 1.06 | 0.93, two, 48 | 64
+// 1.09 | 0.99.  Nor for one position (0.94 - 1.03 over widths 64 - 1024, 1 to 4 layers) or two of one layer (0.96 - 1.07): the clears
+// and copies around a loop.
+inline bool loop_pays(const LoopPlan& p, int L, int T) { return T > 1 && T * L > 2 && p.rows <= 10 + 12 * L + 3 * (p.groups - 1); }
+
+// The same for greedy decoding, whose logits, 16 vocabulary entries at a time (0.6 us each, W_o streaming in), are shared among the
+// group's H / 4 workgroups where the launches spread them over the chip: `tiles` = such tiles per workgroup, each as long as three
+// rows.  So many times as fast with the loop, translations of 30 tokens, one group, 2 - 10 rows, 12 | 18 | 24 tiles:
+//              bf16 width 16        128                  fp32 width 16        128
+//   1 layer    1.08 | 0.93 | 0.82   1.15 | 1.00 | 0.89   1.01 | 0.85 | 0.76   1.09 | 0.95 | 0.83
+//   2 layers   1.15 | 1.00 | 0.90   1.22 | 1.07 | 0.96   1.08 | 0.95 | 0.82   1.17 | 1.03 | 0.91
+//   4 layers   1.22 | 1.08 | 1.00   1.28 | 1.16 | 1.06   1.22 | 1.08 | 0.96   1.27 | 1.14 | 1.03
+// and with 50 rows (bf16, width 16, 2 layers) 0.89 | 0.82 | 0.75.  A wide layer's launches take longer (1 layer, 24 tiles, widths 256 | 512: bf16
+// 0.93 | 1.16, fp32 1.17 | 1.65), and so do those of several groups of sentences (bf16, 128, 1 layer, 24 tiles, 1 | 4 | 8 groups 0.90 | 0.96 | 0.98).
+constexpr int LOOP_DECODE_TILES = 24;      // (the most that was measured)
+inline bool loop_decode_pays(const LoopPlan& p, int prec, int L, int H, int V) {
+  const int tiles = ((V + 15) / 16 + p.nwg - 1) / p.nwg, launches = prec ? 44 + H * H / 8192 : 34 + H * H / 2048;
+  return tiles <= LOOP_DECODE_TILES && 3 * tiles + p.rows <= launches + 10 * L + 3 * (p.groups - 1);
 }
 
 inline bool loop_runs_alone(const LoopPlan& p) { return p.groups * p.nwg > SEQ_MAX_GROUP; }

@@ -39,13 +39,45 @@ int main() {
 """
 
 
-def test_every_workgroup_of_a_loop_fits_the_chip(tmp_path):
-    src = tmp_path / "plan.cpp"
-    src.write_text(PROGRAM)
-    exe = tmp_path / "plan"
+def _compile_and_run(tmp_path, program, *args):
+    src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
+    src.write_text(program)
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", f"-I{ROOT}", str(src), "-o", str(exe)], check=True)
-    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    return subprocess.run([str(exe), *map(str, args)], capture_output=True, text=True)
+
+
+def test_every_workgroup_of_a_loop_fits_the_chip(tmp_path):
+    r = _compile_and_run(tmp_path, PROGRAM)
     assert r.returncode == 0, r.stdout
+
+
+PAYS = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "paper_1802_07170_amd/csrc/recur_plan.h"
+int main(int argc, char** argv) {
+  using namespace cmt;
+  for (int i = 1; i + 5 < argc; i += 6) {
+    int v[6];
+    for (int k = 0; k < 6; ++k) v[k] = atoi(argv[i + k]);
+    const LoopPlan p = loop_plan(v[0], v[2], (v[3] + 15) / 16 * 16, v[1], v[4], 256);
+    putchar('0' + (p.ok && (v[5] > 0 ? loop_pays(p, v[2], v[5]) : loop_decode_pays(p, v[0], v[2], v[1], -v[5]))));
+  }
+  return 0;
+}
+"""
+
+
+def test_loops_are_taken_where_they_are_faster(tmp_path):
+    """Shapes measured on both sides of the lines by 7 % and more (precision, hidden, layers, sentences, source length, target
+    length, or for a translation minus the vocabulary), and the usual ones."""
+    faster = [(1, 16, 1, 16, 24, 40), (1, 32, 1, 128, 128, 40), (1, 48, 3, 16, 128, 40), (0, 16, 2, 128, 64, 40), (1, 64, 1, 16, 20, 3), (1, 64, 1, 8, 10, 10),
+              (1, 1024, 4, 64, 50, 50), (0, 512, 2, 64, 50, 50), (1, 512, 2, 32, 120, 120), (1, 1024, 4, 128, 80, 80), (1, 1024, 4, 64, 50, -32000),
+              (0, 512, 2, 1, 25, -32000), (1, 16, 1, 16, 20, -768), (0, 128, 4, 16, 20, -9216), (1, 512, 1, 64, 20, -49152), (0, 256, 1, 16, 20, -24576)]
+    slower = [(1, 16, 1, 16, 64, 40), (0, 16, 1, 16, 128, 40), (1, 32, 1, 16, 128, 40), (1, 16, 2, 16, 96, 40), (1, 512, 2, 16, 20, 1), (1, 16, 1, 16, 20, -1536),
+              (0, 64, 1, 16, 20, -6144), (0, 128, 2, 16, 20, -12288), (1, 16, 2, 16, 100, -768), (1, 64, 2, 16, 100, -6144), (1, 256, 1, 16, 20, -24576)]
+    r = _compile_and_run(tmp_path, PAYS, *(x for c in faster + slower for x in c))
+    assert r.stdout == "1" * len(faster) + "0" * len(slower)
 
 
 # How the passes of a handle ran, by (CMT_DEC_LOOP, CMT_RECUR): a training step has two loops, an evaluation or a translation one.
@@ -104,8 +136,8 @@ def test_loops_agree_with_the_launch_per_position(prec, B, S, T, H, E, L, reg, m
     cfg = dict(src_vocab=128, tgt_vocab=136, emb=E, hidden=H, layers=L)
     batch = _batch(cfg, B, S, T, seed=H + B)
     res = {}
-    for mode in ("0", "1"):
-        monkeypatch.setenv("CMT_DEC_LOOP", mode)
+    for mode, switch in (("0", "0"), ("1", "2")):         # (2: also where launches would be faster)
+        monkeypatch.setenv("CMT_DEC_LOOP", switch)
         res[mode] = _step(cfg, batch, B, S, T, prec, reg, loops=mode == "1")
     assert abs(res["0"][0] - res["1"][0]) <= (1e-6 if prec == 0 else 2e-4) * abs(res["0"][0])
     assert abs(res["0"][2][0] - res["1"][2][0]) <= (1e-6 if prec == 0 else 2e-4) * abs(res["0"][2][0])
