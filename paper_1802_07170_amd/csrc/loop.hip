@@ -35,6 +35,8 @@ namespace cmt {
 // partial sums for their four units.  Those go through a few slots that are used again every other position: the reader puts
 // the empty pattern back, a position before the slot's next writer could come (it needs gate gradients that the reader sends
 // afterwards).
+// s_sleep units before a workgroup looks for a layer's gate gradients, and for its partial sums
+struct LoopNaps { int gates, sums; };
 template <typename T, int NK, int BT>
 __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_bwd_kernel(LoopBwdArgs args_, int L, int Tn, int Bp, int H, int S, LoopPlan plan, LoopNaps nap) {
   constexpr bool FAST = sizeof(T) == 2;
@@ -271,7 +273,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_bwd_kernel(LoopBwdArgs a
     // (not before every wavefront's gate gradients are on their way: the loads would stand in front of those stores; and
     // `red` has been read)
     loop_barrier();
-    recur_nap(nap.layer);
+    recur_nap(nap.gates);
     issue(x, 4 * tile, 0);
     if (l > 0) cell_fetch(lo, j, in);
     else if (j > 0) dpre_fetch(j - 1);
@@ -302,7 +304,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_bwd_kernel(LoopBwdArgs a
       const int ln = fresh(), b = 16 * bt0 + w * per + min(ln >> 2, per - 1);
       float v[4];
       float* const mine = part_at(part, j, 0, place.pos);
-      recur_nap(nap.first);
+      recur_nap(nap.sums);
       ask(mine, b, v);
       float dy = take(mine, b, v);
       if (a->l[lo].drop.on) {
@@ -339,7 +341,6 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_bwd_kernel(LoopBwdArgs a
           pr[q] = *(const P4*)(kg + (size_t)(q * tps * (int)sizeof(P4)) + off * (unsigned)sizeof(P4));
         }
       }
-      if (s0 == 0) recur_nap(nap.mix);
       loop_words_issue<QT>(da, 4 * tps, 4 * off, sr, tps, n, dv, true);
       if (s0 == 0) loop_barrier();                                 // (s_u is there)
       loop_words_settle<QT>(da, 4 * tps, 4 * off, dv, dead, gave_up, ticks);
@@ -436,10 +437,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_bwd_kernel(LoopBwdArgs a
         const int p = (8 * ln + 512 * q < H ? ln + 64 * q : 0) + (int)zero;
         return (unsigned)((p >> 2) * 512 + (p & 3) * 128) * (unsigned)sizeof(T);
       };
-      if (t == task0) {
-        loop_barrier();                                            // (every wavefront's dpre is on its way)
-        recur_nap(nap.score);
-      }
+      if (t == task0) loop_barrier();                              // (every wavefront's dpre is on its way)
       if (some) loop_issue<T, NQ>(hrow, piece, hv);
       if (!some) break;
       loop_settle<T, NQ>(hrow, piece, hv, dead, gave_up, ticks);
@@ -674,7 +672,7 @@ void launch_loop_bwd(int prec, const LoopBwdArgs& args, int L, int T, int Bp, in
   const LoopPlan p = loop_plan(prec, L, Bp, H, S, std::min(run.cus, 256));
   LoopBwdArgs a = args;
   a.wait_ticks = run.mode == SEQ_RUN_GIVE_UP ? 0 : RECUR_WAIT_TICKS;
-  const LoopNaps nap{16, p.nk * std::min(p.tiles, 4) < 16 ? 0 : 16, 0, 0};
+  const LoopNaps nap{16, p.nk * std::min(p.tiles, 4) < 16 ? 0 : 16};
   const dim3 grid(p.groups * p.nwg), block(64 * LOOP_WAVES);
 #define GO(TT, NK, BT) hipLaunchKernelGGL((loop_bwd_kernel<TT, NK, BT>), grid, block, 0, st, a, L, T, Bp, H, S, p, nap)
   if (prec) {

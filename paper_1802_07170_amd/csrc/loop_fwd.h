@@ -7,15 +7,12 @@
 
 namespace cmt {
 
-// s_sleep units before a workgroup looks for a layer's input, H_t (scores), the scores (mix)
-struct LoopNaps { int layer, first, score, mix; };
-
 // DEC: greedy decoding (LoopTokens).  Every workgroup takes each H / 4-th tile of 16 vocabulary entries, W_o's rows streaming in from
 // memory (they do not fit the chip) while H_o's fragments stay in registers between the bottom layer's product and this one; the best
 // of its entries per sentence go to the wavefront that owns the sentence, which sends the token to all.
 template <typename T, int NK, int BT, int NCH, bool DEC, int LM = LOOP_MAX_LAYERS>
 __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_kernel(LoopFwdArgs args_, int L, int Tn, int Bp, int H, int S, LoopPlan plan,
-                                                                   LoopNaps nap) {
+                                                                   int nap) {
   constexpr bool FAST = sizeof(T) == 2;
   constexpr int LREG = NK * sizeof(T) >= 8 ? 2 : LM;               // layers whose recurrent weights are in registers, not LDS
   constexpr int LLDS = LM - LREG;
@@ -355,7 +352,6 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_kernel(LoopFwdArgs a
         const T* x = loop_global((const T*)A()->XO) + (size_t)j * slot;
         VocabRows wo[PD];
         first_rows(wo);
-        recur_nap(nap.first);
         issue(x, 0);
         settle(x, 0);
         best_tokens(j - 1, wo);
@@ -383,7 +379,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_kernel(LoopFwdArgs a
                  : a->l[lo].XY ? loop_global((const T*)a->l[lo].XY) + (size_t)j * slot : loop_global((const T*)a->l[lo].X) + (size_t)(j + 1) * slot;
     }
     if constexpr (!(DEC && l == 0)) {
-      recur_nap(l == 0 ? nap.first : nap.layer);
+      if (l > 0) recur_nap(nap);
       issue(x, 0);
     }
 #pragma unroll
@@ -479,8 +475,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_kernel(LoopFwdArgs a
       LOOP_FRESH(ln);
       const int sr = ln & (tps - 1), bs = s0 + w * spw + ln / tps, bc = min(bs, NB - 1), bg = 16 * bt0 + bc, n = bs < NB ? s_len[bc] : 0;
       const unsigned off = (unsigned)(bg * S + sr);
-      if (s0 == 0) recur_nap(nap.mix);
-      else rows(s0, 0);
+      if (s0 > 0) rows(s0, 0);
       float sv[QT];
       loop_words_issue<QT>(loop_global(a->scores) + (size_t)j * Bp * S, 4 * tps, 4 * off, sr, tps, n, sv, true);
       loop_words_settle<QT>(loop_global(a->scores) + (size_t)j * Bp * S, 4 * tps, 4 * off, sv, dead, gave_up, ticks);
@@ -560,7 +555,6 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_kernel(LoopFwdArgs a
       float* const sc = loop_global(a->scores) + ((size_t)j * Bp + bg) * S;
       Frag<T> hv[NQ];
       key_rows(t, part, n);
-      recur_nap(nap.score);
       const T* hrow = ht + (size_t)(bg >> 4) * ns * 512 + (bg & 15) * 8;
       auto piece = [&](int q, unsigned zero) {                     // (a lane beyond the row's end repeats the first)
         const int p = (8 * ln + 512 * q < H ? ln + 64 * q : 0) + (int)zero;
@@ -798,9 +792,9 @@ static void loop_fwd_go(int prec, const LoopFwdArgs& args, int L, int T, int Bp,
   const LoopPlan p = loop_plan(prec, L, Bp, H, S, std::min(run.cus, 256));
   LoopFwdArgs a = args;
   a.wait_ticks = run.mode == SEQ_RUN_GIVE_UP ? 0 : RECUR_WAIT_TICKS;
-  // A nap before a layer's input is looked for, where the reading of its recurrent half does not take as long as the exchange: whole
+  // s_sleep units before the input of a layer above the bottom one is looked for, where the reading of its recurrent half does not take as long as the exchange: whole
   // evaluations with 0 | 16 units, us: attn 1874 | 1770, paper_512x2 846 | 809, 336 units x 3 layers 714 | 669, medium 2216 | 2268.
-  const LoopNaps nap{p.nk * p.bt < 16 ? 16 : 0, 0, 0, 0};
+  const int nap = p.nk * p.bt < 16 ? 16 : 0;
   const dim3 grid(p.groups * p.nwg), block(64 * LOOP_WAVES);
   // (decoding networks of one or two layers: the registers that more would take hold tiles of W_o on their way)
 #define GO(TT, NK, BT)                                                                                                             \
