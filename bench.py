@@ -3,7 +3,7 @@
 python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload medium] [--no-cpu-baseline]
 
 Prints ONE JSON line: target tokens/s of the whole step with inputs resident in HBM, the roofline
-figures of the decoder's layer step kernel (measured live with HIP events), and the CPU oracle timed on a
+figures of the dominant kernel of its critical path (measured live with HIP events), and the CPU oracle timed on a
 bounded sample of the same workload."""
 from __future__ import annotations
 
@@ -23,19 +23,20 @@ from paper_1802_07170_amd import inputs as I  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of the timed kernel from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE),
-# scaled by what the same counters read for a plain 256 MiB copy (x2 and x1): the summary under
+# scaled by what the same counters read for a plain 256 MiB copy (x2 and x1) and with the clears and copies that belong to it: the summary under
 # profiles/ gives the commands and the figures.  Valid for the workload and the kernel source it was
-# measured with: (workload, first 12 hex digits of the sha256 of STEP_KERNEL_SOURCES) -> bytes;
+# measured with: (workload, first 12 hex digits of the sha256 of LOOP_KERNEL_SOURCES) -> bytes;
 # with another source the figure is stale and reported as null.
-MEASURED_TRAFFIC_BYTES = {("medium", "e675f64d3e81"): 22864896}      # profiles/step_kernels_medium_bf16_memory_counters.md
+MEASURED_TRAFFIC_BYTES = {}      # profiles/loop_kernels_medium_bf16_memory_counters.md
 
-STEP_KERNEL_SOURCES = ("step.hip", "cell.h", "common.h", "kernels.h")   # the timed kernel's file and what it includes
+# the timed kernel's file and what it includes
+LOOP_KERNEL_SOURCES = ("loop.hip", "loop_fwd.h", "loop_core.h", "recur_core.h", "recur_plan.h", "cell.h", "common.h", "kernels.h")
 
 
-def step_kernel_source_tag():
+def loop_kernel_source_tag():
     import hashlib
     h = hashlib.sha256()
-    for f in STEP_KERNEL_SOURCES:
+    for f in LOOP_KERNEL_SOURCES:
         h.update(open(os.path.join(ROOT, "paper_1802_07170_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:12]
 MFMA_BF16_PEAK_TFLOPS = 2500.0
@@ -162,16 +163,18 @@ def main():
     tr.set_regularization(0.0, 0.0, 0)
     tr.train_step_async(dev)
     torch.cuda.synchronize()
-    # the decoder layer step of the launch-per-position form, replayed alone: what the timed step runs where its shapes are beyond
-    # the one-launch loops (loop_fwd_kernel, loop_bwd_kernel, which wait for exchanges between workgroups, not for HBM, and which
-    # the traces under profiles/ hold).  HBM carries its weights once; what it waits for is the L2 -> CU traffic of weights plus
-    # re-read activations (see the summaries under profiles/).
-    us, nbytes = tr.time_kernel("lstm_fwd_dec", 400)
+    # the decoder's whole backward loop (all positions and layers in one launch, with the clears and copies before it), replayed
+    # alone: the longest kernel of the step's critical path.  Its bytes go through HBM once; what it waits for are the exchanges
+    # between its workgroups and the path from L2 into the CUs (see the summaries under profiles/).
+    us, nbytes = tr.time_kernel("dec_loop_bwd", 20)
     achieved = nbytes / (us * 1e-6) / 1e9
-    out["roofline"] = {"kernel": "lstm_fwd_kernel (decoder layer step: gate GEMM + fused cell)", "bound": "hbm",
+    traffic = MEASURED_TRAFFIC_BYTES.get((args.workload, loop_kernel_source_tag()))
+    out["roofline"] = {"kernel": "loop_bwd_kernel (decoder backward: every layer, the attention and H_o of every position)", "bound": "hbm",
                        "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                       "traffic": MEASURED_TRAFFIC_BYTES.get((args.workload, step_kernel_source_tag())), "us_per_launch": us,
-                       "algorithmic_bytes_per_launch": nbytes, "kernel_source_tag": step_kernel_source_tag()}
+                       "us_per_launch": us, "us_per_position": us / T, "algorithmic_bytes_per_launch": nbytes,
+                       "kernel_source_tag": loop_kernel_source_tag()}
+    if traffic is not None:
+        out["roofline"]["traffic"] = traffic
     # forward-only greedy translation of the same source batch (not part of the headline metric)
     max_len = T
     tr.greedy_decode(src, sl, max_len)
@@ -194,10 +197,11 @@ def main():
         out["beam_decode"] = {"beam": 10, "length_penalty": 0.6, "ms": dtb * 1e3, "steps": max_len,
                               "emitted_tokens": int(blens.sum()), "tokens_per_s": float(blens.sum() / dtb)}
         tb.close()
-    # the other kernel classes of the step, each replayed alone (no second stream active)
+    # other kernel classes, each replayed alone (no second stream active)
     peak_mfma = MFMA_BF16_PEAK_TFLOPS if c["precision"] else MFMA_FP32_PEAK_TFLOPS
     kernels = {}
-    for name, kind, iters in [("step_bwd_fused_dec", "hbm", 400), ("step2d_bwd_dec", "hbm", 400), ("att_fwd", "hbm", 400),
+    # (dec_loop_fwd: the step's forward loop; lstm_fwd_dec to att_bwd: what shapes beyond the loops take per position)
+    for name, kind, iters in [("dec_loop_fwd", "hbm", 20), ("lstm_fwd_dec", "hbm", 400), ("step_bwd_fused_dec", "hbm", 400), ("step2d_bwd_dec", "hbm", 400), ("att_fwd", "hbm", 400),
                               ("att_bwd", "hbm", 400),
                               ("gemm_gx", "mfma", 50), ("gemm_dw", "mfma", 50), ("ce_fwd", "mfma", 20)]:
         kus, work = tr.time_kernel(name, iters)

@@ -221,6 +221,9 @@ int cmt_padded_batch(const cmt_handle* h);
  * those values, not the timing: run a step before using gradients again).  Returns the mean microseconds per launch and the algorithmic work of one launch:
  * bytes (operands read once, outputs written once) for the bandwidth-bound kernels, flops
  * (2 per multiply-add) for the matrix-core-bound ones.  Names:
+ *   "dec_loop_fwd", "dec_loop_bwd"  the decoder's forward / backward loop as the step runs it, one launch with the clears and
+ *                    copies before it and the launch behind it (CMT_EINVAL where the last step took a launch
+ *                    per layer and position; the other decoder kernels below are replayed either way)   bytes
  *   "lstm_fwd_dec"   fused decoder LSTM step (gate GEMM + cell), cycling over the layers   bytes
  *   "step2d_bwd_dec" [dx; dh] = dgates [W_x; W_h] of a decoder layer's backward step       bytes
  *   "att_fwd"        attention forward of one decoder step as the step runs it: below 256 sentences the scores

@@ -34,6 +34,7 @@ namespace {
 
 // Which of the decoder's whole loops a workspace has slots for: none, the forward one without dropout (an evaluation), all.
 enum { LOOP_SLOTS_NONE = 0, LOOP_SLOTS_EVAL = 1, LOOP_SLOTS_ALL = 2 };
+enum { LOOP_RAN_FWD = 1, LOOP_RAN_BWD = 2 };
 
 struct ParamInfo { std::string name; int64_t rows, cols; size_t off; };
 
@@ -164,6 +165,7 @@ struct cmt_handle {
   int loop_slots = LOOP_SLOTS_ALL;      // what the layout holds for them
   int* again = nullptr;                 // launches made again after a wait that was given up, counted on the device
   int64_t n_loops = 0;                  // decoder loops enqueued as one launch
+  int ran_loops = 0;                    // those of the last step
   bool capturing = false;               // the pass being enqueued is captured into a graph
   Gate* gate = nullptr; Gate::Client* section = nullptr;   // the device's gate, and this handle's place in it
   char* dzs = nullptr; char* dzTs = nullptr; float* dbo_parts = nullptr;
@@ -837,7 +839,6 @@ void enqueue_dec_loop_fwd(cmt_handle* h, int S, int T) {
   if (drop) a.drop_o = drop_spec(h, DROP_SITE_HO, 0);
   a.drop_step = (unsigned long long)h->B * H;
   a.ticket = h->tickets + LOOP_TICKET_FWD; a.again = h->again;
-  h->n_loops++;
   add_empty(z, h->HoFeedX + slot * esz, T * slot, esz);
   add_empty(z, h->att_s, (size_t)T * Bp * S, 4);
   // (slot 0 of the bottom layer's input, H_o^{<-1>} = 0)
@@ -907,18 +908,21 @@ void enqueue_dec_loop_bwd(cmt_handle* h, int S, int T) {
   if (drop) a.drop_o = drop_spec(h, DROP_SITE_HO, 0);
   a.drop_step = (unsigned long long)h->B * H;
   a.ticket = h->tickets + LOOP_TICKET_BWD; a.again = h->again;
-  h->n_loops++;
   add_empty(z, h->dPreX, T * slot, esz);
   add_empty(z, h->dYa, (size_t)T * Bp * S, 4);
   launch_fill_multi(z.data(), (int)z.size(), st);
   launch_loop_columns(p, h->Kmat, h->dKT, S, Bp, H, st);
   launch_loop_bwd(p, a, L, T, Bp, H, S, h->seq, st);
-  // dC_s of all positions (the deferred gradients read it): dpre W_c1
+}
+// dC_s of all positions (the deferred gradients read it): dpre W_c1
+void enqueue_dec_contexts_bwd(cmt_handle* h, int T) {
+  const int p = h->prec, H = h->cfg.hidden, Bp = h->Bp;
+  const size_t esz = h->esz;
   // (fp32: a quarter of k at a time.  Summed up in one go it made the encoder's gradients 10 - 30 % worse against 64 bits than the launch per
   // position, whose wavefronts share k, did: 512 units, 2 layers, error of the upper encoder layer's dW 5.0e-7 instead of 3.9e-7, 3.8e-7 so)
   for (int k = 0, kc = p ? H : std::max(round_up(H, 64) / 4, 32); k < H; k += kc)
     launch_gemm_nt(p, (const char*)h->dPre + k * esz, h->PH, (const char*)h->WcT + k * esz, H, T * Bp, H, std::min(kc, H - k), h->dCs, nullptr, H,
-                   nullptr, k > 0, st);
+                   nullptr, k > 0, h->st);
 }
 
 int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, const int32_t* tgt_ids,
@@ -964,6 +968,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   note_capture(h);
   const LoopFit fit = loop_fits(p, L, Bp, H, S, T, h->seq);
   const bool loop = dec_loop(h, fit), alone = loop && fit.alone;   // the whole decoder loop as one launch
+  h->ran_loops = loop ? LOOP_RAN_FWD : 0;
   const bool split = alone && h->gate->crowded();
   Section sec(h);
   sec.open(alone && !split);
@@ -985,6 +990,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
       sec.open(alone);
       enqueue_dec_loop_fwd(h, S, T);
       sec.close();
+      h->n_loops++;
     }
     for (int j = loop ? T : 0; j < T; ++j) {
       for (int l = 0; l < L; ++l) dec_lstm_fwd(h, l, j);
@@ -1121,7 +1127,10 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   if (loop && (h->bwd_fused & 1) && h->wc_whole_k) {
     sec.open(alone);
     enqueue_dec_loop_bwd(h, S, T);
+    enqueue_dec_contexts_bwd(h, T);
     if (split) sec.close();
+    h->n_loops++;
+    h->ran_loops = LOOP_RAN_FWD | LOOP_RAN_BWD;
   } else if ((h->bwd_fused & 1) && Bp <= 128) {            // (measured at 128 sentences: 8.1 against 8.7 ms for the k-split form)
     // one launch per layer and step (dec_bwd_gemm): no pointwise launches, no planes
     for (int j = T - 1; j >= 0; --j) {
@@ -1863,7 +1872,21 @@ int cmt_time_kernel(cmt_handle* h, const char* name, int iters, float* us_per_la
   const int j = T / 2;                                  // the middle target position
   std::function<void(int)> launch;
   const int* probe_flag = nullptr;                      // set by a probe whose bounded wait may give up
-  if (s == "lstm_fwd_dec") {
+  Section sec(h);                                       // (open until the replays have ended)
+  if (s == "dec_loop_fwd" || s == "dec_loop_bwd") {
+    // a whole loop as the step enqueues it, with the clears and copies before it and the launch behind it
+    const bool bwd = s == "dec_loop_bwd";
+    if (!(h->ran_loops & (bwd ? LOOP_RAN_BWD : LOOP_RAN_FWD))) return fail(h, CMT_EINVAL, "the last step took a launch per layer and position");
+    const double state = (double)Bp * H, scores = (double)Bp * S;
+    *algo_work = (8.0 * L + 1.0) * H * H * esz                         // [input; recurrent] columns of all layers, W_c's H_t half
+               + S * state * (esz + (bwd ? 4 : esz))                   // keys and projected rows
+               + (bwd ? T * (L * state * (16 + 4 + 4 * esz)            // activations, cell states; gate gradients
+                             + state * (4 + 2 * esz) + 8 * scores)     // the output layer's gradient, H_o, dpre; weights, their gradients
+                      : T * (state * 16 + L * state * (16 + 4 + esz)   // input part; activations, cell states, states
+                             + state * esz + 4 * scores));             // H_o; weights
+    sec.open(loop_fits(p, L, Bp, H, S, T, h->seq).alone);
+    launch = [=](int) { if (bwd) enqueue_dec_loop_bwd(h, S, T); else enqueue_dec_loop_fwd(h, S, T); };
+  } else if (s == "lstm_fwd_dec") {
     // decoder LSTM forward step, cycling over the layers like the real loop (weights not L2-resident)
     const int K = 2 * H;                                // per-step contraction (layer 0: [feed; h], others: [x; h])
     *algo_work = 4.0 * H * K * esz                      // weights, read once

@@ -9,11 +9,11 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 
 def test_the_tag_covers_the_timed_kernel_s_file_and_all_that_it_includes():
-    seen, todo = set(), ["step.hip"]
+    seen, todo = set(), ["loop.hip"]
     while todo:
         name = todo.pop()
         if name not in seen:
             seen.add(name)
             with open(os.path.join(CSRC, name)) as f:
                 todo += re.findall(r'^#include "([^"]+)"', f.read(), re.M)
-    assert seen == set(bench.STEP_KERNEL_SOURCES)
+    assert seen == set(bench.LOOP_KERNEL_SOURCES)

@@ -891,7 +891,7 @@ def test_kernel_replay_timer_covers_its_kernels_and_leaves_results_alone():
     dev = tr.upload_batch(*ragged_batch(rng, 20, 7, 9, 104, 328))
     loss = tr.train_step(dev)
     g = tr.get_grads()
-    for name in ["lstm_fwd_dec", "step2d_bwd_dec", "step_bwd_fused_dec", "att_fwd", "gemm_gx", "gemm_dw", "ce_fwd", "mfma_rate",
+    for name in ["dec_loop_fwd", "dec_loop_bwd", "lstm_fwd_dec", "step2d_bwd_dec", "step_bwd_fused_dec", "att_fwd", "gemm_gx", "gemm_dw", "ce_fwd", "mfma_rate",
                  "grid_barrier", "grid_barrier_nofence"]:
         us, work = tr.time_kernel(name, 5 if "barrier" not in name else 2)
         assert us > 0 and work > 0, name
