@@ -782,9 +782,9 @@ void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
 // the device's gate (section_gate.h): a loop may take every CU there is, and if parts of two such launches were on the chip
 // at once, neither might get on until its waits are given up.  Nothing of the kind under capture, where an event from outside
 // must not be waited for; loops are not captured.
-// A loop that runs alone shares its section with the encoder's recurrences beside it while this is the device's only handle (each
-// section's end costs an event, 5 us of a step), and has one of its own otherwise: steps of three handles on their streams, 512 units,
-// 32 sentences 3.88 | 3.68 ms a round, 256 units, 64 sentences 3.50 | 3.23.
+// A loop that runs alone shares its section with the encoder's recurrences beside it while no handle of the device has another stream
+// (each section's end costs an event, 5 us of a step), and has one of its own otherwise: steps of three handles on their streams, 512
+// units, 32 sentences 3.88 | 3.68 ms a round, 256 units, 64 sentences 3.50 | 3.23.
 class Section {
  public:
   explicit Section(cmt_handle* h) : h_(h) {}
@@ -969,7 +969,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   const LoopFit fit = loop_fits(p, L, Bp, H, S, T, h->seq);
   const bool loop = dec_loop(h, fit), alone = loop && fit.alone;   // the whole decoder loop as one launch
   h->ran_loops = loop ? LOOP_RAN_FWD : 0;
-  const bool split = alone && h->gate->crowded();
+  const bool split = alone && h->gate->crowded(*h->section);
   Section sec(h);
   sec.open(alone && !split);
   enqueue_encoder(h, S, &Hs, &ldHs);
@@ -1392,7 +1392,7 @@ int cmt_create(const cmt_config* cfg, void* params_dev, void* grads_dev, void* w
   if (e != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
   h->gate = &g_gates[dev % GATES];
   h->section = new Gate::Client();
-  h->gate->add(*h->section);
+  h->gate->add(*h->section, h->st);
   for (hipEvent_t* ev : {&h->section->shared, &h->section->alone})
     if (hipEventCreateWithFlags(ev, hipEventDisableTiming) != hipSuccess) { cmt_destroy(h); return CMT_EHIP; }
   // second stream at the default priority, and a pool of events for the hand-offs between the two
@@ -1631,7 +1631,7 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
   const bool proj = h->att_proj && Bp < 256;
   const LoopFit fit = loop_decode_fits(p, L, Bp, H, S, V, h->seq);
   const bool loop = proj && dec_loop(h, fit), alone = loop && fit.alone;
-  const bool split = alone && h->gate->crowded();
+  const bool split = alone && h->gate->crowded(*h->section);
   Section sec(h);
   sec.open(alone && !split);
   enqueue_encoder(h, S, &Hs, &ldHs);

@@ -20,10 +20,21 @@ class SectionGate {
   struct Client {
     typename Rt::Event shared{}, alone{};              // the ends of its last sections of either kind; the events are the caller's
     bool pending = false;                              // its last shared section is one that the next one alone has to wait for
+    typename Rt::Stream stream{};                      // where its sections go, as far as the value tells
   };
-  void add(Client&) { std::lock_guard<std::mutex> lock(mu_); ++clients_; }
-  // whether there are others that short sections leave more room
-  bool crowded() { std::lock_guard<std::mutex> lock(mu_); return clients_ > 1; }
+  void add(Client& c, typename Rt::Stream st) {
+    std::lock_guard<std::mutex> lock(mu_);
+    c.stream = st;
+    clients_.push_back(&c);
+  }
+  // Whether there are others that short sections leave more room: some on another stream.  (Several streams of one value are
+  // taken for one here: their sections are then longer than they need be, no more.)
+  bool crowded(const Client& c) {
+    std::lock_guard<std::mutex> lock(mu_);
+    for (const Client* p : clients_)
+      if (p->stream != c.stream) return true;
+    return false;
+  }
   void enter(Client& c, typename Rt::Stream st, bool alone) {
     std::unique_lock<std::mutex> lock(mu_);
     if (alone) {
@@ -60,16 +71,16 @@ class SectionGate {
     Rt::finish(c.alone);
     std::unique_lock<std::mutex> lock(mu_);
     free_.wait(lock, [&] { return !alone_; });
-    --clients_;
     if (last_ == &c) last_ = nullptr;
-    for (size_t i = 0; i < pending_.size(); ++i)
-      if (pending_[i] == &c) { pending_[i] = pending_.back(); pending_.pop_back(); break; }
+    for (std::vector<Client*>* v : {&clients_, &pending_})
+      for (size_t i = 0; i < v->size(); ++i)
+        if ((*v)[i] == &c) { (*v)[i] = v->back(); v->pop_back(); break; }
   }
 
  private:
   std::mutex mu_;
   std::condition_variable free_;
-  int clients_ = 0;
+  std::vector<Client*> clients_;
   int queued_ = 0, sharing_ = 0;                       // sections being enqueued on the host: waiting to run alone, sharing,
   bool alone_ = false;                                 // alone
   Client* last_ = nullptr;                             // whose section ran alone last

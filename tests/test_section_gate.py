@@ -56,7 +56,10 @@ CASES = {
     # an end that could not be recorded: the ones before it are still waited for
     "not recorded": ("in(a, 7, 0); broken = true; in(b, 8, 1); broken = false; in(c, 9, 1);", "R7.2 W8.2 W9.2 R9.5 "),
     # a client that goes is waited for, and then by nobody
-    "gone": ("in(a, 7, 1); in(a, 7, 0); g.add(a); g.add(b); if (g.crowded()) g.remove(a); if (!g.crowded()) in(b, 7, 1);", "R7.1 R7.2 F2 F1 R7.3 "),
+    "gone": ("in(a, 7, 1); in(a, 7, 0); g.add(a, 7); g.add(b, 8); if (g.crowded(b)) g.remove(a); if (!g.crowded(b)) in(b, 7, 1);", "R7.1 R7.2 F2 F1 R7.3 "),
+    # several clients on one stream follow each other: nobody there has a use for shorter sections
+    "crowded": ("g.add(a, 7); g.add(b, 7); if (!g.crowded(a) && !g.crowded(b)) said += 'n'; g.add(c, 8); for (auto* p : {&a, &b, &c}) if (g.crowded(*p)) said += 'y'; "
+                "g.remove(a); if (g.crowded(b)) said += 'y';", "nyyyF2 F1 y"),
     # on the host: two shared sections open at once; one alone is enqueued when both are closed, and before a third
     "order on the host": ("""
       g.enter(a, 7, false); g.enter(b, 8, false);
