@@ -352,6 +352,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_kernel(LoopFwdArgs a
         const T* x = loop_global((const T*)A()->XO) + (size_t)j * slot;
         VocabRows wo[PD];
         first_rows(wo);
+        LOOP_PHASE();
         issue(x, 0);
         settle(x, 0);
         best_tokens(j - 1, wo);
@@ -380,6 +381,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_kernel(LoopFwdArgs a
     }
     if constexpr (!(DEC && l == 0)) {
       if (l > 0) recur_nap(nap);
+      else LOOP_PHASE();
       issue(x, 0);
     }
 #pragma unroll
@@ -476,6 +478,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_kernel(LoopFwdArgs a
       const int sr = ln & (tps - 1), bs = s0 + w * spw + ln / tps, bc = min(bs, NB - 1), bg = 16 * bt0 + bc, n = bs < NB ? s_len[bc] : 0;
       const unsigned off = (unsigned)(bg * S + sr);
       if (s0 > 0) rows(s0, 0);
+      LOOP_PHASE();
       float sv[QT];
       loop_words_issue<QT>(loop_global(a->scores) + (size_t)j * Bp * S, 4 * tps, 4 * off, sr, tps, n, sv, true);
       loop_words_settle<QT>(loop_global(a->scores) + (size_t)j * Bp * S, 4 * tps, 4 * off, sv, dead, gave_up, ticks);
@@ -555,6 +558,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void loop_fwd_kernel(LoopFwdArgs a
       float* const sc = loop_global(a->scores) + ((size_t)j * Bp + bg) * S;
       Frag<T> hv[NQ];
       key_rows(t, part, n);
+      LOOP_PHASE();
       const T* hrow = ht + (size_t)(bg >> 4) * ns * 512 + (bg & 15) * 8;
       auto piece = [&](int q, unsigned zero) {                     // (a lane beyond the row's end repeats the first)
         const int p = (8 * ln + 512 * q < H ? ln + 64 * q : 0) + (int)zero;
