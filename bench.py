@@ -22,12 +22,12 @@ if ROOT not in sys.path:
 from paper_1802_07170_amd import inputs as I  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
-# HBM bytes per launch of the timed kernel from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE),
-# scaled by what the same counters read for a plain 256 MiB copy (x2 and x1) and with the clears and copies that belong to it: the summary under
-# profiles/ gives the commands and the figures.  Valid for the workload and the kernel source it was
+# Memory-side bytes per launch of the timed kernel from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE),
+# scaled by what the same counters read for a plain 256 MiB copy (x2 and x1) and with the clears and copies that belong to
+# it: the summary under profiles/ gives the commands and the figures.  Valid for the workload and the kernel source it was
 # measured with: (workload, first 12 hex digits of the sha256 of LOOP_KERNEL_SOURCES) -> bytes;
-# with another source the figure is stale and reported as null.
-MEASURED_TRAFFIC_BYTES = {}      # profiles/loop_kernels_medium_bf16_memory_counters.md
+# with another source the figure is stale and left out.
+MEASURED_TRAFFIC_BYTES = {("medium", "7107f947bb2a"): 4400978784}      # profiles/loop_kernels_medium_bf16_memory_counters.md
 
 # the timed kernel's file and what it includes
 LOOP_KERNEL_SOURCES = ("loop.hip", "loop_fwd.h", "loop_core.h", "recur_core.h", "recur_plan.h", "cell.h", "common.h", "kernels.h")

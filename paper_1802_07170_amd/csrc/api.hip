@@ -191,8 +191,9 @@ struct cmt_handle {
   int kb_bwd_dec = 0;                   // the layers' backward GEMMs
   // Workgroup caps of the second stream's GEMMs (weight gradients; dW_o), 0 = none (env CMT_SIDE_WGS, CMT_SIDE_WGS_WO).  A cap leaves
   // part of the chip to the kernels of the caller's stream, which paid while the decoder's loops were chains of short launches
-  // beside them; a loop that takes the whole chip waits for them instead.  Step time with a cap of 128 / without, ms: medium 6.68 /
-  // 6.54, attn 5.42 / 5.29, paper_512x2 2.64 / 2.57, small (fp32) 4.52 / 4.52; at 128 sentences (large) 20.7 / 20.2.
+  // beside them; a loop that takes the whole chip waits for them instead.  Step time with a cap of 128 / without, ms: medium 6.01 /
+  // 6.04, attn 5.02 / 4.92, small (fp32) 6.43 / 6.39; at 128 sentences (large) 19.6 / 19.0; with the update paper_512x2 2.64 / 2.58,
+  // paper_1024x2 4.38 / 4.24.
   int side_wgs = 0, side_wgs_wo = 0;
   int wc_whole_k = 1;                   // fused decoder loop: dpre W_c with the whole k range per workgroup (env CMT_WC_WHOLE_K)
   // decoder's backward loop with the whole-k step GEMM and the consumer in its epilogue (env CMT_BWD_FUSED, bit 1), up

@@ -287,7 +287,7 @@ struct SeqFwdDir {
 // ticket: two words, zero before the launch (roles taken; whether a wait was given up); wait_ticks is set by the launcher;
 // *again counts the launches that were made again because of that
 struct SeqFwdArgs { SeqFwdDir d[2]; int* ticket; int wait_ticks; int* again; };
-constexpr int SEQ_TICKETS = 64;           // two words per launch: 18 for the encoder's recurrences, then the decoder's loops
+constexpr int SEQ_TICKETS = 64;           // two words per launch: 16 for the encoder's recurrences (8 layers), then the decoder's loops
 constexpr int LOOP_TICKET_FWD = 32, LOOP_TICKET_BWD = 34;
 inline size_t seq_exchange_elems(int slots, int Bp, int Hh) { return (size_t)slots * Bp * ((Hh + 31) / 32 * 32); }
 // Backward of the same: builds the gate gradients of every position.

@@ -13,8 +13,10 @@
 // measured, 0.85 at that rate), then 0.65 until the sums have met, 0.5 the cells, 0.7 until a store can be seen.  So the recurrent
 // half is read while the layer below is still being exchanged.  Narrow layers are bound by the exchange alone: width 512, 2 layers,
 // 32 sentences 9 us a position (21).  Backward 36 us (54) and 15 us (24): a layer is two exchanges there.
-// Whole steps with everything else alike, launch per step | one launch, ms: medium 8.33 | 6.45, attn 7.68 | 5.10, small (fp32) 8.99 | 6.45, 336 units x 3 layers, 23
-// sentences 2.99 | 1.92, large 21.9 | 20.3; forward-only evaluation of medium 3.17 | 2.20.
+// Counted (64 | 128 sentences, width 1024): a CU's L1 takes 1.38 | 2.85 MB a position from L2 forward, 9 of 20.8 | 19 of 51 us at 64 bytes
+// a clock, and 1.00 | 2.03 MB backward, 6.5 of 36 | 13 of 59 us: volume is less than half of either, the rest are the exchanges.
+// Whole steps with everything else alike, launch per step | one launch, ms: medium 8.33 | 6.45, attn 7.68 | 5.10, small (fp32)
+// 8.99 | 6.45, 336 units x 3 layers, 23 sentences 2.99 | 1.92, large 21.9 | 20.3; forward-only evaluation of medium 3.17 | 2.20.
 //
 // The waits are bounded, and a launch behind each loop makes it again without waits where one was given up, as the encoder's
 // recurrences have it; loops of several streams are kept apart (section_gate.h).

@@ -796,8 +796,9 @@ static void loop_fwd_go(int prec, const LoopFwdArgs& args, int L, int T, int Bp,
   const LoopPlan p = loop_plan(prec, L, Bp, H, S, std::min(run.cus, 256));
   LoopFwdArgs a = args;
   a.wait_ticks = run.mode == SEQ_RUN_GIVE_UP ? 0 : RECUR_WAIT_TICKS;
-  // s_sleep units before the input of a layer above the bottom one is looked for, where the reading of its recurrent half does not take as long as the exchange: whole
-  // evaluations with 0 | 16 units, us: attn 1874 | 1770, paper_512x2 846 | 809, 336 units x 3 layers 714 | 669, medium 2216 | 2268.
+  // s_sleep units before the input of a layer above the bottom one is looked for, where the reading of its recurrent half does not take
+  // as long as the exchange: whole evaluations with 0 | 16 units, us: attn 1874 | 1770, paper_512x2 846 | 809, 336 units x 3 layers
+  // 714 | 669, medium 2216 | 2268.
   const int nap = p.nk * p.bt < 16 ? 16 : 0;
   const dim3 grid(p.groups * p.nwg), block(64 * LOOP_WAVES);
   // (decoding networks of one or two layers: the registers that more would take hold tiles of W_o on their way)
