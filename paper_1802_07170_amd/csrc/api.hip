@@ -1106,10 +1106,10 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
       n_dbo += (Mc + 63) / 64;
       stream_after(h, sd, st);
       launch_gemm_nt(p, dz, V, h->WoT, V, Mc, H, V, h->dHoCE + (size_t)m0 * H, nullptr, H, nullptr, 0, st, h->gsplit,
-                     h->gsplit_floats, lim, 1);                           // dH_o[slab] = dz W_o
+                     h->gsplit_floats, lim, 1, 0, 1);                     // dH_o[slab] = dz W_o
       // dW_o (+)= dz^T H_o[slab]; the first slab always holds a row, so W_o's gradient is always written
       launch_gemm_nt(p, dzT, h->ce_pitch, h->HocT + (size_t)m0 * esz, Mt, V, H, Mc, G + h->off_Wo, nullptr, H, nullptr, sl > 0,
-                     sd, nullptr, 0, lim, 2, sd != st ? h->side_wgs_wo : 0);
+                     sd, nullptr, 0, lim, 2, sd != st ? h->side_wgs_wo : 0, 1);
       if (sd != st) {
         done[sl] = h->ev[h->ev_next++ % h->ev.size()];
         (void)hipEventRecord(done[sl], sd);

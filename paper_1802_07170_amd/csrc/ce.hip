@@ -16,37 +16,41 @@
 
 namespace cmt {
 
-using CeG = GemmBig;                                      // 256 x 256 logit tile, 16 wavefronts of 64 x 64
-int ce_num_partials(int V) { return 4 * ((V + CeG::BN - 1) / CeG::BN); }
+// logit tile: 256 vocabulary rows x 256 (fp32: 128) positions, wavefronts of 64 x 64
+constexpr int CE_BM = 256;
+int ce_num_partials(int V) { return 4 * ((V + CE_BM - 1) / CE_BM); }
 
 // The tile is computed transposed — vocabulary rows on the matrix cores' row side, target positions
 // on the column side — so that in the accumulator layout a lane holds 32 vocabulary entries of ONE
 // target position (two 32x32 tiles x 16 registers) and the other 32 of the wavefront's 64 sit in the
 // lane 32 away: the row statistics need one cross-lane exchange instead of a 32-lane butterfly.
 template <typename T>
-__global__ __launch_bounds__(CeG::NT) void ce_fwd_kernel(const T* __restrict__ Ho, int ldho, const T* __restrict__ Wo,
+__global__ __launch_bounds__(GemmBig<T>::NT) void ce_fwd_kernel(const T* __restrict__ Ho, int ldho, const T* __restrict__ Wo,
                                                          const float* __restrict__ Bo, const int32_t* __restrict__ labels,
                                                          int M, int V, int H, T* __restrict__ ET, int ldet,
                                                          float* __restrict__ pmax, float* __restrict__ psum,
                                                          float* __restrict__ psz, float* __restrict__ zy, int np, RowLimit lim) {
+  using CeG = GemmBig<T>;
+  static_assert(CeG::BM == CE_BM && CeG::TA == 2 && CeG::TB == 2, "groups of 64 entries x 64 positions per wavefront");
   __shared__ __align__(16) char smem[CeG::SMEM_BYTES];    // main-loop stages; afterwards the staged e tile
   if (lim.n) M = min(M, max(*lim.n - lim.base, 0));       // rows that exist (uniform over the grid)
   if (M <= 0) return;
   int v0, r0;                                             // tile: vocabulary rows v0.., target positions r0..
   if (!gemm_tile_of_block((V + CeG::BM - 1) / CeG::BM, (M + CeG::BN - 1) / CeG::BN, CeG::BM, CeG::BN, v0, r0)) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wm = w >> 2, wn = w & 3;
+  const int wm = w / CeG::WN, wn = w % CeG::WN;
   // the accumulators start from the bias of their vocabulary entries, so the main loop leaves the logits
   v16f acc[2][2];
+  gemm_mainloop<T, CeG::WM, CeG::WN, 2, 2, GEMM_F32_ONE_SUM>(Wo, H, Ho, ldho, V, M, H, v0, r0, acc, smem, [&](v16f (&acc)[2][2]) {   // ends with a barrier: LDS is free
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
+    for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int v = v0 + wm * 64 + mt * 32 + acc32_row(lane, i);
-      const float bv = v < V ? Bo[v] : 0.f;
-      acc[mt][0][i] = bv; acc[mt][1][i] = bv;
-    }
-  gemm_mainloop<T, 4, 4, 2, 2, 128, false>(Wo, H, Ho, ldho, V, M, H, v0, r0, acc, smem);   // ends with a barrier: LDS is free
+      for (int i = 0; i < 16; ++i) {
+        const int v = v0 + wm * 64 + mt * 32 + acc32_row(lane, i);
+        const float bv = v < V ? Bo[v] : 0.f;
+        acc[mt][0][i] = bv; acc[mt][1][i] = bv;
+      }
+  });
   const int pidx = (v0 >> 6) + wm;                        // this wavefront's group of 64 vocabulary entries
   // e leaves through LDS: every wavefront stages its 64 vocabulary entries x 64 (fp32: 32) target positions
   // and writes them out as whole rows of E^T — 128 contiguous bytes per row instead of the 64-byte pieces of
@@ -54,7 +58,7 @@ __global__ __launch_bounds__(CeG::NT) void ce_fwd_kernel(const T* __restrict__ H
   constexpr int NTS = sizeof(T) == 2 ? 2 : 1;             // 32-position halves staged together
   constexpr int SROW = 32 * NTS * (int)sizeof(T) + 16;    // staged row pitch in bytes (padded against bank conflicts)
   char* stage = smem + w * (64 * SROW);
-  static_assert(16 * 64 * SROW <= CeG::SMEM_BYTES, "staging area exceeds the kernel's LDS");
+  static_assert(CeG::NT * SROW <= CeG::SMEM_BYTES, "staging area exceeds the kernel's LDS");
   // The epilogue handles 64 logits per lane with a handful of vector instructions each (it is bound by their
   // count, not by memory): the vocabulary bound is tested only in the tile that contains it, the label's logit is
   // picked outside the loops, and the 16-bit path uses the hardware exponential and the packed bf16 conversion.
@@ -150,14 +154,15 @@ __global__ __launch_bounds__(CeG::NT) void ce_fwd_kernel(const T* __restrict__ H
 void launch_ce_fwd(int prec, const void* Ho, int ldho, const void* Wo, const float* Bo, const int32_t* labels,
                    int M, int V, int H, void* ET, int pitch, float* pmax, float* psum, float* psz, float* zy, hipStream_t st,
                    RowLimit lim) {
-  const int ntv = (V + CeG::BM - 1) / CeG::BM, ntr = (M + CeG::BN - 1) / CeG::BN;
+  const int bn = prec ? GemmBig<bf16_t>::BN : GemmBig<float>::BN;
+  const int ntv = (V + CE_BM - 1) / CE_BM, ntr = (M + bn - 1) / bn;
   const int grid = ((ntv * ntr + 7) / 8) * 8;
   const int np = ce_num_partials(V);
   if (prec)
-    hipLaunchKernelGGL(ce_fwd_kernel<bf16_t>, dim3(grid), dim3(CeG::NT), 0, st, (const bf16_t*)Ho, ldho, (const bf16_t*)Wo, Bo,
+    hipLaunchKernelGGL(ce_fwd_kernel<bf16_t>, dim3(grid), dim3(GemmBig<bf16_t>::NT), 0, st, (const bf16_t*)Ho, ldho, (const bf16_t*)Wo, Bo,
                        labels, M, V, H, (bf16_t*)ET, pitch, pmax, psum, psz, zy, np, lim);
   else
-    hipLaunchKernelGGL(ce_fwd_kernel<float>, dim3(grid), dim3(CeG::NT), 0, st, (const float*)Ho, ldho, (const float*)Wo, Bo,
+    hipLaunchKernelGGL(ce_fwd_kernel<float>, dim3(grid), dim3(GemmBig<float>::NT), 0, st, (const float*)Ho, ldho, (const float*)Wo, Bo,
                        labels, M, V, H, (float*)ET, pitch, pmax, psum, psz, zy, np, lim);
 }
 

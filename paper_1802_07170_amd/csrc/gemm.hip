@@ -16,8 +16,8 @@ namespace cmt {
 // that the medium tile only with a round of workgroups and a k to spread its prologue and store over: 200 medium tiles
 // 25.8 | 27.3 (k 1024; 1472 x 2048, k 512: 16.5 | 9.9), 100 (3200 x 1024, k 1024) 21.5 | 15.3, (1472 x 1024, k 512) 16.1 | 7.6,
 // one or two tiles 11 | 5; rows or columns that fit a small tile (16 x 32000, k 1024) 17.5 | 12.3.
-// fp32 (matrix-core bound, the shape hardly matters once the chip is full): 400 medium tiles 78 | 76, 200 (3200 x 1024, k 512)
-// 48 | 46, 100 46 | 24, two 21 | 7.7.
+// fp32 (256 x 128 | 64 x 64, bound by the matrix cores): 208 big tiles (3200 x 2048, k 512) 51 | 62, 104 (3200 x 1024) 46 | 38; 128 x 128 in
+// between 38, and 54 against 32 at 1000 x 1000, k 1000: no such tile.
 static int env_int(const char* name, int dflt) {
   const char* e = getenv(name);
   return e && *e ? atoi(e) : dflt;
@@ -33,29 +33,30 @@ static const int GEMM_BIGSPLIT_MAX_TILES = env_int("CMT_GEMM_BIGSPLIT_MAX_TILES"
 
 // the 64 x 64 tile instead of the 128 x 128 one, of which there would be `tiles`
 static bool gemm_small_tile(int prec, long tiles, int M, int N, int K) {
-  if (!prec) return tiles < 512;
-  return tiles < 192 || K < 1024 || M <= GemmSmall::BM || N <= GemmSmall::BN;
+  if (!prec) return true;
+  return tiles < 192 || K < 1024 || M <= GemmSmall<bf16_t>::BM || N <= GemmSmall<bf16_t>::BN;
 }
 
 // Number of k splits when the row count is known to the device alone: as many as make one round of workgroups
-// over the chip's 256 CUs out of the tiles that exist, at most the launched number.  The kernel and the plane
+// (fp32, whose tiles are half as large: two) over the chip's 256 CUs out of the tiles that exist, at most the launched number.  The kernel and the plane
 // sum both derive it from the same count.
-__host__ __device__ inline int gemm_dyn_splits(int tiles, int launched) {
-  const int ns = 256 / (tiles > 0 ? tiles : 1);
+#define GEMM_DYN_ROUNDS(prec) ((prec) ? 1 : 2)
+__host__ __device__ inline int gemm_dyn_splits(int tiles, int launched, int rounds) {
+  const int ns = 256 * rounds / (tiles > 0 ? tiles : 1);
   return ns < 1 ? 1 : (ns > launched ? launched : ns);
 }
 
 // One output tile (the one of virtual workgroup id vb) of C (+)= A B^T (+ bias): main loop and store.
-template <typename T, int WM, int WN, int TA, int TB, int KB>
+template <typename T, int WM, int WN, int TA, int TB, bool CHAIN>
 __device__ __forceinline__ void gemm_nt_tile(const T* __restrict__ A, int lda, const T* __restrict__ B, int ldb, int M, int N, int K,
                                              float* __restrict__ Cf0, T* __restrict__ Ct, int ldc, const float* __restrict__ bias,
                                              int accumulate, int ntn, int kchunk, size_t plane_stride, int dyn_split, int vb,
                                              char* smem) {
-  using G = GemmTile<WM, WN, TA, TB, KB>;
+  using G = GemmTile<T, WM, WN, TA, TB>;
   int m0, n0;
   if (!gemm_tile_of_block((M + G::BM - 1) / G::BM, ntn, G::BM, G::BN, m0, n0, vb)) return;
   if (dyn_split) {                                 // the number of k splits follows the tiles that exist: one round of workgroups
-    const int ns = gemm_dyn_splits((M + G::BM - 1) / G::BM * ntn, gridDim.y);
+    const int ns = gemm_dyn_splits((M + G::BM - 1) / G::BM * ntn, gridDim.y, GEMM_DYN_ROUNDS(sizeof(T) == 2));
     if ((int)blockIdx.y >= ns) return;
     kchunk = ((K + ns - 1) / ns + 63) / 64 * 64;
   }
@@ -63,7 +64,7 @@ __device__ __forceinline__ void gemm_nt_tile(const T* __restrict__ A, int lda, c
   const int klen = min(kchunk, K - k0);
   if (klen <= 0 && gridDim.y == 1) return;
   v16f acc[TA][TB];
-  gemm_mainloop<T, WM, WN, TA, TB, KB>(A + k0, lda, B + k0, ldb, M, N, klen, m0, n0, acc, smem);
+  gemm_mainloop<T, WM, WN, TA, TB, CHAIN ? GEMM_F32_CHAIN : GEMM_F32_SPLIT>(A + k0, lda, B + k0, ldb, M, N, klen, m0, n0, acc, smem, GemmZero{});
   float* const Cf = gridDim.y > 1 ? Cf0 + blockIdx.y * plane_stride : Cf0;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wm = w / WN, wn = w % WN;
@@ -93,13 +94,13 @@ __device__ __forceinline__ void gemm_nt_tile(const T* __restrict__ A, int lda, c
 // WALK: the launch has fewer workgroups than tiles (it is to leave part of the chip to other streams) and every
 // workgroup walks the tiles of the virtual ids blockIdx.x, blockIdx.x + grid, ...  It is a variant of its own because
 // the loop costs the one-tile-per-workgroup kernel a spilled register.
-template <typename T, int WM, int WN, int TA, int TB, int KB, bool WALK = false>
+template <typename T, int WM, int WN, int TA, int TB, bool WALK = false, bool CHAIN = false>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_kernel(const T* __restrict__ A, int lda, const T* __restrict__ B, int ldb,
                                                                int M, int N, int K, float* __restrict__ Cf0, T* __restrict__ Ct,
                                                                int ldc, const float* __restrict__ bias, int accumulate, int ntn,
                                                                int kchunk, size_t plane_stride, RowLimit lim, int lim_kind,
                                                                int dyn_split) {
-  using G = GemmTile<WM, WN, TA, TB, KB>;
+  using G = GemmTile<T, WM, WN, TA, TB>;
   __shared__ __align__(16) char smem[G::SMEM_BYTES];
   if (lim.n) {                                     // a bound that only the device knows (uniform over the grid)
     const int e = max(*lim.n - lim.base, 0);
@@ -110,12 +111,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_kernel(const T* __restri
   if constexpr (WALK) {
     const int ntiles8 = (((M + G::BM - 1) / G::BM * ntn + 7) >> 3) << 3;
     for (int vb = blockIdx.x; vb < ntiles8; vb += gridDim.x) {
-      gemm_nt_tile<T, WM, WN, TA, TB, KB>(A, lda, B, ldb, M, N, K, Cf0, Ct, ldc, bias, accumulate, ntn, kchunk, plane_stride, dyn_split,
+      gemm_nt_tile<T, WM, WN, TA, TB, CHAIN>(A, lda, B, ldb, M, N, K, Cf0, Ct, ldc, bias, accumulate, ntn, kchunk, plane_stride, dyn_split,
                                           vb, smem);
       __syncthreads();                             // (the next tile refills the LDS)
     }
   } else {
-    gemm_nt_tile<T, WM, WN, TA, TB, KB>(A, lda, B, ldb, M, N, K, Cf0, Ct, ldc, bias, accumulate, ntn, kchunk, plane_stride, dyn_split,
+    gemm_nt_tile<T, WM, WN, TA, TB, CHAIN>(A, lda, B, ldb, M, N, K, Cf0, Ct, ldc, bias, accumulate, ntn, kchunk, plane_stride, dyn_split,
                                         (int)blockIdx.x, smem);
   }
 }
@@ -126,9 +127,9 @@ template <int VEC>
 __global__ __launch_bounds__(256) void gemm_planes_sum_kernel(const float* __restrict__ planes, int np, size_t stride,
                                                               float* __restrict__ out, int M, int N, int ldc,
                                                               const float* __restrict__ bias, int accumulate, RowLimit lim,
-                                                              int dyn_bm, int dyn_ntn) {
+                                                              int dyn_bm, int dyn_ntn, int dyn_rounds) {
   if (lim.n) M = min(M, max(*lim.n - lim.base, 0));
-  if (dyn_bm) np = gemm_dyn_splits((M + dyn_bm - 1) / dyn_bm * dyn_ntn, np);   // the planes the GEMM wrote
+  if (dyn_bm) np = gemm_dyn_splits((M + dyn_bm - 1) / dyn_bm * dyn_ntn, np, dyn_rounds);   // the planes the GEMM wrote
   const unsigned nq = (unsigned)N / VEC;                  // column groups per row
   const size_t n = (size_t)M * nq;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
@@ -155,44 +156,51 @@ __global__ __launch_bounds__(256) void gemm_planes_sum_kernel(const float* __res
 }
 
 static void launch_planes_sum(const float* planes, int nks, size_t pstride, float* Cf, int M, int N, int ldc, const float* bias,
-                              int accumulate, RowLimit rl, hipStream_t st, int dyn_bm = 0, int dyn_ntn = 0) {
+                              int accumulate, RowLimit rl, hipStream_t st, int dyn_bm = 0, int dyn_ntn = 0, int dyn_rounds = 0) {
   const bool vec = N % 4 == 0 && ldc % 4 == 0 && pstride % 4 == 0 && ((size_t)Cf | (size_t)planes | (size_t)bias) % 16 == 0;
   size_t g = (pstride / (vec ? 4 : 1) + 255) / 256;
   if (g > 4096) g = 4096;
   if (vec)
     hipLaunchKernelGGL(gemm_planes_sum_kernel<4>, dim3((unsigned)g), dim3(256), 0, st, planes, nks, pstride, Cf, M, N, ldc, bias,
-                       accumulate, rl, dyn_bm, dyn_ntn);
+                       accumulate, rl, dyn_bm, dyn_ntn, dyn_rounds);
   else
     hipLaunchKernelGGL(gemm_planes_sum_kernel<1>, dim3((unsigned)g), dim3(256), 0, st, planes, nks, pstride, Cf, M, N, ldc, bias,
-                       accumulate, rl, dyn_bm, dyn_ntn);
+                       accumulate, rl, dyn_bm, dyn_ntn, dyn_rounds);
 }
 
 template <typename T, int WM, int WN, int TA, int TB>
 static void gemm_go(dim3 grid, hipStream_t st, const void* A, int lda, const void* B, int ldb, int M, int N, int K, float* out,
                     void* Ct, int ldc, const float* bias, int acc, int ntn, int kchunk, size_t pstride, RowLimit lim, int lim_kind,
-                    int dyn_split = 0, int wg_cap = 0) {
-  if (wg_cap > 0 && (int)grid.x > (wg_cap + 7) / 8 * 8) {
-    grid.x = (wg_cap + 7) / 8 * 8;
-    hipLaunchKernelGGL((gemm_nt_kernel<T, WM, WN, TA, TB, 128, true>), grid, dim3(64 * WM * WN), 0, st, (const T*)A, lda, (const T*)B, ldb,
-                       M, N, K, out, (T*)Ct, ldc, bias, acc, ntn, kchunk, pstride, lim, lim_kind, dyn_split);
-    return;
-  }
-  hipLaunchKernelGGL((gemm_nt_kernel<T, WM, WN, TA, TB, 128>), grid, dim3(64 * WM * WN), 0, st, (const T*)A, lda, (const T*)B, ldb,
-                     M, N, K, out, (T*)Ct, ldc, bias, acc, ntn, kchunk, pstride, lim, lim_kind, dyn_split);
+                    int dyn_split = 0, int wg_cap = 0, int chain = 0) {
+  const bool walk = wg_cap > 0 && (int)grid.x > (wg_cap + 7) / 8 * 8;
+  if (walk) grid.x = (wg_cap + 7) / 8 * 8;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * WM * WN), 0, st, (const T*)A, lda, (const T*)B, ldb, M, N, K, out, (T*)Ct, ldc, bias, acc, ntn,
+                       kchunk, pstride, lim, lim_kind, dyn_split);
+  };
+  if constexpr (sizeof(T) == 4)
+    if (chain) {
+      if (walk) go(gemm_nt_kernel<T, WM, WN, TA, TB, true, true>);
+      else go(gemm_nt_kernel<T, WM, WN, TA, TB, false, true>);
+      return;
+    }
+  if (walk) go(gemm_nt_kernel<T, WM, WN, TA, TB, true>);
+  else go(gemm_nt_kernel<T, WM, WN, TA, TB>);
 }
 
 void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                     float* Cf, void* Ct, int ldc, const float* bias, int accumulate, hipStream_t st,
-                    float* split_scratch, size_t split_scratch_floats, RowLimit lim, int lim_kind, int wg_cap) {
+                    float* split_scratch, size_t split_scratch_floats, RowLimit lim, int lim_kind, int wg_cap, int chain) {
   if (M <= 0 || N <= 0) return;
   // enough 256 x 256 tiles to fill the chip: the big tile (half the L2 traffic per flop)
-  const int ntm_b = (M + GemmBig::BM - 1) / GemmBig::BM, ntn_b = (N + GemmBig::BN - 1) / GemmBig::BN;
+  const int bn_b = prec ? GemmBig<bf16_t>::BN : GemmBig<float>::BN;
+  const int ntm_b = (M + GemmBig<bf16_t>::BM - 1) / GemmBig<bf16_t>::BM, ntn_b = (N + bn_b - 1) / bn_b;
   // (of rows that only the device counts, the valid target positions, some 60 - 75 % exist)
   const bool counted = lim.n && lim_kind == 1;
   if (ntm_b * ntn_b >= (counted ? GEMM_BIG_MIN_TILES * 5 / 3 : GEMM_BIG_MIN_TILES)) {
     const int grid = ((ntm_b * ntn_b + 7) / 8) * 8;
     if (prec) gemm_go<bf16_t, 4, 4, 2, 2>(dim3(grid, 1), st, A, lda, B, ldb, M, N, K, Cf, Ct, ldc, bias, accumulate, ntn_b, K, 0, lim, lim_kind, 0, wg_cap);
-    else gemm_go<float, 4, 4, 2, 2>(dim3(grid, 1), st, A, lda, B, ldb, M, N, K, Cf, Ct, ldc, bias, accumulate, ntn_b, K, 0, lim, lim_kind, 0, wg_cap);
+    else gemm_go<float, 4, 2, 2, 2>(dim3(grid, 1), st, A, lda, B, ldb, M, N, K, Cf, Ct, ldc, bias, accumulate, ntn_b, K, 0, lim, lim_kind, 0, wg_cap, chain);
     return;
   }
   // a long contraction over few output tiles (dH_o = dz W_o: k = the vocabulary): big tiles with k split into
@@ -208,16 +216,16 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
       const int nks = dyn ? ks : (K + kchunk - 1) / kchunk;
       const size_t pstride = (size_t)M * N;
       const int grid = ((ntm_b * ntn_b + 7) / 8) * 8;
-      if (prec) gemm_go<bf16_t, 4, 4, 2, 2>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, split_scratch, nullptr, N, nullptr, 0, ntn_b, kchunk, pstride, lim, lim_kind, dyn, wg_cap);
-      else gemm_go<float, 4, 4, 2, 2>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, split_scratch, nullptr, N, nullptr, 0, ntn_b, kchunk, pstride, lim, lim_kind, dyn, wg_cap);
+      if (prec) gemm_go<bf16_t, 4, 4, 2, 2>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, split_scratch, nullptr, N, nullptr, 0, ntn_b, kchunk, pstride, lim, lim_kind, dyn, wg_cap, chain);
+      else gemm_go<float, 4, 2, 2, 2>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, split_scratch, nullptr, N, nullptr, 0, ntn_b, kchunk, pstride, lim, lim_kind, dyn, wg_cap, chain);
       launch_planes_sum(split_scratch, nks, pstride, Cf, M, N, ldc, bias, accumulate, lim_kind == 1 ? lim : RowLimit{}, st,
-                        dyn ? GemmBig::BM : 0, ntn_b);
+                        dyn ? GemmBig<bf16_t>::BM : 0, ntn_b, GEMM_DYN_ROUNDS(prec));
       return;
     }
   }
-  const auto medium = [&](int d) { return (d + GemmMedium::BM - 1) / GemmMedium::BM; };
+  const auto medium = [&](int d) { return (d + GemmMedium<bf16_t>::BM - 1) / GemmMedium<bf16_t>::BM; };
   const bool small = gemm_small_tile(prec, (long)medium(M) * medium(N), M, N, K);
-  const int bm = small ? GemmSmall::BM : GemmMedium::BM;
+  const int bm = small ? GemmSmall<bf16_t>::BM : GemmMedium<bf16_t>::BM;
   const int ntm = (M + bm - 1) / bm, ntn = (N + bm - 1) / bm;
   const int nb = ntm * ntn;
   const int grid = ((nb + 7) / 8) * 8;
@@ -242,14 +250,14 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
   auto go = [&](auto type, auto shape) {
     using T = decltype(type);
     if constexpr (decltype(shape)::value == 1)
-      gemm_go<T, 2, 2, 1, 1>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, cap);
+      gemm_go<T, 2, 2, 1, 1>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, cap, chain);
     else
-      gemm_go<T, 2, 2, 2, 2>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, cap);
+      gemm_go<T, 2, 2, 2, 2>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, cap, chain);
   };
   using One = std::integral_constant<int, 1>;
   using Two = std::integral_constant<int, 2>;
   if (prec) { if (small) go(bf16_t{}, One{}); else go(bf16_t{}, Two{}); }
-  else { if (small) go(float{}, One{}); else go(float{}, Two{}); }
+  else go(float{}, One{});
   if (nks > 1) launch_planes_sum(split_scratch, nks, pstride, Cf, M, N, ldc, bias, accumulate, lim_kind == 1 ? lim : RowLimit{}, st);
 }
 
@@ -258,7 +266,7 @@ struct GemmGroupArgs { int n; int tile_start[GEMM_GROUP_MAX + 1]; GemmProb p[GEM
 
 template <typename T, int WM, int WN, int TA, int TB>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_group_kernel(GemmGroupArgs g) {
-  using G = GemmTile<WM, WN, TA, TB, 128>;
+  using G = GemmTile<T, WM, WN, TA, TB>;
   __shared__ __align__(16) char smem[G::SMEM_BYTES];
   // the workgroups walk the tile queue: workgroup v takes the tiles of the virtual ids v, v + grid, v + 2 grid, ...
   // (the grid is a multiple of 8, so a workgroup stays with the tile range of its XCD); a grid as large as the
@@ -274,7 +282,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_group_kernel(GemmGroupAr
   int m0, n0;
   gemm_tile_from_index(id - g.tile_start[q], (M + G::BM - 1) / G::BM, (N + G::BN - 1) / G::BN, G::BM, G::BN, m0, n0);
   v16f acc[TA][TB];
-  gemm_mainloop<T, WM, WN, TA, TB, 128>((const T*)pr.A, pr.lda, (const T*)pr.B, pr.ldb, M, N, pr.K, m0, n0, acc, smem);
+  gemm_mainloop<T, WM, WN, TA, TB>((const T*)pr.A, pr.lda, (const T*)pr.B, pr.ldb, M, N, pr.K, m0, n0, acc, smem, GemmZero{});
   __syncthreads();                                        // (the next tile of a walking workgroup refills the LDS)
   float* __restrict__ C = pr.C;
   const int accumulate = pr.accumulate;
@@ -300,7 +308,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_group_kernel(GemmGroupAr
 
 template <typename T, int WM, int WN, int TA, int TB>
 static void gemm_group_go(const GemmProb* probs, int n, hipStream_t st, int wg_cap) {
-  using G = GemmTile<WM, WN, TA, TB, 128>;
+  using G = GemmTile<T, WM, WN, TA, TB>;
   for (int c0 = 0; c0 < n; c0 += GEMM_GROUP_MAX) {
     GemmGroupArgs g{};
     g.n = std::min(GEMM_GROUP_MAX, n - c0);
@@ -334,8 +342,8 @@ void launch_gemm_nt_group(int prec, const GemmProb* probs, int n, hipStream_t st
   for (int i = 0; i < n; ++i) {
     if (probs[i].M <= 0 || probs[i].N <= 0) continue;
     live.push_back(probs[i]);
-    big += (long)((probs[i].M + GemmBig::BM - 1) / GemmBig::BM) * ((probs[i].N + GemmBig::BN - 1) / GemmBig::BN);
-    medium += (long)((probs[i].M + GemmMedium::BM - 1) / GemmMedium::BM) * ((probs[i].N + GemmMedium::BN - 1) / GemmMedium::BN);
+    big += (long)((probs[i].M + GemmBig<bf16_t>::BM - 1) / GemmBig<bf16_t>::BM) * ((probs[i].N + GemmBig<bf16_t>::BN - 1) / GemmBig<bf16_t>::BN);
+    medium += (long)((probs[i].M + GemmMedium<bf16_t>::BM - 1) / GemmMedium<bf16_t>::BM) * ((probs[i].N + GemmMedium<bf16_t>::BN - 1) / GemmMedium<bf16_t>::BN);
   }
   if (live.empty()) return;
   // the tile by the number of them over the whole group (k is the batch's positions: long)

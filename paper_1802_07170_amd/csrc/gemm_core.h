@@ -10,30 +10,35 @@
 //   * 4x4 wavefronts, 2x2 tiles each: 256 x 256, 1024 threads, 144 KB of LDS, one workgroup per CU.
 //     Half the L2 traffic per flop (64 KB per k tile): 1.3 PFLOP/s on large problems, and faster than the
 //     others from about 150 tiles up.
+// (fp32: the first, and 256 x 128 on 512 threads.)
 // What bounds both is the rate at which a CU takes data from L2: about 49 GB/s per CU measured with the main
 // loop's loads alone (12.6 TB/s over the chip), i.e. at most 1.6 PFLOP/s for the big tile and 0.8 for the small.
-// Tiles of KB bytes of k per row are double-buffered in LDS; the next tile's global loads are in
+// Tiles of k are double-buffered in LDS; the next tile's global loads are in
 // flight while the current one feeds the matrix cores.  16-bit operands go from global memory straight
 // into LDS (global_load_lds_dwordx4, no staging registers): rows of 128 bytes without padding, the
 // 16-byte chunks of a row XOR-swizzled by the row number so that fragment reads stay free of bank
-// conflicts (gemm_swz).  32-bit operands are staged through registers into rows padded by 16 bytes.
+// conflicts (gemm_swz).  32-bit operands are staged through registers, where each becomes three bf16 numbers whose
+// sum it is (gemm_mainloop_f32).
 #pragma once
 #include "common.h"
 
 namespace cmt {
 
-// KB = bytes of k per row and stage; LDS row pitch = KB + 16 (padding against bank conflicts)
-template <int WM, int WN, int TA, int TB, int KB = 128> struct GemmTile {
+// T's tile shape: WM x WN wavefronts of TA x TB tiles of 32 x 32.
+template <typename T, int WM_, int WN_, int TA_, int TB_> struct GemmTile {
+  static constexpr int WM = WM_, WN = WN_, TA = TA_, TB = TB_;
   static constexpr int NT = 64 * WM * WN;                  // threads
   static constexpr int BM = 32 * TA * WM, BN = 32 * TB * WN;
-  static constexpr int ROWB = KB + 16;
-  static constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB;
-  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-  static constexpr int SMEM_BYTES = 2 * STAGE_BYTES;
+  static constexpr int BK = 128 / (int)sizeof(T);          // k per stage
+  static constexpr int ROWB = BK * (int)sizeof(T) + 16;    // row pitch of the padded LDS image
+  static constexpr int STAGE_BYTES = (BM + BN) * ROWB;
+  static constexpr int SPLIT_BYTES = (BM + BN) * BK * 6;   // a stage of three bf16 planes
+  static constexpr int SMEM_BYTES = 2 * (sizeof(T) == 4 && SPLIT_BYTES > STAGE_BYTES ? SPLIT_BYTES : STAGE_BYTES);
 };
-using GemmSmall = GemmTile<2, 2, 1, 1, 128>;               // 64 x 64, 256 threads
-using GemmMedium = GemmTile<2, 2, 2, 2, 128>;              // 128 x 128, 256 threads
-using GemmBig = GemmTile<4, 4, 2, 2, 128>;                 // 256 x 256, 1024 threads
+template <typename T> using GemmSmall = GemmTile<T, 2, 2, 1, 1>;                     // 64 x 64, 256 threads
+template <typename T> using GemmMedium = GemmTile<T, 2, 2, 2, 2>;                    // 128 x 128, 256 threads
+// 256 x 256, 1024 threads; fp32, whose three planes are one and a half times the LDS: 256 x 128, 512 threads
+template <typename T> using GemmBig = GemmTile<T, 4, sizeof(T) == 2 ? 4 : 2, 2, 2>;
 
 // Workgroup id -> output tile.  Consecutive workgroup ids go round-robin to the 8 XCDs (each with
 // its own L2), so XCD x is given the contiguous range of tile numbers [x * per, (x + 1) * per); tile
@@ -156,22 +161,14 @@ __device__ __forceinline__ void gemm_dl_fill_tail(const bf16_t* __restrict__ bas
   }
 }
 
-template <int WM, int WN, int TA, int TB, bool ZERO>
+template <int WM, int WN, int TA, int TB>
 __device__ __forceinline__ void gemm_mainloop_dl(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
                                                  int M, int N, int K, int m0, int n0, v16f (&acc)[TA][TB], char* smem) {
   constexpr int NT = 64 * WM * WN, BM = 32 * TA * WM, BN = 32 * TB * WN;
   constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
-  static_assert(2 * STAGE <= GemmTile<WM, WN, TA, TB, 128>::SMEM_BYTES, "LDS image larger than the tile's allocation");
+  static_assert(2 * STAGE <= GemmTile<bf16_t, WM, WN, TA, TB>::SMEM_BYTES, "LDS image larger than the tile's allocation");
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = w / WN, wn = w % WN;
-  if (ZERO) {
-#pragma unroll
-    for (int a = 0; a < TA; ++a)
-#pragma unroll
-      for (int b = 0; b < TB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-  }
   unsigned oa[BM * 8 / NT], ob[BN * 8 / NT];
   gemm_dl_offsets<NT, BM>(lda, M, m0, oa);
   gemm_dl_offsets<NT, BN>(ldb, N, n0, ob);
@@ -217,31 +214,140 @@ __device__ __forceinline__ void gemm_mainloop_dl(const bf16_t* __restrict__ A, i
   }
 }
 
-// With w = wavefront index, wm = w / WN, wn = w % WN:
-// acc[a][b]: rows m0 + (wm*TA + a)*32 + acc32_row(lane,i), cols n0 + (wn*TB + b)*32 + lane%32
-// ZERO = false: the accumulators come in initialised by the caller (e.g. with a bias) and are added to.
-template <typename T, int WM, int WN, int TA, int TB, int KB, bool ZERO = true>
-__device__ __forceinline__ void gemm_mainloop(const T* __restrict__ A, int lda, const T* __restrict__ B, int ldb,
-                                              int M, int N, int K, int m0, int n0, v16f (&acc)[TA][TB], char* smem) {
-  if constexpr (sizeof(T) == 2 && KB == 128) {
-    gemm_mainloop_dl<WM, WN, TA, TB, ZERO>(A, lda, B, ldb, M, N, K, m0, n0, acc, smem);
-    return;
+// ---- 32-bit operands ----
+// fp32 products on the bf16 matrix cores, which are 16 times as fast: x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m,
+// all three bf16 and (round to nearest, 3 x 8 significant bits and their signs) without a remainder while l is a normal number, so that
+// a b = ha hb + (ha mb + ma hb) + (ha lb + la hb + ma mb) + what is below 2^-25 of |a b| and of either sign.  Six products of bf16
+// instead of one of fp32: 2.7 times the rate.  Error against 64 bits, relative (fp32 instructions | split): 3200 x 2048, k 512 4.0e-7 |
+// 1.1e-7; k 3200 4.6e-7 | 1.9e-7; gradients of 32 shapes of training steps 0.40 - 1.00 times as far off as they were.  REST: the five small
+// products go into a sum of their own.  In one sum with ha hb they are lost where that has grown large - and together, as what is
+// lost is much the same for every row of a coherent operand (bias gradients up to 2.6 times as far off).
+// It is bound by power as much as by instructions: 8192 x 8192, k 4096 128 TFLOP/s with fp32 instructions, 206 with the split
+// (1.24 PFLOP/s of bf16) at 1.8 GHz with the matrix cores busy 70 % of the time; k 512, 3200 x 2048 82 | 51 us.
+//
+// LDS image of a stage, per operand and plane: blocks of 32 rows x 16 k as the matrix cores take them, 1 KB [k half][row][8], rows
+// permuted by the k chunk so that neither the 8-byte stores (a quad of k of one row) nor the fragment reads meet bank conflicts.
+template <int BK> __device__ __forceinline__ int gemm_split_at(int r, int c /* chunk of 8 k */) {
+  return ((r >> 5) * (BK / 16) + (c >> 1)) * 1024 + (c & 1) * 512 + ((r & 31) ^ (c * (64 / BK))) * 16;
+}
+struct GemmSplit2 { uint32_t h, m, l; };
+__device__ __forceinline__ GemmSplit2 gemm_split2(float x, float y) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  GemmSplit2 s;
+  s.h = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));
+  x -= __uint_as_float(s.h << 16); y -= __uint_as_float(s.h & 0xffff0000u);
+  s.m = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));
+  x -= __uint_as_float(s.m << 16); y -= __uint_as_float(s.m & 0xffff0000u);
+  s.l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));
+  return s;
+}
+// A quad of k of row r, chunk half c (4 k each) -> the three planes of a tile of ROWS rows; top = the largest magnitude seen.
+template <int ROWS, int BK>
+__device__ __forceinline__ void gemm_split_store(char* tile, int r, int c, const float4& x, float& top) {
+  constexpr int PLANE = ROWS * BK * 2;
+  top = fmaxf(fmaxf(top, fabsf(x.x)), fabsf(x.y));
+  top = fmaxf(fmaxf(top, fabsf(x.z)), fabsf(x.w));
+  const GemmSplit2 a = gemm_split2(x.x, x.y), b = gemm_split2(x.z, x.w);
+  char* const at = tile + gemm_split_at<BK>(r, c >> 1) + (c & 1) * 8;
+  *reinterpret_cast<uint2*>(at) = make_uint2(a.h, b.h);
+  *reinterpret_cast<uint2*>(at + PLANE) = make_uint2(a.m, b.m);
+  *reinterpret_cast<uint2*>(at + 2 * PLANE) = make_uint2(a.l, b.l);
+}
+// A thread's pieces of a stage (16 bytes of one row each, first A's, then B's) are asked for two stages ahead and split one stage
+// ahead, piece by piece between the matrix instructions: those take 32 clocks each, the splitting of a piece some 27 others.
+// false: an operand is infinite or rounds to that in bf16, and the sums are to be made by gemm_mainloop_regs.  (A NaN stays one.)
+template <int WM, int WN, int TA, int TB, bool REST>
+__device__ __forceinline__ bool gemm_mainloop_f32(const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb,
+                                                  int M, int N, int K, int m0, int n0, v16f (&acc)[TA][TB], char* smem) {
+  using G = GemmTile<float, WM, WN, TA, TB>;
+  constexpr int NT = G::NT, BK = G::BK, CPR = BK / 4, RPP = NT / CPR, NA = G::BM / RPP, NP = NA + G::BN / RPP;
+  constexpr int A_PLANE = G::BM * BK * 2, B_PLANE = G::BN * BK * 2, STEPS = BK / 16 * 6;
+  if (K <= 0) return true;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int wm = w / WN, wn = w % WN, pr = threadIdx.x / CPR, pc = threadIdx.x % CPR;
+  unsigned off[NP];                                        // of the pieces' rows (rows beyond the last: the last, never stored)
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+    off[p] = p < NA ? (unsigned)(min(m0 + pr + RPP * p, M - 1) - m0) * (unsigned)lda : (unsigned)(min(n0 + pr + RPP * (p - NA), N - 1) - n0) * (unsigned)ldb;
+  const float* __restrict__ pa = A + (size_t)m0 * lda;
+  const float* __restrict__ pb = B + (size_t)n0 * ldb;
+  float4 x[NP];
+  auto load = [&](int p, int kt) {                         // (k beyond the last: the last, made zero when it is split)
+    const unsigned k = (unsigned)min(kt * BK + 4 * pc, K - 4);
+    x[p] = *reinterpret_cast<const float4*>((p < NA ? pa : pb) + (off[p] + k));
+  };
+  v16f rest[TA][TB];
+#pragma unroll
+  for (int a = 0; a < TA; ++a)
+#pragma unroll
+    for (int b = 0; b < TB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) rest[a][b][i] = 0.f;   // (REST)
+  float top = 0.f;
+  auto store = [&](char* stage, int p, int kt) {
+    const bool in = kt * BK + 4 * pc < K;
+    const float4 v = make_float4(in ? x[p].x : 0.f, in ? x[p].y : 0.f, in ? x[p].z : 0.f, in ? x[p].w : 0.f);
+    if (p < NA) gemm_split_store<G::BM, BK>(stage, pr + RPP * p, pc, v, top);
+    else gemm_split_store<G::BN, BK>(stage + 3 * A_PLANE, pr + RPP * (p - NA), pc, v, top);
+  };
+#pragma unroll
+  for (int p = 0; p < NP; ++p) load(p, 0);
+#pragma unroll
+  for (int p = 0; p < NP; ++p) { store(smem, p, 0); load(p, 1); }
+  __syncthreads();
+  const int nk = (K + BK - 1) / BK;
+  for (int kt = 0; kt < nk; ++kt) {
+    const char* cur = smem + (kt & 1) * G::SPLIT_BYTES;
+    char* nxt = smem + ((kt + 1) & 1) * G::SPLIT_BYTES;
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks) {
+      Frag<bf16_t> fa[TA][3], fb[TB][3];
+      const int at = gemm_split_at<BK>(lane & 31, 2 * ks + (lane >> 5));
+#pragma unroll
+      for (int p = 2; p >= 0; --p) {
+#pragma unroll
+        for (int a = 0; a < TA; ++a) fa[a][p].load(reinterpret_cast<const bf16_t*>(cur + p * A_PLANE + (wm * TA + a) * (BK / 16) * 1024 + at));
+#pragma unroll
+        for (int b = 0; b < TB; ++b) fb[b][p].load(reinterpret_cast<const bf16_t*>(cur + 3 * A_PLANE + p * B_PLANE + (wn * TB + b) * (BK / 16) * 1024 + at));
+      }
+      // the small products first
+      constexpr int PA[6] = {0, 1, 2, 0, 1, 0}, PB[6] = {2, 1, 0, 1, 0, 0};
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+#pragma unroll
+        for (int a = 0; a < TA; ++a)
+#pragma unroll
+          for (int b = 0; b < TB; ++b) mma32(q == 5 || !REST ? acc[a][b] : rest[a][b], fa[a][PA[q]], fb[b][PB[q]]);
+        // the pieces of this part of the stage
+#pragma unroll
+        for (int p = NP * (ks * 6 + q) / STEPS; p < NP * (ks * 6 + q + 1) / STEPS; ++p) {
+          store(nxt, p, kt + 1);
+          load(p, kt + 2);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0x108);               // (fragment reads and matrix instructions may cross)
+    }
+    __syncthreads();
   }
-  using G = GemmTile<WM, WN, TA, TB, KB>;
-  constexpr int NT = G::NT;
-  constexpr int BK = KB / sizeof(T);
-  constexpr int GEMM_ROWB = G::ROWB;
+#pragma unroll
+  for (int a = 0; REST && a < TA; ++a)
+#pragma unroll
+    for (int b = 0; b < TB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] += rest[a][b][i];
+  return !__syncthreads_or(top >= 0x1.ffp127f);            // (from there on bf16 rounds up to infinity)
+}
+
+// fp32 on the fp32 matrix cores.
+template <int WM, int WN, int TA, int TB>
+__device__ __forceinline__ void gemm_mainloop_regs(const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb,
+                                                   int M, int N, int K, int m0, int n0, v16f (&acc)[TA][TB], char* smem) {
+  typedef float T;
+  using G = GemmTile<T, WM, WN, TA, TB>;
+  constexpr int NT = G::NT, BK = G::BK, KB = 4 * BK, GEMM_ROWB = G::ROWB, A_BYTES = G::BM * G::ROWB;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wm = w / WN, wn = w % WN;
-  if (ZERO) {
-#pragma unroll
-    for (int a = 0; a < TA; ++a)
-#pragma unroll
-      for (int b = 0; b < TB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-  }
-
   uint4 ra[G::BM * KB / 16 / NT], rb[G::BN * KB / 16 / NT];
   unsigned oa[G::BM * KB / 16 / NT], ob[G::BN * KB / 16 / NT];
   gemm_tile_offsets<T, NT, G::BM, KB>(lda, M, m0, oa);
@@ -251,7 +357,7 @@ __device__ __forceinline__ void gemm_mainloop(const T* __restrict__ A, int lda, 
   gemm_load_tile<T, NT, G::BM, KB>(pa, oa, K, ra);
   gemm_load_tile<T, NT, G::BN, KB>(pb, ob, K, rb);
   gemm_store_tile<NT, G::BM, KB>(smem, ra);
-  gemm_store_tile<NT, G::BN, KB>(smem + G::A_BYTES, rb);
+  gemm_store_tile<NT, G::BN, KB>(smem + A_BYTES, rb);
   __syncthreads();
   const int nk = (K + BK - 1) / BK;
   for (int kt = 0; kt < nk; ++kt) {
@@ -263,7 +369,7 @@ __device__ __forceinline__ void gemm_mainloop(const T* __restrict__ A, int lda, 
       gemm_load_tile<T, NT, G::BN, KB>(pb + (kt + 1) * BK, ob, K - (kt + 1) * BK, rb);
     }
     const char* ta = cur + (wm * 32 * TA + (lane & 31)) * GEMM_ROWB + (lane >> 5) * 8 * sizeof(T);
-    const char* tb = cur + G::A_BYTES + (wn * 32 * TB + (lane & 31)) * GEMM_ROWB + (lane >> 5) * 8 * sizeof(T);
+    const char* tb = cur + A_BYTES + (wn * 32 * TB + (lane & 31)) * GEMM_ROWB + (lane >> 5) * 8 * sizeof(T);
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) {
       Frag<T> fa[TA], fb[TB];
@@ -278,10 +384,37 @@ __device__ __forceinline__ void gemm_mainloop(const T* __restrict__ A, int lda, 
     }
     if (more) {
       gemm_store_tile<NT, G::BM, KB>(nxt, ra);
-      gemm_store_tile<NT, G::BN, KB>(nxt + G::A_BYTES, rb);
+      gemm_store_tile<NT, G::BN, KB>(nxt + A_BYTES, rb);
     }
     __syncthreads();
   }
 }
+
+// With w = wavefront index, wm = w / WN, wn = w % WN:
+// acc[a][b]: rows m0 + (wm*TA + a)*32 + acc32_row(lane,i), cols n0 + (wn*TB + b)*32 + lane%32
+// init(acc) sets what the products are added to (zeros, or e.g. a bias).  
+// FORM, of fp32: split with the small products in a sum of their own; all products in one sum; fp32 instructions.
+enum { GEMM_F32_SPLIT = 0, GEMM_F32_ONE_SUM = 1, GEMM_F32_CHAIN = 2 };
+template <typename T, int WM, int WN, int TA, int TB, int FORM = 0, typename Init>
+__device__ __forceinline__ void gemm_mainloop(const T* __restrict__ A, int lda, const T* __restrict__ B, int ldb,
+                                              int M, int N, int K, int m0, int n0, v16f (&acc)[TA][TB], char* smem, Init init) {
+  init(acc);
+  if constexpr (sizeof(T) == 2) gemm_mainloop_dl<WM, WN, TA, TB>(A, lda, B, ldb, M, N, K, m0, n0, acc, smem);
+  else if constexpr (FORM == GEMM_F32_CHAIN) gemm_mainloop_regs<WM, WN, TA, TB>(A, lda, B, ldb, M, N, K, m0, n0, acc, smem);
+  else if (!gemm_mainloop_f32<WM, WN, TA, TB, FORM != GEMM_F32_ONE_SUM>(A, lda, B, ldb, M, N, K, m0, n0, acc, smem)) {
+    init(acc);
+    gemm_mainloop_regs<WM, WN, TA, TB>(A, lda, B, ldb, M, N, K, m0, n0, acc, smem);
+  }
+}
+struct GemmZero {
+  template <int TA, int TB> __device__ __forceinline__ void operator()(v16f (&acc)[TA][TB]) const {
+#pragma unroll
+    for (int a = 0; a < TA; ++a)
+#pragma unroll
+      for (int b = 0; b < TB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+  }
+};
 
 }  // namespace cmt

@@ -22,7 +22,10 @@ struct RowLimit { const int32_t* n = nullptr; int base = 0; };
 void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, int M, int N, int K,
                     float* Cf, void* Ct, int ldc, const float* bias, int accumulate, hipStream_t st,
                     float* split_scratch = nullptr, size_t split_scratch_floats = 0, RowLimit limit = RowLimit{},
-                    int limit_kind = 0, int wg_cap = 0);
+                    int limit_kind = 0, int wg_cap = 0, int chain = 0);
+// chain (fp32): the products on the fp32 instructions, added in ascending order.  For the output layer's backward products: their
+// sums of thousands of nearly equal addends carry rounding errors of up to 9e-6 of W_o's gradient (the split form's 1e-6), and
+// moving a gradient by its own error is more than sums in another order may do; everything else runs split (gemm_core.h).
 // wg_cap > 0: at most that many workgroups (rounded up to a multiple of 8) walk the tiles — for a GEMM on a second
 // stream that is to leave part of the chip to the kernels of the first.  The cap counts workgroups of the two larger tiles; of
 // the 64 x 64 tile, which fits a CU four times, four times as many are launched.

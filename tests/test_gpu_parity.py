@@ -1158,3 +1158,36 @@ def test_batched_products_at_the_edges_of_their_tiles(prec, B, S, T, H, E, L, V)
         relax = dict(l2_override={k: max(2e-2, SWEEP_SENS_C * v) for k, v in sens.items()})
     loss, oloss, worst, tr = run_case(cfg, params, batch, prec, **relax)
     tr.close()
+
+
+@pytest.mark.parametrize("B,S,E,H", [(16, 1, 8, 16), (33, 5, 40, 48), (128, 50, 264, 512), (128, 100, 72, 1024)])
+def test_fp32_products_in_three_parts(B, S, E, H):
+    """The input half of the first encoder layer, x W^T + b at positions whose recurrent half is zero, against 64 bits: both tiles
+    of the fp32 product, k that ends inside a stage, and operands with a part that no split holds (infinite, or rounding to that in bf16:
+    the tile is made again on the fp32 instructions).  Bound: every x w is off by less than 2^-25 of it, a sum of k of them in steps of 16
+    (fp32 instructions: 2) by half a unit of the largest partial sum each; then a logistic function of slope at most 1/4."""
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=64, tgt_vocab=64, emb=E, hidden=H, layers=1)
+    rng = np.random.default_rng(77 + E)
+    params = I.make_params(cfg, seed=E, scale=0.3)
+    params["E_src"] *= np.exp(rng.uniform(-12, 2, params["E_src"].shape)).astype(np.float32)
+    params["E_src"][8, 3], params["E_src"][9, E - 1], params["E_src"][10, 0] = 3.4e38, -np.inf, 3.3e38
+    src = rng.integers(4, 64, size=(B, S)).astype(np.int32)
+    src[:, 0] = 4 + np.arange(B) % 60
+    tr = binding.Trainer(cfg, B, S, 2, precision=0)
+    tr.set_params(I.flatten(params, cfg))
+    tr.train_step_async(tr.upload_batch(src, np.full(B, S, np.int32), np.full((B, 2), 4, np.int32), np.full(B, 2, np.int32)))
+    Hd = H // 2
+    got = tr.debug_fetch("enc.l0.fwd.gates", (S, tr.padded_batch(), 4 * Hd))[0, :B].astype(np.float64)
+    tr.close()
+    W, b = params["enc.l0.fwd.W"].astype(np.float64), params["enc.l0.fwd.b"].astype(np.float64)
+    x = params["E_src"].astype(np.float64)[src[:, 0]]
+    with np.errstate(all="ignore"):
+        pre = x @ W[:, :E].T + b
+        size = np.abs(x) @ np.abs(W[:, :E]).T + np.abs(b)
+        ref = np.where(np.arange(4 * Hd) // Hd == 2, np.tanh(pre), 1 / (1 + np.exp(-pre)))
+    plain = ~np.isin(src[:, 0], (8, 9, 10))
+    bound = 2.0 ** -24 * (E / 16 + 4) * size[plain] + 4e-7             # (gates: two units of the library's functions)
+    assert (np.abs(got[plain] - ref[plain]) <= bound).all(), np.abs(got[plain] - ref[plain]).max()
+    # (pre-activations of 1e36 and more: gates of exactly 0, 1 or -1 whatever the rounding)
+    assert np.array_equal(got[~plain], ref[~plain])
