@@ -211,7 +211,6 @@ struct cmt_handle {
   char* xcat = nullptr; int ldxcat = 0; // decoder bottom-layer input [emb(y_{j-1}) ; H_o^{<j-1>}] of the current step
   int32_t* dec_tok = nullptr; int32_t* dec_done = nullptr; float* dec_mask = nullptr; float* logits = nullptr;
   // beam search: encoder outputs repeated per hypothesis row, and the search state
-  char* Hs_exp = nullptr; char* K_exp = nullptr; int32_t* len_exp = nullptr;
   BeamState beam{};
   char* HoDrop = nullptr;               // H_o after dropout: what the output layer and the input feed read
   float* psz = nullptr;                 // per-group sums of logits (label smoothing)
@@ -380,8 +379,6 @@ size_t layout(cmt_handle* h, char* base) {
   h->dec_tok = (int32_t*)a.take((size_t)Bp * 4); h->dec_done = (int32_t*)a.take((size_t)Bp * 4);
   h->dec_mask = (float*)a.take((size_t)Bp * 4);
   h->logits = (float*)a.take((size_t)Bp * c.tgt_vocab * 4);
-  h->Hs_exp = a.take(Ms * H * esz); h->K_exp = a.take(Ms * H * esz);
-  h->len_exp = (int32_t*)a.take((size_t)Bp * 4);
   {
     BeamState& bs = h->beam;
     bs.cum = (float*)a.take((size_t)Bp * 4); bs.new_cum = (float*)a.take((size_t)Bp * 4); bs.mask = (float*)a.take((size_t)Bp * 4);
@@ -391,8 +388,6 @@ size_t layout(cmt_handle* h, char* base) {
     bs.fin_par = (int32_t*)a.take((size_t)Bp * 4); bs.fin_tok = (int32_t*)a.take((size_t)Bp * 4);
     bs.hist_tok = (int32_t*)a.take(Mt * 4); bs.hist_par = (int32_t*)a.take(Mt * 4);
     bs.hist_ld = Bp;
-    bs.row_lse = (float*)a.take((size_t)Bp * 4);
-    bs.cand_z = (float*)a.take((size_t)Bp * 16 * 4); bs.cand_tok = (int32_t*)a.take((size_t)Bp * 16 * 4);
   }
   h->Cs = a.take(Mt * PH * esz); h->CsT = a.take(Mt * H * esz);
   h->att_a = (float*)a.take(Mt * Sm * 4); h->att_ds = (float*)a.take(Mt * Sm * 4);
@@ -1751,20 +1746,12 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
   enqueue_encoder(h, S, &Hs, &ldHs);                 // also leaves the decoder's initial states in slot 0 (BpE rows)
   sec.close();
   h->drop_p = keep_p;
-  // one decoder row per hypothesis: encoder outputs, keys, lengths and initial states repeated K times
+  // one decoder row per hypothesis: the initial states repeated K times; the attention runs on the projected source rows, as in
+  // the training step, and a sentence's hypotheses share them
   BeamState& bs = h->beam;
   bs.hist_ld = Rp;
-  launch_beam_init(bs, B, Rp, K, c.bos_id, h->len_s, h->len_exp, st);
-  // (below 256 rows the attention runs on the projected source rows, as in the training step: those are expanded
-  // in the place of the source states)
-  const bool proj = h->att_proj && Rp < 256;
-  if (proj) {
-    launch_gemm_nt(p, Hs, ldHs, h->Pw(h->off_Wc), 2 * H, S * BpE, H, H, nullptr, h->PmatT, H, nullptr, 0, st);
-    launch_beam_expand((int)esz, h->PmatT, H, BpE, h->Hs_exp, H, S, R, Rp, K, H, st);
-  } else {
-    launch_beam_expand((int)esz, Hs, ldHs, BpE, h->Hs_exp, H, S, R, Rp, K, H, st);
-  }
-  launch_beam_expand((int)esz, h->Kmat, H, BpE, h->K_exp, H, S, R, Rp, K, H, st);
+  launch_beam_init(bs, B, Rp, K, c.bos_id, st);
+  launch_gemm_nt(p, Hs, ldHs, h->Pw(h->off_Wc), 2 * H, S * BpE, H, H, nullptr, h->PmatT, H, nullptr, 0, st);
   const size_t slotT = (size_t)Rp * PH * esz, slotC = (size_t)Rp * H * 4;   // state slots of Rp rows: 1 = read, 2 = written
   const size_t slotF = (size_t)Rp * H * esz;                                // the same slots of the fragment-major copies
   for (int l = 0; l < L; ++l) {
@@ -1807,24 +1794,15 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
       launch_lstm_fwd(p, d, Rp, H, st);
     }
     const char* Ht = h->dec[L - 1].Hst + 2 * slotT;
-    StepGemm g{};
-    g.a0 = h->Cs; g.lda0 = PH; g.K0 = H; g.w0_off = 0;
-    g.a1 = Ht; g.lda1 = PH; g.K1 = H; g.w1_off = H;
-    g.W = h->Pw(h->off_Wc); g.ldw = 2 * H; g.N = H; g.mode = 0;
-    g.outT = h->HoBuf; g.ldo = PH;
-    g.out = h->wcp; g.ldout = H; g.plane_stride = (size_t)Rp * H;
-    if (h->CsF && h->dec[L - 1].fm) { g.W_fm = h->WcF; g.a0_fm = h->CsF; g.a1_fm = h->dec[L - 1].HstF + 2 * slotF; }
-    if (proj) {
-      AttOut o{};
-      o.outT = g.outT; o.ldo = g.ldo;
-      g.mode = 3; g.skip0 = 1; g.a0_fm = g.a1_fm;
-      launch_att_fwd_proj(p, h->K_exp, H, h->Hs_exp, H, Ht, PH, g, o, h->len_exp, S, Rp, H, h->dots, h->att_a, st);
-    } else {
-      launch_att_fwd(p, h->K_exp, H, h->Hs_exp, H, Ht, PH, h->len_exp, S, Rp, H, h->dots, h->att_a, h->Cs, PH, st, h->CsF);
-      launch_step_gemm(p, g, Rp, st);
-    }
-    launch_gemm_nt(p, h->HoBuf, PH, h->Pw(h->off_Wo), H, Rp, V, H, h->logits, nullptr, V, h->params + h->off_Bo, 0, st);
-    launch_beam_select(h->logits, V, bs, B, K, j, max_len, eos_id, length_penalty, st, p);
+    StepGemm g{};                                    // W_c2 H_t
+    g.a0 = g.a1 = Ht; g.lda0 = g.lda1 = PH; g.K0 = g.K1 = H; g.w0_off = 0; g.w1_off = H;
+    g.W = h->Pw(h->off_Wc); g.ldw = 2 * H; g.N = H; g.mode = 3; g.skip0 = 1;
+    g.out = h->wcp; g.ldout = H;
+    if (h->CsF && h->dec[L - 1].fm) { g.W_fm = h->WcF; g.a0_fm = g.a1_fm = h->dec[L - 1].HstF + 2 * slotF; }
+    launch_beam_attention(p, h->Kmat, h->PmatT, BpE, Ht, PH, g, h->len_s, S, B, K, H, h->dots, h->HoBuf, PH, st);
+    // (the output layer's partials of a training step are of no use here)
+    launch_beam_select(p, h->HoBuf, PH, h->Pw(h->off_Wo), h->params + h->off_Bo, Rp, V, H, h->logits, h->pmax, h->psum, bs, B, K, j, max_len,
+                       eos_id, length_penalty, st);
     launch_beam_reorder(p, ro, bs, R, H, L, st);
   }
   launch_beam_finish(bs, B, K, max_len, c.pad_id, out_ids_dev, out_len_dev, out_score_dev, st);

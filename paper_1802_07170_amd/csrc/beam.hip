@@ -1,15 +1,17 @@
 // Beam search bookkeeping on the device (hyperparameter table: beam size 10, length penalty 0.6;
 // the Settings section names the length normalisation of Wu et al. 2016).  The decoder runs on
 // R = B * K rows, row r = b * K + s holding live hypothesis s of sentence b.  Per step:
-//   beam_row_topk_kernel one workgroup per live row: log-sum-exp of its logits and its K best tokens;
-//   beam_merge_kernel   one workgroup per sentence: the K best one-token extensions over all live
+//   beam_logits_kernel  the logits of all rows, and the maximum and sum of exponentials of every group of them;
+//   beam_pick_kernel    one workgroup per sentence: log-sum-exp of its rows, and the K best one-token extensions over all live
 //                       hypotheses (equal scores: the lower (slot, token) pair first), finished
 //                       hypotheses split off, history written;
 //   beam_reorder_kernel the surviving hypotheses' decoder states and H_o move to their new rows, and
 //                       the embeddings of their tokens become the next step's input.
 // After the last step beam_finish_kernel walks the back-pointers of each sentence's best finished
 // hypothesis.  Nothing returns to the host inside the loop.
-#include "common.h"
+#include <type_traits>
+
+#include "gemm_core.h"
 #include "kernels.h"
 
 namespace cmt {
@@ -38,8 +40,7 @@ void launch_beam_expand(int elem_bytes, const void* src, int ld_src, int rows_sr
 }
 
 // start of a search: one live hypothesis per sentence (slot 0, score 0, previous token bos)
-__global__ __launch_bounds__(256) void beam_init_kernel(BeamState bs, int B, int Rp, int K, int bos, const int32_t* __restrict__ len_src,
-                                                        int32_t* __restrict__ len_exp) {
+__global__ __launch_bounds__(256) void beam_init_kernel(BeamState bs, int B, int Rp, int K, int bos) {
   const int r = blockIdx.x * 256 + threadIdx.x;
   if (r < Rp) {
     const int b = r / K, s = r - b * K;
@@ -47,16 +48,14 @@ __global__ __launch_bounds__(256) void beam_init_kernel(BeamState bs, int B, int
     bs.cum[r] = real && s == 0 ? 0.f : -INFINITY;
     bs.tok[r] = bos;
     bs.mask[r] = real && s == 0 ? 1.f : 0.f;
-    len_exp[r] = real ? len_src[b] : 0;
   }
   if (r < B) { bs.nlive[r] = 1; bs.fin_score[r] = -INFINITY; bs.fin_step[r] = -1; bs.fin_par[r] = 0; bs.fin_tok[r] = 0; }
 }
-void launch_beam_init(const BeamState& bs, int B, int Rp, int K, int bos, const int32_t* len_src, int32_t* len_exp, hipStream_t st) {
-  hipLaunchKernelGGL(beam_init_kernel, dim3((Rp + 255) / 256), dim3(256), 0, st, bs, B, Rp, K, bos, len_src, len_exp);
+void launch_beam_init(const BeamState& bs, int B, int Rp, int K, int bos, hipStream_t st) {
+  hipLaunchKernelGGL(beam_init_kernel, dim3((Rp + 255) / 256), dim3(256), 0, st, bs, B, Rp, K, bos);
 }
 
 constexpr int BEAM_MAX = 16;
-constexpr int BEAM_CAND_CAP = 1024;     // candidates a row's workgroup keeps in LDS
 
 // (value, index) ordering: larger value first, then lower index
 __device__ __forceinline__ bool beam_better(float v, int f, float bv, int bf) { return v > bv || (v == bv && f < bf); }
@@ -89,151 +88,217 @@ __device__ __forceinline__ void beam_block_best(float& v, int& f, float* s_v, in
     if (beam_better(s_v[q], s_f[q], v, f)) { v = s_v[q]; f = s_f[q]; }
 }
 
-// One workgroup per hypothesis row: log-sum-exp of the row's logits and its K best tokens (larger
-// logit first, then lower token), written best first; entries beyond the row's candidates are
-// (-inf, INT_MAX).  The K best of a row contain every extension of it that can be among the K best
-// of its sentence (log-softmax is monotonic within a row).
-//   pass 1: every thread's best value; the K-th best of one wavefront's 64 of them is a lower bound on the row's K-th
-//           best logit, tau the largest of these bounds;
-//   pass 2: sum of exp(z - max), and the elements >= tau are appended to a list in LDS;
-//   then every list element counts how many are better: that is its place.  A list that overflows (many equal
-//   logits) falls back to K rounds of a workgroup-wide arg-max over the row.
-// The row stays in registers (NV 16-byte pieces per thread, all in flight at once) and memory is read once; NV = 0:
-// each pass reads the row again, four pieces in flight.  What bounds it: the latency of the read and of the selection's
-// chain, hence DPP instead of shuffles and counting instead of rounds (with reorder and merge, one sentence x 10 beams,
-// 25 steps: 2.74 -> 2.32 ms per search).
-// FAST (16-bit path): the hardware exponential in the log-sum-exp.
-template <bool FAST, int NT, int NV>
-__global__ __launch_bounds__(NT) void beam_row_topk_kernel(const float* __restrict__ z, int V, BeamState bs, int K) {
-  constexpr int NW = NT / 64, G = NV ? NV : 4;
-  __shared__ float s_v[NW];
-  __shared__ int s_f[NW];
-  __shared__ float s_sum[NW];
-  __shared__ float s_cv[BEAM_CAND_CAP];
-  __shared__ int s_ci[BEAM_CAND_CAP];
-  __shared__ int s_n;
-  const int r = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int b = r / K, slot = r - b * K;
-  if (slot >= bs.nlive[b]) return;                       // dead row (uniform over the workgroup)
-  const float* zr = z + (size_t)r * V;
-  const int nv4 = V >> 2;                                // V is a multiple of 8
-  float4 q[G];
-  auto load = [&](int c0) {
+// z^T = W_o Ho^T + B_o, [V, pitch] fp32 with the R rows of the search side by side, and per group of 32 TA vocabulary entries
+// (gmax, gsum: [rows, groups]) each row's largest logit and its sum of exp(logit - that).  The tile is computed as in the output
+// layer's forward kernel, vocabulary entries on the matrix cores' row side, so that a lane holds 32 TA / 2 entries of one row.
+// With the groups' statistics the choice of the K best reads 40 KB per sentence and the K best groups instead of every logit.
+// The row tile is as wide as makes the rounds of workgroups over the chip come out (beam_logits_plan): what a workgroup takes in is
+// its rows and its weights, 49 GB/s per CU.  640 rows x 32000, k 1024: 256 x 320 tiles, one round of 250: 80 -> 52 us.
+template <typename T, int WM, int WN, int TA, int TB>
+__global__ __launch_bounds__(64 * WM * WN) void beam_logits_kernel(const T* __restrict__ Ho, int ldho, const T* __restrict__ Wo,
+                                                                   const float* __restrict__ Bo, int R, int V, int H, float* __restrict__ zT,
+                                                                   int pitch, float* __restrict__ gmax, float* __restrict__ gsum) {
+  using G = GemmTile<T, WM, WN, TA, TB>;
+  constexpr bool FAST = sizeof(T) == 2;
+  __shared__ __align__(16) char smem[FAST ? 2 * (G::BM + G::BN) * 128 : G::SMEM_BYTES];
+  int v0, r0;
+  if (!gemm_tile_of_block((V + G::BM - 1) / G::BM, (R + G::BN - 1) / G::BN, G::BM, G::BN, v0, r0)) return;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ng = (V + 32 * TA - 1) / (32 * TA);
+  const int wm = w / WN, wn = w % WN, vw = v0 + wm * 32 * TA;
+  v16f acc[TA][TB];
+  gemm_mainloop<T, WM, WN, TA, TB, TA * TB == 1 ? GEMM_F32_SPLIT : GEMM_F32_ONE_SUM>(Wo, H, Ho, ldho, V, R, H, v0, r0, acc, smem, [&](v16f (&acc)[TA][TB]) {
 #pragma unroll
-    for (int k = 0; k < G; ++k) {
-      const int c = c0 + NT * k;
-      q[k] = c < nv4 ? *reinterpret_cast<const float4*>(zr + 4 * c) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-    }
-  };
-  auto visit = [&](auto f) {                             // f(value, token) of this thread's elements
-    int first = t;
-    asm volatile("" : "+v"(first));                      // (opaque: token numbers are made on the spot, not kept in registers)
-    for (int c0 = first; c0 < nv4; c0 += G * NT) {
-      if (NV == 0) load(c0);
+    for (int mt = 0; mt < TA; ++mt)
 #pragma unroll
-      for (int k = 0; k < G; ++k) {
-        const int c = c0 + NT * k;
-        if (c < nv4) { f(q[k].x, 4 * c); f(q[k].y, 4 * c + 1); f(q[k].z, 4 * c + 2); f(q[k].w, 4 * c + 3); }
-        __builtin_amdgcn_sched_barrier(0);               // (one piece at a time: registers)
+      for (int i = 0; i < 16; ++i) {
+        const int v = vw + mt * 32 + acc32_row(lane, i);
+        const float bv = v < V ? Bo[v] : 0.f;
+#pragma unroll
+        for (int nt = 0; nt < TB; ++nt) acc[mt][nt][i] = bv;
       }
-      if (NV) break;
-    }
-  };
-  if (NV) load(t);
-  if (t == 0) s_n = 0;
-  float tv = -INFINITY;
-  visit([&](float x, int) { tv = fmaxf(tv, x); });       // (a NaN is never the best)
-  float mx = -INFINITY, tau = -INFINITY;
-  {
-    bool taken = false;
-    for (int round = 0; round < K; ++round) {
-      tau = beam_wave_max(taken ? -INFINITY : tv);       // -inf when fewer than K of its threads hold an element
-      if (round == 0) mx = tau;
-      const unsigned long long at = __ballot(!taken && tv == tau);
-      if (at && lane == __ffsll(at) - 1) taken = true;
-    }
-  }
-  if (lane == 0) { s_v[w] = tau; s_sum[w] = mx; }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NW; ++i) { tau = fmaxf(tau, s_v[i]); mx = fmaxf(mx, s_sum[i]); }
-  __syncthreads();                                       // (s_sum is written again below)
-  float e = 0.f;
-  visit([&](float x, int token) {
-    e += FAST ? __expf(x - mx) : expf(x - mx);
-    if (x >= tau) {
-      const int pos = atomicAdd(&s_n, 1);
-      if (pos < BEAM_CAND_CAP) { s_cv[pos] = x; s_ci[pos] = token; }
-    }
   });
-  e = wave_sum(e);
-  if (lane == 0) s_sum[w] = e;
-  __syncthreads();
-  if (t == 0) {
-    float sum = 0.f;
+  if (vw >= V) return;                                     // (no barrier behind this)
+  const int g = vw / (32 * TA), q = lane >> 5;
+  if (vw + 32 * TA > V) {                                  // the group that reaches past the vocabulary
 #pragma unroll
-    for (int i = 0; i < NW; ++i) sum += s_sum[i];
-    bs.row_lse[r] = mx + logf(sum);
+    for (int mt = 0; mt < TA; ++mt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (vw + mt * 32 + acc32_row(lane, i) >= V) {
+#pragma unroll
+          for (int nt = 0; nt < TB; ++nt) acc[mt][nt][i] = -INFINITY;
+        }
   }
-  const int n = s_n;
-  float* const out_z = bs.cand_z + (size_t)r * BEAM_MAX;
-  int32_t* const out_t = bs.cand_tok + (size_t)r * BEAM_MAX;
-  if (n <= BEAM_CAND_CAP) {
-    if (t >= n && t < K) { out_z[t] = -INFINITY; out_t[t] = 0x7fffffff; }
-    for (int i = t; i < n; i += NT) {
-      const float v = s_cv[i];
-      const int f = s_ci[i];
-      int place = 0;
-#pragma unroll 8
-      for (int k = 0; k < n; ++k) place += beam_better(s_cv[k], s_ci[k], v, f);
-      if (place < K) { out_z[place] = v; out_t[place] = f; }
+  const bool whole = vw + 32 * TA <= V;
+#pragma unroll
+  for (int nt = 0; nt < TB; ++nt) {
+    const int r = r0 + wn * 32 * TB + nt * 32 + (lane & 31);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int mt = 0; mt < TA; ++mt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc[mt][nt][i]);   // (a NaN is never the best)
+    if (r < R) {                                           // row of entry i: a uniform one plus the lane's 4 q
+      const unsigned off = (unsigned)(4 * q * pitch + r);
+#pragma unroll
+      for (int mt = 0; mt < TA; ++mt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int v = vw + mt * 32 + 8 * (i >> 2) + (i & 3);
+          if (whole || v + 4 * q < V) (zT + (size_t)v * pitch)[off] = acc[mt][nt][i];
+        }
     }
-    return;
-  }
-  // K rounds: the best element strictly after the previous winner in the (value, token) order
-  float pv = INFINITY; int pi = -1;
-  for (int round = 0; round < K; ++round) {
-    float v = -INFINITY; int f = 0x7fffffff;
-    visit([&](float x, int xi) {
-      if ((x < pv || (x == pv && xi > pi)) && beam_better(x, xi, v, f)) { v = x; f = xi; }
-    });
-    beam_block_best<NW>(v, f, s_v, s_f);
-    if (t == 0) { out_z[round] = v; out_t[round] = f; }
-    pv = v; pi = f;
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float ms = mx > -INFINITY ? mx : 0.f;
+    float e = 0.f;
+#pragma unroll
+    for (int mt = 0; mt < TA; ++mt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) e += FAST ? __expf(acc[mt][nt][i] - ms) : expf(acc[mt][nt][i] - ms);
+    e += __shfl_xor(e, 32, 64);
+    if (lane < 32 && r < R) { gmax[(size_t)r * ng + g] = mx; gsum[(size_t)r * ng + g] = e; }
+    __builtin_amdgcn_sched_barrier(0);                     // (one column tile at a time: registers)
   }
 }
 
-// One workgroup per sentence: the K best one-token extensions over the candidates of its live rows
-// (equal scores: the lower (slot, token) pair first), finished hypotheses split off, history written.
-// Every candidate counts how many are better, then lane q of the first wavefront takes the q-th best: the chain of this
-// launch is what it costs.
-__global__ __launch_bounds__(256) void beam_merge_kernel(int V, BeamState bs, int K, int j, int max_len, int eos, float alpha) {
-  __shared__ float s_cv[BEAM_MAX * BEAM_MAX];
-  __shared__ int s_cf[BEAM_MAX * BEAM_MAX];
-  __shared__ float s_winv[BEAM_MAX];
+// One workgroup per sentence.  A group's largest extension, (score - lse) + gmax, is one of its extensions, so the K-th best of the
+// groups is a bound for the K-th best extension, and every extension as good as that lies in a group as good as that:
+//   lse of the live rows from the groups' statistics;
+//   the K-th best group: the K-th best of a row's 64 threads' best is a bound that few groups pass; those are listed in LDS
+//   and each counts how many are better;
+//   the entries of the K best groups that pass are listed, and each counts how many are better: that is its place.
+// Lists that overflow (many equal logits) fall back to K rounds of a workgroup-wide arg-max over all extensions.
+// What bounds it is the chain of these steps, each a trip to memory or a barrier.  640 rows, V = 32000: 14.7 us in the place of 29
+// for the rows' K best (a pass over 82 MB) and 11 for their merge.
+constexpr int BEAM_PICK_NT = 1024, BEAM_PICK_CAP = 1024;
+__global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __restrict__ zT, int pitch, const float* __restrict__ gmax,
+                                                                 const float* __restrict__ gsum, int gbits, int V, BeamState bs, int K, int j,
+                                                                 int max_len, int eos, float alpha) {
+  constexpr int NW = BEAM_PICK_NT / 64;
+  __shared__ float s_base[BEAM_MAX];
+  __shared__ float s_gv[BEAM_PICK_CAP], s_cv[BEAM_PICK_CAP];
+  __shared__ int s_gi[BEAM_PICK_CAP], s_cf[BEAM_PICK_CAP], s_top[BEAM_PICK_CAP];
+  __shared__ float s_v[NW];
+  __shared__ int s_f[NW];
+  __shared__ float s_winv[BEAM_MAX], s_tau;
   __shared__ int s_winf[BEAM_MAX];
-  const int b = blockIdx.x, t = threadIdx.x;
-  // thread t holds candidate t % K of live row t / K (K * K <= 256); everything is requested at once, before it is known
-  // which rows live
-  const int row0 = b * K, slot = t / K, row = row0 + min(slot, K - 1);
+  __shared__ int s_ng, s_n, s_ntop;
+  constexpr int NQ = 16;                                 // a row's first 64 NQ groups stay in its wavefront's registers
+  const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int row0 = b * K, ng = (V + (1 << gbits) - 1) >> gbits;
+  // wavefront s takes row s; everything is requested at once, before it is known which rows live
+  const size_t r = row0 + min(w, K - 1);
+  float m[NQ], x[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const bool in = lane + 64 * q < ng;
+    m[q] = in ? gmax[r * ng + lane + 64 * q] : -INFINITY;
+    x[q] = in ? gsum[r * ng + lane + 64 * q] : 0.f;
+  }
   const int nl = bs.nlive[b];
-  const float zc = bs.cand_z[(size_t)row * BEAM_MAX + t - slot * K], cum = bs.cum[row], lse = bs.row_lse[row];
-  const int tok = bs.cand_tok[(size_t)row * BEAM_MAX + t - slot * K];
-  const float fin_score = bs.fin_score[b];
+  const float fin_score = bs.fin_score[b], cum = bs.cum[r];
   if (nl == 0) {                                         // the sentence is done (uniform over the workgroup)
     if (t < K) { bs.parent[row0 + t] = -1; bs.new_cum[row0 + t] = -INFINITY; }
     return;
   }
-  float cv = -INFINITY; int cf = 0x7fffffff;
-  if (slot < nl && tok != 0x7fffffff) { cv = (cum - lse) + zc; cf = slot * V + tok; }
-  s_cv[t] = cv; s_cf[t] = cf;
+  if (t == 0) { s_ng = 0; s_n = 0; s_ntop = 0; s_tau = -INFINITY; }
   if (t < BEAM_MAX) { s_winv[t] = -INFINITY; s_winf[t] = 0; }
+  float base = 0.f, tau = -INFINITY;
+  if (w < nl) {                                          // (uniform over the wavefront)
+    float tv = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) tv = fmaxf(tv, m[q]);
+    for (int g = lane + 64 * NQ; g < ng; g += 64) tv = fmaxf(tv, gmax[r * ng + g]);
+    const float mx = beam_wave_max(tv);
+    float e = 0.f;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) e += m[q] > -INFINITY ? x[q] * expf(m[q] - mx) : x[q];   // (a group of -inf alone has the sum 0, one with NaN a NaN)
+    for (int g = lane + 64 * NQ; g < ng; g += 64) {
+      const float mg = gmax[r * ng + g], xg = gsum[r * ng + g];
+      e += mg > -INFINITY ? xg * expf(mg - mx) : xg;
+    }
+    base = cum - (mx + logf(wave_sum(e)));
+    if (lane == 0) s_base[w] = base;
+    // ---- the K best groups ---------------------------------------------------------------------------------
+    tv += base;
+    bool taken = false;
+    for (int round = 0; round < K; ++round) {
+      tau = beam_wave_max(taken ? -INFINITY : tv);       // -inf when fewer than K of its threads hold a group
+      const unsigned long long at = __ballot(!taken && tv == tau);
+      if (at && lane == __ffsll(at) - 1) taken = true;
+    }
+  }
+  if (lane == 0) s_v[w] = tau;
   __syncthreads();
-  if (cv > -INFINITY) {                                  // (neither NaN nor an empty entry)
-    int place = 0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) tau = fmaxf(tau, s_v[i]);
+  if (w < nl) {
+    auto list = [&](float bound, int g) {
+      if (bound >= tau) {
+        const int pos = atomicAdd(&s_ng, 1);
+        if (pos < BEAM_PICK_CAP) { s_gv[pos] = bound; s_gi[pos] = g * BEAM_MAX + w; }
+      }
+    };
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (lane + 64 * q < ng) list(base + m[q], lane + 64 * q);
+    for (int g = lane + 64 * NQ; g < ng; g += 64) list(base + gmax[r * ng + g], g);
+  }
+  __syncthreads();
+  bool fits = s_ng <= BEAM_PICK_CAP;
+  if (fits) {
+    const int n = s_ng;
+    for (int i = t; i < n; i += BEAM_PICK_NT) {
+      const float v = s_gv[i];
+      const int f = s_gi[i];
+      int place = 0;
 #pragma unroll 8
-    for (int k = 0; k < nl * K; ++k) place += beam_better(s_cv[k], s_cf[k], cv, cf);
-    if (place < K) { s_winv[place] = cv; s_winf[place] = cf; }
+      for (int k = 0; k < n; ++k) place += beam_better(s_gv[k], s_gi[k], v, f);
+      if (place == K - 1) s_tau = v;                     // (fewer than K groups: every entry passes)
+    }
+    __syncthreads();
+    const float least = s_tau;
+    for (int i = t; i < n; i += BEAM_PICK_NT)
+      if (s_gv[i] >= least) s_top[atomicAdd(&s_ntop, 1)] = s_gi[i];
+    __syncthreads();
+    // ---- their entries -------------------------------------------------------------------------------------
+    const int entries = s_ntop << gbits;
+    for (int i = t; i < entries; i += BEAM_PICK_NT) {
+      const int id = s_top[i >> gbits], s = id % BEAM_MAX, v = ((id / BEAM_MAX) << gbits) + (i & ((1 << gbits) - 1));
+      if (v >= V) continue;
+      const float x = s_base[s] + zT[(size_t)v * pitch + row0 + s];
+      if (x >= least && x > -INFINITY) {                 // (neither NaN nor impossible)
+        const int pos = atomicAdd(&s_n, 1);
+        if (pos < BEAM_PICK_CAP) { s_cv[pos] = x; s_cf[pos] = s * V + v; }
+      }
+    }
+    __syncthreads();
+    fits = s_n <= BEAM_PICK_CAP;
+  }
+  if (fits) {
+    const int n = s_n;
+    for (int i = t; i < n; i += BEAM_PICK_NT) {
+      const float v = s_cv[i];
+      const int f = s_cf[i];
+      int place = 0;
+#pragma unroll 8
+      for (int k = 0; k < n; ++k) place += beam_better(s_cv[k], s_cf[k], v, f);
+      if (place < K) { s_winv[place] = v; s_winf[place] = f; }
+    }
+  } else {
+    // K rounds: the best extension strictly after the previous winner in the (value, slot and token) order
+    float pv = INFINITY; int pi = -1;
+    for (int round = 0; round < K; ++round) {
+      float v = -INFINITY; int f = 0x7fffffff;
+      for (int i = t; i < V * nl; i += BEAM_PICK_NT) {
+        const int tk = i / nl, s = i - tk * nl, xi = s * V + tk;
+        const float x = s_base[s] + zT[(size_t)tk * pitch + row0 + s];
+        if (x > -INFINITY && (x < pv || (x == pv && xi > pi)) && beam_better(x, xi, v, f)) { v = x; f = xi; }
+      }
+      beam_block_best<NW>(v, f, s_v, s_f);
+      if (t == 0) { s_winv[round] = v; s_winf[round] = f; }
+      pv = v; pi = f;
+    }
   }
   __syncthreads();
   if (t >= 64) return;
@@ -267,22 +332,41 @@ __global__ __launch_bounds__(256) void beam_merge_kernel(int V, BeamState bs, in
     if (t == at) { bs.fin_score[b] = best; bs.fin_step[b] = j; bs.fin_par[b] = s; bs.fin_tok[b] = tk; }
   }
 }
-void launch_beam_select(const float* z, int V, const BeamState& bs, int B, int K, int j, int max_len, int eos, float alpha,
-                        hipStream_t st, int fast_exp) {
-#define GO(NT, NV)                                                                                                  \
-  do {                                                                                                              \
-    if (fast_exp) hipLaunchKernelGGL((beam_row_topk_kernel<true, NT, NV>), dim3(B * K), dim3(NT), 0, st, z, V, bs, K); \
-    else hipLaunchKernelGGL((beam_row_topk_kernel<false, NT, NV>), dim3(B * K), dim3(NT), 0, st, z, V, bs, K);      \
-  } while (0)
-  // Short rows, and rows for a chip's worth of workgroups, take 256 threads; fewer rows wait for their own chain, not for the
-  // chip, and take 512.  Measured at V = 32000, whole searches, ms (256 threads reading twice | 512 | 512 with the row in
-  // registers | 1024 in registers): one sentence of 10 rows 2.39 | 2.32 | 2.30 | 2.35, 64 sentences 14.90 | 15.00 | 15.01 | 15.09.
-  if (V <= 4 * 256 * 8) GO(256, 8);
-  else if (B * K >= 256) GO(256, 0);
-  else if (V <= 4 * 512 * 16) GO(512, 16);
-  else GO(512, 0);
-#undef GO
-  hipLaunchKernelGGL(beam_merge_kernel, dim3(B), dim3(256), 0, st, V, bs, K, j, max_len, eos, alpha);
+
+// 0: 64 x 64 tiles (groups of 32 entries); 1 .. 5: 256 x (64 n) tiles (groups of 64).  Few rows or a short vocabulary leave the big tiles
+// short of workgroups; else rounds over the chip's CUs times what a workgroup takes in decides.
+static int beam_logits_plan(int prec, int R, int V) {
+  const long tv = (V + 255) / 256;
+  if (R <= 64 || tv * ((R + 127) / 128) < 96) return 0;
+  if (!prec) return 2;
+  int best = 0; long cost = 0;
+  for (int n = 1; n <= 5; ++n) {
+    const long c = (tv * ((R + 64 * n - 1) / (64 * n)) + 255) / 256 * (256 + 64 * n);
+    if (best == 0 || c <= cost) { best = n; cost = c; }
+  }
+  return best;
+}
+void launch_beam_select(int prec, const void* Ho, int ldho, const void* Wo, const float* Bo, int Rp, int V, int H, float* zT, float* gmax,
+                        float* gsum, const BeamState& bs, int B, int K, int j, int max_len, int eos, float alpha, hipStream_t st) {
+  const int R = B * K, plan = beam_logits_plan(prec, R, V);
+  auto go = [&](auto type, auto wm, auto ta, auto tb) {
+    using T = decltype(type);
+    using G = GemmTile<T, decltype(wm)::value, 2, decltype(ta)::value, decltype(tb)::value>;
+    const int grid = ((V + G::BM - 1) / G::BM * ((R + G::BN - 1) / G::BN) + 7) / 8 * 8;
+    hipLaunchKernelGGL((beam_logits_kernel<T, G::WM, G::WN, G::TA, G::TB>), dim3(grid), dim3(G::NT), 0, st, (const T*)Ho, ldho, (const T*)Wo, Bo,
+                       R, V, H, zT, Rp, gmax, gsum);
+  };
+  using std::integral_constant;
+  const integral_constant<int, 1> one; const integral_constant<int, 2> two; const integral_constant<int, 3> three;
+  const integral_constant<int, 4> four; const integral_constant<int, 5> five;
+  if (!prec) { if (plan) go(float{}, four, two, two); else go(float{}, two, one, one); }
+  else if (plan == 0) go(bf16_t{}, two, one, one);
+  else if (plan == 1) go(bf16_t{}, four, two, one);
+  else if (plan == 2) go(bf16_t{}, four, two, two);
+  else if (plan == 3) go(bf16_t{}, four, two, three);
+  else if (plan == 4) go(bf16_t{}, four, two, four);
+  else go(bf16_t{}, four, two, five);
+  hipLaunchKernelGGL(beam_pick_kernel, dim3(B), dim3(BEAM_PICK_NT), 0, st, zT, Rp, gmax, gsum, plan ? 6 : 5, V, bs, K, j, max_len, eos, alpha);
 }
 // New row r takes the states of row parent[r] (or stays dead): blockIdx.y < L the h (T) and c (fp32) of that layer, L the H_o
 // that becomes its input feed, L + 1 the embedding of its token and the scores, tokens and masks.  One part per

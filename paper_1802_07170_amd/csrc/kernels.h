@@ -456,8 +456,6 @@ struct BeamState {
   float* fin_score; int32_t* fin_step; int32_t* fin_par; int32_t* fin_tok;   // [B] best finished hypothesis
   int32_t* hist_tok; int32_t* hist_par;  // [steps, hist_ld] token / parent slot of every live hypothesis per step
   int hist_ld;
-  float* row_lse;                        // [Rp] log-sum-exp of the row's logits of the current step
-  float* cand_z; int32_t* cand_tok;      // [Rp, 16] the row's best logits / tokens of the current step, best first
 };
 struct BeamReorder {
   const void* h_src[8]; void* h_dst[8]; int ldh;     // per layer: states written by the step -> states the next step reads
@@ -472,11 +470,15 @@ struct BeamReorder {
 // dst[i, r, 0:cols] = src[i, r / K, 0:cols] (r < R), zero rows up to Rp; elem_bytes 2 or 4.
 void launch_beam_expand(int elem_bytes, const void* src, int ld_src, int rows_src, void* dst, int ld_dst, int n_outer, int R, int Rp,
                         int K, int cols, hipStream_t st);
-void launch_beam_init(const BeamState& bs, int B, int Rp, int K, int bos, const int32_t* len_src, int32_t* len_exp, hipStream_t st);
-// z [Rp, V] = logits incl. bias.  Step j of max_len; K <= 16.  fast_exp: the hardware exponential in the rows'
-// log-sum-exp (the 16-bit path).
-void launch_beam_select(const float* z, int V, const BeamState& bs, int B, int K, int j, int max_len, int eos, float alpha,
-                        hipStream_t st, int fast_exp = 0);
+void launch_beam_init(const BeamState& bs, int B, int Rp, int K, int bos, hipStream_t st);
+// Step j of max_len: logits Ho W_o^T + B_o of the rows (Ho [Rp, ldho] T*, Wo [V, H] T*) and the K best extensions of every sentence.
+// Scratch: zT V * Rp floats, gmax and gsum ceil(V / 32) * Rp floats each.  K <= 16; V and H multiples of 8.
+void launch_beam_select(int prec, const void* Ho, int ldho, const void* Wo, const float* Bo, int Rp, int V, int H, float* zT, float* gmax,
+                        float* gsum, const BeamState& bs, int B, int K, int j, int max_len, int eos, float alpha, hipStream_t st);
+// H_o of the step's rows: the K hypotheses of a sentence share its keys and projected source rows (Kmat, Pmat: T* [S * Bs, H]).
+// Ht T* [R, ldt]; u: a StepGemm of mode 3 with skip0 set, W_c2 H_t -> u.out (fp32 [R, ldout]); dots [R, S] is scratch; out T* [R, ldo].
+void launch_beam_attention(int prec, const void* Kmat, const void* Pmat, int Bs, const void* Ht, int ldt, const StepGemm& u, const int32_t* len,
+                           int S, int B, int K, int H, float* dots, void* out, int ldo, hipStream_t st);
 void launch_beam_reorder(int prec, const BeamReorder& ro, const BeamState& bs, int R, int H, int L, hipStream_t st);
 void launch_beam_finish(const BeamState& bs, int B, int K, int max_len, int pad, int32_t* out_ids, int32_t* out_len, float* out_score,
                         hipStream_t st);

@@ -1348,6 +1348,167 @@ void launch_att_fwd_proj(int prec, const void* Kmat, int ldk, const void* Pmat, 
                        H, a, o.outT, up, 0, LstmBwdPoint{}, 0, nullptr, dr);
 }
 
+// ---- beam search: the K <= 16 hypotheses of a sentence share its source rows ----------------------------------------------
+// Scores of 16 positions of one sentence for all its hypotheses: a 16 x 16 tile of the matrix cores, k split over the KS wavefronts.
+struct BeamScores { const void* Mat; int Bs; const void* Ht; int ldt; const int32_t* len; int S, K, H; float* dots; };
+template <typename T, int KS>
+__device__ __forceinline__ void beam_scores(const BeamScores& d, int blk, float* red) {
+  const int tiles = (d.S + 15) >> 4;
+  int b, tile;
+  divmod_uniform(blk, tiles, b, tile);
+  const int n = min(d.len[b], d.S), i0 = 16 * tile;
+  if (i0 >= n) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, ns = (d.H + 31) >> 5;
+  const T* const krow = (const T*)d.Mat + ((size_t)min(i0 + (lane & 15), n - 1) * d.Bs + b) * d.H;
+  const T* const hrow = (const T*)d.Ht + (size_t)(b * d.K + min(lane & 15, d.K - 1)) * d.ldt;
+  v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
+  constexpr int U = 32 / KS > 4 ? 4 : 2;
+  for (int s0 = w; s0 < ns; s0 += KS * U) {
+    Frag<T> fk[U], fh[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = 32 * (s0 + KS * u) + 8 * (lane >> 4);
+      if (k < d.H) { fk[u].load(krow + k); fh[u].load(hrow + k); }
+      else { fk[u].zero(); fh[u].zero(); }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) mma16(acc, fk[u], fh[u]);
+  }
+  *reinterpret_cast<v4f*>(red + (w * 64 + lane) * 4) = acc;
+  __syncthreads();
+  if (w != 0) return;
+  acc = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int q = 0; q < KS; ++q) acc += *reinterpret_cast<const v4f*>(red + (q * 64 + lane) * 4);
+  const int hyp = lane & 15, i = i0 + 4 * (lane >> 4);
+  if (hyp >= d.K) return;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (i + e < n) d.dots[(size_t)(b * d.K + hyp) * d.S + i + e] = acc[e];
+}
+// The scores and, in the workgroups before them, W_c2 H_t: below 256 rows as att_dots_pre_kernel has it (16 x 16 tiles, k split over the
+// wavefronts), from there on 32 x 64 tiles, of which 16 x 16 ones would take in 2.7 times the bytes.
+// 640 rows, 64 sentences x 50 positions, width 1024: 11.6 us, and beam_mix_kernel 7.2, for scores 12, C_s 18 on source rows that were
+// there ten times, and W_c [C_s; H_t] 12 + 5.
+template <typename T, int KS, bool FM>
+__global__ __launch_bounds__(64 * KS) void beam_att_pre_kernel(int Bp, int n_gemm, StepGemm g, BeamScores d) {
+  __shared__ __align__(16) float red[KS * 256];
+  if ((int)blockIdx.x >= n_gemm) { beam_scores<T, KS>(d, (int)blockIdx.x - n_gemm, red); return; }
+  step_tanh_body<T, KS, 2, FM, true>(g, Bp, StepGrid{(g.N + 15) / 16, 1, (Bp + 15) / 16}, red);
+}
+template <typename T, bool FM>
+__global__ __launch_bounds__(512) void beam_att_pre_wide_kernel(int Bp, int n_gemm, StepGemm g, BeamScores d) {
+  constexpr int RT = 2, KS = 8, BT = 4;
+  __shared__ __align__(16) float red[KS * RT * BT * 256];
+  if ((int)blockIdx.x >= n_gemm) { beam_scores<T, KS>(d, (int)blockIdx.x - n_gemm, red); return; }
+  const int nbt_all = (Bp + 15) >> 4;
+  int x, kb, z;
+  if (!decode_block(StepGrid{(g.N + 16 * RT - 1) / (16 * RT), 1, (nbt_all + BT - 1) / BT}, x, kb, z)) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, n0 = x * 16 * RT, bt0 = z * BT, nbt = min(BT, nbt_all - bt0);
+  if constexpr (FM) {
+    const int ns0 = g.K0 >> 5, ns1 = g.K1 >> 5;
+    const bf16_t* wt[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) wt[rt] = (const bf16_t*)g.W_fm + (size_t)min(RT * x + rt, (g.N >> 4) - 1) * (ns0 + ns1) * 512;
+    step_contract_fm<RT, KS, 2, BT>(wt, (const bf16_t*)g.a0_fm, ns0, (const bf16_t*)g.a1_fm, ns1, bt0, nbt, red, ns0);
+  } else {
+    const T* wrow[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) wrow[rt] = (const T*)g.W + (size_t)min(n0 + 16 * rt + (lane & 15), g.N - 1) * g.ldw;
+    step_contract<T, RT, KS, 1, BT>(wrow, g.w0_off, g.w1_off, (const T*)g.a0, g.lda0, 0, (const T*)g.a1, g.lda1, g.K1, Bp, bt0, nbt, red);
+  }
+  const int rt = w / BT, bt = w - rt * BT;               // a tile of sums per wavefront
+  if (bt >= nbt) return;
+  const v4f r = step_tile_sum<RT, KS, BT>(red, rt, bt);
+  const int n = n0 + 16 * rt + 4 * (lane >> 4), b = 16 * (bt0 + bt) + (lane & 15);
+  if (b >= Bp) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (n + i < g.N) g.out[(size_t)b * g.ldout + n + i] = r[i];
+}
+// H_o = tanh(sum_i softmax(scores)_i P_i + u): 64 columns of a sentence's hypotheses per workgroup, a thread four columns of one.  The
+// sentence's rows pass through LDS 64 positions at a time, requested before the coefficients are worked out.
+template <typename T>
+__global__ __launch_bounds__(256) void beam_mix_kernel(const T* __restrict__ P, int Bs, const float* __restrict__ dots, const int32_t* __restrict__ len,
+                                                       int S, int K, int H, const float* __restrict__ u, int ldu, T* __restrict__ out, int ldo) {
+  constexpr int VE = 16 / sizeof(T), PPR = 64 / VE, NP = 64 * PPR / 256;   // 16-byte pieces of a row's 64 columns; a thread's of 64 rows
+  __shared__ __align__(16) T s_p[64][64];
+  extern __shared__ float s_a[];                           // [16][S | 1]
+  const int b = blockIdx.y, t = threadIdx.x, h0 = blockIdx.x * 64, n = min(len[b], S), pitch = S | 1;
+  const int hyp = t >> 4, l = t & 15, row = b * K + min(hyp, K - 1), col = h0 + 4 * l;
+  uint4 p[NP];
+  auto rows = [&](int i0) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int i = i0 + (t + 256 * q) / PPR, c = h0 + (t + 256 * q) % PPR * VE;
+      if (i < n && c < H) p[q] = *reinterpret_cast<const uint4*>(P + ((size_t)i * Bs + b) * H + c);
+      else p[q] = make_uint4(0, 0, 0, 0);
+    }
+  };
+  rows(0);
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  const bool mine = hyp < K && col < H;
+  float4 add = acc;
+  if (mine) add = *reinterpret_cast<const float4*>(u + (size_t)row * ldu + col);
+  {
+    float* const a = s_a + hyp * pitch;
+    float mx = -INFINITY, sum = 0.f;
+    for (int i = l; i < n; i += 16) { const float x = dots[(size_t)row * S + i]; a[i] = x; mx = fmaxf(mx, x); }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    for (int i = l; i < n; i += 16) { const float e = expf(a[i] - mx); a[i] = e; sum += e; }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    const float inv = n > 0 ? 1.f / sum : 0.f;
+    for (int i = l; i < n; i += 16) a[i] *= inv;            // (a thread's own, read by its 15 neighbours behind the barrier)
+  }
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    if (i0 > 0) __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NP; ++q) *reinterpret_cast<uint4*>(&s_p[(t + 256 * q) / PPR][(t + 256 * q) % PPR * VE]) = p[q];
+    __syncthreads();
+    if (i0 + 64 < n) rows(i0 + 64);
+    const int m = min(64, n - i0);
+    const float* const a = s_a + hyp * pitch + i0;
+#pragma unroll 8
+    for (int i = 0; i < m; ++i) {
+      const float c = a[i];
+      const T* const x = &s_p[i][4 * l];
+      acc.x += c * to_f<T>(x[0]); acc.y += c * to_f<T>(x[1]); acc.z += c * to_f<T>(x[2]); acc.w += c * to_f<T>(x[3]);
+    }
+  }
+  if (!mine) return;
+  constexpr bool FAST = sizeof(T) == 2;
+  const float o[4] = {tanh_of<FAST>(acc.x + add.x), tanh_of<FAST>(acc.y + add.y), tanh_of<FAST>(acc.z + add.z), tanh_of<FAST>(acc.w + add.w)};
+  store4<T>(out + (size_t)row * ldo + col, o);
+}
+void launch_beam_attention(int prec, const void* Kmat, const void* Pmat, int Bs, const void* Ht, int ldt, const StepGemm& u, const int32_t* len,
+                           int S, int B, int K, int H, float* dots, void* out, int ldo, hipStream_t st) {
+  const int Bp = (B * K + 15) / 16 * 16;
+  const BeamScores d{Kmat, Bs, Ht, ldt, len, S, K, H, dots};
+  const int n_scores = B * ((S + 15) / 16);
+  if (Bp >= 256) {
+    const int n_gemm = step_grid_blocks(StepGrid{(u.N + 31) / 32, 1, (Bp / 16 + 3) / 4});
+    const dim3 grid(n_gemm + n_scores);
+    if (prec && step_gemm_has_fm(u)) hipLaunchKernelGGL((beam_att_pre_wide_kernel<bf16_t, true>), grid, dim3(512), 0, st, Bp, n_gemm, u, d);
+    else if (prec) hipLaunchKernelGGL((beam_att_pre_wide_kernel<bf16_t, false>), grid, dim3(512), 0, st, Bp, n_gemm, u, d);
+    else hipLaunchKernelGGL((beam_att_pre_wide_kernel<float, false>), grid, dim3(512), 0, st, Bp, n_gemm, u, d);
+  } else {
+    const StepGrid sg{(u.N + 15) / 16, 1, Bp / 16};
+    const int n_gemm = step_grid_blocks(sg);
+    const int nsteps = (u.K1 / 8 + 3) / 4;
+#define GO(TT, KS, FM) hipLaunchKernelGGL((beam_att_pre_kernel<TT, KS, FM>), dim3(n_gemm + n_scores), dim3(64 * KS), 0, st, Bp, n_gemm, u, d)
+    if (prec && step_gemm_has_fm(u)) { if (nsteps > 16) GO(bf16_t, 16, true); else GO(bf16_t, 8, true); }
+    else if (prec) { if (nsteps > 16) GO(bf16_t, 16, false); else GO(bf16_t, 8, false); }
+    else { if (nsteps > 16) GO(float, 16, false); else GO(float, 8, false); }
+#undef GO
+  }
+  const dim3 gm((H + 63) / 64, B);
+  const size_t lds = (size_t)16 * (S | 1) * sizeof(float);
+  if (prec) hipLaunchKernelGGL(beam_mix_kernel<bf16_t>, gm, dim3(256), lds, st, (const bf16_t*)Pmat, Bs, dots, len, S, K, H, u.out, u.ldout, (bf16_t*)out, ldo);
+  else hipLaunchKernelGGL(beam_mix_kernel<float>, gm, dim3(256), lds, st, (const float*)Pmat, Bs, dots, len, S, K, H, u.out, u.ldout, (float*)out, ldo);
+}
+
 // One workgroup: 64 columns of one sentence for 16 steps; the rows H_s^i pass through LDS 64 positions at a time.
 template <typename T>
 __global__ __launch_bounds__(256) void att_context_kernel(const T* __restrict__ Hs, int lds, const float* __restrict__ a,

@@ -1191,3 +1191,29 @@ def test_fp32_products_in_three_parts(B, S, E, H):
     assert (np.abs(got[plain] - ref[plain]) <= bound).all(), np.abs(got[plain] - ref[plain]).max()
     # (pre-activations of 1e36 and more: gates of exactly 0, 1 or -1 whatever the rounding)
     assert np.array_equal(got[~plain], ref[~plain])
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("B,beam,S,H,V", [(1, 1, 1, 16, 8), (7, 9, 65, 48, 264), (13, 10, 5, 16, 24584), (17, 15, 17, 32, 24584), (26, 10, 4, 32, 24592),
+                                          (40, 10, 3, 32, 24584), (40, 16, 3, 16, 24584)])
+def test_beam_search_over_the_tile_shapes_of_the_logits(prec, B, beam, S, H, V):
+    """One to 640 rows: every width of the logits' row tile, rows that end inside one, groups that end inside the vocabulary, source
+    sentences longer than the 64 positions that the mix takes at a time, and both forms of W_c2 H_t (256 rows).  Against the
+    oracle: tokens wherever its decision gap exceeds what the precision resolves; the best tokens' biases sit at the ends."""
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=104, tgt_vocab=V, emb=16, hidden=H, layers=1)
+    rng = np.random.default_rng(B + V + S)
+    params = I.make_params(cfg, seed=6, scale=0.3)
+    params["B_o"] = rng.uniform(-1.0, 1.0, V).astype(params["B_o"].dtype)
+    params["B_o"][[4, V // 2, V - 3, V - 1]] += 2.0
+    src, sl, _, _ = ragged_batch(rng, B, S, 4, 104, V)
+    tr = binding.Trainer(cfg, B * beam, S, 4, precision=prec)
+    tr.set_params(I.flatten(params, cfg))
+    ids, lens, score = tr.beam_decode(src, sl, 4, beam=beam, length_penalty=0.6, eos_id=3)
+    oids, olens, oscore, margins = O.beam_decode(cfg, params, src, sl, 4, beam, 0.6, bos_id=2, eos_id=3)
+    tr.close()
+    # (a logit moves by about atol(H_o) * row norm, a score by four of them: see test_beam_search_matches_the_oracle)
+    tol = (2e-5 if prec == 0 else 2e-2) * 2.0 * np.linalg.norm(params["W_o"], axis=1).max() * 4
+    sure = margins > tol
+    assert np.array_equal(ids[sure], oids[sure]) and np.array_equal(lens[sure], olens[sure])
+    assert (np.abs(score - oscore) <= tol + 1e-4 * np.abs(oscore)).all()
