@@ -25,6 +25,9 @@ static int env_int(const char* name, int dflt) {
 static const int GEMM_BIG_MIN_TILES = env_int("CMT_GEMM_BIG_MIN_TILES", 144);
 static const int GEMM_SPLIT_BELOW = env_int("CMT_GEMM_SPLIT_BELOW", 257);       // small tiles
 static const int GEMM_SPLIT_TARGET = env_int("CMT_GEMM_SPLIT_TARGET", 1024);
+// Medium tiles of which there is at most one per CU take four k tiles of LDS, three of them on their way, instead of two for two
+// workgroups per CU, us (two | four): 200 tiles, k 4096 56 | 50, k 2048 35 | 31; 234 tiles, k 1096 29 | 26; 400 tiles, k 1024 28 | 40.
+static const int GEMM_DEEP_MAX_TILES = env_int("CMT_GEMM_DEEP_MAX_TILES", 256);
 static const int GEMM_SPLIT_MAX = env_int("CMT_GEMM_SPLIT_MAX", 16);
 static const int GEMM_BIGSPLIT_MIN_K = env_int("CMT_GEMM_BIGSPLIT_MIN_K", 8192);
 // beyond this many big tiles (by the host's row count) the small tile without a split measured faster (large
@@ -47,7 +50,7 @@ __host__ __device__ inline int gemm_dyn_splits(int tiles, int launched, int roun
 }
 
 // One output tile (the one of virtual workgroup id vb) of C (+)= A B^T (+ bias): main loop and store.
-template <typename T, int WM, int WN, int TA, int TB, bool CHAIN>
+template <typename T, int WM, int WN, int TA, int TB, bool CHAIN, int STAGES>
 __device__ __forceinline__ void gemm_nt_tile(const T* __restrict__ A, int lda, const T* __restrict__ B, int ldb, int M, int N, int K,
                                              float* __restrict__ Cf0, T* __restrict__ Ct, int ldc, const float* __restrict__ bias,
                                              int accumulate, int ntn, int kchunk, size_t plane_stride, int dyn_split, int vb,
@@ -64,7 +67,7 @@ __device__ __forceinline__ void gemm_nt_tile(const T* __restrict__ A, int lda, c
   const int klen = min(kchunk, K - k0);
   if (klen <= 0 && gridDim.y == 1) return;
   v16f acc[TA][TB];
-  gemm_mainloop<T, WM, WN, TA, TB, CHAIN ? GEMM_F32_CHAIN : GEMM_F32_SPLIT>(A + k0, lda, B + k0, ldb, M, N, klen, m0, n0, acc, smem, GemmZero{});
+  gemm_mainloop<T, WM, WN, TA, TB, CHAIN ? GEMM_F32_CHAIN : GEMM_F32_SPLIT, STAGES>(A + k0, lda, B + k0, ldb, M, N, klen, m0, n0, acc, smem, GemmZero{});
   float* const Cf = gridDim.y > 1 ? Cf0 + blockIdx.y * plane_stride : Cf0;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wm = w / WN, wn = w % WN;
@@ -94,14 +97,14 @@ __device__ __forceinline__ void gemm_nt_tile(const T* __restrict__ A, int lda, c
 // WALK: the launch has fewer workgroups than tiles (it is to leave part of the chip to other streams) and every
 // workgroup walks the tiles of the virtual ids blockIdx.x, blockIdx.x + grid, ...  It is a variant of its own because
 // the loop costs the one-tile-per-workgroup kernel a spilled register.
-template <typename T, int WM, int WN, int TA, int TB, bool WALK = false, bool CHAIN = false>
+template <typename T, int WM, int WN, int TA, int TB, bool WALK = false, bool CHAIN = false, int STAGES = 2>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_kernel(const T* __restrict__ A, int lda, const T* __restrict__ B, int ldb,
                                                                int M, int N, int K, float* __restrict__ Cf0, T* __restrict__ Ct,
                                                                int ldc, const float* __restrict__ bias, int accumulate, int ntn,
                                                                int kchunk, size_t plane_stride, RowLimit lim, int lim_kind,
                                                                int dyn_split) {
   using G = GemmTile<T, WM, WN, TA, TB>;
-  __shared__ __align__(16) char smem[G::SMEM_BYTES];
+  __shared__ __align__(16) char smem[STAGES > 2 ? STAGES * (G::BM + G::BN) * 128 : G::SMEM_BYTES];
   if (lim.n) {                                     // a bound that only the device knows (uniform over the grid)
     const int e = max(*lim.n - lim.base, 0);
     if (lim_kind == 1) M = min(M, e);
@@ -111,12 +114,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_kernel(const T* __restri
   if constexpr (WALK) {
     const int ntiles8 = (((M + G::BM - 1) / G::BM * ntn + 7) >> 3) << 3;
     for (int vb = blockIdx.x; vb < ntiles8; vb += gridDim.x) {
-      gemm_nt_tile<T, WM, WN, TA, TB, CHAIN>(A, lda, B, ldb, M, N, K, Cf0, Ct, ldc, bias, accumulate, ntn, kchunk, plane_stride, dyn_split,
+      gemm_nt_tile<T, WM, WN, TA, TB, CHAIN, STAGES>(A, lda, B, ldb, M, N, K, Cf0, Ct, ldc, bias, accumulate, ntn, kchunk, plane_stride, dyn_split,
                                           vb, smem);
       __syncthreads();                             // (the next tile refills the LDS)
     }
   } else {
-    gemm_nt_tile<T, WM, WN, TA, TB, CHAIN>(A, lda, B, ldb, M, N, K, Cf0, Ct, ldc, bias, accumulate, ntn, kchunk, plane_stride, dyn_split,
+    gemm_nt_tile<T, WM, WN, TA, TB, CHAIN, STAGES>(A, lda, B, ldb, M, N, K, Cf0, Ct, ldc, bias, accumulate, ntn, kchunk, plane_stride, dyn_split,
                                         (int)blockIdx.x, smem);
   }
 }
@@ -168,7 +171,7 @@ static void launch_planes_sum(const float* planes, int nks, size_t pstride, floa
                        accumulate, rl, dyn_bm, dyn_ntn, dyn_rounds);
 }
 
-template <typename T, int WM, int WN, int TA, int TB>
+template <typename T, int WM, int WN, int TA, int TB, int STAGES = 2>
 static void gemm_go(dim3 grid, hipStream_t st, const void* A, int lda, const void* B, int ldb, int M, int N, int K, float* out,
                     void* Ct, int ldc, const float* bias, int acc, int ntn, int kchunk, size_t pstride, RowLimit lim, int lim_kind,
                     int dyn_split = 0, int wg_cap = 0, int chain = 0) {
@@ -185,7 +188,7 @@ static void gemm_go(dim3 grid, hipStream_t st, const void* A, int lda, const voi
       return;
     }
   if (walk) go(gemm_nt_kernel<T, WM, WN, TA, TB, true>);
-  else go(gemm_nt_kernel<T, WM, WN, TA, TB>);
+  else go(gemm_nt_kernel<T, WM, WN, TA, TB, false, false, STAGES>);
 }
 
 void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, int M, int N, int K,
@@ -252,7 +255,7 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
     if constexpr (decltype(shape)::value == 1)
       gemm_go<T, 2, 2, 1, 1>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, cap, chain);
     else
-      gemm_go<T, 2, 2, 2, 2>(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, cap, chain);
+      (nb <= GEMM_DEEP_MAX_TILES ? gemm_go<T, 2, 2, 2, 2, 4> : gemm_go<T, 2, 2, 2, 2, 2>)(dim3(grid, nks), st, A, lda, B, ldb, M, N, K, out, Ct, oldc, obias, oacc, ntn, kchunk, pstride, lim, lim_kind, 0, cap, chain);
   };
   using One = std::integral_constant<int, 1>;
   using Two = std::integral_constant<int, 2>;

@@ -6,14 +6,14 @@
 //     products of a small network or batch that are a few dozen tiles of the next size, where what a launch takes is
 //     the chain prologue - contraction - store of one workgroup (16 stores a lane instead of 64).
 //   * 2x2 wavefronts, 2x2 tiles each: 128 x 128, 256 threads, 72 KB of LDS, two workgroups per CU
-//     hiding each other's barriers.  Needs 32 KB from L2 per 2 x 128 x 128 x 64 flops.
+//     hiding each other's barriers (128 KB, four k tiles, where there is one per CU at most).  Needs 32 KB from L2 per 2 x 128 x 128 x 64 flops.
 //   * 4x4 wavefronts, 2x2 tiles each: 256 x 256, 1024 threads, 144 KB of LDS, one workgroup per CU.
 //     Half the L2 traffic per flop (64 KB per k tile): 1.3 PFLOP/s on large problems, and faster than the
 //     others from about 150 tiles up.
 // (fp32: the first, and 256 x 128 on 512 threads.)
 // What bounds both is the rate at which a CU takes data from L2: about 49 GB/s per CU measured with the main
 // loop's loads alone (12.6 TB/s over the chip), i.e. at most 1.6 PFLOP/s for the big tile and 0.8 for the small.
-// Tiles of k are double-buffered in LDS; the next tile's global loads are in
+// Tiles of k are double-buffered in LDS (or four deep); the next tile's global loads are in
 // flight while the current one feeds the matrix cores.  16-bit operands go from global memory straight
 // into LDS (global_load_lds_dwordx4, no staging registers): rows of 128 bytes without padding, the
 // 16-byte chunks of a row XOR-swizzled by the row number so that fragment reads stay free of bank
@@ -161,12 +161,19 @@ __device__ __forceinline__ void gemm_dl_fill_tail(const bf16_t* __restrict__ bas
   }
 }
 
-template <int WM, int WN, int TA, int TB>
+// At most n transfers of this wavefront are still on their way (a stage makes PER of them).
+template <int PER> __device__ __forceinline__ void gemm_dl_wait_but(int stages) {
+  if (stages >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
+  else if (stages == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER) : "memory");
+  else gemm_dl_wait();
+}
+// STAGES k tiles in LDS, STAGES - 1 of them on their way while one feeds the matrix cores.
+template <int WM, int WN, int TA, int TB, int STAGES>
 __device__ __forceinline__ void gemm_mainloop_dl(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
                                                  int M, int N, int K, int m0, int n0, v16f (&acc)[TA][TB], char* smem) {
   constexpr int NT = 64 * WM * WN, BM = 32 * TA * WM, BN = 32 * TB * WN;
-  constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
-  static_assert(2 * STAGE <= GemmTile<bf16_t, WM, WN, TA, TB>::SMEM_BYTES, "LDS image larger than the tile's allocation");
+  constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128, PER = (BM + BN) * 8 / NT;
+  static_assert(STAGES >= 2 && STAGES <= 4, "the waits count up to two later stages");
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = w / WN, wn = w % WN;
   unsigned oa[BM * 8 / NT], ob[BN * 8 / NT];
@@ -183,20 +190,13 @@ __device__ __forceinline__ void gemm_mainloop_dl(const bf16_t* __restrict__ A, i
       gemm_dl_fill_tail<NT, BN>(pb + k0, ob, K - k0, stage + A_BYTES);
     }
   };
-  fill(smem, 0);
-  gemm_dl_wait();
-  __syncthreads();
   // fragment of row r at k step ks: chunk 2 ks + lane / 32, at position chunk ^ gemm_swz(r)
   int fa_row[TA], fa_s[TA], fb_row[TB], fb_s[TB];
 #pragma unroll
   for (int x = 0; x < TA; ++x) { const int r = (wm * TA + x) * 32 + (lane & 31); fa_row[x] = r * 128; fa_s[x] = gemm_swz(r) ^ (lane >> 5); }
 #pragma unroll
   for (int x = 0; x < TB; ++x) { const int r = (wn * TB + x) * 32 + (lane & 31); fb_row[x] = A_BYTES + r * 128; fb_s[x] = gemm_swz(r) ^ (lane >> 5); }
-  const int nk = (K + 63) / 64;
-  for (int kt = 0; kt < nk; ++kt) {
-    char* cur = smem + (kt & 1) * STAGE;
-    char* nxt = smem + ((kt + 1) & 1) * STAGE;
-    if (kt + 1 < nk) fill(nxt, (kt + 1) * 64);
+  auto products = [&](const char* cur) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       Frag<bf16_t> fa[TA], fb[TB];
@@ -209,7 +209,33 @@ __device__ __forceinline__ void gemm_mainloop_dl(const bf16_t* __restrict__ A, i
 #pragma unroll
         for (int b = 0; b < TB; ++b) mma32(acc[a][b], fa[a], fb[b]);
     }
+  };
+  const int nk = (K + 63) / 64;
+  if constexpr (STAGES == 2) {
+    fill(smem, 0);
     gemm_dl_wait();
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+      if (kt + 1 < nk) fill(smem + ((kt + 1) & 1) * STAGE, (kt + 1) * 64);
+      products(smem + (kt & 1) * STAGE);
+      gemm_dl_wait();
+      __syncthreads();
+    }
+  } else {
+    const int whole = K / 64;                              // (a last part of a k tile goes through registers: nothing of it is on its way)
+    int in = 0, out = 0;                                   // stage buffers
+#pragma unroll
+    for (int i = 0; i < STAGES - 1; ++i)
+      if (i < nk) fill(smem + i * STAGE, i * 64);
+    in = STAGES - 1;
+    for (int kt = 0; kt < nk; ++kt) {
+      gemm_dl_wait_but<PER>(min(STAGES - 2, whole - 1 - kt));
+      __syncthreads();                                     // every wavefront's share is there, and the last stage read is free
+      if (kt + STAGES - 1 < nk) fill(smem + in * STAGE, (kt + STAGES - 1) * 64);
+      products(smem + out * STAGE);
+      in = in + 1 == STAGES ? 0 : in + 1;
+      out = out + 1 == STAGES ? 0 : out + 1;
+    }
     __syncthreads();
   }
 }
@@ -395,11 +421,11 @@ __device__ __forceinline__ void gemm_mainloop_regs(const float* __restrict__ A, 
 // init(acc) sets what the products are added to (zeros, or e.g. a bias).  
 // FORM, of fp32: split with the small products in a sum of their own; all products in one sum; fp32 instructions.
 enum { GEMM_F32_SPLIT = 0, GEMM_F32_ONE_SUM = 1, GEMM_F32_CHAIN = 2 };
-template <typename T, int WM, int WN, int TA, int TB, int FORM = 0, typename Init>
+template <typename T, int WM, int WN, int TA, int TB, int FORM = 0, int STAGES = 2, typename Init>
 __device__ __forceinline__ void gemm_mainloop(const T* __restrict__ A, int lda, const T* __restrict__ B, int ldb,
                                               int M, int N, int K, int m0, int n0, v16f (&acc)[TA][TB], char* smem, Init init) {
   init(acc);
-  if constexpr (sizeof(T) == 2) gemm_mainloop_dl<WM, WN, TA, TB>(A, lda, B, ldb, M, N, K, m0, n0, acc, smem);
+  if constexpr (sizeof(T) == 2) gemm_mainloop_dl<WM, WN, TA, TB, STAGES>(A, lda, B, ldb, M, N, K, m0, n0, acc, smem);
   else if constexpr (FORM == GEMM_F32_CHAIN) gemm_mainloop_regs<WM, WN, TA, TB>(A, lda, B, ldb, M, N, K, m0, n0, acc, smem);
   else if (!gemm_mainloop_f32<WM, WN, TA, TB, FORM != GEMM_F32_ONE_SUM>(A, lda, B, ldb, M, N, K, m0, n0, acc, smem)) {
     init(acc);
