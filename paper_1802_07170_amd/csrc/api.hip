@@ -72,11 +72,13 @@ struct LD {
   bool fmb = false;
 };
 
-// Row pitch padding of the per-step activation operands.  The step kernels read 16 sentences x 64
+// Row pitch padding of the per-step activation operands.  The step kernels that read row-major operands take 16 sentences x 64
 // bytes per fragment load; with a power-of-two pitch those 16 segments fall on the same cache banks
 // (measured: 14.3 -> 11.0 us for the decoder LSTM step with 16 bytes of padding; rows kept 128-byte aligned by
 // padding with 64 elements instead: 11.6 us against 9.8 us, 32 / 72 / 136 elements: 10.0 - 10.2 us).
-constexpr int ACT_PAD = 8;
+// Where fragment-major copies serve those kernels, what is left to read the rows are the products over all positions, 128 bytes of a row at
+// a time: rows of whole lines, or each piece takes two (dX of 3200 positions, 4096 -> 1024: 73 -> 47 us; medium step 5.87 -> 5.78 ms).
+constexpr int ACT_PAD = 8, ACT_PAD_LINES = 64;
 
 // Row capacity of an output-layer slab: CE_SLAB_MAX_ROWS unless CMT_CE_SLAB_ROWS asks for less (a multiple of 256
 // from 256 up; read whenever a handle or a size query is set up, so both see the same value).
@@ -120,7 +122,8 @@ struct cmt_handle {
   std::vector<ParamInfo> table;
   std::string err;
   int Bpm = 0;                          // padded max batch
-  int PH = 0;                           // row pitch of HoBuf, Cs, dPre: H + ACT_PAD
+  int PH = 0;                           // row pitch of HoBuf, Cs, dPre: H + padding (see ACT_PAD)
+  bool pad_lines = true;                // (not in the static array: what fits there does not depend on it)
   // last-step shape
   int B = 0, Bp = 0, S = 0, T = 0;
   bool have_step = false;
@@ -278,7 +281,8 @@ size_t layout(cmt_handle* h, char* base) {
   const int Bp = h->Bpm, Sm = c.max_src_len, Tm = c.max_tgt_len;
   const size_t Ms = (size_t)Sm * Bp, Mt = (size_t)Tm * Bp;
   Bump a(base);
-  h->PH = H + ACT_PAD;
+  const int pad = h->pad_lines && c.precision && H >= 256 && H % 64 == 0 ? ACT_PAD_LINES : ACT_PAD;
+  h->PH = H + pad;
   const size_t PH = h->PH;
   h->Pc = c.precision ? a.take(h->nparams * esz) : (char*)h->params;
   // (The whole loops take batches up to LOOP_MAX_BATCH; Bl: the rows of their slots.  The slots are there whether or not
@@ -287,7 +291,7 @@ size_t layout(cmt_handle* h, char* base) {
   const bool loop_all = loops && h->loop_slots == LOOP_SLOTS_ALL;
   const size_t Bl = std::min(Bp, LOOP_MAX_BATCH);
   auto ld_alloc = [&](LD& d, int Kin, int Hh, int Lm, bool gx, int Kstep, bool encoder) {
-    d.Kin = Kin; d.Hh = Hh; d.ph = Hh + ACT_PAD; d.pg = 4 * Hh + ACT_PAD;
+    d.Kin = Kin; d.Hh = Hh; d.ph = Hh + pad; d.pg = 4 * Hh + pad;
     const size_t M = (size_t)Lm * Bp;
     d.Kstep = Kstep;
     d.fm = !encoder && c.precision && Hh % 32 == 0 && Kstep % 32 == 0;
@@ -374,7 +378,7 @@ size_t layout(cmt_handle* h, char* base) {
   else if (h->HoFeedF) h->HoFeedX = h->HoFeedF;
   else if (loop_all) h->HoFeedX = h->HoBufT;                             // (transposed after the forward loop)
   h->HoDrop = a.take((Mt + Bp) * PH * esz);
-  h->ldxcat = E + H + ACT_PAD;
+  h->ldxcat = E + H + pad;
   h->xcat = a.take((size_t)Bp * h->ldxcat * esz);
   h->dec_tok = (int32_t*)a.take((size_t)Bp * 4); h->dec_done = (int32_t*)a.take((size_t)Bp * 4);
   h->dec_mask = (float*)a.take((size_t)Bp * 4);
@@ -1525,6 +1529,7 @@ int cmt_eval_loss_static(cmt_handle* h, const int32_t* src_ids_dev, const int32_
   // buffers that are there already; for one position, or 16 units, one of them is a few KB larger, and a shape that just fits
   // without those gets the launches per position.)
   v.loop_slots = LOOP_SLOTS_EVAL;
+  v.pad_lines = false;
   size_t need = layout(&v, nullptr);
   if (need > (size_t)CMT_STATIC_SCRATCH_BYTES) {
     v.loop_slots = LOOP_SLOTS_NONE;
