@@ -26,6 +26,7 @@
 
 #include "../../include/cytonmt_hip.h"
 #include "kernels.h"
+#include "recur_plan.h"
 #include "section_gate.h"
 
 using namespace cmt;
@@ -517,12 +518,13 @@ void weight_grads(cmt_handle* h, LD& d, int Lsteps, const std::vector<std::pair<
   }
 }
 // launches what weight_grads (and the callers that add W_c / W_a problems) have collected, as one queue of tiles
-void flush_dw_group(cmt_handle* h, hipStream_t st) {
+// big_cap: see launch_gemm_nt_group.
+void flush_dw_group(cmt_handle* h, hipStream_t st, int big_cap = 0) {
   launch_transpose_multi(h->prec, h->dw_tr.data(), (int)h->dw_tr.size(), st);
   launch_sum_parts_multi(h->dw_sums.data(), (int)h->dw_sums.size(), TRANSPOSE_SPLITS, st);
   h->dw_tr.clear(); h->dw_sums.clear();
   launch_gemm_nt_group(h->prec, h->dw_group.data(), (int)h->dw_group.size(), st, h->gsplit2, h->gsplit2_floats,
-                       st != h->st ? h->side_wgs : 0);
+                       st != h->st ? h->side_wgs : 0, st != h->st ? big_cap : 0);
   h->dw_group.clear();
 }
 
@@ -696,7 +698,8 @@ void dec_att_bwd_proj(cmt_handle* h, int j, int S, bool last) {
 // caller): per layer one GEMM for the input part of all positions and one launch for the whole recurrence (bottom layer:
 // both directions), then the attention keys and the decoder's initial states.  Returns H_s (top-layer states) and its
 // row pitch.
-void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
+// states_fm: the decoder's per-position kernels read the initial states (its loops make copies of their own).
+void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out, bool states_fm) {
   const cmt_config& c = h->cfg;
   const int p = h->prec, E = c.emb_dim, H = c.hidden, Hd = H / 2, L = c.layers, Bp = h->Bp;
   const size_t esz = h->esz;
@@ -719,8 +722,14 @@ void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
     add_fill(z, h->tickets, SEQ_TICKETS, 4);
     launch_fill_multi(z.data(), (int)z.size(), st);
   }
-  for (LD* d : {&ef, &eb})
-    launch_gemm_nt(p, h->Xs, E, d->W, E + Hd, Ms, 4 * Hd, E, d->Gx, nullptr, 4 * Hd, P + d->b_off, 0, st);
+  {   // the input parts of both directions: one launch
+    GemmProb g[2];
+    for (int i = 0; i < 2; ++i) {
+      LD& d = i ? eb : ef;
+      g[i] = GemmProb{h->Xs, d.W, d.Gx, E, E + Hd, 4 * Hd, Ms, 4 * Hd, E, 0, P + d.b_off};
+    }
+    launch_gemm_nt_group(p, g, 2, st, nullptr, 0);
+  }
   auto seq_dir = [&](LD& e) {
     SeqFwdDir d{};
     d.W = e.W; d.ldw = e.Kin + e.Hh; d.wh_off = e.Kin; d.gx = e.Gx; d.mask = h->mask_s; d.X = e.X;
@@ -773,7 +782,7 @@ void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out) {
       add_copy(cp, e.Cst + (size_t)S * BH, H, d.Cst, H, Bp, H, 4);
     }
     launch_copy2d_multi(cp.data(), (int)cp.size(), st);
-    for (int l = 0; l < L; ++l)                     // fragment-major copies of the initial states
+    for (int l = 0; states_fm && l < L; ++l)        // fragment-major copies of the initial states
       if (h->dec[l].fm) launch_fm_pack(h->dec[l].Hst, h->dec[l].ph, Bp, H, h->dec[l].HstF, st);
   }
 }
@@ -972,7 +981,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   const bool split = alone && h->gate->crowded(*h->section);
   Section sec(h);
   sec.open(alone && !split);
-  enqueue_encoder(h, S, &Hs, &ldHs);
+  enqueue_encoder(h, S, &Hs, &ldHs, !loop);
   if (!loop || split) sec.close();
   LD& ef = h->enc[0]; LD& eb = h->enc[1];
   // ---- decoder time loop --------------------------------------------------------------------------
@@ -1246,7 +1255,13 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
                                   : std::pair<const char*, int>{h->dec[l - 1].HstT + (size_t)Bp * esz, (T + 1) * Bp},
                              {e.HstT, (T + 1) * Bp}}, {H, H}, sd);
   }
-  flush_dw_group(h, sd);                           // W_c and every decoder layer's weight gradient: one launch
+  // W_c and every decoder layer's weight gradient: one launch.  The top encoder layers' recurrences come beside it, one workgroup to
+  // a CU; where they take half of the chip at most, the 256 x 256 tiles, which hold a CU for long, are left the rest: 64 sentences, width 1024,
+  // first recurrence 267 -> 218 us, the product before it 156 -> 74, this launch 312 -> 506, the step 5.74 -> 5.61 ms.  (128 sentences take
+  // every CU: a cap of 128 19.1 -> 19.4; groups of smaller tiles: width 512 2.564 -> 2.574.)
+  const SeqPlan top = seq_bwd_plan(p, 1, Bp, H);
+  const int beside = top.groups * top.group;
+  flush_dw_group(h, sd, L > 1 && beside <= 128 ? 256 - beside : 0);
   launch_gemm_nt(p, h->dec[0].dG, h->dec[0].pg, h->dec[0].Wt, 4 * H, Mt, E, 4 * H, h->dXt, nullptr, E, nullptr, 0, sd);
   launch_embed_scatter(h->dXt, h->tok_t, Mt, c.tgt_vocab, E, G + h->off_Etgt, sd, false);
 
@@ -1320,8 +1335,8 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
     weight_grads(h, ef, S, {{h->XsT, Ms}, {ef.HstT, (S + 1) * Bp}}, {E, Hd}, sd);
     weight_grads(h, eb, S, {{h->XsT, Ms}, {eb.HstT + (size_t)Bp * esz, (S + 1) * Bp}}, {E, Hd}, sd);
     flush_dw_group(h, sd);
-    launch_gemm_nt(p, ef.dG, ef.pg, ef.Wt, 4 * Hd, Ms, E, 4 * Hd, h->dXs, nullptr, E, nullptr, 0, st);
-    launch_gemm_nt(p, eb.dG, eb.pg, eb.Wt, 4 * Hd, Ms, E, 4 * Hd, h->dXs, nullptr, E, nullptr, 1, st);
+    const GemmProb dx{ef.dG, ef.Wt, h->dXs, ef.pg, 4 * Hd, E, Ms, E, 4 * Hd, 0, nullptr, eb.dG, eb.Wt, eb.pg, 4 * Hd, 4 * Hd};
+    launch_gemm_nt_group(p, &dx, 1, st, nullptr, 0);
     if (esrc_cleared) (void)hipStreamWaitEvent(st, esrc_cleared, 0);
     launch_embed_scatter(h->dXs, h->tok_s, Ms, c.src_vocab, E, G + h->off_Esrc, st, false);
   }
@@ -1635,7 +1650,7 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
   const bool split = alone && h->gate->crowded(*h->section);
   Section sec(h);
   sec.open(alone && !split);
-  enqueue_encoder(h, S, &Hs, &ldHs);
+  enqueue_encoder(h, S, &Hs, &ldHs, !loop);
   if (!loop || split) sec.close();
   if (proj) launch_gemm_nt(p, Hs, ldHs, h->Pw(h->off_Wc), 2 * H, S * Bp, H, H, nullptr, h->PmatT, H, nullptr, 0, st);
   launch_dec_init(B, Bp, max_len, c.bos_id, c.pad_id, h->dec_tok, h->dec_done, out_ids_dev, out_len_dev, h->dec_mask, st);
@@ -1748,7 +1763,7 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
   note_capture(h);
   Section sec(h);
   sec.open(false);
-  enqueue_encoder(h, S, &Hs, &ldHs);                 // also leaves the decoder's initial states in slot 0 (BpE rows)
+  enqueue_encoder(h, S, &Hs, &ldHs, false);                 // also leaves the decoder's initial states in slot 0 (BpE rows)
   sec.close();
   h->drop_p = keep_p;
   // one decoder row per hypothesis: the initial states repeated K times; the attention runs on the projected source rows, as in

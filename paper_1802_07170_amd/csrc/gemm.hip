@@ -267,10 +267,10 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
 constexpr int GEMM_GROUP_MAX = 16;
 struct GemmGroupArgs { int n; int tile_start[GEMM_GROUP_MAX + 1]; GemmProb p[GEMM_GROUP_MAX]; };
 
-template <typename T, int WM, int WN, int TA, int TB>
+template <typename T, int WM, int WN, int TA, int TB, int STAGES>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_group_kernel(GemmGroupArgs g) {
   using G = GemmTile<T, WM, WN, TA, TB>;
-  __shared__ __align__(16) char smem[G::SMEM_BYTES];
+  __shared__ __align__(16) char smem[STAGES > 2 ? STAGES * (G::BM + G::BN) * 128 : G::SMEM_BYTES];
   // the workgroups walk the tile queue: workgroup v takes the tiles of the virtual ids v, v + grid, v + 2 grid, ...
   // (the grid is a multiple of 8, so a workgroup stays with the tile range of its XCD); a grid as large as the
   // queue is the plain one-tile-per-workgroup launch
@@ -285,7 +285,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_group_kernel(GemmGroupAr
   int m0, n0;
   gemm_tile_from_index(id - g.tile_start[q], (M + G::BM - 1) / G::BM, (N + G::BN - 1) / G::BN, G::BM, G::BN, m0, n0);
   v16f acc[TA][TB];
-  gemm_mainloop<T, WM, WN, TA, TB>((const T*)pr.A, pr.lda, (const T*)pr.B, pr.ldb, M, N, pr.K, m0, n0, acc, smem, GemmZero{});
+  GemmZero{}(acc);
+  for (int part = 0; part < (pr.A2 ? 2 : 1); ++part)
+    gemm_mainloop<T, WM, WN, TA, TB, 0, STAGES>((const T*)(part ? pr.A2 : pr.A), part ? pr.lda2 : pr.lda, (const T*)(part ? pr.B2 : pr.B),
+                                                part ? pr.ldb2 : pr.ldb, M, N, part ? pr.K2 : pr.K, m0, n0, acc, smem, [](v16f (&)[TA][TB]) {});
   __syncthreads();                                        // (the next tile of a walking workgroup refills the LDS)
   float* __restrict__ C = pr.C;
   const int accumulate = pr.accumulate;
@@ -295,6 +298,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_group_kernel(GemmGroupAr
   for (int nt = 0; nt < TB; ++nt) {
     const int col = n0 + wn * 32 * TB + nt * 32 + (lane & 31);
     if (col >= N) continue;
+    const float bv = pr.bias ? pr.bias[col] : 0.f;
 #pragma unroll
     for (int mt = 0; mt < TA; ++mt) {
 #pragma unroll
@@ -302,14 +306,15 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_group_kernel(GemmGroupAr
         const int row = m0 + wm * 32 * TA + mt * 32 + acc32_row(lane, i);
         if (row >= M) continue;
         const size_t o = (size_t)row * ldc + col;
-        C[o] = accumulate ? C[o] + acc[mt][nt][i] : acc[mt][nt][i];
+        const float v = acc[mt][nt][i] + bv;
+        C[o] = accumulate ? C[o] + v : v;
       }
     }
   }
   }
 }
 
-template <typename T, int WM, int WN, int TA, int TB>
+template <typename T, int WM, int WN, int TA, int TB, int STAGES = 2>
 static void gemm_group_go(const GemmProb* probs, int n, hipStream_t st, int wg_cap) {
   using G = GemmTile<T, WM, WN, TA, TB>;
   for (int c0 = 0; c0 < n; c0 += GEMM_GROUP_MAX) {
@@ -325,19 +330,24 @@ static void gemm_group_go(const GemmProb* probs, int n, hipStream_t st, int wg_c
     if (nt == 0) continue;
     int grid = ((nt + 7) / 8) * 8;
     if (wg_cap > 0 && grid > (wg_cap + 7) / 8 * 8) grid = (wg_cap + 7) / 8 * 8;
-    hipLaunchKernelGGL((gemm_nt_group_kernel<T, WM, WN, TA, TB>), dim3(grid), dim3(64 * WM * WN), 0, st, g);
+    hipLaunchKernelGGL((gemm_nt_group_kernel<T, WM, WN, TA, TB, STAGES>), dim3(grid), dim3(64 * WM * WN), 0, st, g);
   }
 }
 
 void launch_gemm_nt_group(int prec, const GemmProb* probs, int n, hipStream_t st, float* split_scratch, size_t split_scratch_floats,
-                          int wg_cap) {
+                          int wg_cap, int big_cap) {
   if (!prec) {
     // fp32 operands: one launch per problem, k split over workgroups where there are few tiles.  These GEMMs are
     // matrix-core bound either way, and the shorter workgroups of the split form leave the CUs sooner to the
     // recurrences' kernels running beside them (small workload: 11.2 against 11.4 ms per step).
-    for (int i = 0; i < n; ++i)
-      launch_gemm_nt(prec, probs[i].A, probs[i].lda, probs[i].B, probs[i].ldb, probs[i].M, probs[i].N, probs[i].K, probs[i].C, nullptr,
-                     probs[i].ldc, nullptr, probs[i].accumulate, st, split_scratch, split_scratch_floats, RowLimit{}, 0, wg_cap);
+    for (int i = 0; i < n; ++i) {
+      const GemmProb& q = probs[i];
+      launch_gemm_nt(prec, q.A, q.lda, q.B, q.ldb, q.M, q.N, q.K, q.C, nullptr, q.ldc, q.bias, q.accumulate, st, split_scratch,
+                     split_scratch_floats, RowLimit{}, 0, wg_cap);
+      if (q.A2)
+        launch_gemm_nt(prec, q.A2, q.lda2, q.B2, q.ldb2, q.M, q.N, q.K2, q.C, nullptr, q.ldc, nullptr, 1, st, split_scratch, split_scratch_floats,
+                       RowLimit{}, 0, wg_cap);
+    }
     return;
   }
   std::vector<GemmProb> live;
@@ -350,7 +360,8 @@ void launch_gemm_nt_group(int prec, const GemmProb* probs, int n, hipStream_t st
   }
   if (live.empty()) return;
   // the tile by the number of them over the whole group (k is the batch's positions: long)
-  if (big >= GEMM_BIG_MIN_TILES) gemm_group_go<bf16_t, 4, 4, 2, 2>(live.data(), (int)live.size(), st, wg_cap);
+  if (big >= GEMM_BIG_MIN_TILES) gemm_group_go<bf16_t, 4, 4, 2, 2>(live.data(), (int)live.size(), st, wg_cap ? wg_cap : big_cap);
+  else if (medium >= 192 && medium <= GEMM_DEEP_MAX_TILES) gemm_group_go<bf16_t, 2, 2, 2, 2, 4>(live.data(), (int)live.size(), st, wg_cap);
   else if (medium >= 192) gemm_group_go<bf16_t, 2, 2, 2, 2>(live.data(), (int)live.size(), st, wg_cap);
   else gemm_group_go<bf16_t, 2, 2, 1, 1>(live.data(), (int)live.size(), st, 4 * wg_cap);
 }

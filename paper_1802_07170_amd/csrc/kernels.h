@@ -31,13 +31,18 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
 // the 64 x 64 tile, which fits a CU four times, four times as many are launched.
 // Matrix-core issue-rate probe: `blocks` workgroups of 4 wavefronts, each `iters` x 4 bf16 32x32x16 MFMAs on
 // registers; out needs blocks * 256 floats.  Returns the flops of the launch.
-// Several independent C (+)= A * B^T problems (fp32 C, no bias) as one launch: the tiles of all problems form one
+// Several independent C (+)= A * B^T problems (fp32 C) as one launch: the tiles of all problems form one
 // queue spread over the chip, so that small problems fill each other's partial rounds and there are no gaps between
 // them (the weight-gradient GEMMs of the step, the paper's calculateGradient with beta = 1 batched over time).
-struct GemmProb { const void* A; const void* B; float* C; int lda, ldb, ldc, M, N, K, accumulate; };
+// With A2: C (+)= A * B^T + A2 * B2^T, one sum (k2 columns of the second pair); bias [N] may be null.
+struct GemmProb {
+  const void* A; const void* B; float* C; int lda, ldb, ldc, M, N, K, accumulate;
+  const float* bias = nullptr;
+  const void* A2 = nullptr; const void* B2 = nullptr; int lda2 = 0, ldb2 = 0, K2 = 0;
+};
 // split_scratch: planes for the fp32 path, which launches the problems one by one (see launch_gemm_nt).
 void launch_gemm_nt_group(int prec, const GemmProb* probs, int n, hipStream_t st, float* split_scratch, size_t split_scratch_floats,
-                          int wg_cap = 0);         // (wg_cap as above)
+                          int wg_cap = 0, int big_cap = 0);   // (wg_cap as above; big_cap: such a cap for groups of 256 x 256 tiles)
 double launch_mfma_rate(float* out, int blocks, int iters, hipStream_t st);
 // out[C,R] = in[R,C]^T for T matrices (ldin, ldout in elements); with parts (TRANSPOSE_SPLITS rows of C floats) also partial sums
 // of the columns of `in`.  Any number of them.
