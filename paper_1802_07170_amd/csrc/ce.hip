@@ -328,7 +328,7 @@ void launch_ce_loss(const float* nll, int M, float* loss, int* flags, hipStream_
 template <typename T>
 __global__ __launch_bounds__(256) void ce_scale_kernel(T* __restrict__ ET, int ldet, int V, int Mc, const float* __restrict__ pmax,
                                                        int np, const float* __restrict__ lse, const int32_t* __restrict__ labels,
-                                                       const float* __restrict__ rowscale, float eps, T* __restrict__ dz,
+                                                       const float* __restrict__ rowscale, float eps, T* __restrict__ dz, int lddz,
                                                        float* __restrict__ dbo_part, RowLimit lim) {
   constexpr int VE = 16 / sizeof(T);                      // elements per 16-byte vector
   constexpr int NV = 16 / VE;                             // vectors per thread
@@ -416,21 +416,21 @@ __global__ __launch_bounds__(256) void ce_scale_kernel(T* __restrict__ ET, int l
 #pragma unroll
       for (int q = 0; q < NV; ++q)
         if (v0 + vb + q * VE < V)
-          *reinterpret_cast<uint4*>(dz + (size_t)r * V + v0 + vb + q * VE) = *reinterpret_cast<const uint4*>(&tile[rl][vb + q * VE]);
+          *reinterpret_cast<uint4*>(dz + (size_t)r * lddz + v0 + vb + q * VE) = *reinterpret_cast<const uint4*>(&tile[rl][vb + q * VE]);
     }
   }
 }
 
 void launch_ce_scale(int prec, void* ET, int pitch, int V, int Mc, const float* pmax, const float* lse, const int32_t* labels,
-                     const float* rowscale, float eps, void* dz, float* dbo_part, hipStream_t st, RowLimit lim) {
+                     const float* rowscale, float eps, void* dz, int lddz, float* dbo_part, hipStream_t st, RowLimit lim) {
   dim3 grid((V + 63) / 64, (Mc + 63) / 64);
   const int np = ce_num_partials(V);
   if (prec)
     hipLaunchKernelGGL(ce_scale_kernel<bf16_t>, grid, dim3(256), 0, st, (bf16_t*)ET, pitch, V, Mc, pmax, np, lse, labels,
-                       rowscale, eps, (bf16_t*)dz, dbo_part, lim);
+                       rowscale, eps, (bf16_t*)dz, lddz, dbo_part, lim);
   else
     hipLaunchKernelGGL(ce_scale_kernel<float>, grid, dim3(256), 0, st, (float*)ET, pitch, V, Mc, pmax, np, lse, labels,
-                       rowscale, eps, (float*)dz, dbo_part, lim);
+                       rowscale, eps, (float*)dz, lddz, dbo_part, lim);
 }
 
 }  // namespace cmt

@@ -84,11 +84,11 @@ void launch_ce_rows(const float* pmax, const float* psum, const float* psz, cons
 // loss[0] = sum nll / loss[1]; flags |= 4 if it is not finite.  One block, deterministic order.
 void launch_ce_loss(const float* nll, int M, float* loss, int* flags, hipStream_t st, RowLimit lim = RowLimit{});
 // Backward: ET -> dzT = (ET * exp(pmax - lse) - (1 - eps) onehot - eps / V) * rowscale in place
-// ([V, pitch] T; columns >= Mc up to the next multiple of 64 are zero-filled) and dz [Mc, V] T.  The caller
+// ([V, pitch] T; columns >= Mc up to the next multiple of 64 are zero-filled) and dz [Mc, lddz] T.  The caller
 // then takes dH_o[rows] = dz W_o and dW_o += dz^T H_o[rows] with launch_gemm_nt.  dbo_part
 // [ceil(Mc / 64), V] fp32: column sums of dz over each block of 64 rows (dB_o = their sum over all slabs).
 void launch_ce_scale(int prec, void* ET, int pitch, int V, int Mc, const float* pmax, const float* lse, const int32_t* labels,
-                     const float* rowscale, float eps, void* dz, float* dbo_part, hipStream_t st, RowLimit lim = RowLimit{});
+                     const float* rowscale, float eps, void* dz, int lddz, float* dbo_part, hipStream_t st, RowLimit lim = RowLimit{});
 
 // ---- step.hip ----------------------------------------------------------------------------------
 // A value delivered as `np` partial planes: v(b, c) = sum_k p[k * stride + b * ld + c]  (np = 0: zero).
