@@ -700,8 +700,8 @@ void dec_att_bwd_proj(cmt_handle* h, int j, int S, bool last) {
 // caller): per layer one GEMM for the input part of all positions and one launch for the whole recurrence (bottom layer:
 // both directions), then the attention keys and the decoder's initial states.  Returns H_s (top-layer states) and its
 // row pitch.
-// states_fm: the decoder's per-position kernels read the initial states (its loops make copies of their own).
-void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out, bool states_fm) {
+// states_fm: the decoder's per-position kernels read the initial states (its loops make copies of their own).  z: fills that go along.
+void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out, bool states_fm, std::vector<FillJob> z = {}) {
   const cmt_config& c = h->cfg;
   const int p = h->prec, E = c.emb_dim, H = c.hidden, Hd = H / 2, L = c.layers, Bp = h->Bp;
   const size_t esz = h->esz;
@@ -716,7 +716,6 @@ void enqueue_encoder(cmt_handle* h, int S, const char** Hs_out, int* ldHs_out, b
   const size_t BHd = (size_t)Bp * Hd, BPd = (size_t)Bp * ef.ph;
   const unsigned long long drop_step = (unsigned long long)h->B * H;
   {   // initial states of every encoder LSTM (zero), and the exchange slots and tickets of the recurrences: one launch
-    std::vector<FillJob> z;
     add_fill(z, ef.Hst, BPd, esz); add_fill(z, ef.Cst, BHd, 4);
     add_fill(z, eb.Hst + (size_t)S * BPd * esz, BPd, esz); add_fill(z, eb.Cst + (size_t)S * BHd, BHd, 4);
     for (int l = 1; l < L; ++l) { add_fill(z, h->enc[l + 1].Hst, BP, esz); add_fill(z, h->enc[l + 1].Cst, BH, 4); }
@@ -958,20 +957,18 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
 
   h->phase_n = 0;
   phase_mark(h, "gathers + encoder bottom layer");
-  {   // H_o^{<-1>} = 0, and the decoder's state gradients at the end of time = 0: one launch.  (The error flags
-      // are not cleared here: they accumulate over the steps enqueued since the last read-back.)
-    std::vector<FillJob> z;
-    add_fill(z, h->HoBuf, BP, esz);
-    if (drop) add_fill(z, h->HoDrop, BP, esz);
-    if (h->HoFeedF) add_fill(z, h->HoFeedF, BH, esz);
-    for (int l = 0; l < L; ++l) { add_fill(z, h->dec[l].dh, BH, 4); add_fill(z, h->dec[l].dc, BH, 4); }
-    launch_fill_multi(z.data(), (int)z.size(), st);
-  }
+  // H_o^{<-1>} = 0, and the decoder's state gradients at the end of time = 0: with the encoder's fills.  (The error flags
+  // are not cleared here: they accumulate over the steps enqueued since the last read-back.)
+  std::vector<FillJob> z0;
+  add_fill(z0, h->HoBuf, BP, esz);
+  if (drop) add_fill(z0, h->HoDrop, BP, esz);
+  if (h->HoFeedF) add_fill(z0, h->HoFeedF, BH, esz);
+  for (int l = 0; l < L; ++l) { add_fill(z0, h->dec[l].dh, BH, 4); add_fill(z0, h->dec[l].dc, BH, 4); }
   // ---- embeddings, masks ------------------------------------------------------------------------
-  launch_gather(p, h->Pw(h->off_Esrc), c.src_vocab, E, src_ids, src_len, B, Bp, S, 0, 0, h->Xs, h->mask_s, h->tok_s,
-                nullptr, h->len_s, h->flags, st);
-  launch_gather(p, h->Pw(h->off_Etgt), c.tgt_vocab, E, tgt_ids, tgt_len, B, Bp, T, 1, c.bos_id, h->Xt, h->mask_t,
-                h->tok_t, h->labels, h->len_t, h->flags, st);
+  const GatherSide sides[2] = {
+      {h->Pw(h->off_Esrc), c.src_vocab, src_ids, src_len, S, 0, 0, h->Xs, h->mask_s, h->tok_s, nullptr, h->len_s},
+      {h->Pw(h->off_Etgt), c.tgt_vocab, tgt_ids, tgt_len, T, 1, c.bos_id, h->Xt, h->mask_t, h->tok_t, h->labels, h->len_t}};
+  launch_gather(p, sides, 2, E, B, Bp, h->flags, st);
   // valid target positions numbered densely, n_tok, 1 / n_tok: the lengths give them
   launch_ce_compact(h->mask_t, h->labels, Mt, h->ce_pos, h->ce_row, h->labels_c, h->rowscale, h->ce_nvalid, h->loss, st);
 
@@ -983,7 +980,7 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   const bool split = alone && h->gate->crowded(*h->section);
   Section sec(h);
   sec.open(alone && !split);
-  enqueue_encoder(h, S, &Hs, &ldHs, !loop);
+  enqueue_encoder(h, S, &Hs, &ldHs, !loop, std::move(z0));
   if (!loop || split) sec.close();
   LD& ef = h->enc[0]; LD& eb = h->enc[1];
   // ---- decoder time loop --------------------------------------------------------------------------
@@ -1049,10 +1046,8 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
                      h->lse + m0, h->nll + m0, st, lim);
       m0 += Mc;
     }
-    launch_ce_loss(h->nll, Mt, h->loss, h->flags, st, RowLimit{h->ce_nvalid, 0});
+    launch_ce_loss(h->nll, Mt, h->loss, h->flags, h->h_loss, st, RowLimit{h->ce_nvalid, 0});
     phase_mark(h, "end");
-    (void)hipMemcpyAsync(h->h_loss, h->loss, 2 * sizeof(float), hipMemcpyDeviceToHost, st);
-    (void)hipMemcpyAsync(h->h_flags, h->flags, sizeof(int), hipMemcpyDeviceToHost, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "enqueue");
     h->have_step = true;
@@ -1120,6 +1115,10 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
       stream_after(h, sd, st);
       launch_gemm_nt(p, dz, lddz, h->WoT, h->ldWoT, Mc, H, V, h->dHoCE + (size_t)m0 * H, nullptr, H, nullptr, 0, st, h->gsplit,
                      h->gsplit_floats, lim, 1, 0, 1);                     // dH_o[slab] = dz W_o
+      if (m0 + Mc >= Mt) {                                   // the last slab: dB_o and the loss, which nothing of the pass waits for
+        launch_sum_parts(h->dbo_parts, n_dbo, (size_t)V, G + h->off_Bo, sd);
+        launch_ce_loss(h->nll, Mt, h->loss, h->flags, h->h_loss, sd, RowLimit{h->ce_nvalid, 0});
+      }
       // dW_o (+)= dz^T H_o[slab]; the first slab always holds a row, so W_o's gradient is always written
       launch_gemm_nt(p, dzT, h->ce_pitch, h->HocT + (size_t)m0 * esz, Mt, V, H, Mc, G + h->off_Wo, nullptr, H, nullptr, sl > 0,
                      sd, nullptr, 0, lim, 2, sd != st ? h->side_wgs_wo : 0, 1);
@@ -1129,8 +1128,6 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
       }
       m0 += Mc;
     }
-    launch_sum_parts(h->dbo_parts, n_dbo, (size_t)V, G + h->off_Bo, st);
-    launch_ce_loss(h->nll, Mt, h->loss, h->flags, st, RowLimit{h->ce_nvalid, 0});
   }
 
   phase_mark(h, "decoder backward loop");
@@ -1348,8 +1345,6 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   phase_mark(h, "wait for the second stream");
   stream_after(h, st, sd);                         // join: the step is complete on the caller's stream
   phase_mark(h, "end");
-  (void)hipMemcpyAsync(h->h_loss, h->loss, 2 * sizeof(float), hipMemcpyDeviceToHost, st);
-  (void)hipMemcpyAsync(h->h_flags, h->flags, sizeof(int), hipMemcpyDeviceToHost, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(h, e, "enqueue");
   h->have_step = true;
@@ -1645,8 +1640,8 @@ int cmt_greedy_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* 
   const float keep_p = h->drop_p;
   h->drop_p = 0.f;                                   // inference: no dropout
   launch_fill_f32((float*)h->flags, 1, 0.f, st);
-  launch_gather(p, h->Pw(h->off_Esrc), c.src_vocab, E, src_ids_dev, src_len_dev, B, Bp, S, 0, 0, h->Xs, h->mask_s, h->tok_s,
-                nullptr, h->len_s, h->flags, st);
+  const GatherSide side{h->Pw(h->off_Esrc), c.src_vocab, src_ids_dev, src_len_dev, S, 0, 0, h->Xs, h->mask_s, h->tok_s, nullptr, h->len_s};
+  launch_gather(p, &side, 1, E, B, Bp, h->flags, st);
   const char* Hs; int ldHs;
   note_capture(h);
   const bool proj = h->att_proj && Bp < 256;
@@ -1762,8 +1757,8 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
   const float keep_p = h->drop_p;
   h->drop_p = 0.f;                                   // inference: no dropout
   launch_fill_f32((float*)h->flags, 1, 0.f, st);
-  launch_gather(p, h->Pw(h->off_Esrc), c.src_vocab, E, src_ids_dev, src_len_dev, B, BpE, S, 0, 0, h->Xs, h->mask_s, h->tok_s,
-                nullptr, h->len_s, h->flags, st);
+  const GatherSide side{h->Pw(h->off_Esrc), c.src_vocab, src_ids_dev, src_len_dev, S, 0, 0, h->Xs, h->mask_s, h->tok_s, nullptr, h->len_s};
+  launch_gather(p, &side, 1, E, B, BpE, h->flags, st);
   const char* Hs; int ldHs;
   note_capture(h);
   Section sec(h);

@@ -285,7 +285,7 @@ void launch_ce_gather_rows(int prec, const void* src, int lds, const int32_t* ro
 
 // single block: loss = sum nll / n_tok, summed in a fixed order
 __global__ __launch_bounds__(1024) void ce_loss_kernel(const float* __restrict__ nll, int M, float* __restrict__ loss,
-                                                       int* __restrict__ flags, RowLimit lim) {
+                                                       int* __restrict__ flags, float* __restrict__ host, RowLimit lim) {
   __shared__ float s_sum[1024];
   const int t = threadIdx.x;
   if (lim.n) M = min(M, max(*lim.n - lim.base, 0));
@@ -301,7 +301,10 @@ __global__ __launch_bounds__(1024) void ce_loss_kernel(const float* __restrict__
     const float ntok = loss[1];
     const float l = ntok > 0.f ? s_sum[0] / ntok : 0.f;
     loss[0] = l;
-    if (!isfinite(l)) atomicOr(flags, 4);
+    // (straight to the host's pinned words, in the place of two copies at the end of a pass)
+    const int f = isfinite(l) ? *flags : atomicOr(flags, 4) | 4;
+    host[0] = l; host[1] = ntok;
+    reinterpret_cast<int*>(host)[8] = f;
   }
 }
 
@@ -314,8 +317,8 @@ void launch_ce_rows(const float* pmax, const float* psum, const float* psz, cons
   hipLaunchKernelGGL(ce_row_kernel, dim3((M + CE_ROW_ROWS - 1) / CE_ROW_ROWS), dim3(CE_ROW_ROWS * CE_ROW_STRANDS), 0, st, pmax, psum,
                      psz, zy, mask, M, np, pitch, eps, V, lse, nll, lim);
 }
-void launch_ce_loss(const float* nll, int M, float* loss, int* flags, hipStream_t st, RowLimit lim) {
-  hipLaunchKernelGGL(ce_loss_kernel, dim3(1), dim3(1024), 0, st, nll, M, loss, flags, lim);
+void launch_ce_loss(const float* nll, int M, float* loss, int* flags, float* host, hipStream_t st, RowLimit lim) {
+  hipLaunchKernelGGL(ce_loss_kernel, dim3(1), dim3(1024), 0, st, nll, M, loss, flags, host, lim);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -82,7 +82,8 @@ void launch_ce_gather_rows(int prec, const void* src, int lds, const int32_t* ro
 void launch_ce_rows(const float* pmax, const float* psum, const float* psz, const float* zy, const float* mask, int M, int np,
                     int pitch, float eps, int V, float* lse, float* nll, hipStream_t st, RowLimit lim = RowLimit{});
 // loss[0] = sum nll / loss[1]; flags |= 4 if it is not finite.  One block, deterministic order.
-void launch_ce_loss(const float* nll, int M, float* loss, int* flags, hipStream_t st, RowLimit lim = RowLimit{});
+// host (pinned memory): receives loss[0], loss[1] and, at host + 8, the flags.
+void launch_ce_loss(const float* nll, int M, float* loss, int* flags, float* host, hipStream_t st, RowLimit lim = RowLimit{});
 // Backward: ET -> dzT = (ET * exp(pmax - lse) - (1 - eps) onehot - eps / V) * rowscale in place
 // ([V, pitch] T; columns >= Mc up to the next multiple of 64 are zero-filled) and dz [Mc, lddz] T.  The caller
 // then takes dH_o[rows] = dz W_o and dW_o += dz^T H_o[rows] with launch_gemm_nt.  dbo_part
@@ -393,9 +394,11 @@ void launch_loop_fwd(int prec, const LoopFwdArgs& args, int L, int T, int Bp, in
 // Embedding gather + masks + input validation (flags |= 1 bad id, |= 2 bad length).
 // ids [B, L] row-major; out[t, b, :] = table[shift ? (t == 0 ? bos : ids[b, t-1]) : ids[b, t]] as T;
 // rows b >= B are zero.  mask[t, b] = t < len[b].  labels[t, b] = ids[b, t] (only when shift).
-void launch_gather(int prec, const void* table, int vocab, int E, const int32_t* ids, const int32_t* len,
-                   int B, int Bp, int L, int shift, int bos, void* out, float* mask, int32_t* tok,
-                   int32_t* labels, int32_t* len_p, int* flags, hipStream_t st);
+struct GatherSide {
+  const void* table; int vocab; const int32_t* ids; const int32_t* len; int L, shift, bos;
+  void* out; float* mask; int32_t* tok; int32_t* labels; int32_t* len_p;
+};
+void launch_gather(int prec, const GatherSide* sides, int n /* 1 or 2, one launch */, int E, int B, int Bp, int* flags, hipStream_t st);
 // Dense embedding gradient: dE[V,E] = 0, then row id gets the sum of dX rows of its occurrences,
 // added in ascending position order by the block of the first occurrence (no atomics).
 // zero_first = false: the caller has already cleared dE (e.g. earlier in the step, off the critical path).

@@ -10,54 +10,51 @@
 namespace cmt {
 
 // one workgroup per (position t, sentence b)
+struct GatherSides { GatherSide s[2]; };
 template <typename T>
-__global__ __launch_bounds__(128) void gather_kernel(const T* __restrict__ table, int vocab, int E,
-                                                     const int32_t* __restrict__ ids, const int32_t* __restrict__ len,
-                                                     int B, int Bp, int L, int shift, int bos, T* __restrict__ out,
-                                                     float* __restrict__ mask, int32_t* __restrict__ tok,
-                                                     int32_t* __restrict__ labels, int32_t* __restrict__ len_p,
-                                                     int* __restrict__ flags) {
-  const int t = blockIdx.x, b = blockIdx.y;
+__global__ __launch_bounds__(128) void gather_kernel(GatherSides sides, int E, int B, int Bp, int* __restrict__ flags) {
+  const GatherSide& g = sides.s[blockIdx.z];
+  const int t = blockIdx.x, b = blockIdx.y, L = g.L;
+  if (t >= L) return;
   const size_t row = (size_t)t * Bp + b;
   constexpr int EPC = 16 / sizeof(T);
-  uint4* o = reinterpret_cast<uint4*>(out + row * E);
+  uint4* o = reinterpret_cast<uint4*>((T*)g.out + row * E);
   const int nch = E / EPC;
   if (b >= B) {
     for (int c = threadIdx.x; c < nch; c += 128) o[c] = make_uint4(0, 0, 0, 0);
     if (threadIdx.x == 0) {
-      mask[row] = 0.f; tok[row] = -1;
-      if (labels) labels[row] = 0;
-      if (t == 0) len_p[b] = 0;
+      g.mask[row] = 0.f; g.tok[row] = -1;
+      if (g.labels) g.labels[row] = 0;
+      if (t == 0) g.len_p[b] = 0;
     }
     return;
   }
-  int n = len[b];
+  int n = g.len[b];
   if (n < 1 || n > L) { if (threadIdx.x == 0) atomicOr(flags, 2); n = n < 1 ? 1 : L; }
-  int id = shift ? (t == 0 ? bos : ids[(size_t)b * L + t - 1]) : ids[(size_t)b * L + t];
+  int id = g.shift ? (t == 0 ? g.bos : g.ids[(size_t)b * L + t - 1]) : g.ids[(size_t)b * L + t];
   const bool valid = t < n;
-  if (id < 0 || id >= vocab) { if (valid && threadIdx.x == 0) atomicOr(flags, 1); id = 0; }
-  const uint4* src = reinterpret_cast<const uint4*>(table + (size_t)id * E);
+  if (id < 0 || id >= g.vocab) { if (valid && threadIdx.x == 0) atomicOr(flags, 1); id = 0; }
+  const uint4* src = reinterpret_cast<const uint4*>((const T*)g.table + (size_t)id * E);
   for (int c = threadIdx.x; c < nch; c += 128) o[c] = src[c];
   if (threadIdx.x == 0) {
-    mask[row] = valid ? 1.f : 0.f;
-    tok[row] = valid ? id : -1;
-    if (labels) {
-      int y = ids[(size_t)b * L + t];
-      if (y < 0 || y >= vocab) { if (valid) atomicOr(flags, 1); y = 0; }
-      labels[row] = y;
+    g.mask[row] = valid ? 1.f : 0.f;
+    g.tok[row] = valid ? id : -1;
+    if (g.labels) {
+      int y = g.ids[(size_t)b * L + t];
+      if (y < 0 || y >= g.vocab) { if (valid) atomicOr(flags, 1); y = 0; }
+      g.labels[row] = y;
     }
-    if (t == 0) len_p[b] = n;
+    if (t == 0) g.len_p[b] = n;
   }
 }
 
-void launch_gather(int prec, const void* table, int vocab, int E, const int32_t* ids, const int32_t* len,
-                   int B, int Bp, int L, int shift, int bos, void* out, float* mask, int32_t* tok,
-                   int32_t* labels, int32_t* len_p, int* flags, hipStream_t st) {
-  dim3 grid(L, Bp);
-  if (prec) hipLaunchKernelGGL(gather_kernel<bf16_t>, grid, dim3(128), 0, st, (const bf16_t*)table, vocab, E, ids, len, B, Bp, L,
-                               shift, bos, (bf16_t*)out, mask, tok, labels, len_p, flags);
-  else hipLaunchKernelGGL(gather_kernel<float>, grid, dim3(128), 0, st, (const float*)table, vocab, E, ids, len, B, Bp, L,
-                          shift, bos, (float*)out, mask, tok, labels, len_p, flags);
+void launch_gather(int prec, const GatherSide* sides, int n, int E, int B, int Bp, int* flags, hipStream_t st) {
+  GatherSides g{};
+  int L = 0;
+  for (int i = 0; i < n; ++i) { g.s[i] = sides[i]; L = L > sides[i].L ? L : sides[i].L; }
+  dim3 grid(L, Bp, n);
+  if (prec) hipLaunchKernelGGL(gather_kernel<bf16_t>, grid, dim3(128), 0, st, g, E, B, Bp, flags);
+  else hipLaunchKernelGGL(gather_kernel<float>, grid, dim3(128), 0, st, g, E, B, Bp, flags);
 }
 
 // One workgroup per position p.  If no earlier position holds the same id, this workgroup sums the gradient
