@@ -1788,7 +1788,7 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
     LD& e = h->dec[l];
     ro.h_src[l] = e.Hst + 2 * slotT; ro.h_dst[l] = e.Hst + slotT;
     ro.c_src[l] = (const float*)((char*)e.Cst + 2 * slotC); ro.c_dst[l] = (float*)((char*)e.Cst + slotC);
-    if (e.fm) ro.h_dst_fm[l] = e.HstF + slotF;
+    if (e.fm && (l == 0 ? fm0 : h->dec[l - 1].fm)) ro.h_dst_fm[l] = e.HstF + slotF;   // (where the step reads it)
   }
   ro.ldh = PH;
   ro.ho_src = h->HoBuf; ro.ldho_src = PH; ro.ho_dst = h->xcat + (size_t)E * esz; ro.ldho_dst = h->ldxcat;

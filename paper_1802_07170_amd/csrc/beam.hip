@@ -170,7 +170,7 @@ __global__ __launch_bounds__(64 * WM * WN) void beam_logits_kernel(const T* __re
 // Lists that overflow (many equal logits) fall back to K rounds of a workgroup-wide arg-max over all extensions.
 // What bounds it is the chain of these steps, each a trip to memory or a barrier.  640 rows, V = 32000: 14.7 us in the place of 29
 // for the rows' K best (a pass over 82 MB) and 11 for their merge.
-constexpr int BEAM_PICK_NT = 1024, BEAM_PICK_CAP = 1024;
+constexpr int BEAM_PICK_NT = 1024, BEAM_PICK_CAP = 1024, BEAM_TOKEN_BITS = 27;   // (slot, token) in one ordered word
 __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __restrict__ zT, int pitch, const float* __restrict__ gmax,
                                                                  const float* __restrict__ gsum, int gbits, int V, BeamState bs, int K, int j,
                                                                  int max_len, int eos, float alpha) {
@@ -183,6 +183,10 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
   __shared__ float s_winv[BEAM_MAX], s_tau;
   __shared__ int s_winf[BEAM_MAX];
   __shared__ int s_ng, s_n, s_ntop;
+  // (the pointers that the tail needs are fetched now, not one after the other behind the last barrier)
+  CMT_PIN_UNIFORM_PTR(bs.parent); CMT_PIN_UNIFORM_PTR(bs.new_cum); CMT_PIN_UNIFORM_PTR(bs.new_tok); CMT_PIN_UNIFORM_PTR(bs.hist_tok);
+  CMT_PIN_UNIFORM_PTR(bs.hist_par); CMT_PIN_UNIFORM_PTR(bs.nlive); CMT_PIN_UNIFORM_PTR(bs.fin_score); CMT_PIN_UNIFORM_PTR(bs.fin_step);
+  CMT_PIN_UNIFORM_PTR(bs.fin_par); CMT_PIN_UNIFORM_PTR(bs.fin_tok); CMT_PIN_UNIFORM_PTR(bs.cum);
   constexpr int NQ = 16;                                 // a row's first 64 NQ groups stay in its wavefront's registers
   const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int row0 = b * K, ng = (V + (1 << gbits) - 1) >> gbits;
@@ -269,7 +273,7 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
       const float x = s_base[s] + zT[(size_t)v * pitch + row0 + s];
       if (x >= least && x > -INFINITY) {                 // (neither NaN nor impossible)
         const int pos = atomicAdd(&s_n, 1);
-        if (pos < BEAM_PICK_CAP) { s_cv[pos] = x; s_cf[pos] = s * V + v; }
+        if (pos < BEAM_PICK_CAP) { s_cv[pos] = x; s_cf[pos] = s << BEAM_TOKEN_BITS | v; }
       }
     }
     __syncthreads();
@@ -291,7 +295,7 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
     for (int round = 0; round < K; ++round) {
       float v = -INFINITY; int f = 0x7fffffff;
       for (int i = t; i < V * nl; i += BEAM_PICK_NT) {
-        const int tk = i / nl, s = i - tk * nl, xi = s * V + tk;
+        const int tk = i / nl, s = i - tk * nl, xi = s << BEAM_TOKEN_BITS | tk;
         const float x = s_base[s] + zT[(size_t)tk * pitch + row0 + s];
         if (x > -INFINITY && (x < pv || (x == pv && xi > pi)) && beam_better(x, xi, v, f)) { v = x; f = xi; }
       }
@@ -305,7 +309,7 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
   // ---- split the winners into finished and live hypotheses ---------------------------------------------
   const float v = t < K ? s_winv[t] : -INFINITY;
   const int f = t < K ? s_winf[t] : 0;
-  const int s = f / V, tk = f - s * V;
+  const int s = f >> BEAM_TOKEN_BITS, tk = f & ((1 << BEAM_TOKEN_BITS) - 1);
   const bool won = v > -INFINITY;                        // else fewer candidates than K
   const bool fin = won && (tk == eos || j == max_len - 1), live = won && !fin;
   const unsigned long long m_fin = __ballot(fin), m_live = __ballot(live);
@@ -377,11 +381,12 @@ __global__ __launch_bounds__(256) void beam_reorder_kernel(BeamReorder ro, BeamS
   const int r = blockIdx.x, l = blockIdx.y, t = threadIdx.x;
   const int pr = bs.parent[r];
   constexpr int VE = 16 / sizeof(T);
-  auto copy = [&](const T* src, T* dst, T* dst_fm, int n, int k0, int nsteps) {   // dst_fm: 8 elements of one k chunk at a time
+  // dst_fm: 8 elements of one k chunk at a time; the kernels that read it read no rows (but a dead row's state, which is anything)
+  auto copy = [&](const T* src, T* dst, T* dst_fm, int n, int k0, int nsteps) {
     for (int c = t * VE; c < n; c += 256 * VE) {
       const uint4 v = *reinterpret_cast<const uint4*>(src + c);
-      *reinterpret_cast<uint4*>(dst + c) = v;
       if (sizeof(T) == 2 && dst_fm) *reinterpret_cast<uint4*>(dst_fm + fm_offset(r, k0 + c, nsteps)) = v;
+      else *reinterpret_cast<uint4*>(dst + c) = v;
     }
   };
   if (l == L + 1) {
@@ -409,29 +414,40 @@ void launch_beam_reorder(int prec, const BeamReorder& ro, const BeamState& bs, i
   else hipLaunchKernelGGL(beam_reorder_kernel<float>, grid, dim3(256), 0, st, ro, bs, H, L);
 }
 
-// one thread per sentence: walk the back-pointers of the best finished hypothesis
-__global__ __launch_bounds__(64) void beam_finish_kernel(BeamState bs, int B, int K, int max_len, int pad, int32_t* __restrict__ out_ids,
-                                                         int32_t* __restrict__ out_len, float* __restrict__ out_score) {
-  const int b = blockIdx.x * 64 + threadIdx.x;
-  if (b >= B) return;
-  const int j = bs.fin_step[b];
-  const int len = j + 1;
+// One workgroup per sentence walks the back-pointers of its best finished hypothesis: they are brought to LDS together, a step at a time
+// from memory they took 1 us each (50 steps 47 us); the tokens of the path then come together as well.  (FINISH_SLOTS bytes: a
+// longer history is walked in memory.)
+constexpr int FINISH_SLOTS = 16384;
+__global__ __launch_bounds__(256) void beam_finish_kernel(BeamState bs, int B, int K, int max_len, int pad, int32_t* __restrict__ out_ids,
+                                                          int32_t* __restrict__ out_len, float* __restrict__ out_score) {
+  __shared__ uint8_t s_par[FINISH_SLOTS];
+  __shared__ uint8_t s_path[FINISH_SLOTS];
+  const int b = blockIdx.x, t = threadIdx.x;
+  const int j = bs.fin_step[b];                          // -1: nothing finished
   int32_t* o = out_ids + (size_t)b * max_len;
-  for (int q = 0; q < max_len; ++q) o[q] = pad;
-  out_len[b] = len;
-  out_score[b] = bs.fin_score[b];
-  if (j < 0) { out_len[b] = 0; return; }
-  o[j] = bs.fin_tok[b];
-  int s = bs.fin_par[b];
-  for (int q = j - 1; q >= 0; --q) {
-    const size_t i = (size_t)q * bs.hist_ld + b * K + s;
-    o[q] = bs.hist_tok[i];
-    s = bs.hist_par[i];
+  const bool staged = j * K <= FINISH_SLOTS;             // (K >= 1: the path fits as well)
+  const auto at = [&](int q, int s) { return (size_t)q * bs.hist_ld + b * K + s; };
+  if (staged)
+    for (int i = t; i < j * K; i += 256) s_par[i] = (uint8_t)bs.hist_par[at(i / K, i % K)];
+  for (int q = t; q < max_len; q += 256)
+    if (q >= j) o[q] = q == j && j >= 0 ? bs.fin_tok[b] : pad;
+  __syncthreads();
+  if (t == 0) {
+    out_len[b] = j + 1;
+    out_score[b] = bs.fin_score[b];
+    int s = j < 0 ? 0 : bs.fin_par[b];
+    for (int q = j - 1; q >= 0; --q) {
+      if (staged) { s_path[q] = (uint8_t)s; s = s_par[q * K + s]; }
+      else { o[q] = bs.hist_tok[at(q, s)]; s = bs.hist_par[at(q, s)]; }
+    }
   }
+  __syncthreads();
+  if (staged)
+    for (int q = t; q < j; q += 256) o[q] = bs.hist_tok[at(q, s_path[q])];
 }
 void launch_beam_finish(const BeamState& bs, int B, int K, int max_len, int pad, int32_t* out_ids, int32_t* out_len, float* out_score,
                         hipStream_t st) {
-  hipLaunchKernelGGL(beam_finish_kernel, dim3((B + 63) / 64), dim3(64), 0, st, bs, B, K, max_len, pad, out_ids, out_len, out_score);
+  hipLaunchKernelGGL(beam_finish_kernel, dim3(B), dim3(256), 0, st, bs, B, K, max_len, pad, out_ids, out_len, out_score);
 }
 
 }  // namespace cmt

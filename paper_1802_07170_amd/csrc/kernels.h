@@ -467,10 +467,10 @@ struct BeamState {
 };
 struct BeamReorder {
   const void* h_src[8]; void* h_dst[8]; int ldh;     // per layer: states written by the step -> states the next step reads
-  void* h_dst_fm[8] = {};                            // optional fragment-major copies of h_dst (16-bit types, H / 32 k steps)
+  void* h_dst_fm[8] = {};                            // fragment-major copies in the place of h_dst (16-bit types, H / 32 k steps; null: h_dst)
   const float* c_src[8]; float* c_dst[8];
   const void* ho_src; int ldho_src; void* ho_dst; int ldho_dst;   // H_o of the step -> input feed of the next
-  void* ho_dst_fm = nullptr; int ho_fm_nsteps = 0, ho_fm_k0 = 0;  // optional fragment-major copy: columns [k0, k0 + H) of a
+  void* ho_dst_fm = nullptr; int ho_fm_nsteps = 0, ho_fm_k0 = 0;  // fragment-major in the place of ho_dst and x: columns [k0, k0 + H) of a
                                                                   //   matrix of ho_fm_nsteps k steps (16-bit types)
   const void* table = nullptr; int E = 0; void* x = nullptr;      // embeddings of the new tokens -> x[r, 0:E] (pitch ldho_dst),
                                                                   //   and columns [0, E) of ho_dst_fm
