@@ -60,6 +60,34 @@ constexpr int BEAM_MAX = 16;
 // (value, index) ordering: larger value first, then lower index
 __device__ __forceinline__ bool beam_better(float v, int f, float bv, int bf) { return v > bv || (v == bv && f < bf); }
 
+// The same order as one number: of two keys the larger is the better pair.  (Two comparisons and a branch per pair, with an LDS read
+// in it, made the counting below take 4.7 us for 56 entries; this 0.6.)
+__device__ __forceinline__ unsigned beam_sortable(float v) {
+  const unsigned u = __float_as_uint(v);
+  return u ^ ((int)u < 0 ? 0xffffffffu : 0x80000000u);
+}
+__device__ __forceinline__ float beam_unsortable(unsigned u) { return __uint_as_float((int)u < 0 ? u ^ 0x80000000u : ~u); }
+__device__ __forceinline__ uint64_t beam_key(float v, int f) { return (uint64_t)beam_sortable(v + 0.f) << 32 | (unsigned)~f; }   // (-0 is 0)
+__device__ __forceinline__ float beam_key_value(uint64_t k) { return beam_unsortable((unsigned)(k >> 32)); }
+__device__ __forceinline__ int beam_key_index(uint64_t k) { return (int)~(unsigned)k; }
+// how many of n keys in LDS are better
+__device__ __forceinline__ int beam_place(const uint64_t* keys, int n, uint64_t key) {
+  int place = 0;
+#pragma unroll 8
+  for (int k = 0; k < n; ++k) place += keys[k] > key;
+  return place;
+}
+// Appends the values of the lanes with `take` to a list in LDS of at most cap entries: one atomic per wavefront.
+__device__ __forceinline__ void beam_append(bool take, uint64_t key, uint64_t* list, int* n, int cap) {
+  const unsigned long long at = __ballot(take);
+  if (at == 0) return;
+  const int lane = threadIdx.x & 63;
+  int base = 0;
+  if (lane == 0) base = atomicAdd(n, __popcll(at));
+  const int pos = __builtin_amdgcn_readfirstlane(base) + __popcll(at & ((1ull << lane) - 1));
+  if (take && pos < cap) list[pos] = key;
+}
+
 // Largest value of a wavefront, in every lane, by DPP moves: about a tenth of the time of six shuffles through LDS.
 __device__ __forceinline__ float beam_wave_max(float v) {
 #define STEP(ctrl, rows) v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), ctrl, rows, 0xf, false)))
@@ -164,11 +192,11 @@ __global__ __launch_bounds__(64 * WM * WN) void beam_logits_kernel(const T* __re
 // One workgroup per sentence.  A group's largest extension, (score - lse) + gmax, is one of its extensions, so the K-th best of the
 // groups is a bound for the K-th best extension, and every extension as good as that lies in a group as good as that:
 //   lse of the live rows from the groups' statistics;
-//   the K-th best group: the K-th best of a row's 64 threads' best is a bound that few groups pass; those are listed in LDS
-//   and each counts how many are better;
+//   the K-th best group: the K-th best of a row's 64 threads' best (to 16 bits) is a bound that few groups pass; those are listed in
+//   LDS and each counts how many are better;
 //   the entries of the K best groups that pass are listed, and each counts how many are better: that is its place.
 // Lists that overflow (many equal logits) fall back to K rounds of a workgroup-wide arg-max over all extensions.
-// What bounds it is the chain of these steps, each a trip to memory or a barrier.  640 rows, V = 32000: 14.7 us in the place of 29
+// What bounds it is the chain of these steps, each a trip to memory or a barrier.  640 rows, V = 32000: 9.2 us in the place of 29
 // for the rows' K best (a pass over 82 MB) and 11 for their merge.
 constexpr int BEAM_PICK_NT = 1024, BEAM_PICK_CAP = 1024, BEAM_TOKEN_BITS = 27;   // (slot, token) in one ordered word
 __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __restrict__ zT, int pitch, const float* __restrict__ gmax,
@@ -176,8 +204,8 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
                                                                  int max_len, int eos, float alpha) {
   constexpr int NW = BEAM_PICK_NT / 64;
   __shared__ float s_base[BEAM_MAX];
-  __shared__ float s_gv[BEAM_PICK_CAP], s_cv[BEAM_PICK_CAP];
-  __shared__ int s_gi[BEAM_PICK_CAP], s_cf[BEAM_PICK_CAP], s_top[BEAM_PICK_CAP];
+  __shared__ uint64_t s_g[BEAM_PICK_CAP], s_c[BEAM_PICK_CAP];   // keys of (bound, group and slot) and of (value, slot and token)
+  __shared__ int s_top[BEAM_PICK_CAP];
   __shared__ float s_v[NW];
   __shared__ int s_f[NW];
   __shared__ float s_winv[BEAM_MAX], s_tau;
@@ -225,56 +253,43 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
     if (lane == 0) s_base[w] = base;
     // ---- the K best groups ---------------------------------------------------------------------------------
     tv += base;
-    bool taken = false;
-    for (int round = 0; round < K; ++round) {
-      tau = beam_wave_max(taken ? -INFINITY : tv);       // -inf when fewer than K of its threads hold a group
-      const unsigned long long at = __ballot(!taken && tv == tau);
-      if (at && lane == __ffsll(at) - 1) taken = true;
-    }
+    // (the largest number, of the 16 leading bits, that K lanes reach; where K do not hold a group, -inf)
+    const unsigned key = beam_sortable(tv) >> 16;
+    unsigned least = 0;
+#pragma unroll
+    for (int bit = 15; bit >= 0; --bit)
+      if (__popcll(__ballot(key >= (least | 1u << bit))) >= K) least |= 1u << bit;
+    tau = least < 0x80u ? -INFINITY : beam_unsortable(least << 16);
   }
   if (lane == 0) s_v[w] = tau;
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < NW; ++i) tau = fmaxf(tau, s_v[i]);
   if (w < nl) {
-    auto list = [&](float bound, int g) {
-      if (bound >= tau) {
-        const int pos = atomicAdd(&s_ng, 1);
-        if (pos < BEAM_PICK_CAP) { s_gv[pos] = bound; s_gi[pos] = g * BEAM_MAX + w; }
-      }
-    };
+    auto list = [&](bool in, float bound, int g) { beam_append(in && bound >= tau, beam_key(bound, g * BEAM_MAX + w), s_g, &s_ng, BEAM_PICK_CAP); };
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-      if (lane + 64 * q < ng) list(base + m[q], lane + 64 * q);
-    for (int g = lane + 64 * NQ; g < ng; g += 64) list(base + gmax[r * ng + g], g);
+    for (int q = 0; q < NQ; ++q) list(lane + 64 * q < ng, base + m[q], lane + 64 * q);
+    for (int g0 = 64 * NQ; g0 < ng; g0 += 64) list(g0 + lane < ng, base + gmax[r * ng + min(g0 + lane, ng - 1)], g0 + lane);
   }
   __syncthreads();
   bool fits = s_ng <= BEAM_PICK_CAP;
   if (fits) {
     const int n = s_ng;
-    for (int i = t; i < n; i += BEAM_PICK_NT) {
-      const float v = s_gv[i];
-      const int f = s_gi[i];
-      int place = 0;
-#pragma unroll 8
-      for (int k = 0; k < n; ++k) place += beam_better(s_gv[k], s_gi[k], v, f);
-      if (place == K - 1) s_tau = v;                     // (fewer than K groups: every entry passes)
-    }
+    for (int i = t; i < n; i += BEAM_PICK_NT)
+      if (beam_place(s_g, n, s_g[i]) == K - 1) s_tau = beam_key_value(s_g[i]);   // (fewer than K groups: every entry passes)
     __syncthreads();
     const float least = s_tau;
     for (int i = t; i < n; i += BEAM_PICK_NT)
-      if (s_gv[i] >= least) s_top[atomicAdd(&s_ntop, 1)] = s_gi[i];
+      if (beam_key_value(s_g[i]) >= least) s_top[atomicAdd(&s_ntop, 1)] = beam_key_index(s_g[i]);
     __syncthreads();
     // ---- their entries -------------------------------------------------------------------------------------
     const int entries = s_ntop << gbits;
-    for (int i = t; i < entries; i += BEAM_PICK_NT) {
-      const int id = s_top[i >> gbits], s = id % BEAM_MAX, v = ((id / BEAM_MAX) << gbits) + (i & ((1 << gbits) - 1));
-      if (v >= V) continue;
-      const float x = s_base[s] + zT[(size_t)v * pitch + row0 + s];
-      if (x >= least && x > -INFINITY) {                 // (neither NaN nor impossible)
-        const int pos = atomicAdd(&s_n, 1);
-        if (pos < BEAM_PICK_CAP) { s_cv[pos] = x; s_cf[pos] = s << BEAM_TOKEN_BITS | v; }
-      }
+    for (int i0 = 0; i0 < entries; i0 += BEAM_PICK_NT) {
+      const int i = min(i0 + t, entries - 1), id = s_top[i >> gbits], s = id % BEAM_MAX;
+      const int v = ((id / BEAM_MAX) << gbits) + (i & ((1 << gbits) - 1));
+      const bool in = i0 + t < entries && v < V;
+      const float x = in ? s_base[s] + zT[(size_t)v * pitch + row0 + s] : -INFINITY;
+      beam_append(x >= least && x > -INFINITY, beam_key(x, s << BEAM_TOKEN_BITS | v), s_c, &s_n, BEAM_PICK_CAP);   // (neither NaN nor impossible)
     }
     __syncthreads();
     fits = s_n <= BEAM_PICK_CAP;
@@ -282,12 +297,8 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
   if (fits) {
     const int n = s_n;
     for (int i = t; i < n; i += BEAM_PICK_NT) {
-      const float v = s_cv[i];
-      const int f = s_cf[i];
-      int place = 0;
-#pragma unroll 8
-      for (int k = 0; k < n; ++k) place += beam_better(s_cv[k], s_cf[k], v, f);
-      if (place < K) { s_winv[place] = v; s_winf[place] = f; }
+      const int place = beam_place(s_c, n, s_c[i]);
+      if (place < K) { s_winv[place] = beam_key_value(s_c[i]); s_winf[place] = beam_key_index(s_c[i]); }
     }
   } else {
     // K rounds: the best extension strictly after the previous winner in the (value, slot and token) order
