@@ -291,6 +291,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_group_kernel(GemmGroupAr
                                                 part ? pr.ldb2 : pr.ldb, M, N, part ? pr.K2 : pr.K, m0, n0, acc, smem, [](v16f (&)[TA][TB]) {});
   __syncthreads();                                        // (the next tile of a walking workgroup refills the LDS)
   float* __restrict__ C = pr.C;
+  T* __restrict__ Ct = (T*)pr.Ct;
   const int accumulate = pr.accumulate;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wm = w / WN, wn = w % WN;
@@ -306,8 +307,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_group_kernel(GemmGroupAr
         const int row = m0 + wm * 32 * TA + mt * 32 + acc32_row(lane, i);
         if (row >= M) continue;
         const size_t o = (size_t)row * ldc + col;
-        const float v = acc[mt][nt][i] + bv;
-        C[o] = accumulate ? C[o] + v : v;
+        float v = acc[mt][nt][i] + bv;
+        if (accumulate) v += C[o];
+        if (C) C[o] = v;
+        if (Ct) Ct[o] = from_f<T>(v);
       }
     }
   }
@@ -342,7 +345,7 @@ void launch_gemm_nt_group(int prec, const GemmProb* probs, int n, hipStream_t st
     // recurrences' kernels running beside them (small workload: 11.2 against 11.4 ms per step).
     for (int i = 0; i < n; ++i) {
       const GemmProb& q = probs[i];
-      launch_gemm_nt(prec, q.A, q.lda, q.B, q.ldb, q.M, q.N, q.K, q.C, nullptr, q.ldc, q.bias, q.accumulate, st, split_scratch,
+      launch_gemm_nt(prec, q.A, q.lda, q.B, q.ldb, q.M, q.N, q.K, q.C, q.Ct, q.ldc, q.bias, q.accumulate, st, split_scratch,
                      split_scratch_floats, RowLimit{}, 0, wg_cap);
       if (q.A2)
         launch_gemm_nt(prec, q.A2, q.lda2, q.B2, q.ldb2, q.M, q.N, q.K2, q.C, nullptr, q.ldc, nullptr, 1, st, split_scratch, split_scratch_floats,

@@ -39,6 +39,7 @@ struct GemmProb {
   const void* A; const void* B; float* C; int lda, ldb, ldc, M, N, K, accumulate;
   const float* bias = nullptr;
   const void* A2 = nullptr; const void* B2 = nullptr; int lda2 = 0, ldb2 = 0, K2 = 0;
+  void* Ct = nullptr;                      // T copy of C, same ldc (C may then be null)
 };
 // split_scratch: planes for the fp32 path, which launches the problems one by one (see launch_gemm_nt).
 void launch_gemm_nt_group(int prec, const GemmProb* probs, int n, hipStream_t st, float* split_scratch, size_t split_scratch_floats,
