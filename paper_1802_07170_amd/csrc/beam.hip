@@ -192,7 +192,7 @@ __global__ __launch_bounds__(64 * WM * WN) void beam_logits_kernel(const T* __re
 // One workgroup per sentence.  A group's largest extension, (score - lse) + gmax, is one of its extensions, so the K-th best of the
 // groups is a bound for the K-th best extension, and every extension as good as that lies in a group as good as that:
 //   lse of the live rows from the groups' statistics;
-//   the K-th best group: the K-th best of a row's 64 threads' best (to 16 bits) is a bound that few groups pass; those are listed in
+//   the K-th best group: the K-th best of a row's 64 threads' best is a bound that few groups pass; those are listed in
 //   LDS and each counts how many are better;
 //   the entries of the K best groups that pass are listed, and each counts how many are better: that is its place.
 // Lists that overflow (many equal logits) fall back to K rounds of a workgroup-wide arg-max over all extensions.
@@ -253,13 +253,14 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
     if (lane == 0) s_base[w] = base;
     // ---- the K best groups ---------------------------------------------------------------------------------
     tv += base;
-    // (the largest number, of the 16 leading bits, that K lanes reach; where K do not hold a group, -inf)
-    const unsigned key = beam_sortable(tv) >> 16;
+    // (the largest number that K lanes reach, to the last bit: scores of -500 whose logits lie within 0.5 of each other differ in the
+    // lower half alone, and a bound from the upper one let every group pass, 1300 us a step; where K do not hold a group, -inf)
+    const unsigned key = beam_sortable(tv);
     unsigned least = 0;
 #pragma unroll
-    for (int bit = 15; bit >= 0; --bit)
+    for (int bit = 31; bit >= 0; --bit)
       if (__popcll(__ballot(key >= (least | 1u << bit))) >= K) least |= 1u << bit;
-    tau = least < 0x80u ? -INFINITY : beam_unsortable(least << 16);
+    tau = least < 0x00800000u ? -INFINITY : beam_unsortable(least);
   }
   if (lane == 0) s_v[w] = tau;
   __syncthreads();
