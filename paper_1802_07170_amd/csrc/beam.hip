@@ -189,26 +189,30 @@ __global__ __launch_bounds__(64 * WM * WN) void beam_logits_kernel(const T* __re
   }
 }
 
-// One workgroup per sentence.  A group's largest extension, (score - lse) + gmax, is one of its extensions, so the K-th best of the
-// groups is a bound for the K-th best extension, and every extension as good as that lies in a group as good as that:
+// One workgroup per sentence.  A group's largest extension, (score - lse) + gmax, is one of its extensions.  With groups in the order of
+// (that value, slot, place in the vocabulary) the K best groups hold the K best extensions: an extension of another group is worse than
+// the largest one of each of them, by the value or, where it is equal, by the slot or the token.
 //   lse of the live rows from the groups' statistics;
-//   the K-th best group: the K-th best of a row's 64 threads' best is a bound that few groups pass; those are listed in
-//   LDS and each counts how many are better;
-//   the entries of the K best groups that pass are listed, and each counts how many are better: that is its place.
-// Lists that overflow (many equal logits) fall back to K rounds of a workgroup-wide arg-max over all extensions.
+//   the K best groups: the K-th best of a row's 64 threads' best is a bound that K threads of a row at most pass; their groups that
+//   pass are listed in LDS and each counts how many are better;
+//   the entries of those groups that reach the K-th one's value are listed, and each counts how many are better: that is its place.
+// Equal logits in any number stay within the lists (all extensions of 640 rows equal: 10.7 ms a search, 10.4 else).  More than BEAM_PICK_CAP groups can pass only
+// where a few threads own nearly all the best groups of a long vocabulary: then K rounds of a workgroup-wide arg-max over all extensions.
 // What bounds it is the chain of these steps, each a trip to memory or a barrier.  640 rows, V = 32000: 9.2 us in the place of 29
 // for the rows' K best (a pass over 82 MB) and 11 for their merge.
 constexpr int BEAM_PICK_NT = 1024, BEAM_PICK_CAP = 1024, BEAM_TOKEN_BITS = 27;   // (slot, token) in one ordered word
+constexpr int BEAM_PICK_ENTRIES = BEAM_MAX << 6;        // (groups of 32 or 64 entries)
 __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __restrict__ zT, int pitch, const float* __restrict__ gmax,
                                                                  const float* __restrict__ gsum, int gbits, int V, BeamState bs, int K, int j,
                                                                  int max_len, int eos, float alpha) {
   constexpr int NW = BEAM_PICK_NT / 64;
   __shared__ float s_base[BEAM_MAX];
-  __shared__ uint64_t s_g[BEAM_PICK_CAP], s_c[BEAM_PICK_CAP];   // keys of (bound, group and slot) and of (value, slot and token)
-  __shared__ int s_top[BEAM_PICK_CAP];
+  __shared__ uint64_t s_g[BEAM_PICK_CAP], s_c[BEAM_PICK_ENTRIES];   // keys of (bound, slot and group) and of (value, slot and token)
+  __shared__ uint64_t s_bound[NW];
+  __shared__ int s_top[BEAM_MAX];
   __shared__ float s_v[NW];
   __shared__ int s_f[NW];
-  __shared__ float s_winv[BEAM_MAX], s_tau;
+  __shared__ float s_winv[BEAM_MAX], s_least;
   __shared__ int s_winf[BEAM_MAX];
   __shared__ int s_ng, s_n, s_ntop;
   // (the pointers that the tail needs are fetched now, not one after the other behind the last barrier)
@@ -233,9 +237,10 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
     if (t < K) { bs.parent[row0 + t] = -1; bs.new_cum[row0 + t] = -INFINITY; }
     return;
   }
-  if (t == 0) { s_ng = 0; s_n = 0; s_ntop = 0; s_tau = -INFINITY; }
+  if (t == 0) { s_ng = 0; s_n = 0; s_ntop = 0; s_least = -INFINITY; }
   if (t < BEAM_MAX) { s_winv[t] = -INFINITY; s_winf[t] = 0; }
-  float base = 0.f, tau = -INFINITY;
+  float base = 0.f;
+  uint64_t tau = 0;
   if (w < nl) {                                          // (uniform over the wavefront)
     float tv = -INFINITY;
 #pragma unroll
@@ -253,47 +258,66 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
     if (lane == 0) s_base[w] = base;
     // ---- the K best groups ---------------------------------------------------------------------------------
     tv += base;
+    if (!(tv > -INFINITY)) tv = -INFINITY;               // (nor NaN)
     // (the largest number that K lanes reach, to the last bit: scores of -500 whose logits lie within 0.5 of each other differ in the
     // lower half alone, and a bound from the upper one let every group pass, 1300 us a step; where K do not hold a group, -inf)
-    const unsigned key = beam_sortable(tv);
+    // Where more than K lanes reach it, the K of them with the first groups: equal logits must not overflow the list.)
+    const unsigned key = beam_sortable(tv + 0.f);
     unsigned least = 0;
 #pragma unroll
     for (int bit = 31; bit >= 0; --bit)
       if (__popcll(__ballot(key >= (least | 1u << bit))) >= K) least |= 1u << bit;
-    tau = least < 0x00800000u ? -INFINITY : beam_unsortable(least);
+    if (least >= 0x00800000u) {
+      unsigned first = 0;
+      if (__popcll(__ballot(key >= least)) > K) {
+        int at = 0;                                      // the first of the lane's groups that has its largest value
+        for (int g = lane + 64 * ((ng - 1) / 64); g >= 0; g -= 64)
+          if (g < ng && base + gmax[r * ng + g] == tv) at = g;
+        const unsigned lo = (unsigned)~(w << BEAM_TOKEN_BITS | at);
+        first = (unsigned)~(w << BEAM_TOKEN_BITS | ((1 << BEAM_TOKEN_BITS) - 1));
+#pragma unroll 1
+        for (int bit = BEAM_TOKEN_BITS - 1; bit >= 0; --bit)
+          if (__popcll(__ballot(key > least || (key == least && lo >= (first | 1u << bit)))) >= K) first |= 1u << bit;
+      }
+      tau = (uint64_t)least << 32 | first;
+    }
   }
-  if (lane == 0) s_v[w] = tau;
+  if (lane == 0) s_bound[w] = tau;
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < NW; ++i) tau = fmaxf(tau, s_v[i]);
+  for (int i = 0; i < NW; ++i) tau = max(tau, s_bound[i]);
   if (w < nl) {
-    auto list = [&](bool in, float bound, int g) { beam_append(in && bound >= tau, beam_key(bound, g * BEAM_MAX + w), s_g, &s_ng, BEAM_PICK_CAP); };
+    const float value = tau ? beam_key_value(tau) : -INFINITY;
+    auto list = [&](bool in, float bound, int g) {
+      if (__ballot(in && bound >= value) == 0) return;
+      const uint64_t key = beam_key(bound, w << BEAM_TOKEN_BITS | g);
+      beam_append(in && bound > -INFINITY && key >= tau, key, s_g, &s_ng, BEAM_PICK_CAP);
+    };
 #pragma unroll
     for (int q = 0; q < NQ; ++q) list(lane + 64 * q < ng, base + m[q], lane + 64 * q);
     for (int g0 = 64 * NQ; g0 < ng; g0 += 64) list(g0 + lane < ng, base + gmax[r * ng + min(g0 + lane, ng - 1)], g0 + lane);
   }
   __syncthreads();
-  bool fits = s_ng <= BEAM_PICK_CAP;
+  const bool fits = s_ng <= BEAM_PICK_CAP;
   if (fits) {
     const int n = s_ng;
-    for (int i = t; i < n; i += BEAM_PICK_NT)
-      if (beam_place(s_g, n, s_g[i]) == K - 1) s_tau = beam_key_value(s_g[i]);   // (fewer than K groups: every entry passes)
-    __syncthreads();
-    const float least = s_tau;
-    for (int i = t; i < n; i += BEAM_PICK_NT)
-      if (beam_key_value(s_g[i]) >= least) s_top[atomicAdd(&s_ntop, 1)] = beam_key_index(s_g[i]);
-    __syncthreads();
-    // ---- their entries -------------------------------------------------------------------------------------
-    const int entries = s_ntop << gbits;
-    for (int i0 = 0; i0 < entries; i0 += BEAM_PICK_NT) {
-      const int i = min(i0 + t, entries - 1), id = s_top[i >> gbits], s = id % BEAM_MAX;
-      const int v = ((id / BEAM_MAX) << gbits) + (i & ((1 << gbits) - 1));
-      const bool in = i0 + t < entries && v < V;
-      const float x = in ? s_base[s] + zT[(size_t)v * pitch + row0 + s] : -INFINITY;
-      beam_append(x >= least && x > -INFINITY, beam_key(x, s << BEAM_TOKEN_BITS | v), s_c, &s_n, BEAM_PICK_CAP);   // (neither NaN nor impossible)
+    for (int i = t; i < n; i += BEAM_PICK_NT) {
+      const int place = beam_place(s_g, n, s_g[i]);
+      if (place == K - 1) s_least = beam_key_value(s_g[i]);   // (fewer than K groups: every entry passes)
+      if (place < K) s_top[atomicAdd(&s_ntop, 1)] = beam_key_index(s_g[i]);
     }
     __syncthreads();
-    fits = s_n <= BEAM_PICK_CAP;
+    // ---- their entries -------------------------------------------------------------------------------------
+    const float least = s_least;
+    const int entries = s_ntop << gbits;
+    for (int i0 = 0; i0 < entries; i0 += BEAM_PICK_NT) {
+      const int i = min(i0 + t, entries - 1), id = s_top[i >> gbits], s = id >> BEAM_TOKEN_BITS;
+      const int v = ((id & ((1 << BEAM_TOKEN_BITS) - 1)) << gbits) + (i & ((1 << gbits) - 1));
+      const bool in = i0 + t < entries && v < V;
+      const float x = in ? s_base[s] + zT[(size_t)v * pitch + row0 + s] : -INFINITY;
+      beam_append(x >= least && x > -INFINITY, beam_key(x, s << BEAM_TOKEN_BITS | v), s_c, &s_n, BEAM_PICK_ENTRIES);   // (neither NaN nor impossible)
+    }
+    __syncthreads();
   }
   if (fits) {
     const int n = s_n;

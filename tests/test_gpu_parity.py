@@ -671,6 +671,36 @@ def test_beam_search_at_the_edges_of_the_row_sizes(B, V):
     tr.close()
 
 
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("V,tied", [(72, "all"), (2056, "half"), (40000, "all"), (40000, "half"), (40000, "few threads")])
+def test_beam_search_at_the_bounds_of_the_selections_lists(prec, V, tied):
+    """W_o = 0: every row's logits are B_o, without rounding.  Equal logits of any number go by the lower (slot, token), with the
+    groups of a row in a thread's registers and beyond (1024 groups).  "few threads": the best entries lie in the groups of 15 of a
+    row's 64 threads, so that a beam of 16 lists them all, more than fit, and goes through the rounds over all extensions."""
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=104, tgt_vocab=V, emb=8, hidden=16, layers=1)
+    rng = np.random.default_rng(V)
+    params = I.make_params(cfg, seed=3, scale=0.5)
+    params["W_o"] = np.zeros_like(params["W_o"])
+    bo = np.zeros(V, params["B_o"].dtype)
+    if tied == "half":
+        bo[rng.permutation(V)[: V // 2]] = 1.0
+    if tied == "few threads":
+        sel = np.arange(V) // 32 % 64 < 15
+        bo[sel] = 1.0 + rng.uniform(0.0, 0.1, int(sel.sum()))
+    params["B_o"] = bo
+    src, sl, _, _ = ragged_batch(rng, 2, 3, 4, 104, V)
+    tr = binding.Trainer(cfg, 2 * 16, 4, 6, precision=prec)
+    tr.set_params(I.flatten(params, cfg))
+    for beam in (16, 5):
+        ids, lens, score = tr.beam_decode(src, sl, 4, beam=beam, length_penalty=0.6, eos_id=3)
+        oids, olens, oscore, _ = O.beam_decode(cfg, params, src, sl, 4, beam, 0.6, bos_id=2, eos_id=3)
+        assert np.allclose(score, oscore, rtol=1e-5)     # sums of at most 4 scores near 10 in fp32: 4e-6
+        if tied != "few threads":                        # (there near ties may fall either way, with the same score)
+            assert np.array_equal(ids, oids) and np.array_equal(lens, olens), (beam, ids, oids)
+    tr.close()
+
+
 def test_beam_search_edge_cases():
     """A beam wider than the number of candidates of the first steps (vocabulary 8, beam 16), a single
     step, and the argument checks."""
