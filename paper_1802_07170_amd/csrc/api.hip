@@ -42,7 +42,7 @@ struct ParamInfo { std::string name; int64_t rows, cols; size_t off; };
 // one LSTM (layer, direction)
 struct LD {
   int Kin = 0, Hh = 0;
-  int ph = 0, pg = 0;                // row pitches (elements) of Hst and dG: Hh + 8, 4Hh + 8 (see ACT_PAD)
+  int ph = 0, pg = 0;                // row pitches (elements) of Hst and dG: Hh, 4Hh + ACT_PAD or ACT_PAD_LINES
   size_t w_off = 0, b_off = 0;       // element offsets in the flat parameter vector
   char* W = nullptr;                 // T [4Hh, Kin+Hh]
   char* Wt = nullptr;                // T [Kin+Hh, 4Hh]
