@@ -242,12 +242,16 @@ __device__ __forceinline__ void gemm_mainloop_dl(const bf16_t* __restrict__ A, i
 
 // ---- 32-bit operands ----
 // fp32 products on the bf16 matrix cores, which are 16 times as fast: x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m,
-// all three bf16 and (round to nearest, 3 x 8 significant bits and their signs) without a remainder while l is a normal number, so that
+// all three bf16 and (round to nearest, 3 x 8 significant bits and their signs) without a remainder, so that
 // a b = ha hb + (ha mb + ma hb) + (ha lb + la hb + ma mb) + what is below 2^-25 of |a b| and of either sign.  Six products of bf16
 // instead of one of fp32: 2.7 times the rate.  Error against 64 bits, relative (fp32 instructions | split): 3200 x 2048, k 512 4.0e-7 |
 // 1.1e-7; k 3200 4.6e-7 | 1.9e-7; gradients of 32 shapes of training steps 0.40 - 1.00 times as far off as they were.  REST: the five small
 // products go into a sum of their own.  In one sum with ha hb they are lost where that has grown large - and together, as what is
 // lost is much the same for every row of a coherent operand (bias gradients up to 2.6 times as far off).
+// Range: operands are split at 2^16 times their size, where the last bit that any of them can have, 2^-149, is the least bf16, 2^-133
+// (conversions and products keep subnormal numbers; at their own size parts were cut off below 2^-110).  From 0x1.ffp111 up h is infinite, and sums
+// from 2^96 up can be: a tile with a sum that is infinite or NaN is made again on the fp32 instructions.  That costs nothing: the factor
+// goes into what blanks out k beyond the last, and the sums are looked at once (small_step 5.17 -> 5.14 ms; the operands' magnitudes were looked at before).
 // It is bound by power as much as by instructions: 8192 x 8192, k 4096 128 TFLOP/s with fp32 instructions, 206 with the split
 // (1.24 PFLOP/s of bf16) at 1.8 GHz with the matrix cores busy 70 % of the time; k 512, 3200 x 2048 82 | 51 us.
 //
@@ -256,6 +260,7 @@ __device__ __forceinline__ void gemm_mainloop_dl(const bf16_t* __restrict__ A, i
 template <int BK> __device__ __forceinline__ int gemm_split_at(int r, int c /* chunk of 8 k */) {
   return ((r >> 5) * (BK / 16) + (c >> 1)) * 1024 + (c & 1) * 512 + ((r & 31) ^ (c * (64 / BK))) * 16;
 }
+constexpr float GEMM_SPLIT_SCALE = 0x1p16f;
 struct GemmSplit2 { uint32_t h, m, l; };
 __device__ __forceinline__ GemmSplit2 gemm_split2(float x, float y) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -268,12 +273,10 @@ __device__ __forceinline__ GemmSplit2 gemm_split2(float x, float y) {
   s.l = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));
   return s;
 }
-// A quad of k of row r, chunk half c (4 k each) -> the three planes of a tile of ROWS rows; top = the largest magnitude seen.
+// A quad of k of row r, chunk half c (4 k each) -> the three planes of a tile of ROWS rows.
 template <int ROWS, int BK>
-__device__ __forceinline__ void gemm_split_store(char* tile, int r, int c, const float4& x, float& top) {
+__device__ __forceinline__ void gemm_split_store(char* tile, int r, int c, const float4& x) {
   constexpr int PLANE = ROWS * BK * 2;
-  top = fmaxf(fmaxf(top, fabsf(x.x)), fabsf(x.y));
-  top = fmaxf(fmaxf(top, fabsf(x.z)), fabsf(x.w));
   const GemmSplit2 a = gemm_split2(x.x, x.y), b = gemm_split2(x.z, x.w);
   char* const at = tile + gemm_split_at<BK>(r, c >> 1) + (c & 1) * 8;
   *reinterpret_cast<uint2*>(at) = make_uint2(a.h, b.h);
@@ -282,7 +285,7 @@ __device__ __forceinline__ void gemm_split_store(char* tile, int r, int c, const
 }
 // A thread's pieces of a stage (16 bytes of one row each, first A's, then B's) are asked for two stages ahead and split one stage
 // ahead, piece by piece between the matrix instructions: those take 32 clocks each, the splitting of a piece some 27 others.
-// false: an operand is infinite or rounds to that in bf16, and the sums are to be made by gemm_mainloop_regs.  (A NaN stays one.)
+// false: the sums are to be made by gemm_mainloop_regs.
 template <int WM, int WN, int TA, int TB, bool REST>
 __device__ __forceinline__ bool gemm_mainloop_f32(const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb,
                                                   int M, int N, int K, int m0, int n0, v16f (&acc)[TA][TB], char* smem) {
@@ -304,18 +307,18 @@ __device__ __forceinline__ bool gemm_mainloop_f32(const float* __restrict__ A, i
     x[p] = *reinterpret_cast<const float4*>((p < NA ? pa : pb) + (off[p] + k));
   };
   v16f rest[TA][TB];
+  constexpr float SCALE2 = GEMM_SPLIT_SCALE * GEMM_SPLIT_SCALE;
 #pragma unroll
   for (int a = 0; a < TA; ++a)
 #pragma unroll
     for (int b = 0; b < TB; ++b)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) rest[a][b][i] = 0.f;   // (REST)
-  float top = 0.f;
+      for (int i = 0; i < 16; ++i) { acc[a][b][i] *= SCALE2; rest[a][b][i] = 0.f; }   // (REST)
   auto store = [&](char* stage, int p, int kt) {
-    const bool in = kt * BK + 4 * pc < K;
-    const float4 v = make_float4(in ? x[p].x : 0.f, in ? x[p].y : 0.f, in ? x[p].z : 0.f, in ? x[p].w : 0.f);
-    if (p < NA) gemm_split_store<G::BM, BK>(stage, pr + RPP * p, pc, v, top);
-    else gemm_split_store<G::BN, BK>(stage + 3 * A_PLANE, pr + RPP * (p - NA), pc, v, top);
+    const float s = kt * BK + 4 * pc < K ? GEMM_SPLIT_SCALE : 0.f;
+    const float4 v = make_float4(s * x[p].x, s * x[p].y, s * x[p].z, s * x[p].w);
+    if (p < NA) gemm_split_store<G::BM, BK>(stage, pr + RPP * p, pc, v);
+    else gemm_split_store<G::BN, BK>(stage + 3 * A_PLANE, pr + RPP * (p - NA), pc, v);
   };
 #pragma unroll
   for (int p = 0; p < NP; ++p) load(p, 0);
@@ -356,13 +359,18 @@ __device__ __forceinline__ bool gemm_mainloop_f32(const float* __restrict__ A, i
     }
     __syncthreads();
   }
+  float zero = 0.f;                                        // (NaN as soon as one of the sums is not finite)
 #pragma unroll
-  for (int a = 0; REST && a < TA; ++a)
+  for (int a = 0; a < TA; ++a)
 #pragma unroll
     for (int b = 0; b < TB; ++b)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[a][b][i] += rest[a][b][i];
-  return !__syncthreads_or(top >= 0x1.ffp127f);            // (from there on bf16 rounds up to infinity)
+      for (int i = 0; i < 16; ++i) {
+        if (REST) acc[a][b][i] += rest[a][b][i];
+        zero = fmaf(acc[a][b][i], 0.f, zero);
+        acc[a][b][i] *= 1.f / SCALE2;
+      }
+  return !__syncthreads_or(!(zero == 0.f));
 }
 
 // fp32 on the fp32 matrix cores.

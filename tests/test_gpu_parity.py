@@ -1223,6 +1223,39 @@ def test_fp32_products_in_three_parts(B, S, E, H):
     assert np.array_equal(got[~plain], ref[~plain])
 
 
+@pytest.mark.parametrize("B,S,E,H", [(16, 1, 8, 16), (33, 5, 40, 48), (128, 100, 72, 1024)])
+@pytest.mark.parametrize("ends", ["least", "largest"])
+def test_fp32_products_at_the_ends_of_the_range(ends, B, S, E, H):
+    """The same product where three bf16 parts do not hold an operand, or their products not what the sum holds.  "least": embeddings
+    around 2^-120 (their parts end at 2^-133) times weights around 2^120; same bound.  "largest": two products of 2^128 (1 - 2^-10) that
+    cancel exactly, of factors that bf16 rounds up to 2^65 and 2^63, so that the parts' product overflows."""
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=64, tgt_vocab=64, emb=E, hidden=H, layers=1)
+    rng = np.random.default_rng(78 + E)
+    params = I.make_params(cfg, seed=E, scale=0.3)
+    W, Hd = params["enc.l0.fwd.W"], H // 2
+    if ends == "least":
+        params["E_src"] *= np.float32(2.0 ** -120)
+        W[:, :E] *= np.float32(2.0 ** 120)
+    else:
+        params["E_src"][:] = 0.0                        # (anything added between the two would be lost)
+        params["E_src"][:, :2] = 2.0 ** 65 - 2.0 ** 54
+        W[:, 0] = 2.0 ** 63 - 2.0 ** 52
+        W[:, 1] = -W[:, 0]
+    src = rng.integers(4, 64, size=(B, S)).astype(np.int32)
+    tr = binding.Trainer(cfg, B, S, 2, precision=0)
+    tr.set_params(I.flatten(params, cfg))
+    tr.train_step_async(tr.upload_batch(src, np.full(B, S, np.int32), np.full((B, 2), 4, np.int32), np.full(B, 2, np.int32)))
+    got = tr.debug_fetch("enc.l0.fwd.gates", (S, tr.padded_batch(), 4 * Hd))[0, :B].astype(np.float64)
+    tr.close()
+    x, W, b = params["E_src"].astype(np.float64)[src[:, 0]], W.astype(np.float64), params["enc.l0.fwd.b"].astype(np.float64)
+    pre = x @ W[:, :E].T + b
+    size = (np.abs(x) @ np.abs(W[:, :E]).T if ends == "least" else 0.0) + np.abs(b)
+    ref = np.where(np.arange(4 * Hd) // Hd == 2, np.tanh(pre), 1 / (1 + np.exp(-pre)))
+    bound = 2.0 ** -24 * (E / 16 + 4) * size + 4e-7
+    assert (np.abs(got - ref) <= bound).all(), np.abs(got - ref).max()
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("B,beam,S,H,V", [(1, 1, 1, 16, 8), (7, 9, 65, 48, 264), (13, 10, 5, 16, 24584), (17, 15, 17, 32, 24584), (26, 10, 4, 32, 24592),
                                           (40, 10, 3, 32, 24584), (40, 16, 3, 16, 24584)])
