@@ -57,10 +57,7 @@ void launch_beam_init(const BeamState& bs, int B, int Rp, int K, int bos, hipStr
 
 constexpr int BEAM_MAX = 16;
 
-// (value, index) ordering: larger value first, then lower index
-__device__ __forceinline__ bool beam_better(float v, int f, float bv, int bf) { return v > bv || (v == bv && f < bf); }
-
-// The same order as one number: of two keys the larger is the better pair.  (Two comparisons and a branch per pair, with an LDS read
+// Pairs (value, index), the larger value first, then the lower index, as one number: of two keys the larger is the better pair.  (Two comparisons and a branch per pair, with an LDS read
 // in it, made the counting below take 4.7 us for 56 entries; this 0.6.)
 __device__ __forceinline__ unsigned beam_sortable(float v) {
   const unsigned u = __float_as_uint(v);
@@ -96,24 +93,6 @@ __device__ __forceinline__ float beam_wave_max(float v) {
   STEP(0x143, 0xc);                                                        // row_bcast31 into rows 2, 3
 #undef STEP
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-// Workgroup-wide best (value, index) pair of NW wavefronts; every thread gets the result.
-template <int NW>
-__device__ __forceinline__ void beam_block_best(float& v, int& f, float* s_v, int* s_f) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(v, o, 64);
-    const int of = __shfl_xor(f, o, 64);
-    if (beam_better(ov, of, v, f)) { v = ov; f = of; }
-  }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  __syncthreads();                                       // the previous round's readers are done
-  if (lane == 0) { s_v[w] = v; s_f[w] = f; }
-  __syncthreads();
-  v = s_v[0]; f = s_f[0];
-#pragma unroll
-  for (int q = 1; q < NW; ++q)
-    if (beam_better(s_v[q], s_f[q], v, f)) { v = s_v[q]; f = s_f[q]; }
 }
 
 // z^T = W_o Ho^T + B_o, [V, pitch] fp32 with the R rows of the search side by side, and per group of 32 TA vocabulary entries
@@ -197,7 +176,8 @@ __global__ __launch_bounds__(64 * WM * WN) void beam_logits_kernel(const T* __re
 //   pass are listed in LDS and each counts how many are better;
 //   the entries of those groups that reach the K-th one's value are listed, and each counts how many are better: that is its place.
 // Equal logits in any number stay within the lists (all extensions of 640 rows equal: 10.7 ms a search, 10.4 else).  More than BEAM_PICK_CAP groups can pass only
-// where a few threads own nearly all the best groups of a long vocabulary: then K rounds of a workgroup-wide arg-max over all extensions.
+// where a few threads own nearly all the best groups of a long vocabulary: then K rounds of a workgroup-wide maximum over the groups (64
+// rows x 40000, eight steps: 0.96 ms where the best groups are spread 0.43; rounds over all extensions took 34).
 // What bounds it is the chain of these steps, each a trip to memory or a barrier.  640 rows, V = 32000: 9.2 us in the place of 29
 // for the rows' K best (a pass over 82 MB) and 11 for their merge.
 constexpr int BEAM_PICK_NT = 1024, BEAM_PICK_CAP = 1024, BEAM_TOKEN_BITS = 27;   // (slot, token) in one ordered word
@@ -210,8 +190,6 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
   __shared__ uint64_t s_g[BEAM_PICK_CAP], s_c[BEAM_PICK_ENTRIES];   // keys of (bound, slot and group) and of (value, slot and token)
   __shared__ uint64_t s_bound[NW];
   __shared__ int s_top[BEAM_MAX];
-  __shared__ float s_v[NW];
-  __shared__ int s_f[NW];
   __shared__ float s_winv[BEAM_MAX], s_least;
   __shared__ int s_winf[BEAM_MAX];
   __shared__ int s_ng, s_n, s_ntop;
@@ -298,15 +276,37 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
     for (int g0 = 64 * NQ; g0 < ng; g0 += 64) list(g0 + lane < ng, base + gmax[r * ng + min(g0 + lane, ng - 1)], g0 + lane);
   }
   __syncthreads();
-  const bool fits = s_ng <= BEAM_PICK_CAP;
-  if (fits) {
+  if (s_ng <= BEAM_PICK_CAP) {
     const int n = s_ng;
     for (int i = t; i < n; i += BEAM_PICK_NT) {
       const int place = beam_place(s_g, n, s_g[i]);
       if (place == K - 1) s_least = beam_key_value(s_g[i]);   // (fewer than K groups: every entry passes)
       if (place < K) s_top[atomicAdd(&s_ntop, 1)] = beam_key_index(s_g[i]);
     }
-    __syncthreads();
+  } else {                                               // K rounds, each for the best of those behind the one before
+    uint64_t last = ~0ull;                               // (short code: what is seldom run is fetched all the same)
+#pragma unroll 1
+    for (int round = 0; round < K; ++round) {
+      uint64_t best = 0;
+#pragma unroll 1
+      for (int g = w < nl ? lane : ng; g < ng; g += 64) {
+        const float bound = base + gmax[r * ng + g];
+        const uint64_t key = beam_key(bound, w << BEAM_TOKEN_BITS | g);
+        if (bound > -INFINITY && key < last) best = max(best, key);
+      }
+#pragma unroll 1
+      for (int o = 32; o > 0; o >>= 1) best = max(best, (uint64_t)__shfl_xor((unsigned long long)best, o, 64));
+      if (lane == 0) s_bound[w] = best;
+      __syncthreads();
+#pragma unroll 1
+      for (int i = 0; i < NW; ++i) best = max(best, s_bound[i]);
+      if (t == 0) { s_top[round] = beam_key_index(best); s_least = beam_key_value(best); s_ntop = round + 1; }
+      last = best;                                       // (the list's capacity and more are there: never 0)
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  {
     // ---- their entries -------------------------------------------------------------------------------------
     const float least = s_least;
     const int entries = s_ntop << gbits;
@@ -318,26 +318,10 @@ __global__ __launch_bounds__(BEAM_PICK_NT) void beam_pick_kernel(const float* __
       beam_append(x >= least && x > -INFINITY, beam_key(x, s << BEAM_TOKEN_BITS | v), s_c, &s_n, BEAM_PICK_ENTRIES);   // (neither NaN nor impossible)
     }
     __syncthreads();
-  }
-  if (fits) {
     const int n = s_n;
     for (int i = t; i < n; i += BEAM_PICK_NT) {
       const int place = beam_place(s_c, n, s_c[i]);
       if (place < K) { s_winv[place] = beam_key_value(s_c[i]); s_winf[place] = beam_key_index(s_c[i]); }
-    }
-  } else {
-    // K rounds: the best extension strictly after the previous winner in the (value, slot and token) order
-    float pv = INFINITY; int pi = -1;
-    for (int round = 0; round < K; ++round) {
-      float v = -INFINITY; int f = 0x7fffffff;
-      for (int i = t; i < V * nl; i += BEAM_PICK_NT) {
-        const int tk = i / nl, s = i - tk * nl, xi = s << BEAM_TOKEN_BITS | tk;
-        const float x = s_base[s] + zT[(size_t)tk * pitch + row0 + s];
-        if (x > -INFINITY && (x < pv || (x == pv && xi > pi)) && beam_better(x, xi, v, f)) { v = x; f = xi; }
-      }
-      beam_block_best<NW>(v, f, s_v, s_f);
-      if (t == 0) { s_winv[round] = v; s_winf[round] = f; }
-      pv = v; pi = f;
     }
   }
   __syncthreads();
