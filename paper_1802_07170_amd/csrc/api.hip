@@ -27,6 +27,7 @@
 #include "../../include/cytonmt_hip.h"
 #include "kernels.h"
 #include "recur_plan.h"
+#include "row_pitch.h"
 #include "section_gate.h"
 
 using namespace cmt;
@@ -42,7 +43,7 @@ struct ParamInfo { std::string name; int64_t rows, cols; size_t off; };
 // one LSTM (layer, direction)
 struct LD {
   int Kin = 0, Hh = 0;
-  int ph = 0, pg = 0;                // row pitches (elements) of Hst and dG: Hh, 4Hh + ACT_PAD or ACT_PAD_LINES
+  int ph = 0, pg = 0;                // row pitches (elements) of Hst and dG: Hh, 4Hh + padding (see row_pitch.h)
   size_t w_off = 0, b_off = 0;       // element offsets in the flat parameter vector
   char* W = nullptr;                 // T [4Hh, Kin+Hh]
   char* Wt = nullptr;                // T [Kin+Hh, 4Hh]
@@ -72,14 +73,6 @@ struct LD {
   char* dGF = nullptr;               // [Lmax] slots of [Bp, 4Hh]
   bool fmb = false;
 };
-
-// Row pitch padding of the per-step activation operands.  The step kernels that read row-major operands take 16 sentences x 64
-// bytes per fragment load; with a power-of-two pitch those 16 segments fall on the same cache banks
-// (measured: 14.3 -> 11.0 us for the decoder LSTM step with 16 bytes of padding; rows kept 128-byte aligned by
-// padding with 64 elements instead: 11.6 us against 9.8 us, 32 / 72 / 136 elements: 10.0 - 10.2 us).
-// Where fragment-major copies serve those kernels, what is left to read the rows are the products over all positions, 128 bytes of a row at
-// a time: rows of whole lines, or each piece takes two (dX of 3200 positions, 4096 -> 1024: 73 -> 47 us; medium step 5.87 -> 5.78 ms).
-constexpr int ACT_PAD = 8, ACT_PAD_LINES = 64;
 
 // Row capacity of an output-layer slab: CE_SLAB_MAX_ROWS unless CMT_CE_SLAB_ROWS asks for less (a multiple of 256
 // from 256 up; read whenever a handle or a size query is set up, so both see the same value).
@@ -123,7 +116,7 @@ struct cmt_handle {
   std::vector<ParamInfo> table;
   std::string err;
   int Bpm = 0;                          // padded max batch
-  int PH = 0;                           // row pitch of HoBuf, Cs, dPre: H + padding (see ACT_PAD)
+  int PH = 0;                           // row pitch of HoBuf, Cs, dPre: H + padding (see row_pitch.h)
   int ldWoT = 0;                        // row pitch of WoT
   bool pad_lines = true;                // (not in the static array: what fits there does not depend on it)
   // last-step shape
@@ -283,8 +276,8 @@ size_t layout(cmt_handle* h, char* base) {
   const int Bp = h->Bpm, Sm = c.max_src_len, Tm = c.max_tgt_len;
   const size_t Ms = (size_t)Sm * Bp, Mt = (size_t)Tm * Bp;
   Bump a(base);
-  const int pad = h->pad_lines && c.precision && H >= 256 && H % 64 == 0 ? ACT_PAD_LINES : ACT_PAD;
-  h->PH = H + pad;
+  const RowPitch pad = row_pitch(c.precision, E, H, h->pad_lines);
+  h->PH = H + pad.states;
   const size_t PH = h->PH;
   h->Pc = c.precision ? a.take(h->nparams * esz) : (char*)h->params;
   // (The whole loops take batches up to LOOP_MAX_BATCH; Bl: the rows of their slots.  The slots are there whether or not
@@ -293,7 +286,7 @@ size_t layout(cmt_handle* h, char* base) {
   const bool loop_all = loops && h->loop_slots == LOOP_SLOTS_ALL;
   const size_t Bl = std::min(Bp, LOOP_MAX_BATCH);
   auto ld_alloc = [&](LD& d, int Kin, int Hh, int Lm, bool gx, int Kstep, bool encoder) {
-    d.Kin = Kin; d.Hh = Hh; d.ph = Hh + pad; d.pg = 4 * Hh + pad;
+    d.Kin = Kin; d.Hh = Hh; d.ph = Hh + pad.states; d.pg = 4 * Hh + (&d == &h->dec[0] ? pad.gates_bottom : pad.gates);
     const size_t M = (size_t)Lm * Bp;
     d.Kstep = Kstep;
     d.fm = !encoder && c.precision && Hh % 32 == 0 && Kstep % 32 == 0;
@@ -381,7 +374,7 @@ size_t layout(cmt_handle* h, char* base) {
   else if (h->HoFeedF) h->HoFeedX = h->HoFeedF;
   else if (loop_all) h->HoFeedX = h->HoBufT;                             // (transposed after the forward loop)
   h->HoDrop = a.take((Mt + Bp) * PH * esz);
-  h->ldxcat = E + H + pad;
+  h->ldxcat = E + H + pad.states;
   h->xcat = a.take((size_t)Bp * h->ldxcat * esz);
   h->dec_tok = (int32_t*)a.take((size_t)Bp * 4); h->dec_done = (int32_t*)a.take((size_t)Bp * 4);
   h->dec_mask = (float*)a.take((size_t)Bp * 4);

@@ -35,3 +35,32 @@ def test_groups_that_wait_for_one_another_are_small_enough(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", f"-I{ROOT}", str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+PITCH_PROGRAM = r"""
+#include "paper_1802_07170_amd/csrc/row_pitch.h"
+int main() {
+  using namespace cmt;
+  int bad = 0;
+  for (int H = 16; H <= 1024; H += 16)
+    for (int E = 8; E <= 1024; E += 8)
+      for (int prec = 0; prec < 2; ++prec) {
+        const RowPitch p = row_pitch(prec, E, H, true), q = row_pitch(prec, E, H, false);
+        const bool copies = prec && H % 32 == 0;         // what api.hip's layout makes fragment-major copies of
+        const bool fed = copies && E % 32 == 0, bottom = copies && (E + H) % 16 == 0;
+        bad += (p.states != ACT_PAD && !fed) + (p.gates_bottom != ACT_PAD && !bottom) + (p.gates != ACT_PAD && !copies);
+        bad += H == 1024 && E == 1024 && prec && (p.states != ACT_PAD_LINES || p.gates != ACT_PAD_LINES || p.gates_bottom != ACT_PAD_LINES);
+        bad += q.states != ACT_PAD || q.gates != ACT_PAD || q.gates_bottom != ACT_PAD;
+      }
+  return bad != 0;
+}
+"""
+
+
+def test_rows_that_a_position_reads_are_never_padded_to_whole_lines(tmp_path):
+    """Whole cache lines only for rows of which the kernels of a position read fragment-major copies."""
+    src = tmp_path / "pitch.cpp"
+    src.write_text(PITCH_PROGRAM)
+    exe = tmp_path / "pitch"
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", f"-I{ROOT}", str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)]).returncode == 0
