@@ -24,7 +24,14 @@ static int env_int(const char* name, int dflt) {
 }
 static const int GEMM_BIG_MIN_TILES = env_int("CMT_GEMM_BIG_MIN_TILES", 144);
 static const int GEMM_SPLIT_BELOW = env_int("CMT_GEMM_SPLIT_BELOW", 257);       // small tiles
-static const int GEMM_SPLIT_TARGET = env_int("CMT_GEMM_SPLIT_TARGET", 1024);
+// Workgroups of the 64 x 64 tile that a CU's LDS holds: four, of fp32 products in parts three (the 256 bytes: their vote).  A split of k aims at
+// one round of them over the chip: fp32 training steps with 768 instead of 1024 workgroups wanted: width 512, 64 sentences, vocabulary 16000 4.44 -> 4.38
+// ms, 6400 2.76 -> 2.72; width 256, vocabulary 2000 1.60 -> 1.59; widths 64 - 128 and 768 - 1024 0 - 0.5 %.
+template <typename T> constexpr int gemm_small_per_cu(bool chain) {
+  return 160 * 1024 / ((chain ? GemmSmall<T>::CHAIN_BYTES : GemmSmall<T>::SMEM_BYTES) + 256);
+}
+static_assert(gemm_small_per_cu<bf16_t>(false) == 4 && gemm_small_per_cu<float>(true) == 4 && gemm_small_per_cu<float>(false) == 3,
+              "what the rules below were measured with");
 // Medium tiles of which there is at most one per CU take four k tiles of LDS, three of them on their way, instead of two for two
 // workgroups per CU, us (two | four): 200 tiles, k 4096 56 | 50, k 2048 35 | 31; 234 tiles, k 1096 29 | 26; 400 tiles, k 1024 28 | 40.
 static const int GEMM_DEEP_MAX_TILES = env_int("CMT_GEMM_DEEP_MAX_TILES", 256);
@@ -104,7 +111,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_kernel(const T* __restri
                                                                int kchunk, size_t plane_stride, RowLimit lim, int lim_kind,
                                                                int dyn_split) {
   using G = GemmTile<T, WM, WN, TA, TB>;
-  __shared__ __align__(16) char smem[STAGES > 2 ? STAGES * (G::BM + G::BN) * 128 : G::SMEM_BYTES];
+  __shared__ __align__(16) char smem[STAGES > 2 ? STAGES * (G::BM + G::BN) * 128 : CHAIN ? G::CHAIN_BYTES : G::SMEM_BYTES];
   if (lim.n) {                                     // a bound that only the device knows (uniform over the grid)
     const int e = max(*lim.n - lim.base, 0);
     if (lim_kind == 1) M = min(M, e);
@@ -234,10 +241,11 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
   const int grid = ((nb + 7) / 8) * 8;
   const int esz = prec ? 2 : 4;
   const int bk = 128 / esz;
-  // few output tiles but a long contraction: split k over workgroups (four small workgroups per CU wanted)
+  // few output tiles but a long contraction: split k over workgroups, one round of them over the chip
+  const int per_cu = prec ? gemm_small_per_cu<bf16_t>(false) : gemm_small_per_cu<float>(chain);
   int ks = 1;
   if (split_scratch && Cf && !Ct && small && nb < GEMM_SPLIT_BELOW && K >= 16 * bk) {
-    ks = (GEMM_SPLIT_TARGET + nb - 1) / nb;
+    ks = (256 * per_cu + nb - 1) / nb;
     if (ks > GEMM_SPLIT_MAX) ks = GEMM_SPLIT_MAX;
     while (ks > 1 && ((size_t)ks * M * N > split_scratch_floats || K / ks < 4 * bk)) --ks;
   }
@@ -249,7 +257,7 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
   const int oldc = nks > 1 ? N : ldc;
   const float* obias = nks > 1 ? nullptr : bias;
   const int oacc = nks > 1 ? 0 : accumulate;
-  const int cap = small ? 4 * wg_cap : wg_cap;
+  const int cap = small ? per_cu * wg_cap : wg_cap;
   auto go = [&](auto type, auto shape) {
     using T = decltype(type);
     if constexpr (decltype(shape)::value == 1)
@@ -366,7 +374,7 @@ void launch_gemm_nt_group(int prec, const GemmProb* probs, int n, hipStream_t st
   if (big >= GEMM_BIG_MIN_TILES) gemm_group_go<bf16_t, 4, 4, 2, 2>(live.data(), (int)live.size(), st, wg_cap ? wg_cap : big_cap);
   else if (medium >= 192 && medium <= GEMM_DEEP_MAX_TILES) gemm_group_go<bf16_t, 2, 2, 2, 2, 4>(live.data(), (int)live.size(), st, wg_cap);
   else if (medium >= 192) gemm_group_go<bf16_t, 2, 2, 2, 2>(live.data(), (int)live.size(), st, wg_cap);
-  else gemm_group_go<bf16_t, 2, 2, 1, 1>(live.data(), (int)live.size(), st, 4 * wg_cap);
+  else gemm_group_go<bf16_t, 2, 2, 1, 1>(live.data(), (int)live.size(), st, gemm_small_per_cu<bf16_t>(false) * wg_cap);
 }
 
 // Measurement aid: nothing but matrix-core instructions (4 independent 32x32x16 bf16 accumulator chains per

@@ -2,7 +2,7 @@
 // LinearLayer forward GEMM form; every batched-over-time contraction of the step is brought to
 // this form).  WM x WN wavefronts; each wavefront owns TA x TB MFMA 32x32 tiles, so the workgroup
 // tile is (32 TA WM) x (32 TB WN).  Three shapes are used:
-//   * 2x2 wavefronts, one tile each: 64 x 64, 256 threads, 36 KB of LDS, four workgroups per CU: for the many
+//   * 2x2 wavefronts, one tile each: 64 x 64, 256 threads, 36 KB of LDS, four workgroups per CU (fp32 in parts 48 KB, three): for the many
 //     products of a small network or batch that are a few dozen tiles of the next size, where what a launch takes is
 //     the chain prologue - contraction - store of one workgroup (16 stores a lane instead of 64).
 //   * 2x2 wavefronts, 2x2 tiles each: 128 x 128, 256 threads, 72 KB of LDS, two workgroups per CU
@@ -33,6 +33,7 @@ template <typename T, int WM_, int WN_, int TA_, int TB_> struct GemmTile {
   static constexpr int ROWB = BK * (int)sizeof(T) + 16;    // row pitch of the padded LDS image
   static constexpr int STAGE_BYTES = (BM + BN) * ROWB;
   static constexpr int SPLIT_BYTES = (BM + BN) * BK * 6;   // a stage of three bf16 planes
+  static constexpr int CHAIN_BYTES = 2 * STAGE_BYTES;      // of a kernel that makes fp32 products on the fp32 instructions alone
   static constexpr int SMEM_BYTES = 2 * (sizeof(T) == 4 && SPLIT_BYTES > STAGE_BYTES ? SPLIT_BYTES : STAGE_BYTES);
 };
 template <typename T> using GemmSmall = GemmTile<T, 2, 2, 1, 1>;                     // 64 x 64, 256 threads

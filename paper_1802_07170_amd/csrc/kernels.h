@@ -28,7 +28,7 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
 // moving a gradient by its own error is more than sums in another order may do; everything else runs split (gemm_core.h).
 // wg_cap > 0: at most that many workgroups (rounded up to a multiple of 8) walk the tiles — for a GEMM on a second
 // stream that is to leave part of the chip to the kernels of the first.  The cap counts workgroups of the two larger tiles; of
-// the 64 x 64 tile, which fits a CU four times, four times as many are launched.
+// the 64 x 64 tile as many times more are launched as of it fit a CU (four; fp32 in parts three).
 // Matrix-core issue-rate probe: `blocks` workgroups of 4 wavefronts, each `iters` x 4 bf16 32x32x16 MFMAs on
 // registers; out needs blocks * 256 floats.  Returns the flops of the launch.
 // Several independent C (+)= A * B^T problems (fp32 C) as one launch: the tiles of all problems form one
