@@ -1260,10 +1260,11 @@ int enqueue_step(cmt_handle* h, const int32_t* src_ids, const int32_t* src_len, 
   // W_c and every decoder layer's weight gradient: one launch.  The top encoder layers' recurrences come beside it, one workgroup to
   // a CU; where they take half of the chip at most, the 256 x 256 tiles, which hold a CU for long, are left the rest: 64 sentences, width 1024,
   // first recurrence 267 -> 218 us, the product before it 156 -> 74, this launch 312 -> 506, the step 5.74 -> 5.61 ms.  (128 sentences take
-  // every CU: a cap of 128 19.1 -> 19.4; groups of smaller tiles: width 512 2.564 -> 2.574.)
+  // every CU: a cap of 128 19.1 -> 19.4; groups of smaller tiles: width 512 2.564 -> 2.574.)  14 steps of widths 512 - 1024, 2 to 4 layers, 16 to
+  // 100 sentences of 5 to 110 tokens: 0 - 2.7 % faster with the cap but for one, width 896, 40 sentences, 0.4 % slower.
   const SeqPlan top = seq_bwd_plan(p, 1, Bp, H);
   const int beside = top.groups * top.group;
-  flush_dw_group(h, sd, L > 1 && beside <= 128 ? 256 - beside : 0);
+  flush_dw_group(h, sd, L > 1 && 2 * beside <= h->seq.cus ? h->seq.cus - beside : 0);
   launch_gemm_nt(p, h->dec[0].dG, h->dec[0].pg, h->dec[0].Wt, 4 * H, Mt, E, 4 * H, h->dXt, nullptr, E, nullptr, 0, sd);
   launch_embed_scatter(h->dXt, h->tok_t, Mt, c.tgt_vocab, E, G + h->off_Etgt, sd, false);
 
