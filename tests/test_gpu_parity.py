@@ -577,8 +577,8 @@ def test_beam_search_matches_the_oracle(prec, B, S, H, E, L, max_len, beam):
 
 
 def test_random_decode_sweep():
-    """24 seeded random shapes (batch, source length, step cap, widths, depth, vocabularies incl. one
-    larger than the per-row candidate list, beam 1..16), fp32 path: greedy tokens and beam-search
+    """24 seeded random shapes (batch, source length, step cap, widths, depth, vocabularies of one group of
+    entries to 65, beam 1..16), fp32 path: greedy tokens and beam-search
     hypotheses, lengths and scores identical to the oracle's wherever its decision gap exceeds what fp32
     resolves."""
     from paper_1802_07170_amd import binding
@@ -621,9 +621,8 @@ def test_random_decode_sweep():
 
 def test_beam_search_with_massively_tied_logits():
     """W_o = 0: every row's logits are B_o, here five entries at 1.0, one (the end token) at 0.5 and 2050
-    exact zeros.  The candidate threshold of the per-row selection then admits the whole vocabulary
-    (more than its list holds), so the selection runs over the row itself; ties must resolve to the lower
-    (slot, token) pair exactly as in the oracle."""
+    exact zeros.  Nearly all groups of entries then have the same maximum, and those that go on are the first of
+    them; ties must resolve to the lower (slot, token) pair exactly as in the oracle."""
     from paper_1802_07170_amd import binding
     cfg = dict(src_vocab=104, tgt_vocab=2056, emb=8, hidden=16, layers=1)
     rng = np.random.default_rng(5)
@@ -648,11 +647,12 @@ def test_beam_search_with_massively_tied_logits():
     tr.close()
 
 
-@pytest.mark.parametrize("B,V", [(3, 1000), (3, 8192), (3, 8200), (3, 32768), (3, 32776), (25, 8200), (26, 8192), (26, 8200)])
+@pytest.mark.parametrize("B,V", [(3, 1000), (3, 8192), (3, 8200), (3, 32768), (3, 32776), (25, 8200), (26, 8192), (26, 8200), (7, 65544)])
 def test_beam_search_at_the_edges_of_the_row_sizes(B, V):
-    """The per-row selection keeps a row in the registers of 256 or 512 threads or reads it again, by its length and the
-    number of rows (256): both sides of every line, fp32, against the oracle.  The best tokens' biases sit at the row's
-    ends, so that a piece that a form leaves out changes the result."""
+    """The selection keeps a row's first 1024 groups in a wavefront's registers and reads the others again.  Groups have 32 entries on
+    small tiles (30 rows) and 64 on the others: rows that end with a group or 8 entries into one, that have 1024 groups and one more of
+    either size, and either side of the 256 rows from which W_c2 H_t takes wider tiles; fp32, against the oracle.  The best tokens'
+    biases sit at the row's ends, so that a piece that a form leaves out changes the result."""
     from paper_1802_07170_amd import binding
     cfg = dict(src_vocab=104, tgt_vocab=V, emb=24, hidden=32, layers=2)
     rng = np.random.default_rng(B + V)
@@ -1285,27 +1285,141 @@ def test_fp32_products_at_the_ends_of_the_range(ends, B, S, E, H):
     assert (np.abs(got - ref) <= bound).all(), np.abs(got - ref).max()
 
 
-@pytest.mark.parametrize("prec", [0, 1])
-@pytest.mark.parametrize("B,beam,S,H,V", [(1, 1, 1, 16, 8), (7, 9, 65, 48, 264), (13, 10, 5, 16, 24584), (17, 15, 17, 32, 24584), (26, 10, 4, 32, 24592),
-                                          (40, 10, 3, 32, 24584), (40, 16, 3, 16, 24584)])
-def test_beam_search_over_the_tile_shapes_of_the_logits(prec, B, beam, S, H, V):
-    """One to 640 rows: every width of the logits' row tile, rows that end inside one, groups that end inside the vocabulary, source
-    sentences longer than the 64 positions that the mix takes at a time, and both forms of W_c2 H_t (256 rows).  Against the
-    oracle: tokens wherever its decision gap exceeds what the precision resolves; the best tokens' biases sit at the ends."""
+def out_of_the_parts_range(params, rng):
+    """Puts numbers that three bf16 parts do not hold into the output layer of `params` without changing what it computes: W_o at
+    3.3e38 in a column where H_o is exactly zero, biases that no sum of parts holds on entries that are then never likely."""
+    V = len(params["B_o"])
+    params["W_c"][3] = 0.0                               # H_o[:, 3] = tanh(0)
+    params["W_o"][rng.permutation(V)[: V // 4], 3] = np.float32(3.3e38)
+    params["B_o"][4 + rng.permutation(V - 4)[: V // 8]] = -1e30
+
+
+@pytest.mark.parametrize("special", [False, True])
+@pytest.mark.parametrize("B,T,H,V", [(5, 4, 16, 40), (64, 40, 48, 520), (130, 9, 272, 1032)])
+def test_fp32_logits_in_three_parts(B, T, H, V, special):
+    """The output layer's logits, all products in the accumulators that start at the bias, against 64 bits from the same H_o: log-sum-exp
+    and nll of every position.  Bound: a logit's sum in steps of 16 k, six products each, rounds by half a unit of what its terms amount to
+    per product (the fp32 instructions, where a tile is made again: per two k); then the exponentials and their sum."""
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=64, tgt_vocab=V, emb=16, hidden=H, layers=1)
+    rng = np.random.default_rng(90 + B)
+    params = I.make_params(cfg, seed=B, scale=0.3)
+    params["W_o"] = params["W_o"] * 8
+    if special:
+        out_of_the_parts_range(params, rng)
+    src, sl, tgt, tl = ragged_batch(rng, B, 3, T, 64, V)
+    tr = binding.Trainer(cfg, B, 3, T, precision=0)
+    tr.set_params(I.flatten(params, cfg))
+    tr.eval_loss(tr.upload_batch(src, sl, tgt, tl))
+    n = tr.padded_batch()
+    ho = tr.debug_fetch("h_o", (T, n, H))[:, :B].astype(np.float64)
+    lse, nll = (tr.debug_fetch(k, (T, n))[:, :B].astype(np.float64) for k in ("lse", "nll"))
+    tr.close()
+    W, b = params["W_o"].astype(np.float64), params["B_o"].astype(np.float64)
+    z = ho @ W.T + b
+    size = (np.abs(ho) @ np.abs(W).T + np.abs(b) * (b > -1e29)).max(axis=2)
+    top = z.max(axis=2)
+    want = top + np.log(np.exp(z - top[..., None]).sum(axis=2))
+    label = np.take_along_axis(z, tgt.T[..., None], axis=2)[..., 0]
+    bound = 2.0 ** -24 * (max(6 * H / 16, H / 2) + 4) * size + 4e-6
+    valid = np.arange(T)[:, None] < tl
+    assert (np.abs(lse - want) <= bound)[valid].all(), np.abs(lse - want)[valid].max()
+    likely = valid & (label > -1e29)
+    assert (np.abs(nll - (want - label)) <= 2 * bound)[likely].all() and likely.any()
+
+
+@pytest.mark.parametrize("B,V", [(3, 136), (13, 12304)])
+def test_fp32_beam_search_beyond_the_range_of_the_parts(B, V):
+    """The search's logits where tiles are made again, in both tiles (30 and 130 rows): tokens and scores of the same network with
+    zeros and merely unlikely biases in those places, and the oracle's."""
+    from paper_1802_07170_amd import binding
+    cfg = dict(src_vocab=104, tgt_vocab=V, emb=16, hidden=48, layers=1)
+    params = I.make_params(cfg, seed=B, scale=0.4)
+    params["W_o"] = params["W_o"] * 6
+    src, sl, _, _ = ragged_batch(np.random.default_rng(B), B, 4, 5, 104, V)
+    special = {k: v.copy() for k, v in params.items()}
+    out_of_the_parts_range(special, np.random.default_rng(B))
+    plain = {k: v.copy() for k, v in special.items()}
+    plain["W_o"][plain["W_o"] > 1e38] = 0.0
+    plain["B_o"][plain["B_o"] < -1e29] = -1e4
+    got = []
+    tr = binding.Trainer(cfg, 10 * B, 4, 6, precision=0)
+    for p in (plain, special):
+        tr.set_params(I.flatten(p, cfg))
+        got.append(tr.beam_decode(src, sl, 5, beam=10, length_penalty=0.6, eos_id=3))
+    tr.close()
+    oids, olens, oscore, margins = O.beam_decode(cfg, plain, src, sl, 5, 10, 0.6, bos_id=2, eos_id=3)
+    sure = margins > 1e-3
+    assert sure.any()
+    for ids, lens, score in got:
+        assert np.allclose(score, oscore, rtol=1e-4)
+        assert np.array_equal(ids[sure], oids[sure]) and np.array_equal(lens[sure], olens[sure])
+
+
+def states_of_a_search(cfg, params, src, src_len, paths):
+    """H_o of the decoder's last step over paths[b] ([n, steps] tokens, the first always bos) of every sentence, in 64 bits: [B, n, H]."""
+    p = {k: np.asarray(v, np.float64) for k, v in params.items()}
+    H = cfg["hidden"]
+    out = []
+    for b in range(len(src_len)):
+        m, n = int(src_len[b]), len(paths[b])
+        X, mask = p["E_src"][src[b, :m]][:, None, :], np.ones((m, 1))
+        zero = np.zeros((1, H // 2))
+        Yf, hf, cf, _ = O.lstm_forward(X, mask, p["enc.l0.fwd.W"], p["enc.l0.fwd.b"], zero, zero)
+        Yb, hb, cb, _ = O.lstm_forward(X, mask, p["enc.l0.bwd.W"], p["enc.l0.bwd.b"], zero, zero, reverse=True)
+        Hs = np.repeat(np.concatenate([Yf, Yb], axis=2), n, axis=1)
+        h, c = (np.repeat(np.concatenate(x, axis=1), n, axis=0) for x in ((hf, hb), (cf, cb)))
+        Ho = np.zeros((n, H))
+        for tok in paths[b].T:
+            _, h, c, _ = O.masked_step_forward(np.concatenate([p["E_tgt"][tok], Ho], axis=1), h, c, np.ones((n, 1)), p["dec.l0.W"], p["dec.l0.b"])
+            Ho, _ = O.attention_forward(Hs, np.ones((m, n)), h, p["W_a"], p["W_c"])
+        out.append(Ho)
+    return np.array(out)
+
+
+@pytest.mark.parametrize("B,beam,S,H,V", [(1, 1, 1, 48, 8), (7, 9, 65, 48, 264), (26, 10, 4, 64, 8192), (13, 10, 5, 48, 24584),
+                                          (17, 15, 17, 64, 24584), (26, 10, 4, 64, 24592), (40, 10, 3, 64, 24584), (40, 16, 3, 80, 24584)])
+def test_beam_search_over_the_tile_shapes_of_the_logits(B, beam, S, H, V):
+    """One to 640 rows: every width of the logits' row tile in bf16 (none, none, 1, 2, 2, 3, 4, 5 times 64 rows), rows that end inside
+    one, groups that end inside the vocabulary, source sentences longer than the 64 positions that the mix takes at a time, and both
+    forms of W_c2 H_t (256 rows).  The first token is one of `beam` favoured ones, and every row of the steps behind it has a token
+    of its own, all over the vocabulary, whose row of W_o is the direction of the H_o that the row has there: the right one is ahead by
+    the distance between two rows' H_o, so which token follows which says, at any precision, what row the logits, the selection and
+    the states moved to their new rows are from.  Which of a sentence's hypotheses wins, and its score, against the oracle: as far
+    as four times what rounding the operands moves a score resolves it."""
     from paper_1802_07170_amd import binding
     cfg = dict(src_vocab=104, tgt_vocab=V, emb=16, hidden=H, layers=1)
     rng = np.random.default_rng(B + V + S)
     params = I.make_params(cfg, seed=6, scale=0.3)
-    params["B_o"] = rng.uniform(-1.0, 1.0, V).astype(params["B_o"].dtype)
-    params["B_o"][[4, V // 2, V - 3, V - 1]] += 2.0
-    src, sl, _, _ = ragged_batch(rng, B, S, 4, 104, V)
-    tr = binding.Trainer(cfg, B * beam, S, 4, precision=prec)
-    tr.set_params(I.flatten(params, cfg))
-    ids, lens, score = tr.beam_decode(src, sl, 4, beam=beam, length_penalty=0.6, eos_id=3)
-    oids, olens, oscore, margins = O.beam_decode(cfg, params, src, sl, 4, beam, 0.6, bos_id=2, eos_id=3)
-    tr.close()
-    # (a logit moves by about atol(H_o) * row norm, a score by four of them: see test_beam_search_matches_the_oracle)
-    tol = (2e-5 if prec == 0 else 2e-2) * 2.0 * np.linalg.norm(params["W_o"], axis=1).max() * 4
-    sure = margins > tol
-    assert np.array_equal(ids[sure], oids[sure]) and np.array_equal(lens[sure], olens[sure])
-    assert (np.abs(score - oscore) <= tol + 1e-4 * np.abs(oscore)).all()
+    params["E_src"], params["E_tgt"], params["W_c"] = 8 * params["E_src"], 8 * params["E_tgt"], 8 * params["W_c"]
+    src, sl = rng.integers(4, 104, size=(B, S)).astype(np.int32), rng.integers((S + 1) // 2, S + 1, size=B).astype(np.int32)
+    src[:, 0] = 4 + rng.permutation(100)[:B]             # (no two sentences alike)
+    places = rng.permutation(np.linspace(4, V - 1, beam * (2 * B + 1)).astype(int))
+    first, after = places[:beam], places[beam:].reshape(B, beam, 2)     # after[b, i]: what follows first[i] in sentence b
+    paths = [np.stack([np.full(beam, 2), first, after[b, :, 0]], axis=1) for b in range(B)]
+    params["W_o"], params["B_o"] = np.zeros((V, H), np.float32), rng.uniform(-1.0, 1.0, V).astype(np.float32)
+    params["W_o"][first], params["B_o"][first] = 0.25 * rng.choice([-1, 1], size=(beam, H)), 0.0
+    least = np.inf
+    for j in range(2):
+        ho = states_of_a_search(cfg, params, src, sl, [p[:, :j + 2] for p in paths])
+        size = np.linalg.norm(ho, axis=2, keepdims=True)
+        params["W_o"][after[:, :, j]], params["B_o"][after[:, :, j]] = 4.0 * ho / size, 0.0
+        least = min(least, size.min())
+    params["B_o"][first] = 3.2 * least
+    search = lambda: O.beam_decode(cfg, params, src, sl, 3, beam, 0.6, bos_id=2, eos_id=3)
+    oids, olens, oscore, margins = search()
+    with O.operand_rounding(O.bf16_round):
+        rids, _, rscore, _ = search()
+    follows = lambda ids: [r[0] in first and r[1:] == after[b, list(first).index(r[0])].tolist() for b, r in enumerate(ids.tolist())]
+    assert all(follows(oids)) and all(follows(rids)) and (olens == 3).all()
+    for prec in (0, 1):
+        tr = binding.Trainer(cfg, B * beam, S, 4, precision=prec)
+        tr.set_params(I.flatten(params, cfg))
+        ids, lens, score = tr.beam_decode(src, sl, 3, beam=beam, length_penalty=0.6, eos_id=3)
+        tr.close()
+        tol = 4 * np.abs(rscore - oscore).max() if prec else 1e-4
+        sure = margins > tol
+        assert sure.sum() >= (B + 3) // 4, (prec, tol, np.sort(margins))
+        assert np.array_equal(lens, olens) and all(follows(ids)), prec
+        assert np.array_equal(ids[sure], oids[sure]), prec
+        assert (np.abs(score - oscore) <= tol + 1e-6 * np.abs(oscore)).all(), (prec, tol, np.abs(score - oscore).max())
