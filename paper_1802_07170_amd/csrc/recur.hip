@@ -15,8 +15,8 @@
 //     earlier costs more than it gains, since the reads then stand in the way of the stores they wait for.
 // Roles are taken from a ticket counter, in order of arrival, so that the workgroups on the chip always form complete
 // groups and at most one incomplete one per launch.  Groups have at most 64 workgroups (recur_plan.h), so the four launches
-// that a process's hardware queues can run at once leave a CU free for one of them to complete its group.  Nothing rests on
-// that but speed: more queues, other processes or a stream confined to a few CUs may stop a group from forming.  Every wait
+// that a process's hardware queues can run at once leave a CU free, nearly always for one of them to complete its group.  Nothing rests on
+// that but speed: more queues, other processes or a stream confined to a few CUs may stop a group from forming as well.  Every wait
 // is bounded, a workgroup that gives up says so and finishes without waiting, the others of the launch follow, and a second
 // launch (2 - 4 us of a step where there is nothing to do) makes the recurrence again without waits, one workgroup per 16 sentences:
 // 0.4 ms a position at width 1024.  That form also serves devices too small for the groups.

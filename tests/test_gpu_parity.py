@@ -1148,7 +1148,9 @@ def test_encoder_recurrences_without_waits(prec, how, B, S, H, E, L, reg, monkey
 @pytest.mark.parametrize("prec,H,lengths", [(1, 512, 30), (1, 1024, 20), (0, 1024, 12)])
 def test_recurrences_of_several_streams_at_once(prec, H, lengths):
     """Four handles on four streams, driven by four threads: their recurrences share the chip, and every step's gradients
-    are those of the handle alone, bit for bit.  Width 1024: groups of 64 workgroups that wait for one another, the largest."""
+    are those of the handle alone, bit for bit.  Width 1024: groups of 64 workgroups that wait for one another, the largest; there a
+    step in 100 to 250 gives up a wait (counted), and what was given up is made again with its sums in another order: the bound of the
+    forms of the recurrences against one another."""
     import threading
 
     import torch
@@ -1168,11 +1170,14 @@ def test_recurrences_of_several_streams_at_once(prec, H, lengths):
         trainers.append(tr)
         devs.append(dev)
         alone.append(tr.get_grads())
-    got = [None] * len(batches)
+    got, again = [None] * len(batches), [None] * len(batches)
 
     def work(k):
-        for _ in range(5):
+        for _ in range(4):
             trainers[k].train_step(devs[k])
+        before = trainers[k].wait_counts()[1]
+        trainers[k].train_step(devs[k])
+        again[k] = trainers[k].wait_counts()[1] - before
         got[k] = trainers[k].get_grads()
     threads = [threading.Thread(target=work, args=(k,)) for k in range(len(batches))]
     for t in threads:
@@ -1180,7 +1185,10 @@ def test_recurrences_of_several_streams_at_once(prec, H, lengths):
     for t in threads:
         t.join()
     for k, tr in enumerate(trainers):
-        assert np.array_equal(got[k], alone[k]), k
+        if again[k]:
+            assert np.linalg.norm(got[k] - alone[k]) <= (1e-5 if prec == 0 else 1e-2) * np.linalg.norm(alone[k]), (k, again[k])
+        else:
+            assert np.array_equal(got[k], alone[k]), k
         tr.close()
 
 
