@@ -49,8 +49,10 @@ typedef struct cmt_config {
                                  /* layer is two LSTMs of width H/2                                 */
   int32_t layers;                /* encoder depth = decoder depth, 1..8                             */
   int32_t max_batch, max_src_len, max_tgt_len;
-  int32_t precision;             /* 0: fp32 storage and fp32 matrix cores; 1: bf16 operands with    */
-                                 /* fp32 accumulation, fp32 master weights, fp32 state and sums     */
+  int32_t precision;             /* 0: fp32 storage, products to fp32 accuracy (on fp32 matrix      */
+                                 /* cores, or as products of three bf16 parts that hold all bits);  */
+                                 /* 1: bf16 operands with fp32 accumulation, fp32 master weights,   */
+                                 /* fp32 state and sums                                             */
   int32_t bos_id, pad_id;        /* decoder input at step 0; id stored in padded slots              */
 } cmt_config;
 

@@ -208,7 +208,7 @@ struct cmt_handle {
   // greedy decoding
   char* xcat = nullptr; int ldxcat = 0; // decoder bottom-layer input [emb(y_{j-1}) ; H_o^{<j-1>}] of the current step
   int32_t* dec_tok = nullptr; int32_t* dec_done = nullptr; float* dec_mask = nullptr; float* logits = nullptr;
-  // beam search: encoder outputs repeated per hypothesis row, and the search state
+  // beam search: the search's state
   BeamState beam{};
   char* HoDrop = nullptr;               // H_o after dropout: what the output layer and the input feed read
   float* psz = nullptr;                 // per-group sums of logits (label smoothing)
@@ -1775,8 +1775,8 @@ int cmt_beam_decode(cmt_handle* h, const int32_t* src_ids_dev, const int32_t* sr
   const size_t slotF = (size_t)Rp * H * esz;                                // the same slots of the fragment-major copies
   for (int l = 0; l < L; ++l) {
     LD& e = h->dec[l];
-    launch_beam_expand((int)esz, e.Hst, e.ph, BpE, e.Hst + slotT, e.ph, 1, R, Rp, K, H, st);
-    launch_beam_expand(4, e.Cst, H, BpE, (char*)e.Cst + slotC, H, 1, R, Rp, K, H, st);
+    launch_beam_expand((int)esz, e.Hst, e.ph, e.Hst + slotT, e.ph, R, Rp, K, H, st);
+    launch_beam_expand(4, e.Cst, H, (char*)e.Cst + slotC, H, R, Rp, K, H, st);
     if (e.fm) launch_fm_pack(e.Hst + slotT, e.ph, Rp, H, e.HstF + slotF, st);   // fragment-major copy of the expanded states
   }
   launch_fill_T(p, h->xcat, (size_t)Rp * h->ldxcat, st);               // H_o^{<-1>} = 0

@@ -16,27 +16,23 @@
 
 namespace cmt {
 
-// dst[i, r, 0:cols] = src[i, r / K, 0:cols] for r < R, zero rows for r in [R, Rp); i < n_outer.
+// dst[r, 0:cols] = src[r / K, 0:cols] for r < R, zero rows for r in [R, Rp).
 // Row pitches in elements; cols * sizeof(T) is a multiple of 16.
 template <typename T>
-__global__ __launch_bounds__(128) void beam_expand_kernel(const T* __restrict__ src, int ld_src, int rows_src, T* __restrict__ dst,
-                                                          int ld_dst, int R, int Rp, int K, int cols) {
-  const int r = blockIdx.x, i = blockIdx.y;
+__global__ __launch_bounds__(128) void beam_expand_kernel(const T* __restrict__ src, int ld_src, T* __restrict__ dst, int ld_dst, int R,
+                                                          int K, int cols) {
+  const int r = blockIdx.x;
   constexpr int VE = 16 / sizeof(T);
-  const T* s = r < R ? src + ((size_t)i * rows_src + r / K) * ld_src : nullptr;
-  T* d = dst + ((size_t)i * Rp + r) * ld_dst;
+  const T* s = r < R ? src + (size_t)(r / K) * ld_src : nullptr;
+  T* d = dst + (size_t)r * ld_dst;
   for (int c = threadIdx.x * VE; c < cols; c += 128 * VE)
     *reinterpret_cast<uint4*>(d + c) = s ? *reinterpret_cast<const uint4*>(s + c) : make_uint4(0, 0, 0, 0);
 }
-void launch_beam_expand(int elem_bytes, const void* src, int ld_src, int rows_src, void* dst, int ld_dst, int n_outer, int R, int Rp,
-                        int K, int cols, hipStream_t st) {
-  dim3 grid(Rp, n_outer);
+void launch_beam_expand(int elem_bytes, const void* src, int ld_src, void* dst, int ld_dst, int R, int Rp, int K, int cols, hipStream_t st) {
   if (elem_bytes == 2)
-    hipLaunchKernelGGL(beam_expand_kernel<bf16_t>, grid, dim3(128), 0, st, (const bf16_t*)src, ld_src, rows_src, (bf16_t*)dst, ld_dst,
-                       R, Rp, K, cols);
+    hipLaunchKernelGGL(beam_expand_kernel<bf16_t>, dim3(Rp), dim3(128), 0, st, (const bf16_t*)src, ld_src, (bf16_t*)dst, ld_dst, R, K, cols);
   else
-    hipLaunchKernelGGL(beam_expand_kernel<float>, grid, dim3(128), 0, st, (const float*)src, ld_src, rows_src, (float*)dst, ld_dst, R,
-                       Rp, K, cols);
+    hipLaunchKernelGGL(beam_expand_kernel<float>, dim3(Rp), dim3(128), 0, st, (const float*)src, ld_src, (float*)dst, ld_dst, R, K, cols);
 }
 
 // start of a search: one live hypothesis per sentence (slot 0, score 0, previous token bos)
@@ -100,7 +96,10 @@ __device__ __forceinline__ float beam_wave_max(float v) {
 // layer's forward kernel, vocabulary entries on the matrix cores' row side, so that a lane holds 32 TA / 2 entries of one row.
 // With the groups' statistics the choice of the K best reads 40 KB per sentence and the K best groups instead of every logit.
 // The row tile is as wide as makes the rounds of workgroups over the chip come out (beam_logits_plan): what a workgroup takes in is
-// its rows and its weights, 49 GB/s per CU.  640 rows x 32000, k 1024: 256 x 320 tiles, one round of 250: 80 -> 52 us.
+// its rows and its weights, 49 GB/s per CU.  640 rows x 32000, k 1024: 256 x 320 tiles, one round of 250: 80 -> 52 us.  (That tile has 160
+// accumulators a lane and spills two registers.)
+// fp32: the large tile keeps all products in one sum, as the output layer's does and for its reasons (ce.hip); 3.64 ms a search of 320 rows,
+// 3.67 with two.
 template <typename T, int WM, int WN, int TA, int TB>
 __global__ __launch_bounds__(64 * WM * WN) void beam_logits_kernel(const T* __restrict__ Ho, int ldho, const T* __restrict__ Wo,
                                                                    const float* __restrict__ Bo, int R, int V, int H, float* __restrict__ zT,

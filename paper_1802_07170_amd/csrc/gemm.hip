@@ -103,7 +103,7 @@ __device__ __forceinline__ void gemm_nt_tile(const T* __restrict__ A, int lda, c
 // than one, writes its own fp32 plane Cf + split * plane_stride (summed afterwards, fixed order).
 // WALK: the launch has fewer workgroups than tiles (it is to leave part of the chip to other streams) and every
 // workgroup walks the tiles of the virtual ids blockIdx.x, blockIdx.x + grid, ...  It is a variant of its own because
-// the loop costs the one-tile-per-workgroup kernel a spilled register.
+// the loop costs the one-tile-per-workgroup kernel a spilled register (fp32 in parts on the large tile, which walks under a cap alone: six).
 template <typename T, int WM, int WN, int TA, int TB, bool WALK = false, bool CHAIN = false, int STAGES = 2>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_kernel(const T* __restrict__ A, int lda, const T* __restrict__ B, int ldb,
                                                                int M, int N, int K, float* __restrict__ Cf0, T* __restrict__ Ct,

@@ -23,9 +23,10 @@ void launch_gemm_nt(int prec, const void* A, int lda, const void* B, int ldb, in
                     float* Cf, void* Ct, int ldc, const float* bias, int accumulate, hipStream_t st,
                     float* split_scratch = nullptr, size_t split_scratch_floats = 0, RowLimit limit = RowLimit{},
                     int limit_kind = 0, int wg_cap = 0, int chain = 0);
-// chain (fp32): the products on the fp32 instructions, added in ascending order.  For the output layer's backward products: their
-// sums of thousands of nearly equal addends carry rounding errors of up to 9e-6 of W_o's gradient (the split form's 1e-6), and
-// moving a gradient by its own error is more than sums in another order may do; everything else runs split (gemm_core.h).
+// chain (fp32): the products on the fp32 instructions, added in ascending order.  For the output layer's backward products, and
+// only so that their results stay what they were: their sums of thousands of nearly equal addends carry rounding errors of up to 9e-6 of
+// W_o's gradient, in parts it would be 1e-6 and the step of 512 units 5.07 instead of 5.33 ms, but W_o's gradient would move by the
+// difference.  Everything else runs in parts (gemm_core.h).
 // wg_cap > 0: at most that many workgroups (rounded up to a multiple of 8) walk the tiles — for a GEMM on a second
 // stream that is to leave part of the chip to the kernels of the first.  The cap counts workgroups of the two larger tiles; of
 // the 64 x 64 tile as many times more are launched as of it fit a CU (four; fp32 in parts three).
@@ -476,9 +477,8 @@ struct BeamReorder {
   const void* table = nullptr; int E = 0; void* x = nullptr;      // embeddings of the new tokens -> x[r, 0:E] (pitch ldho_dst),
                                                                   //   and columns [0, E) of ho_dst_fm
 };
-// dst[i, r, 0:cols] = src[i, r / K, 0:cols] (r < R), zero rows up to Rp; elem_bytes 2 or 4.
-void launch_beam_expand(int elem_bytes, const void* src, int ld_src, int rows_src, void* dst, int ld_dst, int n_outer, int R, int Rp,
-                        int K, int cols, hipStream_t st);
+// dst[r, 0:cols] = src[r / K, 0:cols] (r < R), zero rows up to Rp; elem_bytes 2 or 4.
+void launch_beam_expand(int elem_bytes, const void* src, int ld_src, void* dst, int ld_dst, int R, int Rp, int K, int cols, hipStream_t st);
 void launch_beam_init(const BeamState& bs, int B, int Rp, int K, int bos, hipStream_t st);
 // Step j of max_len: logits Ho W_o^T + B_o of the rows (Ho [Rp, ldho] T*, Wo [V, H] T*) and the K best extensions of every sentence.
 // Scratch: zT V * Rp floats, gmax and gsum ceil(V / 32) * Rp floats each.  K <= 16; V and H multiples of 8.
