@@ -253,6 +253,37 @@ def test_attention_on_projected_source_rows(prec, reg, B, S, T, H, E, L, monkeyp
     assert np.linalg.norm(g - g0) <= (1e-5 if prec == 0 else 2e-2) * np.linalg.norm(g0)
 
 
+@pytest.mark.parametrize("B,S,T,H,E,L", [(17, 5, 4, 256, 40, 5), (40, 4, 5, 320, 48, 2), (140, 3, 3, 256, 24, 2), (20, 4, 3, 256, 32, 1)])
+def test_row_pitches_where_some_rows_have_no_fragment_major_copy(B, S, T, H, E, L, monkeypatch):
+    """bf16, widths from 256 that are multiples of 64: with embeddings that are no multiple of 32 or of 16 the bottom decoder layer's
+    rows (or its gate gradients alone) keep the short padding beside rows of whole cache lines.  Training step as launches per position, and a
+    beam search, which reads the bottom layer's input and states by rows."""
+    from paper_1802_07170_amd import binding
+    monkeypatch.setenv("CMT_DEC_LOOP", "0")
+    cfg = dict(src_vocab=104, tgt_vocab=136, emb=E, hidden=H, layers=L)
+    rng = np.random.default_rng(1600 + B)
+    params = I.make_params(cfg, seed=B, scale=0.1)
+    batch = ragged_batch(rng, B, S, T, 104, 136)
+    sens = oracle_sensitivity(cfg, params, batch, None)
+    loss, oloss, worst, tr = run_case(cfg, params, batch, 1, l2_override={k: max(2e-2, SWEEP_SENS_C * v) for k, v in sens.items()})
+    tr.close()
+    params["W_o"] = params["W_o"] * 20
+    src, sl = batch[0][:12], batch[1][:12]
+    tr = binding.Trainer(cfg, 12 * 8, S, 5, precision=1)
+    tr.set_params(I.flatten(params, cfg))
+    ids, lens, score = tr.beam_decode(src, sl, 4, beam=8, length_penalty=0.6, eos_id=3)
+    tr.close()
+    search = lambda: O.beam_decode(cfg, params, src, sl, 4, 8, 0.6, bos_id=2, eos_id=3)
+    oids, olens, oscore, margins = search()
+    with O.operand_rounding(O.bf16_round):
+        _, _, rscore, _ = search()
+    tol = 4 * np.abs(rscore - oscore).max()
+    sure = margins > tol
+    assert np.array_equal(ids[sure], oids[sure]) and np.array_equal(lens[sure], olens[sure])
+    assert oscore.std() > 4 * tol                        # (few decisions are clear, but the scores tell the sentences apart)
+    assert (np.abs(score - oscore) <= tol).all(), (tol, np.abs(score - oscore).max())
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 def test_second_stream_gemms_walking_their_tiles(prec, monkeypatch):
     """The weight-gradient GEMMs of the second stream may be launched with fewer workgroups than tiles
@@ -727,7 +758,7 @@ def test_beam_search_whose_list_overflows_takes_hardly_longer():
         took[name] = min(times)
     tr.close()
     print({k: round(1e6 * v) for k, v in took.items()}, "us")
-    assert took["few threads"] < 3 * took["spread"], took
+    assert took["few threads"] < 8 * took["spread"], took       # (2.2 times, and 77 with rounds over all extensions)
 
 
 def test_beam_search_edge_cases():
